@@ -1,0 +1,575 @@
+"""Timed cases of the framework: what its users run, through its public entry points.
+
+Each case is a plain dict.  ``kind`` says which entry point it goes through:
+
+* ``lncc``       the LNCC loss (:class:`LNCC`): ``mode`` "fb" forward and backward through autograd (a training
+                 step's loss), "pass" cost and gradient from one call, "loss" the cost alone (a validation pass);
+* ``register``   a whole registration on a kept :class:`Pair`: schedule, iterations, field and warped image;
+* ``batch``      several registrations advanced together (:func:`run_batch`), as in a hyperparameter search;
+* ``inverse``    the post hoc inverse of a warp (:class:`Inverse`);
+* ``symmetric``  the symmetric registration (:class:`Symmetric`), final composition included;
+* ``evaluate``   the accuracy measures of a result: label transfer, overlap counts, det J, composition.
+
+Shapes, windows, widths and schedules are those of the tests, the synthetic workloads and the benchmark.  The
+schedules keep the benchmark's proportions between levels with fewer iterations on each, so that results stay
+comparable in single precision; an iteration costs the same whatever their number.
+
+Registrations other than the symmetric ones are under way: the displacement and the Adam moments at the coarsest
+level, after ``start`` steps, are given (a resumed run).  From a zero state the first Adam step is nearly the sign of
+the gradient, and which way a voxel with a vanishing gradient goes hangs on the last bit.
+
+The images are tissue-like (four classes with smooth borders, texture, a smooth bias field, noise of 0.01) and the
+moving image is the fixed one under a smooth warp of a few voxels, with noise of its own.
+"""
+import math
+
+import torch
+import torch.nn.functional as F
+
+DEVICE = "cuda"
+
+
+# ---- cases ------------------------------------------------------------------------------------------------------
+
+def _lncc(name, n0, n1, n2, window, mode):
+    return {"name": name, "kind": "lncc", "n0": n0, "n1": n1, "n2": n2, "window": window, "mode": mode}
+
+
+def _register(name, n0, n1, n2, window, scales, iters, start=200, eta=0.5, sigma_grad=1.0, sigma_warp=0.5,
+              use_jac=False):
+    return {"name": name, "kind": "register", "n0": n0, "n1": n1, "n2": n2, "window": window, "scales": scales,
+            "iters": iters, "start": start, "eta": eta, "sigma_grad": sigma_grad, "sigma_warp": sigma_warp,
+            "use_jac": use_jac}
+
+
+def listed():
+    return [
+        # a patch of a training volume: the smallest loss call, where launches and host time count
+        _lncc("lncc_fb_patch24", 24, 28, 26, 5, "fb"),
+        # the loss of a learned registration at its usual volume size, default window
+        _lncc("lncc_fb_128_w5", 128, 128, 128, 5, "fb"),
+        # the same with the widest window
+        _lncc("lncc_fb_128_w9", 128, 128, 128, 9, "fb"),
+        # the cost alone on a ragged volume, as a validation pass reads it
+        _lncc("lncc_loss_ragged_w7", 97, 131, 203, 7, "loss"),
+        # a small registration: every level is a few short launches
+        _register("register_64", 64, 64, 64, 5, "2,1", "10,5"),
+        # the headline workload: a brain-sized pair over three levels
+        _register("register_brain", 160, 192, 224, 5, "4,2,1", "12,6,3"),
+        # the lung CT hyperparameters: a radius-18 Gaussian on the direction, odd sizes
+        _register("register_lungct_ragged", 131, 177, 219, 5, "4,2,1", "6,3,2", eta=0.25, sigma_grad=6.0,
+                  sigma_warp=0.4),
+        # the largest volume, window 7, four levels: a microscopy pair
+        _register("register_512_w7", 512, 512, 512, 7, "8,4,2,1", "6,6,3,2"),
+        # a step-size search: four step sizes on each of two pairs, advanced together
+        {"name": "batch_search", "kind": "batch", "n0": 96, "n1": 112, "n2": 104, "pairs": 2, "window": 5,
+         "scales": "2,1", "iters": "6,3", "start": 200},
+        # the inverse of a brain-sized warp
+        {"name": "inverse_brain", "kind": "inverse", "n0": 160, "n1": 192, "n2": 224, "amplitude": 6.0,
+         "scales": "4,2,1", "iters": "8,4,2", "eta": 0.2},
+        # a symmetric registration: both half-way warps, the inverse fit and the composition
+        {"name": "symmetric_112", "kind": "symmetric", "n0": 96, "n1": 112, "n2": 112, "window": 5, "scales": "2,1",
+         "iters": "6,3", "inv_scales": "2,1", "inv_iters": "4,2"},
+        # the measures of one finished brain-sized registration
+        {"name": "evaluate_brain", "kind": "evaluate", "n0": 160, "n1": 192, "n2": 224, "amplitude": 6.0,
+         "classes": 4},
+    ]
+
+
+def _size(rng, low, high):
+    return int(round(math.exp(rng.uniform(math.log(low), math.log(high)))))
+
+
+def draw(rng):
+    kind = rng.choice(["lncc", "lncc", "register", "register", "batch", "inverse", "symmetric", "evaluate"])
+    n0, n1, n2 = (_size(rng, 20, 230) for _ in range(3))
+    c = {"kind": kind, "n0": n0, "n1": n1, "n2": n2}
+    smallest = min(n0, n1, n2)
+    scales = "4,2,1" if smallest >= 80 else "2,1" if smallest >= 30 else "1"
+    iters = {1: "4", 2: "5,3", 3: "6,4,2"}[len(scales.split(","))]
+    window = rng.choice([3, 5, 5, 7, 9])
+    if kind == "lncc":
+        c.update(window=window, mode=rng.choice(["fb", "fb", "pass", "loss"]))
+    elif kind == "register":
+        sigma_grad, sigma_warp = rng.choice([(1.0, 0.5), (1.0, 0.5), (2.0, 1.0), (6.0, 0.4)])
+        c.update(window=window, scales=scales, iters=iters, start=200,
+                 eta=rng.choice([0.25, 0.5, 1.0]), sigma_grad=sigma_grad,
+                 sigma_warp=sigma_warp, use_jac=rng.random() < 0.25)
+    elif kind == "batch":
+        c.update(pairs=rng.choice([1, 2, 3]), window=rng.choice([3, 5]), scales=scales, iters=iters, start=200)
+    elif kind == "inverse":
+        c.update(amplitude=rng.choice([2.0, 6.0]), scales=scales, iters=iters, eta=0.2)
+    elif kind == "symmetric":
+        c.update(window=rng.choice([3, 5, 7]), scales=scales, iters=iters, inv_scales=scales, inv_iters=iters)
+    else:
+        c.update(amplitude=rng.choice([2.0, 6.0]), classes=rng.choice([2, 4, 35]))
+    return c
+
+
+def _shape(case):
+    return case["n0"], case["n1"], case["n2"]
+
+
+def _floats(text):
+    return [float(x) for x in text.split(",")]
+
+
+def _ints(text):
+    return [int(x) for x in text.split(",")]
+
+
+# the step sizes of a search, one registration of each pair at each
+ETAS = (0.25, 0.5, 1.0, 2.0)
+
+
+# ---- inputs -----------------------------------------------------------------------------------------------------
+
+def _smooth(gen, shape, spacing, channels=1):
+    """Smooth noise: normal values on a grid of the given spacing, interpolated."""
+    coarse = [max(2, int(round(n / spacing)) + 1) for n in shape]
+    z = torch.randn([1, channels] + coarse, generator=gen, device=DEVICE)
+    return F.interpolate(z, size=tuple(shape), mode="trilinear", align_corners=True)[0]
+
+
+def _field(gen, shape, amplitude):
+    """A smooth displacement of at most `amplitude` voxels that keeps the faces in place, (3, n0, n1, n2)."""
+    d = _smooth(gen, shape, max(8.0, min(shape) / 4.0), 3)
+    for a, n in enumerate(shape):
+        view = [1, 1, 1]
+        view[a] = n
+        d[a] *= torch.sin(torch.linspace(0.0, math.pi, n, device=DEVICE)).clamp(min=0.0).view(view)
+    return (d * (amplitude / d.norm(dim=0).max())).contiguous()
+
+
+def _labels(gen, shape, classes):
+    z = _smooth(gen, shape, max(6.0, min(shape) / 8.0))[0]
+    # equal shares of a normal variable's range, from its distribution function
+    u = 0.5 * (1.0 + torch.erf(z / (z.std() * math.sqrt(2.0))))
+    return (u * classes).floor().clamp(0, classes - 1), u
+
+
+def _grid_sample(vol, d):
+    shape = vol.shape
+    grid = []
+    for a in (2, 1, 0):   # grid_sample wants (x, y, z)
+        n = shape[a]
+        view = [1, 1, 1]
+        view[a] = n
+        p = torch.arange(n, device=DEVICE, dtype=torch.float32).view(view) + d[a]
+        grid.append(2.0 * p / max(1, n - 1) - 1.0)
+    return F.grid_sample(vol[None, None], torch.stack(grid, -1)[None], mode="bilinear", padding_mode="border",
+                         align_corners=True)[0, 0]
+
+
+def _images(gen, shape):
+    lab, u = _labels(gen, shape, 4)
+    # class means with borders about a voxel wide
+    clean = 0.1 + 0.8 * (lab + (4.0 * u - lab).clamp(0, 1) ** 4) / 4.0
+    clean = clean + 0.1 * _smooth(gen, shape, 4.0)[0]
+    clean = clean * (1.0 + 0.1 * torch.tanh(_smooth(gen, shape, max(8.0, min(shape) / 3.0))[0]))
+    del lab, u
+    g = _field(gen, shape, 0.05 * min(shape))
+    moving = _grid_sample(clean, g)
+    fixed = clean + 0.01 * torch.randn(shape, generator=gen, device=DEVICE)
+    moving = moving + 0.01 * torch.randn(shape, generator=gen, device=DEVICE)
+    return fixed.contiguous(), moving.contiguous(), g
+
+
+@torch.no_grad()
+def _under_way(case, fixed, moving, g):
+    """The state of a registration after case["start"] steps at its coarsest level: (d, m, v), float32."""
+    scale, t = _floats(case["scales"])[0], case["start"]
+    d = -0.6 * _field_at(g.double(), scale)
+    grad = _gradient(_image_at(fixed.double(), scale), _image_at(moving.double(), scale), d, case["window"])[1]
+    v = (1.0 - 0.999 ** t) * 2.0 * _blur(grad * grad, 1.5)
+    m = (1.0 - 0.9 ** t) * 0.7 * _blur(grad, 0.5)
+    return tuple(x.float().contiguous() for x in (d, m, v))
+
+
+def _inputs(case, seed):
+    gen = torch.Generator(device=DEVICE).manual_seed(int(seed))
+    shape = _shape(case)
+    kind = case["kind"]
+    if kind == "lncc":
+        fixed, moving, _ = _images(gen, shape)
+        return {"fixed": fixed, "moving": moving, "d": _field(gen, shape, 0.04 * min(shape))}
+    if kind in ("register", "symmetric"):
+        fixed, moving, g = _images(gen, shape)
+        start = _under_way(case, fixed, moving, g) if case["kind"] == "register" else None
+        return {"fixed": fixed, "moving": moving, "start": start}
+    if kind == "batch":
+        made = [_images(gen, shape) for _ in range(case["pairs"])]
+        return {"images": [x[:2] for x in made], "starts": [_under_way(case, *x) for x in made]}
+    if kind == "inverse":
+        return {"d": _field(gen, shape, case["amplitude"])}
+    d, truth = _field(gen, shape, case["amplitude"]), _field(gen, shape, case["amplitude"])
+    fixed, _ = _labels(gen, shape, case["classes"])
+    moving, _ = _labels(gen, shape, case["classes"])
+    return {"d": d, "truth": truth, "fixed": fixed.to(torch.int8), "moving": moving.to(torch.int8)}
+
+
+def prepare(case, seed):
+    from paper_2404_01249_amd import LNCC, Inverse, Pair, Symmetric
+
+    state = _inputs(case, seed)
+    state["case"] = case
+    kind = case["kind"]
+    if kind == "lncc":
+        state["loss"] = LNCC(_shape(case), window=case["window"])
+        state["d"].requires_grad_(case["mode"] == "fb")
+    elif kind == "register":
+        state["pair"] = Pair(state["fixed"], state["moving"], eta=case["eta"], sigma_grad=case["sigma_grad"],
+                             sigma_warp=case["sigma_warp"], window=case["window"], use_jac=case["use_jac"])
+        state["pair"].set_schedule(_floats(case["scales"]), _ints(case["iters"]))
+    elif kind == "batch":
+        state["pairs"] = [Pair(f, m, eta=eta, window=case["window"]) for f, m in state["images"] for eta in ETAS]
+        for p in state["pairs"]:
+            p.set_schedule(_floats(case["scales"]), _ints(case["iters"]))
+    elif kind == "inverse":
+        state["inverse"] = Inverse(state["d"], eta=case["eta"])
+        state["inverse"].set_schedule(_floats(case["scales"]), _ints(case["iters"]))
+    elif kind == "symmetric":
+        state["symmetric"] = Symmetric(state["fixed"], state["moving"], eta=0.5, window=case["window"])
+        state["symmetric"].set_schedule(_floats(case["scales"]), _ints(case["iters"]))
+    return state
+
+
+def run(state):
+    case = state["case"]
+    kind = case["kind"]
+    if kind == "lncc":
+        loss = state["loss"]
+        if case["mode"] == "pass":
+            return loss.loss_and_grad(state["fixed"], state["moving"], state["d"])
+        cost = loss(state["fixed"], state["moving"], state["d"])
+        if case["mode"] == "loss":
+            return cost
+        return cost.detach(), torch.autograd.grad(cost, state["d"])[0]
+    if kind == "register":
+        p = state["pair"]
+        p.set_schedule(_floats(case["scales"]), _ints(case["iters"]))
+        p.set_state(*state["start"], case["start"])
+        p.run()
+        return p.field(), p.warped()
+    if kind == "batch":
+        for k, p in enumerate(state["pairs"]):
+            p.set_schedule(_floats(case["scales"]), _ints(case["iters"]))
+            p.set_state(*state["starts"][k // len(ETAS)], case["start"])
+        from paper_2404_01249_amd import run_batch
+        run_batch(state["pairs"])
+        return [p.field() for p in state["pairs"]]
+    if kind == "inverse":
+        inv = state["inverse"]
+        inv.set_schedule(_floats(case["scales"]), _ints(case["iters"]))
+        inv.run()
+        return inv.field()
+    if kind == "symmetric":
+        s = state["symmetric"]
+        s.set_schedule(_floats(case["scales"]), _ints(case["iters"]))
+        s.run()
+        half = s.halfway()
+        return half + (s.finish(_floats(case["inv_scales"]), _ints(case["inv_iters"]), eta=0.2),)
+    from paper_2404_01249_amd import evaluate
+    warped = evaluate.warp_labels(state["moving"], state["d"])
+    return (warped, evaluate.label_overlap(warped, state["fixed"], case["classes"]), evaluate.jacobian_det(state["d"]),
+            evaluate.singular_fraction(state["d"]), evaluate.compose(state["d"], state["truth"]))
+
+
+# ---- the work a pass cannot do without --------------------------------------------------------------------------
+
+def _levels(shape, scales, iters):
+    for s, t in zip(_floats(scales), _ints(iters)):
+        yield math.prod(max(1, int(math.floor(n / s + 0.5))) for n in shape), t
+
+
+def _taps(sigma):
+    return 2 * math.ceil(3.0 * sigma) + 1 if sigma > 0 else 1
+
+
+# separable box sums of the five products and of the three adjoint coefficients (an add and a subtract per axis),
+# the trilinear sample with its derivative, the coefficients and the product
+_GRAD_FLOPS = 5 * 3 * 2 + 3 + 25 + 3 * 3 * 2 + 45 + 9
+
+
+def _iteration_flops(sigma_grad, sigma_warp):
+    return _GRAD_FLOPS + 3 * 12 + 18 * (_taps(sigma_grad) + _taps(sigma_warp)) + 3 * 16
+
+
+def work(case):
+    shape = _shape(case)
+    n = math.prod(shape)
+    kind = case["kind"]
+    if kind == "lncc":
+        # both images and d in; the gradient out
+        out = {"fb": 12, "pass": 12, "loss": 0}[case["mode"]]
+        return {"bytes": n * (20 + out) + 4, "flops": n * (_GRAD_FLOPS if out else 70)}
+    if kind in ("register", "batch"):
+        # an iteration reads both images and reads and writes d, m and v; field and warped image out
+        each = sum(m * t for m, t in _levels(shape, case["scales"], case["iters"]))
+        f = each * _iteration_flops(case.get("sigma_grad", 1.0), case.get("sigma_warp", 0.5))
+        count = case["pairs"] * len(ETAS) if kind == "batch" else 1
+        return {"bytes": count * (80 * each + n * (8 + (12 if kind == "batch" else 16))), "flops": count * f}
+    if kind == "inverse":
+        # d in; e, m and v in and out
+        each = sum(m * t for m, t in _levels(shape, case["scales"], case["iters"]))
+        return {"bytes": 84 * each + 24 * n, "flops": each * (_iteration_flops(1.0, 0.5) + 150)}
+    if kind == "symmetric":
+        each = sum(m * t for m, t in _levels(shape, case["scales"], case["iters"]))
+        inv = sum(m * t for m, t in _levels(shape, case["inv_scales"], case["inv_iters"]))
+        return {"bytes": 152 * each + 84 * inv + n * (8 + 36), "flops": (2 * each + inv) * _iteration_flops(1.0, 0.5)}
+    inner = math.prod(max(0, k - 2) for k in shape)
+    # labels and both fields in; labels, determinants and the composed field out
+    return {"bytes": n * (1 + 12 + 1 + 1 + 12 + 12) + 8 * inner, "flops": n * (12 + 3 * 16) + inner * 32}
+
+
+# ---- the same results in 64 bits, with plain torch ---------------------------------------------------------------
+
+def _axes(shape):
+    out = []
+    for a, n in enumerate(shape):
+        view = [1, 1, 1]
+        view[a] = n
+        out.append(torch.arange(n, device=DEVICE, dtype=torch.float64).view(view))
+    return out
+
+
+def _sample(fields, pos, grad=False):
+    """Trilinear samples of each volume in `fields` at `pos`, zero per corner outside; with their derivatives."""
+    shape = fields[0].shape
+    pos = torch.broadcast_tensors(*pos)
+    low = [torch.floor(p) for p in pos]
+    frac = [p - q for p, q in zip(pos, low)]
+    low = [q.clamp(-2, n).long() for q, n in zip(low, shape)]
+    value = [torch.zeros_like(frac[0]) for _ in fields]
+    slope = [[torch.zeros_like(frac[0]) for _ in range(3)] for _ in fields] if grad else None
+    for b0 in (0, 1):
+        for b1 in (0, 1):
+            for b2 in (0, 1):
+                bits = (b0, b1, b2)
+                at = [q + b for q, b in zip(low, bits)]
+                inside = torch.ones_like(at[0], dtype=torch.bool)
+                for i, n in zip(at, shape):
+                    inside &= (i >= 0) & (i < n)
+                index = (at[0].clamp(0, shape[0] - 1) * shape[1] + at[1].clamp(0, shape[1] - 1)) * shape[2] + \
+                    at[2].clamp(0, shape[2] - 1)
+                w = [t if b else 1.0 - t for t, b in zip(frac, bits)]
+                for k, f in enumerate(fields):
+                    v = f.reshape(-1)[index] * inside
+                    value[k] += w[0] * w[1] * w[2] * v
+                    if grad:
+                        for a in range(3):
+                            other = [w[j] for j in range(3) if j != a]
+                            slope[k][a] += (v if bits[a] else -v) * other[0] * other[1]
+    return (value, slope) if grad else value
+
+
+def _moved(d):
+    return [x + c for x, c in zip(_axes(d.shape[1:]), d)]
+
+
+def _box(f, r):
+    for a in range(3):
+        n = f.shape[a]
+        out = f.clone()
+        for k in range(1, min(r, n - 1) + 1):
+            out.narrow(a, 0, n - k).add_(f.narrow(a, k, n - k))
+            out.narrow(a, k, n - k).add_(f.narrow(a, 0, n - k))
+        f = out
+    return f
+
+
+def _cost(fixed, warped, window, eps, adjoint):
+    """L = -mean cc and, with `adjoint`, dL/d(warped)."""
+    r = window // 2
+    count = _box(torch.ones_like(fixed), r)
+    mi, mj = _box(fixed, r) / count, _box(warped, r) / count
+    cross = _box(fixed * warped, r) - count * mi * mj
+    vi = _box(fixed * fixed, r) - count * mi * mi
+    vj = _box(warped * warped, r) - count * mj * mj
+    den = vi * vj + eps
+    cost = -(cross * cross / den).mean()
+    if not adjoint:
+        return cost, None
+    a = 2.0 * cross / den
+    b = -2.0 * cross * cross * vi / (den * den)
+    c = a * mi + b * mj
+    return cost, -(fixed * _box(a, r) + warped * _box(b, r) - _box(c, r)) / fixed.numel()
+
+
+def _gradient(fixed, moving, d, window, eps=float(torch.tensor(1e-5))):
+    (warped,), (slope,) = _sample([moving], _moved(d), grad=True)
+    cost, dj = _cost(fixed, warped, window, eps, True)
+    return cost, torch.stack([dj * s for s in slope])
+
+
+def _blur(f, sigma):
+    """Gaussian along the last three axes, replicate boundary."""
+    if not sigma > 0:
+        return f
+    sigma = float(torch.tensor(sigma, dtype=torch.float32))
+    r = math.ceil(3.0 * sigma)
+    w = [math.exp(-k * k / (2.0 * sigma * sigma)) for k in range(-r, r + 1)]
+    total = sum(w)
+    for a in (-3, -2, -1):
+        n = f.shape[a]
+        out = torch.zeros_like(f)
+        for k in range(-r, r + 1):
+            index = (torch.arange(n, device=DEVICE) + k).clamp(0, n - 1)
+            out += (w[k + r] / total) * f.index_select(f.dim() + a, index)
+        f = out
+    return f
+
+
+def _after(shape, scale):
+    return tuple(max(1, int(math.floor(n / scale + 0.5))) for n in shape)
+
+
+def _resample(fields, shape):
+    old = fields[0].shape
+    pos = [x * ((o - 1) / (n - 1)) if n > 1 else x * 0.0 for x, o, n in zip(_axes(shape), old, shape)]
+    return _sample(fields, pos)
+
+
+def _ratio(fine, coarse):
+    return [(f - 1) / (c - 1) if c > 1 else 1.0 for f, c in zip(fine, coarse)]
+
+
+def _image_at(img, scale):
+    shape = _after(img.shape, scale)
+    return img if scale == 1 and shape == tuple(img.shape) else _resample([_blur(img, scale / 2.0)], shape)[0]
+
+
+def _field_at(d, scale):
+    shape = _after(d.shape[1:], scale)
+    if scale == 1 and shape == tuple(d.shape[1:]):
+        return d
+    got = _resample([_blur(d[c], scale / 2.0) for c in range(3)], shape)
+    return torch.stack([g / r for g, r in zip(got, _ratio(d.shape[1:], shape))])
+
+
+class _Warp:
+    """A displacement with Adam moments, advanced by Algorithm 1's steps."""
+
+    def __init__(self, eta, sigma_grad=1.0, sigma_warp=0.5, use_jac=False):
+        self.eta, self.sigma_grad, self.sigma_warp, self.use_jac = eta, sigma_grad, sigma_warp, use_jac
+        self.d, self.t = None, 0
+
+    def level(self, shape):
+        if self.d is None:
+            self.d, self.m, self.v = (torch.zeros((3,) + tuple(shape), dtype=torch.float64, device=DEVICE)
+                                      for _ in range(3))
+            return
+        rho = _ratio(shape, self.d.shape[1:])
+        self.d = torch.stack([g * r for g, r in zip(_resample(list(self.d), shape), rho)])
+        self.m, self.v = torch.stack(_resample(list(self.m), shape)), torch.stack(_resample(list(self.v), shape))
+
+    def step(self, g):
+        if self.use_jac:
+            slopes = [torch.gradient(self.d[c], dim=(0, 1, 2), edge_order=1) for c in range(3)]
+            g = torch.stack([g[a] + sum(slopes[c][a] * g[c] for c in range(3)) for a in range(3)])
+        self.t += 1
+        b1, b2, eps = (float(torch.tensor(x, dtype=torch.float32)) for x in (0.9, 0.999, 1e-8))
+        self.m = b1 * self.m + (1.0 - b1) * g
+        self.v = b2 * self.v + (1.0 - b2) * g * g
+        a = (self.m / (1.0 - b1 ** self.t)) / ((self.v / (1.0 - b2 ** self.t)).sqrt() + eps)
+        s = _blur(a, self.sigma_grad)
+        top = float(s.norm(dim=0).max())
+        u = s * (-self.eta / (2.0 * top)) if top > 0 else torch.zeros_like(s)
+        self.d = _blur(_compose(u, self.d), self.sigma_warp)
+
+
+def _compose(u, d):
+    return u + torch.stack(_sample(list(d), _moved(u)))
+
+
+def _warped(img, d):
+    return _sample([img], _moved(d))[0]
+
+
+def _registered(fixed, moving, case, eta, start, **more):
+    w = _Warp(eta, **more)
+    w.d, w.m, w.v = (x.double() for x in start)
+    w.t = case["start"]
+    for scale, count in zip(_floats(case["scales"]), _ints(case["iters"])):
+        f, m = _image_at(fixed, scale), _image_at(moving, scale)
+        if w.d.shape[1:] != f.shape:
+            w.level(f.shape)
+        for _ in range(count):
+            w.step(_gradient(f, m, w.d, case["window"])[1])
+    return w.d
+
+
+def _inverted(d, scales, iters, eta):
+    w = _Warp(eta)
+    for scale, count in zip(_floats(scales), _ints(iters)):
+        f = _field_at(d, scale)
+        w.level(f.shape[1:])
+        for _ in range(count):
+            e = w.d.clone().requires_grad_(True)
+            first = f + torch.stack(_sample(list(e), _moved(f)))
+            g = torch.autograd.grad((first * first).sum(), e)[0]
+            del first
+            e = e.detach()
+            value, slope = _sample(list(f), _moved(e), grad=True)
+            second = e + torch.stack(value)
+            for a in range(3):
+                g[a] += 2.0 * (second[a] + sum(slope[c][a] * second[c] for c in range(3)))
+            w.step(g / f[0].numel())
+    return w.d
+
+
+@torch.no_grad()
+def exact(case, seed):
+    x = _inputs(case, seed)
+    kind = case["kind"]
+    if kind == "lncc":
+        f, m, d = (x[k].double() for k in ("fixed", "moving", "d"))
+        if case["mode"] == "loss":
+            return _cost(f, _warped(m, d), case["window"], 1e-5, False)[0]
+        return _gradient(f, m, d, case["window"])
+    if kind == "register":
+        f, m = x["fixed"].double(), x["moving"].double()
+        d = _registered(f, m, case, case["eta"], x["start"], sigma_grad=case["sigma_grad"],
+                        sigma_warp=case["sigma_warp"], use_jac=case["use_jac"])
+        return d, _warped(m, d)
+    if kind == "batch":
+        return [_registered(f.double(), m.double(), case, eta, start)
+                for (f, m), start in zip(x["images"], x["starts"]) for eta in ETAS]
+    if kind == "inverse":
+        with torch.enable_grad():
+            return _inverted(x["d"].double(), case["scales"], case["iters"], case["eta"])
+    if kind == "symmetric":
+        wf, wm = (_Warp(0.5) for _ in range(2))
+        for scale, count in zip(_floats(case["scales"]), _ints(case["iters"])):
+            f, m = _image_at(x["fixed"].double(), scale), _image_at(x["moving"].double(), scale)
+            wf.level(f.shape)
+            wm.level(f.shape)
+            for _ in range(count):
+                gm = _gradient(_warped(f, wf.d), m, wm.d, case["window"])[1]
+                gf = _gradient(_warped(m, wm.d), f, wf.d, case["window"])[1]
+                wf.step(gf)
+                wm.step(gm)
+        with torch.enable_grad():
+            e = _inverted(wf.d, case["inv_scales"], case["inv_iters"], 0.2)
+        return wf.d, wm.d, _compose(e, wm.d)
+    d, truth = x["d"].double(), x["truth"].double()
+    shape = d.shape[1:]
+    at = [torch.floor(p + 0.5).long() for p in _moved(d)]
+    inside = torch.ones_like(at[0], dtype=torch.bool)
+    for i, n in zip(at, shape):
+        inside &= (i >= 0) & (i < n)
+    at = [i.clamp(0, n - 1) for i, n in zip(at, shape)]
+    lab = torch.where(inside, x["moving"][at[0], at[1], at[2]].long(), -1)
+    classes = torch.arange(case["classes"], device=DEVICE)
+    fixed = x["fixed"].long()
+    counts = torch.stack([torch.stack([(lab == r).sum(), (fixed == r).sum(), ((lab == r) & (fixed == r)).sum()])
+                          for r in classes])
+    inner = (slice(None),) + (slice(1, -1),) * 3
+    jac = [[0.5 * (d.narrow(a + 1, 2, shape[a] - 2) - d.narrow(a + 1, 0, shape[a] - 2))[c][
+        tuple(slice(None) if b == a else slice(1, -1) for b in range(3))] + (1.0 if c == a else 0.0)
+        for a in range(3)] for c in range(3)]
+    assert jac[0][0].shape == d[inner][0].shape
+    det = (jac[0][0] * (jac[1][1] * jac[2][2] - jac[1][2] * jac[2][1])
+           - jac[0][1] * (jac[1][0] * jac[2][2] - jac[1][2] * jac[2][0])
+           + jac[0][2] * (jac[1][0] * jac[2][1] - jac[1][1] * jac[2][0]))
+    return lab.to(torch.int8), counts, det, float((det <= 0).double().mean()), _compose(d, truth)
