@@ -59,8 +59,9 @@ def listed():
         # the lung CT hyperparameters: a radius-18 Gaussian on the direction, odd sizes
         _register("register_lungct_ragged", 131, 177, 219, 5, "4,2,1", "6,3,2", eta=0.25, sigma_grad=6.0,
                   sigma_warp=0.4),
-        # the largest volume, window 7, four levels: a microscopy pair
-        _register("register_512_w7", 512, 512, 512, 7, "8,4,2,1", "6,6,3,2"),
+        # the largest volume, window 7, four levels: a microscopy pair (wide windows take the fewest iterations here:
+        # their sums are the longest and round the most)
+        _register("register_512_w7", 512, 512, 512, 7, "8,4,2,1", "2,2,1,1"),
         # a step-size search: four step sizes on each of two pairs, advanced together
         {"name": "batch_search", "kind": "batch", "n0": 96, "n1": 112, "n2": 104, "pairs": 2, "window": 5,
          "scales": "2,1", "iters": "6,3", "start": 200},
@@ -86,8 +87,8 @@ def draw(rng):
     c = {"kind": kind, "n0": n0, "n1": n1, "n2": n2}
     smallest = min(n0, n1, n2)
     scales = "4,2,1" if smallest >= 80 else "2,1" if smallest >= 30 else "1"
-    iters = {1: "4", 2: "5,3", 3: "6,4,2"}[len(scales.split(","))]
     window = rng.choice([3, 5, 5, 7, 9])
+    iters = ({1: "4", 2: "5,3", 3: "6,4,2"} if window < 7 else {1: "2", 2: "2,1", 3: "2,1,1"})[len(scales.split(","))]
     if kind == "lncc":
         c.update(window=window, mode=rng.choice(["fb", "fb", "pass", "loss"]))
     elif kind == "register":
@@ -96,11 +97,11 @@ def draw(rng):
                  eta=rng.choice([0.25, 0.5, 1.0]), sigma_grad=sigma_grad,
                  sigma_warp=sigma_warp, use_jac=rng.random() < 0.25)
     elif kind == "batch":
-        c.update(pairs=rng.choice([1, 2, 3]), window=rng.choice([3, 5]), scales=scales, iters=iters, start=200)
+        c.update(pairs=rng.choice([1, 2, 3]), window=window, scales=scales, iters=iters, start=200)
     elif kind == "inverse":
         c.update(amplitude=rng.choice([2.0, 6.0]), scales=scales, iters=iters, eta=0.2)
     elif kind == "symmetric":
-        c.update(window=rng.choice([3, 5, 7]), scales=scales, iters=iters, inv_scales=scales, inv_iters=iters)
+        c.update(window=min(window, 5), scales=scales, iters=iters, inv_scales=scales, inv_iters=iters)
     else:
         c.update(amplitude=rng.choice([2.0, 6.0]), classes=rng.choice([2, 4, 35]))
     return c
