@@ -34,16 +34,15 @@ extern "C" {
 typedef struct fa_lncc_s* fa_lncc;   /* opaque; owns its reduction buffers */
 
 /* Create an evaluator for volumes of `shape` (every dimension >= 2,
- * n0*n1*n2 < 2^29), window w (odd, 1..9) and eps >= 0.  Allocates a copy of
- * the moving image with a two-voxel zero border, (n0+4)(n1+4)(n2+4) floats,
- * the same grid as corner quads (four times that, for volumes whose quad copy
- * stays below 4 GiB), plus a few KB of device memory; work is enqueued on
+ * n0*n1*n2 < 2^29), window w (odd, 1..9) and eps >= 0.  Allocates the warped
+ * image, n0*n1*n2 floats, plus a few KB of device memory; work is enqueued on
  * `hip_stream` (NULL = null stream). */
 fa_status fa_lncc_create(fa_shape shape, int window, float cc_eps, void* hip_stream, fa_lncc* out);
 
 /* Evaluate at (fixed, moving, d), all device pointers of the evaluator's shape.
  *   loss_dev:  device float receiving L (may be NULL).
- *   grad_dev:  device [3][n0][n1][n2] receiving dL/dd, or NULL for the loss only.
+ *   grad_dev:  device [3][n0][n1][n2] receiving dL/dd, or NULL for the loss only
+ *              (written twice: the slope of the moving image passes through it).
  *   grad_scale_dev: device float multiplying the gradient (the upstream
  *              derivative of a chain rule), or NULL for 1.
  * At least one of loss_dev and grad_dev must be non-NULL.  Enqueued; calls on
@@ -63,15 +62,13 @@ void fa_lncc_destroy(fa_lncc h);
  * forbid hipMalloc.  It computes exactly what fa_lncc_create(shape, window,
  * cc_eps, hip_stream) followed by fa_lncc_eval(fixed, moving, d, loss_dev,
  * grad_dev, grad_scale_dev) computes (same arithmetic in the same launch
- * shapes, so the same bits: the evaluator samples the corner-quad copy and
- * this call the scalar zero-bordered copy, which give every trilinear sample
- * the same corner values), with arguments as documented there.
+ * shapes, so the same bits), with arguments as documented there.
  *
  * It calls no hipMalloc, hipFree or other allocating routine.  Every buffer
  * besides the caller's inputs and outputs (control block, reduction partials,
- * zero-bordered copy of the moving image) lives in a fixed device array of
- * FA_LNCC_NOALLOC_SCRATCH_BYTES; a call needs about 4 (n0+4)(n1+4)(n2+4)
- * bytes of it plus a few KB (160x192x224 takes 29.3 MB).  A larger volume is
+ * warped image) lives in a fixed device array of
+ * FA_LNCC_NOALLOC_SCRATCH_BYTES.  Volumes with 4 (n0+4)(n1+4)(n2+4) bytes plus
+ * a few KB within it are accepted (160x192x224 counts 29.3 MB).  A larger one is
  * rejected with FA_EINVAL before any work is enqueued.  The first call on a
  * device looks up the array's address on that device (hipGetSymbolAddress).
  *

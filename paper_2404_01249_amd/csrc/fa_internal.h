@@ -57,7 +57,6 @@ struct Ctl {
 struct Tiling {
   int ty, tx, zc;
   int tiles_y, tiles_x, chunks;
-  int variant = 0;   // gradient kernel: 2 = gathers issued after the LDS passes
   bool cube = false;
   int blocks() const { return tiles_y * tiles_x * chunks; }
 };
@@ -71,9 +70,8 @@ inline int record_launch(const Tiling& warp_smoothing) { return warp_smoothing.c
 // ---- fused gradient (+ Adam) kernel -------------------------------------
 struct GradArgs {
   const float* fixed;
-  const float* moving_pad;   // moving image with a zero border of kPad voxels
-  const float* moving_quad;  // the same as corner quads (launch_pad_quad), or NULL
-  const float* d;        // [3][N]
+  const float* warped;   // J = I_m(x + d) (launch_warp, launch_warp_slope)
+  const float* slope;    // [3][N]: dI_m/dp at x + d (modes 0 and 1; may alias out)
   float* m;              // [3][N] (Adam mode)
   float* v;              // [3][N]
   float* out;            // [3][N]: Adam direction (mode 0) or gradient (mode 1)
@@ -93,18 +91,24 @@ struct GradArgs {
 // EPI_COMPOSE_LDS stages three planes of d in LDS and needs |u| <= 1 voxel
 // (eta <= 2, since max |u| = eta / 2).
 // EPI_SMOOTH_MAX stores the smoothed field and takes M = max |s| in one pass.
+// EPI_STORE_WARP stores the smoothed field d and, for the next iteration's
+// gradient, J = I_m(x + d) and its slope.
 enum GaussEpilogue {
   EPI_STORE = 0,
-  EPI_MAXNORM = 1,
   EPI_COMPOSE = 2,
   EPI_COMPOSE_LDS = 4,
-  EPI_SMOOTH_MAX = 5
+  EPI_SMOOTH_MAX = 5,
+  EPI_STORE_WARP = 6
 };
 
 struct GaussArgs {
   const float* in;       // [3][N]
   float* out;            // [3][N] (store / compose)
   const float* d;        // [3][N] displacement sampled by the composition
+  const float* moving;   // EPI_STORE_WARP: the moving image, its row pairs (launch_row_pairs) or NULL, and
+  const float* moving_pairs;  // where J and its slope go ([N], [3][N])
+  float* warped;
+  float* slope;
   const float* wts;      // 2R+1 normalised taps (device)
   Ctl* ctl;
   const double* partials;  // loss partials of the gradient kernel (final epilogue)
@@ -139,10 +143,9 @@ hipError_t launch_gauss(const GaussArgs& a, int radius, int epilogue, const Tili
 // Batched forms: `total` workgroups over the entries E (device memory) with
 // owner (device memory, `total` ints); t gives the template parameters only
 // (tile shape, brick or march) and must be the tiling of every entry.
-// quad: every entry's moving_quad is set (the corner-quad gathers).  adam:
-// every entry's mode is 0 (gradient and Adam; a kernel specialised for it).
+// adam: every entry's mode is 0 (else every entry's is 1).
 hipError_t launch_grad_batch(const BatchEntry<GradArgs>* E, const int* owner, int total, int window,
-                             const Tiling& t, bool quad, bool adam, hipStream_t s);
+                             const Tiling& t, bool adam, hipStream_t s);
 hipError_t launch_gauss_batch(const BatchEntry<GaussArgs>* E, const int* owner, int total, int radius,
                               int epilogue, const Tiling& t, hipStream_t s);
 // Whether a batched form exists for these parameters.
@@ -154,11 +157,9 @@ bool gauss_batch_supported(int radius, int epilogue, const Tiling& t);
 hipError_t launch_eulerian_adam(float* ga, const float* d, float* m, float* v, Ctl* ctl, int n0, int n1,
                                 int n2, float beta1, float beta2, float adam_eps, hipStream_t s);
 hipError_t launch_fill(float* p, float value, int64_t n, hipStream_t s);
-// out = in with a zero border of kPad voxels (padded_voxels(n0, n1, n2) floats).
-hipError_t launch_pad(const float* in, float* out, int n0, int n1, int n2, hipStream_t s);
-// Corner quads of the padded image `pad` (padded_voxels(n0, n1, n2) float4s
-// into quad, 16-byte aligned; quad_supported must hold).
-hipError_t launch_pad_quad(const float* pad, float* quad, int n0, int n1, int n2, hipStream_t s);
+// Row pairs of the moving image with a zero border (2 * padded_voxels floats,
+// 8-byte aligned; row_pairs_supported must hold).
+hipError_t launch_row_pairs(const float* in, float* out, int n0, int n1, int n2, hipStream_t s);
 hipError_t launch_blur_axis(const float* in, float* out, int n0, int n1, int n2, int axis,
                             const float* wts, int radius, hipStream_t s);
 hipError_t launch_resample(const float* in, float* out, int nin0, int nin1, int nin2,
@@ -166,6 +167,9 @@ hipError_t launch_resample(const float* in, float* out, int nin0, int nin1, int 
                            float rho0, float rho1, float rho2, hipStream_t s);
 hipError_t launch_warp(const float* img, const float* d, float* out, int n0, int n1, int n2,
                        hipStream_t s);
+// The same with the position derivative of the sample ([3][N]).
+hipError_t launch_warp_slope(const float* img, const float* d, float* out, float* slope, int n0, int n1, int n2,
+                             hipStream_t s);
 hipError_t launch_soa_to_aos(const float* in, float* out, int64_t n, hipStream_t s);
 // out = u + d(x + u) ([3][n] fields; out must not alias d).
 hipError_t launch_compose_fields(const float* u, const float* d, float* out, int n0, int n1, int n2,
@@ -188,22 +192,21 @@ bool gauss_tile_supported(int ty, int tx);
 // Whether a brick (cube) launch exists for this radius and epilogue.
 bool gauss_cube_supported(int radius, int epilogue);
 bool grad_cube_supported(int window);
-size_t grad_lds_bytes(int window, int ty, int tx);
 size_t gauss_lds_bytes(int radius, int ty, int tx);
 
 constexpr int kMaxWindow = 9;
-// Zero border of the padded moving image the gradient kernel samples.
+// Zero border of the row pairs.  A volume with kPad voxels added on every side must hold fewer than 2^30
+// voxels (check_shape), and the allocation-free LNCC call accepts the volumes
+// whose padded copy fits its scratch array.
 constexpr int kPad = 2;
 inline int64_t padded_voxels(int n0, int n1, int n2) {
   return (int64_t)(n0 + 2 * kPad) * (n1 + 2 * kPad) * (n2 + 2 * kPad);
 }
-// Whether the corner-quad copy of a padded volume stays below 4 GiB (its
-// gathers use 32-bit byte offsets).
-inline bool quad_supported(int n0, int n1, int n2) {
-  // 32-bit byte offsets; padded plane size and padded indices below 2^24
-  // (the gathers multiply them in 24 bits)
+// Whether the row pairs of a padded volume stay below 4 GiB (32-bit byte
+// offsets) and its padded plane size and indices below 2^24 (24-bit products).
+inline bool row_pairs_supported(int n0, int n1, int n2) {
   const uint64_t p0 = (uint64_t)n0 + 2 * kPad, p1 = (uint64_t)n1 + 2 * kPad, p2 = (uint64_t)n2 + 2 * kPad;
-  return (uint64_t)padded_voxels(n0, n1, n2) * 16u < ((uint64_t)1 << 32) && p1 * p2 < ((uint64_t)1 << 24) &&
+  return (uint64_t)padded_voxels(n0, n1, n2) * 8u < ((uint64_t)1 << 32) && p1 * p2 < ((uint64_t)1 << 24) &&
          p0 < ((uint64_t)1 << 24);
 }
 // Gaussian radii: the streaming and brick kernels take 0..kMaxRadius as a

@@ -2,14 +2,15 @@
 //
 // One iteration of Algorithm 1 runs as four streaming launches:
 //
-//   grad   : warp J = I_m(x + d), LNCC window statistics, LNCC adjoint, the
-//            Gateaux gradient g = dL/dJ * grad_p I_m (Jacobian-free Eulerian
-//            descent, Section 4.4.2) and the Adam update (Section 4.4) ->
-//            m, v, direction a; per-workgroup loss partials.
+//   grad   : LNCC window statistics of I_f and the warped image J = I_m(x + d),
+//            LNCC adjoint, the Gateaux gradient g = dL/dJ * grad_p I_m
+//            (Jacobian-free Eulerian descent, Section 4.4.2) and the Adam
+//            update (Section 4.4) -> m, v, direction a; loss partials.
 //   gauss  : s = G_sigma_grad * a stored, M = max |s|     (EPI_SMOOTH_MAX)
 //   gauss  : single tap: u = -eta s / (2M) (Appendix E), d' = u + d(x + u)
 //            (the retraction phi o (id + u) of Algorithm 1)  (EPI_COMPOSE_LDS)
-//   gauss  : d = G_sigma_warp * d'                          (EPI_STORE)
+//   gauss  : d = G_sigma_warp * d', and for the next iteration J = I_m(x + d)
+//            with its slope grad_p I_m                       (EPI_STORE_WARP)
 // The first workgroup of the composition, or of the warp smoothing where that
 // is a brick launch, also records the loss and advances the Adam step count.
 //
@@ -261,21 +262,25 @@ __device__ float block_max(float v, float* red) {
 }
 
 // ---------------------------------------------------------------------------
-// Fused warp + LNCC + adjoint + Adam.
+// Fused LNCC + adjoint + Adam.
 //
 // Stage 1 (window statistics) runs on the tile plus a 2r halo: each column
 // keeps the last W planes of I and J in registers, sums them along n0, and
 // the in-plane box sums are two passes over LDS.  Stage 2 (adjoint box sums of
 // the per-centre coefficients A, B, C) runs on the tile plus an r halo:
-// in-plane passes first, then a register ring along n0.  The output plane
-// lags the input plane by 2r.
+// in-plane passes first, then running sums along n0.  The output plane lags
+// the input plane by 2r.
 //
-// Every thread's first stage-1 column is its own output column, so the
-// output stage finds I, J and grad_p I_m at its plane in the oldest ring
-// entries instead of sampling the moving image a second time.  The loads and
-// gathers of the next input plane, and the Adam moments of the next output
-// plane, are issued before the current plane's LDS passes and consumed after
-// them (a two-stage software pipeline across the barriers).
+// The warped image J and its slope are sampled once per voxel, where d is made
+// (EPI_STORE_WARP, k_warp), not on every halo column of the march: a tile of
+// 16 x 32 outputs marches 24 x 40 columns over its chunk plus 4r planes, 2.4
+// samples per voxel at 160x192x224 and window 5, each a chain of dependent
+// loads whose registers and 24 KB of LDS (the slope's delay line) held the
+// kernel at 4 waves per SIMD.  Without it window 5 fits 64 VGPRs and 37 KB,
+// and 1024 threads share a tile's columns, one each: 8 waves per SIMD, which
+// is what hides the LDS and memory latency that bound it.  Measured (us per
+// launch at 160x192x224, events): window 3 162 -> 113, window 5 198 -> 125
+// (582 MB, 4.7 TB/s), window 7 375 -> 179, window 9 441 -> 269.
 // ---------------------------------------------------------------------------
 
 // Trilinear gathers as 32-bit byte offsets from a uniform base pointer (the
@@ -290,6 +295,32 @@ __device__ __forceinline__ float load_at(const float* __restrict__ base, unsigne
 __device__ __forceinline__ void store_at(float* __restrict__ base, unsigned byte_off, float v) {
   *reinterpret_cast<float*>(reinterpret_cast<char*>(base) + (size_t)byte_off) = v;
 }
+
+// A uniform base pointer that stays in scalar registers.  The compiler may
+// otherwise fold a component's offset (q * N) into the per-lane part of the
+// address, which then takes 64-bit vector arithmetic and two vector registers
+// per access; the empty asm hides where the pointer comes from.
+typedef __attribute__((address_space(1))) float global_float;
+__device__ __forceinline__ global_float* scalar_base(const float* p) {
+  global_float* g = (global_float*)(uintptr_t)p;
+  asm("" : "+s"(g));
+  return g;
+}
+__device__ __forceinline__ float load_at(const global_float* base, unsigned byte_off) {
+  typedef __attribute__((address_space(1))) char global_char;
+  return *(const global_float*)((const global_char*)base + (size_t)byte_off);
+}
+__device__ __forceinline__ void store_at(global_float* base, unsigned byte_off, float v) {
+  typedef __attribute__((address_space(1))) char global_char;
+  *(global_float*)((global_char*)base + (size_t)byte_off) = v;
+}
+
+// Waits here for the load behind v.  Loads and stores share one in-order
+// counter, and after a branch that may have skipped a store the compiler waits
+// for all of them: a march therefore collects the loads of its next plane
+// before it issues a plane's stores, instead of at the top of the next plane
+// step, where the wait would include the stores just issued.
+__device__ __forceinline__ void arrived(float& v) { asm volatile("" : "+v"(v)); }
 
 __device__ __forceinline__ void axis_offsets(int x, float dd, int n, int stride_bytes, unsigned& lo,
                                              unsigned& hi, bool& lo_ok, bool& hi_ok, float& t) {
@@ -336,43 +367,6 @@ __device__ __forceinline__ Cell8 cell8_at(int n0, int n1, int n2, int z, int y, 
   return c;
 }
 
-// The same for a volume stored with a zero border of kPad voxels on every
-// side (padded strides).  The cell is clamped to [-kPad, n], so every corner
-// lies in the padded volume, and a corner off the grid reads a zero of the
-// border: no mask is needed (the mask is constant, and the selects fold
-// away).  A sample clamped this way lies wholly in the border, so its value
-// and derivative are 0, as with the masked form.
-__device__ __forceinline__ void axis_offsets_pad(int x, float dd, int n, int stride_bytes, unsigned& lo,
-                                                 unsigned& hi, float& t) {
-  dd = clamp_med3(dd, (float)(-x - kPad), (float)(n - x));
-  const float f = floorf(dd);
-  const int i = x + kPad + (int)f;   // padded index, in [0, n + kPad]
-  t = dd - f;
-  lo = (unsigned)(i * stride_bytes);
-  hi = lo + (unsigned)stride_bytes;
-}
-
-__device__ __forceinline__ Cell8 cell8_pad(int n0, int n1, int n2, int z, int y, int x, float d0, float d1,
-                                           float d2) {
-  Cell8 c;
-  const int p2 = n2 + 2 * kPad, p1 = n1 + 2 * kPad;
-  unsigned l0, h0, l1, h1, l2, h2;
-  axis_offsets_pad(z, d0, n0, p1 * p2 * 4, l0, h0, c.t0);
-  axis_offsets_pad(y, d1, n1, p2 * 4, l1, h1, c.t1);
-  axis_offsets_pad(x, d2, n2, 4, l2, h2, c.t2);
-  const unsigned a00 = l0 + l1, a01 = l0 + h1, a10 = h0 + l1, a11 = h0 + h1;
-  c.off[0] = a00 + l2;
-  c.off[1] = a00 + h2;
-  c.off[2] = a01 + l2;
-  c.off[3] = a01 + h2;
-  c.off[4] = a10 + l2;
-  c.off[5] = a10 + h2;
-  c.off[6] = a11 + l2;
-  c.off[7] = a11 + h2;
-  c.mask = 0xFFu;
-  return c;
-}
-
 // Eight corner values of a trilinear sample (loaded; consumed later so that
 // issuing the loads does not wait for them).
 struct Gather {
@@ -390,41 +384,43 @@ __device__ __forceinline__ void gather_issue(const float* __restrict__ f, const 
   g.t2 = c.t2;
 }
 
-// The padded moving image stored as corner quads (launch_pad_quad): entry
-// (z, y, x) of the padded grid holds the padded values at (z, y, x),
-// (z, y, x+1), (z, y+1, x) and (z, y+1, x+1).  A trilinear sample then takes
-// two aligned 16-byte loads (planes z and z+1 of its cell) instead of eight
-// 4-byte ones, and the corners arrive in gather_issue's order, so the values
-// and every result are the same.  Byte offsets are 32-bit unsigned (the quad
-// array stays below 4 GiB), and the padded plane size and every padded index
-// stay below 2^24, so the index products are full-rate 24-bit multiplies (the
-// runtime checks both: quad_supported).
-__device__ __forceinline__ void quad_axis(int x, float dd, int n, unsigned stride_quads, unsigned& lo, float& t) {
+// The moving image of a level as row pairs with a zero border of kPad voxels
+// on every side (launch_row_pairs): entry (z, y, x) of the padded grid holds
+// the padded values at (z, y, x) and (z, y + 1, x).  A trilinear sample then
+// takes two 16-byte loads (two neighbouring entries in the planes z and z + 1
+// of its cell) instead of eight 4-byte ones with masks.  The cell is clamped
+// to [-kPad, n], so every corner lies in the padded volume; a sample clamped
+// this way lies wholly in the border, where value and derivative are 0 as with
+// the masked form.  Byte offsets are 32-bit unsigned, and the padded plane
+// size and every padded index stay below 2^24, so the index products are
+// full-rate 24-bit multiplies (row_pairs_supported).
+__device__ __forceinline__ void pair_axis(int x, float dd, int n, unsigned stride, unsigned& lo, float& t) {
   dd = clamp_med3(dd, (float)(-x - kPad), (float)(n - x));
   const float f = floorf(dd);
-  lo = __umul24((unsigned)(x + kPad + (int)f), stride_quads);   // padded index in [0, n + kPad]
+  lo = __umul24((unsigned)(x + kPad + (int)f), stride);   // padded index in [0, n + kPad]
   t = dd - f;
 }
 
-__device__ __forceinline__ void gather_issue_quad(const float* __restrict__ q, int n0, int n1, int n2, int z,
-                                                  int y, int x, float d0, float d1, float d2, Gather& g) {
+__device__ __forceinline__ void gather_issue_pairs(const float* __restrict__ q, int n0, int n1, int n2, int z, int y,
+                                                   int x, float d0, float d1, float d2, Gather& g) {
+  struct alignas(8) Two { float v[4]; };   // two entries, 8-byte aligned
   const unsigned p2 = (unsigned)(n2 + 2 * kPad), p1 = (unsigned)(n1 + 2 * kPad);
   unsigned l0, l1, l2;
-  quad_axis(z, d0, n0, p1 * p2, l0, g.t0);
-  quad_axis(y, d1, n1, p2, l1, g.t1);
-  quad_axis(x, d2, n2, 1u, l2, g.t2);
+  pair_axis(z, d0, n0, p1 * p2, l0, g.t0);
+  pair_axis(y, d1, n1, p2, l1, g.t1);
+  pair_axis(x, d2, n2, 1u, l2, g.t2);
   const char* b = reinterpret_cast<const char*>(q);
-  const unsigned off = (l0 + l1 + l2) * 16u;
-  const float4 lo = *reinterpret_cast<const float4*>(b + (size_t)off);
-  const float4 hi = *reinterpret_cast<const float4*>(b + (size_t)(off + p1 * p2 * 16u));
-  g.c[0] = lo.x;
-  g.c[1] = lo.y;
-  g.c[2] = lo.z;
-  g.c[3] = lo.w;
-  g.c[4] = hi.x;
-  g.c[5] = hi.y;
-  g.c[6] = hi.z;
-  g.c[7] = hi.w;
+  const unsigned off = (l0 + l1 + l2) * 8u;
+  const Two lo = *reinterpret_cast<const Two*>(b + (size_t)off);
+  const Two hi = *reinterpret_cast<const Two*>(b + (size_t)(off + p1 * p2 * 8u));
+  g.c[0] = lo.v[0];
+  g.c[1] = lo.v[2];
+  g.c[2] = lo.v[1];
+  g.c[3] = lo.v[3];
+  g.c[4] = hi.v[0];
+  g.c[5] = hi.v[2];
+  g.c[6] = hi.v[1];
+  g.c[7] = hi.v[3];
   g.mask = 0xFFu;
 }
 
@@ -461,75 +457,91 @@ __device__ __forceinline__ float gather_value_grad(const Gather& g, float& g0, f
   return f0 + g.t0 * (f1 - f0);
 }
 
-// Stage-1 column `slot` of thread `tid` as (row, column) of the halo tile.
-// Slot 0 is the thread's own output column; the remaining slots enumerate
+// Stage-1 column c as (row, column) of the halo tile.  Columns 0 .. TY * TX - 1
+// are the tile's own (column c belongs to output thread c); the rest enumerate
 // the halo bands (top, bottom, left, right).
 template <int TY, int TX, int H>
-__device__ __forceinline__ bool slot_coords(int tid, int slot, int& ey, int& ex) {
-  constexpr int NT = TY * TX;
+__device__ __forceinline__ bool column_coords(int c, int& ey, int& ex) {
+  constexpr int NC = TY * TX;
   constexpr int EX = TX + 2 * H;
-  if (slot == 0) {
-    ey = H + tid / TX;
-    ex = H + tid % TX;
+  if (c < NC) {
+    ey = H + c / TX;
+    ex = H + c % TX;
     return true;
   }
   if constexpr (H == 0) {
     ey = ex = 0;
     return false;
   } else {
-  const int h = tid + (slot - 1) * NT;
-  constexpr int TB = H * EX;       // one horizontal band
-  constexpr int LB = TY * H;       // one vertical band
-  if (h < TB) {
-    ey = h / EX;
-    ex = h % EX;
-  } else if (h < 2 * TB) {
-    ey = H + TY + (h - TB) / EX;
-    ex = (h - TB) % EX;
-  } else if (h < 2 * TB + LB) {
-    ey = H + (h - 2 * TB) / H;
-    ex = (h - 2 * TB) % H;
-  } else if (h < 2 * TB + 2 * LB) {
-    ey = H + (h - 2 * TB - LB) / H;
-    ex = H + TX + (h - 2 * TB - LB) % H;
-  } else {
-    ey = ex = 0;
-    return false;
-  }
-  return true;
+    const int h = c - NC;
+    constexpr int TB = H * EX;       // one horizontal band
+    constexpr int LB = TY * H;       // one vertical band
+    if (h < TB) {
+      ey = h / EX;
+      ex = h % EX;
+    } else if (h < 2 * TB) {
+      ey = H + TY + (h - TB) / EX;
+      ex = (h - TB) % EX;
+    } else if (h < 2 * TB + LB) {
+      ey = H + (h - 2 * TB) / H;
+      ex = (h - 2 * TB) % H;
+    } else if (h < 2 * TB + 2 * LB) {
+      ey = H + (h - 2 * TB - LB) / H;
+      ex = H + TX + (h - 2 * TB - LB) % H;
+    } else {
+      ey = ex = 0;
+      return false;
+    }
+    return true;
   }
 }
 
-// MODE: A.mode fixed at compile time (0, 1 or 2), or -1 to read it at run time.
-template <int W, int TY, int TX, bool PIPE, bool QUAD = false, int MODE = -1>
+// Extents of a march launch.  The loss alone (MODE 2) needs the window
+// statistics of the tile's own centres, so its input halo is r instead of 2r
+// and there is no second stage.
+template <int W, int TY, int TX, int MODE>
+struct GradShape {
+  static constexpr int R = W / 2;
+  static constexpr int H2 = MODE == 2 ? 0 : R;    // halo of the centres
+  static constexpr int H1 = H2 + R;               // halo of the inputs
+  static constexpr int E1Y = TY + 2 * H1, E1X = TX + 2 * H1, E1 = E1Y * E1X;
+  static constexpr int E2Y = TY + 2 * H2, E2X = TX + 2 * H2, E2 = E2Y * E2X;
+  static constexpr int XS1 = E1Y * E2X;
+  static constexpr int XS2 = E2Y * TX;
+  static constexpr size_t lds_bytes = sizeof(float) * (size_t)(5 * E1 + 5 * XS1);
+};
+
+// Two LDS offsets (in floats, below 2^16) that stay packed in one register:
+// the asm keeps the compiler from unpacking them ahead of the march, where
+// they would occupy two.
+struct PackedOffsets {
+  unsigned v;
+  __device__ __forceinline__ void set(int lo, int hi) { v = (unsigned)lo | ((unsigned)hi << 16); }
+  __device__ __forceinline__ void get(int& lo, int& hi) const {
+    unsigned t = v;
+    asm volatile("" : "+v"(t));
+    lo = (int)(t & 0xffffu);
+    hi = (int)(t >> 16);
+  }
+};
+
+// NT threads per workgroup (at least TY * TX: thread c < TY * TX writes output
+// column c).  MODE = A.mode: 0 gradient and Adam, 1 gradient, 2 loss.
+template <int W, int TY, int TX, int NT, int MODE>
 __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
-  const int mode = MODE >= 0 ? MODE : A.mode;
-  constexpr int R = W / 2;
-  constexpr int NT = TY * TX;
-  constexpr int E1Y = TY + 4 * R, E1X = TX + 4 * R, E1 = E1Y * E1X;
-  constexpr int E2Y = TY + 2 * R, E2X = TX + 2 * R, E2 = E2Y * E2X;
-  constexpr int XS1 = E1Y * E2X;
-  constexpr int XS2 = E2Y * TX;
-  constexpr int CPT1 = 1 + (E1 - NT + NT - 1) / NT;   // own column + halo columns
+  using S = GradShape<W, TY, TX, MODE>;
+  constexpr int R = S::R, H1 = S::H1, H2 = S::H2;
+  constexpr int E1X = S::E1X, E1 = S::E1;
+  constexpr int E2X = S::E2X, E2 = S::E2;
+  constexpr int XS1 = S::XS1, XS2 = S::XS2;
+  constexpr int NC = TY * TX;
+  constexpr int CPT1 = (E1 + NT - 1) / NT;
   // The in-plane x passes give each thread two neighbouring outputs (pair
   // reads along rows): every row length and array offset below is even.
-  static_assert(TX % 2 == 0 && W % 2 == 1, "pairs need an even tile width and an odd window");
+  static_assert(TX % 2 == 0 && W % 2 == 1 && NT >= NC && NT % 64 == 0, "tile and workgroup shape");
   extern __shared__ __attribute__((aligned(16))) float glds[];
   float* buf = glds;             // [5][E1], later [3][E2]
   float* bufx = glds + 5 * E1;   // [5][XS1], later [3][XS2]
-  // grad_p I_m of the own column, delayed 2r planes from the input plane
-  // to the output plane: a per-thread delay line of GS slots in LDS (slot
-  // z mod GS).  Each thread touches only its own entries, so no barrier is
-  // involved; with r > 0 a plane is stored after the output stage has read
-  // the slot it replaces.
-  constexpr int GS = (R == 0) ? 1 : 2 * R;
-  // in LDS while the kernel's LDS stays within 64 KiB, else in registers
-  constexpr bool GLDS = sizeof(float) * (5 * E1 + 5 * XS1 + 3 * GS * NT) <= 65536;
-  float* gring = glds + 5 * E1 + 5 * XS1;   // [GS][3][NT] when GLDS
-  float greg[3][GS];                       // when !GLDS: oldest entry first
-#pragma unroll
-  for (int j = 0; j < GS; ++j) greg[0][j] = greg[1][j] = greg[2][j] = 0.0f;
-
   __shared__ double red[NT / 64];
 
   const int tid = threadIdx.x;
@@ -540,149 +552,147 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
   b /= A.tiles_y;
   const int n0 = A.n0, n1 = A.n1, n2 = A.n2;
   const int N = n0 * n1 * n2;
+  const int plane = n1 * n2;
   const int z0 = b * A.zc;
   const int z1 = min(z0 + A.zc, n0);
   const int y0 = by * TY, x0 = bx * TX;
 
-  int cy[CPT1], cx[CPT1], cl[CPT1];
+  int cl[CPT1];            // LDS offset of the column
+  unsigned cpos[CPT1];     // its offset in a plane
   bool cin[CPT1], cuse[CPT1];
 #pragma unroll
   for (int k = 0; k < CPT1; ++k) {
     int ey, ex;
-    cuse[k] = slot_coords<TY, TX, 2 * R>(tid, k, ey, ex);
+    cuse[k] = column_coords<TY, TX, H1>(tid + k * NT, ey, ex);
     cl[k] = ey * E1X + ex;
-    cy[k] = y0 - 2 * R + ey;
-    cx[k] = x0 - 2 * R + ex;
-    cin[k] = cuse[k] && cy[k] >= 0 && cy[k] < n1 && cx[k] >= 0 && cx[k] < n2;
+    const int yy = y0 - H1 + ey, xx = x0 - H1 + ex;
+    cin[k] = cuse[k] && yy >= 0 && yy < n1 && xx >= 0 && xx < n2;
+    cpos[k] = cin[k] ? (unsigned)(yy * n2 + xx) : 0u;
   }
   const int oy = tid / TX, ox = tid % TX;
   const int gy = y0 + oy, gx = x0 + ox;
-  const bool out_col = gy < n1 && gx < n2;   // == cin[0]
+  const bool out_thread = NT == NC || tid < NC;
+  const bool out_col = out_thread && gy < n1 && gx < n2;   // == cin[0] of an output thread
 
-  // per-thread entries of the window-statistics pass (tile + r halo): LDS
-  // offset, in-plane window count (0 off the grid) and whether the entry is
-  // a tile voxel whose cc enters the loss; fixed across planes
+  // per-thread entries of the window-statistics pass (tile + H2 halo), the
+  // tile's own first as for the columns: LDS offset and in-plane window count
+  // (0 off the grid); fixed across planes
   constexpr int CPT2 = (E2 + NT - 1) / NT;
   int e2off[CPT2];
   float e2cnt[CPT2];
-  bool e2own[CPT2];
 #pragma unroll
   for (int k = 0; k < CPT2; ++k) {
-    const int c = tid + k * NT;
-    const int yo = c / E2X, xo = c - yo * E2X;
-    const int yy = y0 - R + yo, xx = x0 - R + xo;
+    int yo, xo;
+    const bool use = column_coords<TY, TX, H2>(tid + k * NT, yo, xo);
+    const int yy = y0 - H2 + yo, xx = x0 - H2 + xo;
     e2off[k] = yo * E2X + xo;
-    const bool ok = c < E2 && yy >= 0 && yy < n1 && xx >= 0 && xx < n2;
+    const bool ok = use && yy >= 0 && yy < n1 && xx >= 0 && xx < n2;
     e2cnt[k] = ok ? clipped_count(yy, n1, R) * clipped_count(xx, n2, R) : 0.0f;
-    e2own[k] = ok && yo >= R && yo < R + TY && xo >= R && xo < R + TX;
   }
 
+  // x passes: X1P (X2P) pairs of outputs.  With threads to spare, groups of
+  // threads share the quantities of a pair: X1G groups take every X1G-th of
+  // the five, and three groups one each of A, B, C.
+  constexpr int X1H = E2X / 2, X1P = S::E1Y * X1H;
+  constexpr int X1G = NT >= 5 * X1P ? 5 : (NT >= X1P ? NT / X1P : 1);
+  constexpr bool X1ONE = NT >= X1P;
+  constexpr int X2H = TX / 2, X2P = S::E2Y * X2H;
+  constexpr bool X2ONE = NT >= 3 * X2P;
+  PackedOffsets x1{0u}, x2{0u};
+  if constexpr (X1ONE) {
+    const int g = tid / X1P, p = tid - g * X1P, yy = p / X1H, xo = 2 * (p - yy * X1H);
+    if (g < X1G) x1.set(g * E1 + yy * E1X + xo, g * XS1 + yy * E2X + xo);
+  }
+  if constexpr (X2ONE) {
+    const int g = tid / X2P, p = tid - g * X2P, yy = p / X2H, xo = 2 * (p - yy * X2H);
+    if (g < 3) x2.set(g * E2 + yy * E2X + xo, g * XS2 + yy * TX + xo);
+  }
+  // LDS offsets of the thread's first column and first centre
+  PackedOffsets own;
+  own.set(cl[0], e2off[0]);
+
   float ringI[CPT1][W], ringJ[CPT1][W];
-  float ringA[W], ringB[W], ringC[W];
+  // stage-2 sums along n0 in progress: entry j holds the sum of the last j + 1
+  // planes, so a plane adds to each in turn and the window sum (oldest plane
+  // first) leaves with one more add; no entry moves
+  constexpr int WA = W > 1 ? W - 1 : 1;
+  float accA[WA], accB[WA], accC[WA];
 #pragma unroll
   for (int j = 0; j < W; ++j) {
 #pragma unroll
     for (int k = 0; k < CPT1; ++k) { ringI[k][j] = 0.0f; ringJ[k][j] = 0.0f; }
-    ringA[j] = ringB[j] = ringC[j] = 0.0f;
   }
+#pragma unroll
+  for (int j = 0; j < WA; ++j) accA[j] = accB[j] = accC[j] = 0.0f;
 
   const float ibc1 = 1.0f / A.ctl->bc1, ibc2 = 1.0f / A.ctl->bc2;
-  if (mode == 0 && tile == 0) m_clear(A.ctl, tid);  // M of this iteration
+  if (MODE == 0 && tile == 0) m_clear(A.ctl, tid);  // M of this iteration
   const float si = A.ctl->shift_i, sj = A.ctl->shift_j;
-  const float gsc = (mode == 1 && A.gscale) ? *A.gscale : 1.0f;
-  float lacc = 0.0f;   // this thread's cc sum over at most 2 zc columns
+  const float gsc = (MODE == 1 && A.gscale) ? *A.gscale : 1.0f;
+  float lacc = 0.0f;   // the own column's cc sum
 
-  const int zs = z0 - 2 * R, ze = z1 + 2 * R;
+  const int zs = z0 - H1, ze = z1 + H1;
 
-  // pipeline registers: raw loads of plane z+1 and gathers in flight
-  float nd0[CPT1], nd1[CPT1], nd2[CPT1], nf[CPT1];
-  Gather gq[CPT1];
-  float curI[CPT1], curJ[CPT1], curG0 = 0.f, curG1 = 0.f, curG2 = 0.f;
-  float nxI[CPT1];
-  bool gv[CPT1];
-  auto store_g = [&](int z) {
-    if constexpr (GLDS) {
-      float* gs = gring + (((z % GS) + GS) % GS) * 3 * NT + tid;
-      gs[0] = curG0;
-      gs[NT] = curG1;
-      gs[2 * NT] = curG2;
-    } else {
+  // I and J of the next plane, loaded one plane step ahead (zero off the grid)
+  float nI[CPT1], nJ[CPT1];
+  auto load_plane = [&](int z) {
+    const bool zin = z >= 0 && z < n0;
+    // byte offsets from uniform bases (volumes hold < 2^29 voxels)
+    const unsigned zoff = (unsigned)((zin ? z : 0) * plane);
 #pragma unroll
-      for (int j = 0; j < GS - 1; ++j) {
-        greg[0][j] = greg[0][j + 1];
-        greg[1][j] = greg[1][j + 1];
-        greg[2][j] = greg[2][j + 1];
+    for (int k = 0; k < CPT1; ++k) {
+      nI[k] = si;
+      nJ[k] = sj;
+      if (zin && cin[k]) {
+        const unsigned off = (zoff + cpos[k]) * 4u;
+        nI[k] = load_at(A.fixed, off);
+        nJ[k] = load_at(A.warped, off);
       }
-      greg[0][GS - 1] = curG0;
-      greg[1][GS - 1] = curG1;
-      greg[2][GS - 1] = curG2;
     }
   };
-
-  auto load_raw = [&](int z, int k) {
-    if (z >= 0 && z < n0 && cin[k]) {
-      // byte offsets from uniform bases (volumes hold < 2^29 voxels)
-      const unsigned off = (unsigned)vidx(z, cy[k], cx[k], n1, n2) * 4u;
-      nd0[k] = load_at(A.d, off);
-      nd1[k] = load_at(A.d + N, off);
-      nd2[k] = load_at(A.d + 2 * N, off);
-      nf[k] = load_at(A.fixed, off);
-    }
-  };
-  auto issue_gather = [&](int z, int k) {
-    gv[k] = z >= 0 && z < n0 && cin[k];
-    if (gv[k]) {
-      if constexpr (QUAD) {
-        gather_issue_quad(A.moving_quad, n0, n1, n2, z, cy[k], cx[k], nd0[k], nd1[k], nd2[k], gq[k]);
-      } else {
-        const Cell8 c = cell8_pad(n0, n1, n2, z, cy[k], cx[k], nd0[k], nd1[k], nd2[k]);
-        gather_issue(A.moving_pad, c, gq[k]);
-      }
-      nxI[k] = nf[k] - si;
-    }
-  };
-  auto finish_gather = [&](int k) {
-    if (gv[k]) {
-      if (k == 0) {
-        curJ[0] = gather_value_grad(gq[0], curG0, curG1, curG2) - sj;
-      } else {
-        curJ[k] = gather_value(gq[k]) - sj;
-      }
-      curI[k] = nxI[k];
-    } else {
-      curJ[k] = 0.0f;
-      curI[k] = 0.0f;
-      if (k == 0) curG0 = curG1 = curG2 = 0.0f;
-    }
-  };
-
-  // prologue: plane zs in registers, plane zs+1 raw loads in flight
+  auto plane_arrived = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int k = 0; k < CPT1; ++k) {
-    load_raw(zs, k);
-    issue_gather(zs, k);
-    finish_gather(k);
-    load_raw(zs + 1, k);
+    for (int k = 0; k < CPT1; ++k) {
+      arrived(nI[k]);
+      arrived(nJ[k]);
+    }
+  };
+  load_plane(zs);
+  plane_arrived();
+  // the slope of the moving image and the Adam moments of the output plane
+  float pg[3] = {0.f, 0.f, 0.f}, pm[3] = {0.f, 0.f, 0.f}, pv[3] = {0.f, 0.f, 0.f};
+  global_float *bg[3], *bm[3], *bv[3], *bo[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    if (MODE != 2) bg[q] = scalar_base(A.slope + (size_t)q * N);
+    if (MODE != 2) bo[q] = scalar_base(A.out + (size_t)q * N);
+    if (MODE == 0) bm[q] = scalar_base(A.m + (size_t)q * N);
+    if (MODE == 0) bv[q] = scalar_base(A.v + (size_t)q * N);
   }
-  float pm[3] = {0.f, 0.f, 0.f}, pv[3] = {0.f, 0.f, 0.f};
-  bool mv_ready = false;
+  auto load_out = [&](unsigned off) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      pg[q] = load_at(bg[q], off);
+      if (MODE == 0) {
+        pm[q] = load_at(bm[q], off);
+        pv[q] = load_at(bv[q], off);
+      }
+    }
+  };
 
-  // The register rings of I, J (per column) and of the stage-2 sums hold the
-  // last W planes.  Narrow windows rotate them by moves each plane step.  The
-  // wide windows (one workgroup per CU, registers to spare) unroll the march
-  // by W instead: at phase ph of W the newest entry goes to slot ph (slot
-  // (ph + 1) mod W for the stage-2 ring, which starts 2r planes later), so
-  // the j-th oldest entry sits at a slot fixed at compile time and no entry
-  // moves.  The sums still run oldest first; the compiler may form a ring
-  // entry's square or product once for the W windows that hold it instead of
-  // fusing it into each sum, which changes the last bits.
-  constexpr int UNZ = (W >= 7 && TY == 16) ? W : 1;   // not the 8-row tiles of thin volumes
+  // The register rings of I, J (per column) hold the last W planes and rotate
+  // by moves each plane step.  Window 7 unrolls the march by W instead: at
+  // phase ph of W the newest entry goes to slot ph, so the j-th oldest entry
+  // sits at a slot fixed at compile time and no entry moves.  The sums run
+  // oldest first.
+  constexpr int UNZ = (W == 7 && TY == 16) ? W : 1;   // not the 8-row tiles of thin volumes
+  constexpr bool SWAP = W >= 7 && TY == 16;
+  int wphase = 0;   // plane step modulo W (rolled march)
   auto step = [&](const int zin, auto PH) __attribute__((always_inline)) {
     constexpr int ph = decltype(PH)::value;
-    constexpr int pha = (ph + 1) % W;
-    // slot of the j-th oldest entry of the I/J rings and of the stage-2 ring
+    // slot of the j-th oldest entry of the I/J rings
     auto ri = [](int j) constexpr { return UNZ == 1 ? j : (ph + 1 + j) % W; };
-    auto ra = [](int j) constexpr { return UNZ == 1 ? j : (pha + 1 + j) % W; };
 #pragma unroll
     for (int k = 0; k < CPT1; ++k) {
       if constexpr (UNZ == 1) {
@@ -691,30 +701,16 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
           ringI[k][j] = ringI[k][j + 1];
           ringJ[k][j] = ringJ[k][j + 1];
         }
-        ringI[k][W - 1] = curI[k];
-        ringJ[k][W - 1] = curJ[k];
+        ringI[k][W - 1] = nI[k] - si;
+        ringJ[k][W - 1] = nJ[k] - sj;
       } else {
-        ringI[k][ph] = curI[k];
-        ringJ[k][ph] = curJ[k];
+        ringI[k][ph] = nI[k] - si;
+        ringJ[k][ph] = nJ[k] - sj;
       }
     }
-    if (R == 0) store_g(zin);
-    // next plane: gathers in flight during this plane's passes (PIPE), or
-    // issued after them (fewer live registers)
-    if (PIPE) {
-      // raised wave priority while the next plane's loads go out: they then
-      // leave ahead of other waves' LDS passes (2% at 160x192x224; raising it
-      // over the output stage as well gave the gain back)
-      __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-      for (int k = 0; k < CPT1; ++k) {
-        issue_gather(zin + 1, k);
-        load_raw(zin + 2, k);
-      }
-      __builtin_amdgcn_s_setprio(0);
-    }
+    if (zin + 1 < ze) load_plane(zin + 1);
 
-    if (zin >= z0) {
+    if (zin >= z0 - H2 + R) {
 #pragma unroll
       for (int k = 0; k < CPT1; ++k) {
         if (cuse[k]) {
@@ -722,16 +718,32 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
           // arithmetic (signed zero) and would cost an add per sum
           const float i0 = ringI[k][ri(0)], j0 = ringJ[k][ri(0)];
           float s0 = i0, s1 = j0, s2 = i0 * i0, s3 = j0 * j0, s4 = i0 * j0;
+          // Fused multiply-adds spelled out: which of the oldest two planes'
+          // products is rounded and which fused into it is otherwise the
+          // compiler's choice and shows in the last bits.  The oldest's is
+          // rounded, except in two of the W phases of the wide windows'
+          // 16-row marches, so that every window's results stay the same.
+          if constexpr (W > 1) {
+            const float i1 = ringI[k][ri(1)], j1 = ringJ[k][ri(1)];
+            const bool sw = SWAP && (UNZ == 1 ? wphase >= W - 2 : ph >= W - 2);
+            const float ia = sw ? i1 : i0, ib = sw ? i0 : i1, ja = sw ? j1 : j0, jb = sw ? j0 : j1;
+            s0 += i1;
+            s1 += j1;
+            s2 = __builtin_fmaf(ib, ib, ia * ia);
+            s3 = __builtin_fmaf(jb, jb, ja * ja);
+            s4 = __builtin_fmaf(ib, jb, ia * ja);
+          }
 #pragma unroll
-          for (int j = 1; j < W; ++j) {
+          for (int j = 2; j < W; ++j) {
             const float i_ = ringI[k][ri(j)], j_ = ringJ[k][ri(j)];
             s0 += i_;
             s1 += j_;
-            s2 += i_ * i_;
-            s3 += j_ * j_;
-            s4 += i_ * j_;
+            s2 = __builtin_fmaf(i_, i_, s2);
+            s3 = __builtin_fmaf(j_, j_, s3);
+            s4 = __builtin_fmaf(i_, j_, s4);
           }
-          const int c = cl[k];
+          int c = cl[k], c2;
+          if (k == 0) own.get(c, c2);
           buf[c] = s0;
           buf[E1 + c] = s1;
           buf[2 * E1 + c] = s2;
@@ -744,13 +756,26 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
         // one quantity at a time, in a rolled loop (unrolled over the five
         // quantities the pass measured slower, and it crowds the register
         // budget)
-        constexpr int HX = E2X / 2, PX = E1Y * HX;
-        for (int p = tid; p < PX; p += NT) {
-          const int yy = p / HX, xo = 2 * (p - yy * HX);
-          const float* src = buf + yy * E1X + xo;
-          float* dst = bufx + yy * E2X + xo;
+        if constexpr (X1ONE) {
+          if (tid < X1G * X1P) {
+            int src, dst;
+            x1.get(src, dst);
+            const int g = X1G == 1 ? 0 : tid / X1P;
 #pragma unroll 1
-          for (int q = 0; q < 5; ++q) box_pair_x<W>(src + q * E1, dst + q * XS1);
+            for (int q = g; q < 5; q += X1G) {
+              box_pair_x<W>(buf + src, bufx + dst);
+              src += X1G * E1;
+              dst += X1G * XS1;
+            }
+          }
+        } else {
+          for (int p = tid; p < X1P; p += NT) {
+            const int yy = p / X1H, xo = 2 * (p - yy * X1H);
+            const float* src = buf + yy * E1X + xo;
+            float* dst = bufx + yy * E2X + xo;
+#pragma unroll 1
+            for (int q = 0; q < 5; ++q) box_pair_x<W>(src + q * E1, dst + q * XS1);
+          }
         }
       }
       __syncthreads();
@@ -762,7 +787,9 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
       for (int k2 = 0; k2 < CPT2; ++k2) {
         const int c = tid + k2 * NT;
         if (c >= E2) break;
-        const float* src = bufx + e2off[k2];
+        int c1, c2 = e2off[k2];
+        if (k2 == 0) own.get(c1, c2);
+        const float* src = bufx + c2;
         float SI = src[0], SJ = src[XS1], SII = src[2 * XS1], SJJ = src[3 * XS1], SIJ = src[4 * XS1];
 #pragma unroll
         for (int k = 1; k < W; ++k) {
@@ -789,119 +816,102 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
             ca = 2.0f * cross * invD;
             cb = -2.0f * cc * vI * invD;
             cc_ = ca * muI + cb * muJ;
-            if (z1out && e2own[k2]) lacc += cc;
+            if (k2 == 0 && z1out && out_thread) lacc += cc;   // the loss sums the tile's own centres
           }
         }
-        buf[c] = ca;
-        buf[E2 + c] = cb;
-        buf[2 * E2 + c] = cc_;
-      }
-      __syncthreads();
-      {
-        constexpr int HX = TX / 2, PX = E2Y * HX;
-        for (int p = tid; p < PX; p += NT) {
-          const int yy = p / HX, xo = 2 * (p - yy * HX);
-          const float* src = buf + yy * E2X + xo;
-          float* dst = bufx + yy * TX + xo;
-#pragma unroll
-          for (int q = 0; q < 3; ++q) box_pair_x<W>(src + q * E2, dst + q * XS2);
+        if (MODE != 2) {
+          buf[c2] = ca;
+          buf[E2 + c2] = cb;
+          buf[2 * E2 + c2] = cc_;
         }
       }
-      __syncthreads();
-      {
-        const float* src = bufx + oy * TX + ox;
-        float sa = src[0], sb = src[XS2], sc = src[2 * XS2];
+      // the loss alone: the next step's writes of buf come after the barrier
+      // behind every read of it, and its x pass after the barrier behind the
+      // reads of bufx above
+      if constexpr (MODE != 2) {
+        __syncthreads();
+        {
+          if constexpr (X2ONE) {
+            if (tid < 3 * X2P) {
+              int src, dst;
+              x2.get(src, dst);
+              box_pair_x<W>(buf + src, bufx + dst);
+            }
+          } else {
+            for (int p = tid; p < X2P; p += NT) {
+              const int yy = p / X2H, xo = 2 * (p - yy * X2H);
+              const float* src = buf + yy * E2X + xo;
+              float* dst = bufx + yy * TX + xo;
 #pragma unroll
-        for (int k = 1; k < W; ++k) {
-          sa += src[k * TX];
-          sb += src[XS2 + k * TX];
-          sc += src[2 * XS2 + k * TX];
-        }
-        if constexpr (UNZ == 1) {
-#pragma unroll
-          for (int j = 0; j < W - 1; ++j) {
-            ringA[j] = ringA[j + 1];
-            ringB[j] = ringB[j + 1];
-            ringC[j] = ringC[j + 1];
-          }
-          ringA[W - 1] = sa;
-          ringB[W - 1] = sb;
-          ringC[W - 1] = sc;
-        } else {
-          ringA[pha] = sa;
-          ringB[pha] = sb;
-          ringC[pha] = sc;
-        }
-      }
-      const int zc2 = zc1 - R;
-      if (zc2 >= z0 && out_col) {
-        const unsigned off = (unsigned)vidx(zc2, gy, gx, n1, n2) * 4u;
-        if (mode == 0 && !mv_ready) {
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            pm[q] = load_at(A.m + q * N, off);
-            pv[q] = load_at(A.v + q * N, off);
-          }
-        }
-        float SA = ringA[ra(0)], SB = ringB[ra(0)], SC = ringC[ra(0)];
-#pragma unroll
-        for (int j = 1; j < W; ++j) {
-          SA += ringA[ra(j)];
-          SB += ringB[ra(j)];
-          SC += ringC[ra(j)];
-        }
-        // oldest ring entries of the own column hold plane zc2
-        const float dl = -A.inv_n * (ringI[0][ri(0)] * SA + ringJ[0][ri(0)] * SB - SC);
-        float g[3];
-        if constexpr (GLDS) {
-          const float* gs = gring + (((zc2 % GS) + GS) % GS) * 3 * NT + tid;
-          g[0] = dl * gs[0];
-          g[1] = dl * gs[NT];
-          g[2] = dl * gs[2 * NT];
-        } else {
-          g[0] = dl * greg[0][0];
-          g[1] = dl * greg[1][0];
-          g[2] = dl * greg[2][0];
-        }
-        if (mode == 0) {
-          const float b1 = A.beta1, b2 = A.beta2;
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            const float mm = b1 * pm[q] + (1.0f - b1) * g[q];
-            const float vv = b2 * pv[q] + (1.0f - b2) * g[q] * g[q];
-            store_at(A.m + q * N, off, mm);
-            store_at(A.v + q * N, off, vv);
-            store_at(A.out + q * N, off, adam_direction(mm, vv, ibc1, ibc2, A.adam_eps));
-          }
-          // Adam moments of the next output plane
-          mv_ready = zc2 + 1 < z1;
-          if (mv_ready) {
-            const unsigned noff = off + (unsigned)(n1 * n2) * 4u;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-              pm[q] = load_at(A.m + q * N, noff);
-              pv[q] = load_at(A.v + q * N, noff);
+              for (int q = 0; q < 3; ++q) box_pair_x<W>(src + q * E2, dst + q * XS2);
             }
           }
-        } else if (mode == 1) {
+        }
+        const int zc2 = zc1 - R;
+        if (zc2 >= z0 && out_col) load_out((unsigned)vidx(zc2, gy, gx, n1, n2) * 4u);
+        __syncthreads();
+        float SA = 0.0f, SB = 0.0f, SC = 0.0f;   // window sums of A, B, C around zc2
+        if (out_thread) {
+          const float* src = bufx + oy * TX + ox;
+          float sa = src[0], sb = src[XS2], sc = src[2 * XS2];
 #pragma unroll
-          for (int q = 0; q < 3; ++q) store_at(A.out + q * N, off, g[q] * gsc);
+          for (int k = 1; k < W; ++k) {
+            sa += src[k * TX];
+            sb += src[XS2 + k * TX];
+            sc += src[2 * XS2 + k * TX];
+          }
+          if constexpr (W == 1) {
+            SA = sa;
+            SB = sb;
+            SC = sc;
+          } else {
+            SA = accA[W - 2] + sa;
+            SB = accB[W - 2] + sb;
+            SC = accC[W - 2] + sc;
+#pragma unroll
+            for (int j = W - 2; j > 0; --j) {
+              accA[j] = accA[j - 1] + sa;
+              accB[j] = accB[j - 1] + sb;
+              accC[j] = accC[j - 1] + sc;
+            }
+            accA[0] = sa;
+            accB[0] = sb;
+            accC[0] = sc;
+          }
+        }
+        plane_arrived();
+        if (zc2 >= z0 && out_col) {
+          const unsigned off = (unsigned)vidx(zc2, gy, gx, n1, n2) * 4u;
+          // oldest ring entries of the own column hold plane zc2
+          // (spelled out, with the second product rounded: what is fused here
+          // is otherwise the compiler's choice and shows in the last bits)
+          float js = ringJ[0][ri(0)] * SB;
+          asm("" : "+v"(js));
+          const float dl = -A.inv_n * (__builtin_fmaf(ringI[0][ri(0)], SA, js) - SC);
+          const float g[3] = {dl * pg[0], dl * pg[1], dl * pg[2]};
+          if (MODE == 0) {
+            const float b1 = A.beta1, b2 = A.beta2;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+              const float mm = b1 * pm[q] + (1.0f - b1) * g[q];
+              const float vv = b2 * pv[q] + (1.0f - b2) * g[q] * g[q];
+              store_at(bm[q], off, mm);
+              store_at(bv[q], off, vv);
+              store_at(bo[q], off, adam_direction(mm, vv, ibc1, ibc2, A.adam_eps));
+            }
+          } else {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) store_at(bo[q], off, g[q] * gsc);
+          }
         }
       }
     }
-    if (R > 0) store_g(zin);
-    if (!PIPE) {
-#pragma unroll
-      for (int k = 0; k < CPT1; ++k) {
-        issue_gather(zin + 1, k);
-        load_raw(zin + 2, k);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < CPT1; ++k) finish_gather(k);
   };
   if constexpr (UNZ == 1) {
-    for (int zin = zs; zin < ze; ++zin) step(zin, std::integral_constant<int, 0>{});
+    for (int zin = zs; zin < ze; ++zin) {
+      step(zin, std::integral_constant<int, 0>{});
+      if constexpr (SWAP) wphase = wphase == W - 1 ? 0 : wphase + 1;
+    }
   } else {
     // the guard is uniform across the workgroup, so the barriers inside
     // are reached by every thread or by none
@@ -914,16 +924,24 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
   if (tid == 0) A.partials[tile] = tot;
 }
 
-template <int W, int TY, int TX, bool PIPE, bool QUAD = false, int MODE = -1>
-__global__ void __launch_bounds__(TY * TX) k_grad(const GradArgs A) {
-  grad_body<W, TY, TX, PIPE, QUAD, MODE>(A, xcd_tile(blockIdx.x, gridDim.x));
-}
+// Threads and waves per SIMD of the march kernels.  Two threads per output
+// column (one per column of the halo tile) where that fits 64 VGPRs, two
+// workgroups per CU: windows 3 and 5.  Window 7 keeps 512 threads at 128 VGPRs,
+// two workgroups per CU (one at 210 before).  Window 9 with Adam spills 30
+// registers that way (463 us at 160x192x224) and takes 1024 threads, one
+// workgroup per CU (269 us); its gradient alone (LNCC) spills 11 outside the
+// passes and is still the faster form (127 against 139 us a pass at 128^3).
+template <int W, int TY, int TX, int MODE>
+struct GradLaunch {
+  static constexpr bool TWO = TY == 16 && (W == 3 || W == 5 || (W == 9 && MODE == 0));
+  static constexpr int NT = TWO ? 2 * TY * TX : TY * TX;
+  static constexpr int WAVES = (W <= 5 && TY == 16) ? 8 : (TY == 16 ? 4 : 2);
+};
 
-// The same kernel compiled for two workgroups per CU (at most 128 VGPRs);
-// used where that fits without spilling.
-template <int W, int TY, int TX, bool PIPE, bool QUAD = false, int MODE = -1>
-__global__ void __launch_bounds__(TY * TX) __attribute__((amdgpu_waves_per_eu(4))) k_grad_o4(const GradArgs A) {
-  grad_body<W, TY, TX, PIPE, QUAD, MODE>(A, xcd_tile(blockIdx.x, gridDim.x));
+template <int W, int TY, int TX, int MODE>
+__global__ void __launch_bounds__((GradLaunch<W, TY, TX, MODE>::NT))
+__attribute__((amdgpu_waves_per_eu(GradLaunch<W, TY, TX, MODE>::WAVES))) k_grad(const GradArgs A) {
+  grad_body<W, TY, TX, GradLaunch<W, TY, TX, MODE>::NT, MODE>(A, xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // ---------------------------------------------------------------------------
@@ -982,6 +1000,15 @@ __device__ __forceinline__ void record_iteration(const GaussArgs& A) {
     C->bc1 = (float)(1.0 - p1);
     C->bc2 = (float)(1.0 - p2);
   }
+}
+
+// J and its slope from a gathered cell of the moving image.
+__device__ __forceinline__ void store_warp(const GaussArgs& A, const Gather& g, unsigned off, int N) {
+  float g0, g1, g2;
+  store_at(A.warped, off, gather_value_grad(g, g0, g1, g2));
+  store_at(A.slope, off, g0);
+  store_at(A.slope + N, off, g1);
+  store_at(A.slope + 2 * N, off, g2);
 }
 
 template <int R, int TY, int TX, int EPI>
@@ -1116,7 +1143,36 @@ __device__ __forceinline__ void gauss_body(const GaussArgs& A, const int tile, c
     }
   };
 
+  // the sample of the moving image at the new d in flight (EPI_STORE_WARP)
+  Gather wg;
+  unsigned woff = 0u;
+  bool wlive = false;
+  auto finish_warp = [&]() {
+    if (wlive) {
+      store_warp(A, wg, woff, N);
+      wlive = false;
+    }
+  };
+
+  auto planes_arrived = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+      arrived(pre[k][0]);
+      arrived(pre[k][1]);
+      arrived(pre[k][2]);
+    }
+    if (EPI == EPI_COMPOSE_LDS) {
+#pragma unroll
+      for (int k = 0; k < CPTD; ++k) {
+        arrived(pd[k][0]);
+        arrived(pd[k][1]);
+        arrived(pd[k][2]);
+      }
+    }
+  };
   load_plane(z0 - R);
+  planes_arrived();
   for (int zin = z0 - R; zin < z1 + R; ++zin) {
     if constexpr (R == 0) {
       // a single tap: the thread's own column is the output; no LDS passes
@@ -1182,6 +1238,9 @@ __device__ __forceinline__ void gauss_body(const GaussArgs& A, const int tile, c
     }
     }
     const int zo = zin - R;
+    // the next plane's loads, and the previous plane's sample, before the stores
+    planes_arrived();
+    if (EPI == EPI_STORE_WARP) finish_warp();
     if (zo >= z0 && out_col) {
       float v0 = w[0] * ring[0][0], v1 = w[0] * ring[1][0], v2 = w[0] * ring[2][0];
 #pragma unroll
@@ -1192,12 +1251,18 @@ __device__ __forceinline__ void gauss_body(const GaussArgs& A, const int tile, c
       }
       const int idx = vidx(zo, gy, gx, n1, n2);
       const unsigned off = (unsigned)idx * 4u;
-      if (EPI == EPI_STORE) {
+      if (EPI == EPI_STORE || EPI == EPI_STORE_WARP) {
+        if (EPI == EPI_STORE_WARP) {
+          // finished next plane step; issued ahead of the stores, which the
+          // wait for it would otherwise include (one counter, in order)
+          gather_issue_pairs(A.moving_pairs, n0, n1, n2, zo, gy, gx, v0, v1, v2, wg);
+          woff = off;
+          wlive = true;
+          __builtin_amdgcn_sched_barrier(0);
+        }
         store_at(A.out, off, v0);
         store_at(A.out + N, off, v1);
         store_at(A.out + 2 * N, off, v2);
-      } else if (EPI == EPI_MAXNORM) {
-        mx = fmaxf(mx, v0 * v0 + v1 * v1 + v2 * v2);
       } else if (EPI == EPI_SMOOTH_MAX) {
         store_at(A.out, off, v0);
         store_at(A.out + N, off, v1);
@@ -1244,8 +1309,9 @@ __device__ __forceinline__ void gauss_body(const GaussArgs& A, const int tile, c
     }
   }
   if (EPI == EPI_COMPOSE) finish_compose();
+  if (EPI == EPI_STORE_WARP) finish_warp();
 
-  if (EPI == EPI_MAXNORM || EPI == EPI_SMOOTH_MAX) {
+  if (EPI == EPI_SMOOTH_MAX) {
     const float bm = block_max<NT>(mx, reinterpret_cast<float*>(red));
     if (tid == 0) m_raise(A.ctl, sqrtf(bm), blockIdx.x);
   }
@@ -1258,7 +1324,8 @@ __device__ __forceinline__ void gauss_body(const GaussArgs& A, const int tile, c
 // separable passes (x, y, z), the per-centre coefficients A, B, C on the
 // brick plus an r halo, their window sums with three more passes, and the
 // output as in k_grad.  No plane-by-plane march: the launch is a short chain
-// of dependent steps, which is what bounds small volumes.  The sums run in a
+// of dependent steps, which is what bounds small volumes (I, J and the slope
+// come from memory as in the march: 19.5 -> 17.9 us at 64^3).  The sums run in a
 // different order from the streaming form (x, y, z instead of z, x, y), so
 // the two agree to rounding, not bitwise.
 // ---------------------------------------------------------------------------
@@ -1277,10 +1344,9 @@ struct GradCubeShape {
   static constexpr size_t lds_bytes = sizeof(float) * (size_t)(SA + SB);
 };
 
-// MODE as for grad_body: A.mode fixed at compile time, or -1 to read it.
-template <int W, int TZ, int TY, int TX, bool QUAD = false, int MODE = -1>
+// MODE = A.mode (0 gradient and Adam, 1 gradient, 2 loss).
+template <int W, int TZ, int TY, int TX, int MODE>
 __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile) {
-  const int mode = MODE >= 0 ? MODE : A.mode;
   using S = GradCubeShape<W, TZ, TY, TX>;
   constexpr int R = S::R;
   constexpr int NT = TZ * TY * TX;
@@ -1302,84 +1368,55 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
   const int N = n0 * n1 * n2;
   const int z0 = b * TZ, y0 = by * TY, x0 = bx * TX;
   const float si = A.ctl->shift_i, sj = A.ctl->shift_j;
-  if (mode == 0 && tile == 0) m_clear(A.ctl, tid);  // M of this iteration
+  if (MODE == 0 && tile == 0) m_clear(A.ctl, tid);  // M of this iteration
 
-  // the thread's own output voxel: I, J and grad_p I_m, Adam moments
+  // stage-1 inputs on the brick plus 2r (zero off the grid): every load is
+  // issued before any is consumed
+  constexpr int KQ = (NQ + NT - 1) / NT;   // voxels per thread
+  float qI[KQ], qJ[KQ];
+#pragma unroll
+  for (int j = 0; j < KQ; ++j) {
+    const int c = tid + j * NT;
+    const int qz = c / (QY * QX), r = c - qz * (QY * QX);
+    const int qy = r / QX, qx = r - qy * QX;
+    const int z = z0 - 2 * R + qz, y = y0 - 2 * R + qy, x = x0 - 2 * R + qx;
+    const bool ok = c < NQ && z >= 0 && z < n0 && y >= 0 && y < n1 && x >= 0 && x < n2;
+    qI[j] = si;
+    qJ[j] = sj;
+    if (ok) {
+      const unsigned off = (unsigned)vidx(z, y, x, n1, n2) * 4u;
+      qI[j] = load_at(A.fixed, off);
+      qJ[j] = load_at(A.warped, off);
+    }
+  }
+
+  // the thread's own output voxel: I, J, the slope and the Adam moments
   const int tz = tid / (TY * TX), tr = tid - tz * (TY * TX);
   const int ty = tr / TX, tx = tr - ty * TX;
   const int oz = z0 + tz, oy = y0 + ty, ox = x0 + tx;
   const bool own = oz < n0 && oy < n1 && ox < n2;
   // byte offset of the own voxel from uniform bases (volumes hold < 2^29 voxels)
   const unsigned ooff = own ? (unsigned)vidx(oz, oy, ox, n1, n2) * 4u : 0u;
-  float oI = 0.f, oJ = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
-  float pm[3] = {0.f, 0.f, 0.f}, pv[3] = {0.f, 0.f, 0.f};
-  if (own) {
-    Gather gq;
-    if constexpr (QUAD) {
-      gather_issue_quad(A.moving_quad, n0, n1, n2, oz, oy, ox, load_at(A.d, ooff), load_at(A.d + N, ooff),
-                        load_at(A.d + 2 * N, ooff), gq);
-    } else {
-      const Cell8 c = cell8_pad(n0, n1, n2, oz, oy, ox, load_at(A.d, ooff), load_at(A.d + N, ooff),
-                                load_at(A.d + 2 * N, ooff));
-      gather_issue(A.moving_pad, c, gq);
-    }
+  float oI = 0.f, oJ = 0.f;
+  float pg[3] = {0.f, 0.f, 0.f}, pm[3] = {0.f, 0.f, 0.f}, pv[3] = {0.f, 0.f, 0.f};
+  if (MODE != 2 && own) {
     oI = load_at(A.fixed, ooff) - si;
-    if (mode == 0) {
+    oJ = load_at(A.warped, ooff) - sj;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < 3; ++q) {
+      pg[q] = load_at(A.slope + q * N, ooff);
+      if (MODE == 0) {
         pm[q] = load_at(A.m + q * N, ooff);
         pv[q] = load_at(A.v + q * N, ooff);
       }
     }
-    oJ = gather_value_grad(gq, g0, g1, g2) - sj;
   }
-
-  // stage-1 inputs on the brick plus 2r (zero off the grid), in batches of
-  // KB voxels per thread: the batch's loads of d, then its gathers, are all
-  // in flight together instead of one voxel's dependent loads at a time
-  constexpr int KQ = (NQ + NT - 1) / NT;   // voxels per thread
-  constexpr int KB = 3;                    // batch
-#pragma unroll 1
-  for (int k0 = 0; k0 < KQ; k0 += KB) {
-    bool qok[KB];
-    float qd0[KB], qd1[KB], qd2[KB], qf[KB];
-    __builtin_amdgcn_s_setprio(2);   // as in the march: the batch's loads leave first
 #pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      const int c = tid + (k0 + j) * NT;
-      const int qz = c / (QY * QX), r = c - qz * (QY * QX);
-      const int qy = r / QX, qx = r - qy * QX;
-      const int z = z0 - 2 * R + qz, y = y0 - 2 * R + qy, x = x0 - 2 * R + qx;
-      qok[j] = k0 + j < KQ && c < NQ && z >= 0 && z < n0 && y >= 0 && y < n1 && x >= 0 && x < n2;
-      const unsigned off = qok[j] ? (unsigned)vidx(z, y, x, n1, n2) * 4u : 0u;
-      qd0[j] = qok[j] ? load_at(A.d, off) : 0.0f;
-      qd1[j] = qok[j] ? load_at(A.d + N, off) : 0.0f;
-      qd2[j] = qok[j] ? load_at(A.d + 2 * N, off) : 0.0f;
-      qf[j] = qok[j] ? load_at(A.fixed, off) : 0.0f;
-    }
-    Gather gq[KB];
-#pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      const int c = tid + (k0 + j) * NT;
-      const int qz = c / (QY * QX), r = c - qz * (QY * QX);
-      const int qy = r / QX, qx = r - qy * QX;
-      if constexpr (QUAD) {
-        gather_issue_quad(A.moving_quad, n0, n1, n2, z0 - 2 * R + qz, y0 - 2 * R + qy, x0 - 2 * R + qx, qd0[j],
-                          qd1[j], qd2[j], gq[j]);
-      } else {
-        const Cell8 c8 = cell8_pad(n0, n1, n2, z0 - 2 * R + qz, y0 - 2 * R + qy, x0 - 2 * R + qx,
-                                   qd0[j], qd1[j], qd2[j]);
-        gather_issue(A.moving_pad, c8, gq[j]);
-      }
-    }
-    __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      const int c = tid + (k0 + j) * NT;
-      if (k0 + j < KQ && c < NQ) {
-        bufA[c] = qok[j] ? qf[j] - si : 0.0f;
-        bufA[NQ + c] = qok[j] ? gather_value(gq[j]) - sj : 0.0f;
-      }
+  for (int j = 0; j < KQ; ++j) {
+    const int c = tid + j * NT;
+    if (c < NQ) {
+      bufA[c] = qI[j] - si;
+      bufA[NQ + c] = qJ[j] - sj;
     }
   }
   __syncthreads();
@@ -1461,6 +1498,7 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
     bufB[NC + c] = cb;
     bufB[2 * NC + c] = cc_;
   }
+  if constexpr (MODE != 2) {
   __syncthreads();
   // stage 2 (sums of A, B, C over the window around each brick voxel), x
   for (int c = tid; c < NX2; c += NT) {
@@ -1502,8 +1540,8 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
       SC += src[2 * NY2 + k * TY * TX];
     }
     const float dl = -A.inv_n * (oI * SA + oJ * SB - SC);
-    const float g[3] = {dl * g0, dl * g1, dl * g2};
-    if (mode == 0) {
+    const float g[3] = {dl * pg[0], dl * pg[1], dl * pg[2]};
+    if (MODE == 0) {
       const float ibc1 = 1.0f / A.ctl->bc1, ibc2 = 1.0f / A.ctl->bc2;
       const float b1 = A.beta1, b2 = A.beta2;
 #pragma unroll
@@ -1514,11 +1552,12 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
         store_at(A.v + q * N, ooff, vv);
         store_at(A.out + q * N, ooff, adam_direction(mm, vv, ibc1, ibc2, A.adam_eps));
       }
-    } else if (mode == 1) {
+    } else {
       const float gsc = A.gscale ? *A.gscale : 1.0f;
 #pragma unroll
       for (int q = 0; q < 3; ++q) store_at(A.out + q * N, ooff, g[q] * gsc);
     }
+  }
   }
   const double tot = block_sum<NT>((double)lacc, red);
   if (tid == 0) A.partials[tile] = tot;
@@ -1548,7 +1587,7 @@ __device__ __forceinline__ void gauss_cube_body(const GaussArgs& A, const int ti
 
   const int tid = threadIdx.x;
   // the first brick of a warp smoothing that records the iteration does so first
-  if (EPI == EPI_STORE && A.partials && tile == 0) record_iteration<NT>(A);
+  if ((EPI == EPI_STORE || EPI == EPI_STORE_WARP) && A.partials && tile == 0) record_iteration<NT>(A);
   int b = tile;
   const int bx = b % A.tiles_x;
   b /= A.tiles_x;
@@ -1637,6 +1676,11 @@ __device__ __forceinline__ void gauss_cube_body(const GaussArgs& A, const int ti
     store_at(A.out + N, off, v1);
     store_at(A.out + 2 * N, off, v2);
     if (EPI == EPI_SMOOTH_MAX) mx = v0 * v0 + v1 * v1 + v2 * v2;
+    if (EPI == EPI_STORE_WARP) {
+      Gather g;
+      gather_issue_pairs(A.moving_pairs, n0, n1, n2, gz, gy, gx, v0, v1, v2, g);
+      store_warp(A, g, off, N);
+    }
   }
   if (EPI == EPI_SMOOTH_MAX) {
     const float bm = block_max<NT>(mx, reinterpret_cast<float*>(red));
@@ -1752,9 +1796,8 @@ __device__ __forceinline__ T* as_global(T* p) {
 
 __device__ __forceinline__ void load_args(const GradArgs* __restrict__ s, GradArgs& A) {
   A.fixed = as_global(s->fixed);
-  A.moving_pad = as_global(s->moving_pad);
-  A.moving_quad = as_global(s->moving_quad);
-  A.d = as_global(s->d);
+  A.warped = as_global(s->warped);
+  A.slope = as_global(s->slope);
   A.m = as_global(s->m);
   A.v = as_global(s->v);
   A.out = as_global(s->out);
@@ -1779,6 +1822,9 @@ __device__ __forceinline__ void load_args(const GaussArgs* __restrict__ s, Gauss
   A.in = as_global(s->in);
   A.out = as_global(s->out);
   A.d = as_global(s->d);
+  A.moving_pairs = as_global(s->moving_pairs);
+  A.warped = as_global(s->warped);
+  A.slope = as_global(s->slope);
   A.wts = as_global(s->wts);
   A.ctl = as_global(s->ctl);
   A.partials = as_global(s->partials);
@@ -1805,22 +1851,14 @@ __device__ __forceinline__ int batch_entry(const BatchEntry<Args>* __restrict__ 
   return g - E[e].first;
 }
 
-template <int W, int TY, int TX, bool QUAD = false, int MODE = -1>
-__global__ void __launch_bounds__(TY * TX) k_grad_batch(const BatchEntry<GradArgs>* __restrict__ E,
-                                                        const int* __restrict__ owner) {
+template <int W, int TY, int TX, int MODE>
+__global__ void __launch_bounds__((GradLaunch<W, TY, TX, MODE>::NT))
+__attribute__((amdgpu_waves_per_eu(GradLaunch<W, TY, TX, MODE>::WAVES)))
+k_grad_batch(const BatchEntry<GradArgs>* __restrict__ E, const int* __restrict__ owner) {
   GradArgs A;
   int nb;
   const int tile = batch_entry(E, owner, A, nb);
-  grad_body<W, TY, TX, true, QUAD, MODE>(A, tile);
-}
-
-template <int W, int TY, int TX, bool QUAD = false, int MODE = -1>
-__global__ void __launch_bounds__(TY * TX) __attribute__((amdgpu_waves_per_eu(4)))
-k_grad_o4_batch(const BatchEntry<GradArgs>* __restrict__ E, const int* __restrict__ owner) {
-  GradArgs A;
-  int nb;
-  const int tile = batch_entry(E, owner, A, nb);
-  grad_body<W, TY, TX, true, QUAD, MODE>(A, tile);
+  grad_body<W, TY, TX, GradLaunch<W, TY, TX, MODE>::NT, MODE>(A, tile);
 }
 
 template <int R, int TY, int TX, int EPI>
@@ -1837,18 +1875,18 @@ __global__ void __launch_bounds__(TY * TX) k_gauss_batch(const BatchEntry<GaussA
   gauss_body<R, TY, TX, EPI>(A, tile, nb);
 }
 
-template <int W, int TZ, int TY, int TX, bool QUAD = false, int MODE = -1>
+template <int W, int TZ, int TY, int TX, int MODE>
 __global__ void __launch_bounds__(TZ * TY * TX) k_grad_cube(const GradArgs A) {
-  grad_cube_body<W, TZ, TY, TX, QUAD, MODE>(A, xcd_tile(blockIdx.x, gridDim.x));
+  grad_cube_body<W, TZ, TY, TX, MODE>(A, xcd_tile(blockIdx.x, gridDim.x));
 }
 
-template <int W, int TZ, int TY, int TX, bool QUAD = false, int MODE = -1>
+template <int W, int TZ, int TY, int TX, int MODE>
 __global__ void __launch_bounds__(TZ * TY * TX) k_grad_cube_batch(const BatchEntry<GradArgs>* __restrict__ E,
                                                                   const int* __restrict__ owner) {
   GradArgs A;
   int nb;
   const int tile = batch_entry(E, owner, A, nb);
-  grad_cube_body<W, TZ, TY, TX, QUAD, MODE>(A, tile);
+  grad_cube_body<W, TZ, TY, TX, MODE>(A, tile);
 }
 
 template <int R, int TZ, int TY, int TX, int EPI>
@@ -1925,36 +1963,43 @@ k_eulerian_adam(float* __restrict__ ga, const float* __restrict__ d, float* __re
   }
 }
 
-// Copy of a volume with a zero border of kPad voxels on every side.
-__global__ void k_pad(const float* __restrict__ in, float* __restrict__ out, int n0, int n1, int n2) {
-  const int p0 = n0 + 2 * kPad, p1 = n1 + 2 * kPad, p2 = n2 + 2 * kPad;
-  const int64_t total = (int64_t)p0 * p1 * p2;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int x = (int)(i % p2) - kPad;
-    const int64_t t = i / p2;
-    const int y = (int)(t % p1) - kPad;
-    const int z = (int)(t / p1) - kPad;
-    const bool in_grid = z >= 0 && z < n0 && y >= 0 && y < n1 && x >= 0 && x < n2;
-    out[i] = in_grid ? in[((int64_t)z * n1 + y) * n2 + x] : 0.0f;
+// Voxel (z, y, x) and flat index i of this thread in an n0 x n1 x n2 launch:
+// on a (n2 / blockDim, n1, n0) grid (G3) from the block indices, with no
+// integer divisions; else from a flat index.  False past the end of a row or
+// of the volume.
+template <bool G3>
+__device__ __forceinline__ bool grid_voxel(int n0, int n1, int n2, int& z, int& y, int& x, int& i) {
+  if constexpr (G3) {
+    x = blockIdx.x * blockDim.x + threadIdx.x;
+    y = blockIdx.y;
+    z = blockIdx.z;
+    i = (z * n1 + y) * n2 + x;
+    return x < n2;
+  } else {
+    i = blockIdx.x * blockDim.x + threadIdx.x;
+    x = i % n2;
+    y = (i / n2) % n1;
+    z = i / (n1 * n2);
+    return i < n0 * n1 * n2;
   }
 }
 
-// Corner quads of the padded image (gather_issue_quad): quad[i] = (pad[i],
-// pad[i+1], pad[i+p2], pad[i+p2+1]) over the padded grid, zero where a corner
-// leaves it (the last padded row and column, never the low corner of a cell).
-__global__ void k_pad_quad(const float* __restrict__ pad, float4* __restrict__ quad, int p0, int p1, int p2) {
-  const int64_t n = (int64_t)p0 * p1 * p2;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int x = (int)(i % p2);
-  const int y = (int)((i / p2) % p1);
-  const bool xo = x + 1 < p2, yo = y + 1 < p1;
-  float4 q;
-  q.x = pad[i];
-  q.y = xo ? pad[i + 1] : 0.0f;
-  q.z = yo ? pad[i + p2] : 0.0f;
-  q.w = (xo && yo) ? pad[i + p2 + 1] : 0.0f;
-  quad[i] = q;
+// Row pairs of the padded image (gather_issue_pairs), from the image itself:
+// grid (ceil(p2 / blockDim), p1, p0) over the padded extents, or flat.
+template <bool G3>
+__global__ void k_row_pairs(const float* __restrict__ in, float2* __restrict__ out, int n0, int n1, int n2) {
+  int z, y, x, i;
+  if (!grid_voxel<G3>(n0 + 2 * kPad, n1 + 2 * kPad, n2 + 2 * kPad, z, y, x, i)) return;
+  z -= kPad;
+  y -= kPad;
+  x -= kPad;
+  const bool zx = z >= 0 && z < n0 && x >= 0 && x < n2;
+  const bool lo = zx && y >= 0 && y < n1, hi = zx && y >= -1 && y + 1 < n1;
+  const int at = vidx(z, y, x, n1, n2);
+  float2 v;
+  v.x = lo ? in[at] : 0.0f;
+  v.y = hi ? in[at + n2] : 0.0f;
+  out[i] = v;
 }
 
 __global__ void k_fill(float* __restrict__ p, float value, int64_t n) {
@@ -2135,27 +2180,6 @@ __global__ void __launch_bounds__(256) k_blur_x(const float* __restrict__ in, fl
   out[row + x] = s;
 }
 
-// Voxel (z, y, x) and flat index i of this thread in an n0 x n1 x n2 launch:
-// on a (n2 / blockDim, n1, n0) grid (G3) from the block indices, with no
-// integer divisions; else from a flat index.  False past the end of a row or
-// of the volume.
-template <bool G3>
-__device__ __forceinline__ bool grid_voxel(int n0, int n1, int n2, int& z, int& y, int& x, int& i) {
-  if constexpr (G3) {
-    x = blockIdx.x * blockDim.x + threadIdx.x;
-    y = blockIdx.y;
-    z = blockIdx.z;
-    i = (z * n1 + y) * n2 + x;
-    return x < n2;
-  } else {
-    i = blockIdx.x * blockDim.x + threadIdx.x;
-    x = i % n2;
-    y = (i / n2) % n1;
-    z = i / (n1 * n2);
-    return i < n0 * n1 * n2;
-  }
-}
-
 __device__ __forceinline__ float aligned_pos(int i, int nin, int nout) {
   return nout > 1 ? (float)(i * (nin - 1)) / (float)(nout - 1) : 0.0f;
 }
@@ -2177,16 +2201,27 @@ __global__ void k_resample(const float* __restrict__ in, float* __restrict__ out
   }
 }
 
-template <bool G3>
-__global__ void k_warp(const float* __restrict__ img, const float* __restrict__ d,
-                       float* __restrict__ out, int n0, int n1, int n2) {
+// J = I_m(x + d) and, with SLOPE, its position derivative ([3][N]): one
+// trilinear sample per voxel, zero outside the grid.
+template <bool G3, bool SLOPE>
+__global__ void k_warp(const float* __restrict__ img, const float* __restrict__ d, float* __restrict__ out,
+                       float* __restrict__ slope, int n0, int n1, int n2) {
   const int N = n0 * n1 * n2;
   int z, y, x, i;
   if (!grid_voxel<G3>(n0, n1, n2, z, y, x, i)) return;
-  const Cell8 c = cell8_at(n0, n1, n2, z, y, x, d[i], d[N + i], d[2 * N + i]);
+  const unsigned off = (unsigned)i * 4u;
+  const Cell8 c = cell8_at(n0, n1, n2, z, y, x, load_at(d, off), load_at(d + N, off), load_at(d + 2 * N, off));
   Gather g;
   gather_issue(img, c, g);
-  out[i] = gather_value(g);
+  if constexpr (SLOPE) {
+    float g0, g1, g2;
+    store_at(out, off, gather_value_grad(g, g0, g1, g2));
+    store_at(slope, off, g0);
+    store_at(slope + N, off, g1);
+    store_at(slope + 2 * N, off, g2);
+  } else {
+    store_at(out, off, gather_value(g));
+  }
 }
 
 // out = u + d(x + u): the displacement of phi o (id + u) for phi = id + d,
@@ -2259,40 +2294,27 @@ __global__ void k_sum_final(const double* __restrict__ part, int np, double* __r
 // ---------------------------------------------------------------------------
 // Dispatch tables
 // ---------------------------------------------------------------------------
-template <int W, int TY, int TX>
-constexpr size_t grad_lds() {
-  constexpr int R = W / 2;
-  constexpr int GS = (R == 0) ? 1 : 2 * R;
-  constexpr size_t base = sizeof(float) * (5 * (TY + 4 * R) * (TX + 4 * R) + 5 * (TY + 4 * R) * (TX + 2 * R));
-  constexpr size_t ring = sizeof(float) * 3 * GS * TY * TX;
-  return base + ring <= 65536 ? base + ring : base;
-}
-
 template <int R, int TY, int TX>
 constexpr size_t gauss_lds(bool staged_d) {
   return sizeof(float) * (3 * (TY + 2 * R) * (TX + 2 * R) + 3 * (TY + 2 * R) * TX +
                           (staged_d ? 9 * (((TY + 2) * (TX + 2) + 31) / 32 * 32) : 0));
 }
 
+template <int W, int TY, int TX, int MODE>
+hipError_t grad_launch_m(const GradArgs& a, const Tiling& t, hipStream_t s) {
+  constexpr size_t sh = GradShape<W, TY, TX, MODE>::lds_bytes;
+  static_assert(sh <= 65536, "gradient kernel LDS exceeds 64 KiB");
+  k_grad<W, TY, TX, MODE><<<dim3(t.blocks()), dim3(GradLaunch<W, TY, TX, MODE>::NT), sh, s>>>(a);
+  return hipGetLastError();
+}
+
 template <int W, int TY, int TX>
 hipError_t grad_launch_t(const GradArgs& a, const Tiling& t, hipStream_t s) {
-  constexpr size_t sh = grad_lds<W, TY, TX>();
-  static_assert(sh <= 65536, "gradient kernel LDS exceeds 64 KiB");
-  // two workgroups per CU where 128 VGPRs hold the kernel without spills
-  constexpr bool occ2 = (W <= 5) && TY == 16 && TX == 32;
-  const dim3 g(t.blocks()), blk(TY * TX);
-  if constexpr (occ2) {
-    if (t.variant == 2) k_grad_o4<W, TY, TX, false><<<g, blk, sh, s>>>(a);
-    else if (a.moving_quad && a.mode == 0) k_grad_o4<W, TY, TX, true, true, 0><<<g, blk, sh, s>>>(a);
-    else if (a.moving_quad) k_grad_o4<W, TY, TX, true, true><<<g, blk, sh, s>>>(a);
-    else k_grad_o4<W, TY, TX, true><<<g, blk, sh, s>>>(a);
-  } else {
-    if (t.variant == 2) k_grad<W, TY, TX, false><<<g, blk, sh, s>>>(a);
-    else if (a.moving_quad && a.mode == 0) k_grad<W, TY, TX, true, true, 0><<<g, blk, sh, s>>>(a);
-    else if (a.moving_quad) k_grad<W, TY, TX, true, true><<<g, blk, sh, s>>>(a);
-    else k_grad<W, TY, TX, true><<<g, blk, sh, s>>>(a);
+  switch (a.mode) {
+    case 0: return grad_launch_m<W, TY, TX, 0>(a, t, s);
+    case 1: return grad_launch_m<W, TY, TX, 1>(a, t, s);
+    default: return grad_launch_m<W, TY, TX, 2>(a, t, s);
   }
-  return hipGetLastError();
 }
 
 template <int TY, int TX>
@@ -2313,10 +2335,18 @@ hipError_t gauss_launch_r(const GaussArgs& a, int epi, const Tiling& t, hipStrea
   const size_t sh = gauss_lds<R, TY, TX>(epi == EPI_COMPOSE_LDS);
   switch (epi) {
     case EPI_STORE: k_gauss<R, TY, TX, EPI_STORE><<<g, blk, sh, s>>>(a); break;
-    case EPI_MAXNORM: k_gauss<R, TY, TX, EPI_MAXNORM><<<g, blk, sh, s>>>(a); break;
-    case EPI_COMPOSE: k_gauss<R, TY, TX, EPI_COMPOSE><<<g, blk, sh, s>>>(a); break;
-    case EPI_COMPOSE_LDS: k_gauss<R, TY, TX, EPI_COMPOSE_LDS><<<g, blk, sh, s>>>(a); break;
+    case EPI_STORE_WARP: k_gauss<R, TY, TX, EPI_STORE_WARP><<<g, blk, sh, s>>>(a); break;
     case EPI_SMOOTH_MAX: k_gauss<R, TY, TX, EPI_SMOOTH_MAX><<<g, blk, sh, s>>>(a); break;
+    case EPI_COMPOSE:
+    case EPI_COMPOSE_LDS:
+      // the composition runs with the single tap (radius 0) only
+      if constexpr (R == 0) {
+        if (epi == EPI_COMPOSE_LDS) k_gauss<0, TY, TX, EPI_COMPOSE_LDS><<<g, blk, sh, s>>>(a);
+        else k_gauss<0, TY, TX, EPI_COMPOSE><<<g, blk, sh, s>>>(a);
+        break;
+      } else {
+        return hipErrorInvalidValue;
+      }
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -2346,6 +2376,7 @@ hipError_t gauss_cube_r(const GaussArgs& a, int epi, const Tiling& t, hipStream_
   switch (epi) {
     case EPI_SMOOTH_MAX: k_gauss_cube<R, TZ, TY, TX, EPI_SMOOTH_MAX><<<g, blk, sh, s>>>(a); break;
     case EPI_STORE: k_gauss_cube<R, TZ, TY, TX, EPI_STORE><<<g, blk, sh, s>>>(a); break;
+    case EPI_STORE_WARP: k_gauss_cube<R, TZ, TY, TX, EPI_STORE_WARP><<<g, blk, sh, s>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -2368,26 +2399,29 @@ hipError_t gauss_launch_cube(const GaussArgs& a, int radius, int epi, const Tili
   }
 }
 
-template <int W, bool QUAD, int MODE = -1>
-hipError_t grad_cube_wq(const GradArgs& a, const Tiling& t, hipStream_t s) {
+template <int W, int MODE>
+hipError_t grad_cube_m(const GradArgs& a, const Tiling& t, hipStream_t s) {
   constexpr int TZ = kCubeZ, TY = kCubeY, TX = kCubeX;
   constexpr size_t sh = GradCubeShape<W, TZ, TY, TX>::lds_bytes;
   static_assert(sh <= 160 * 1024 - 1024, "brick gradient LDS exceeds the 160 KiB of a CU");
   static bool attr_set = false;   // raise the dynamic LDS limit once per process
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grad_cube<W, TZ, TY, TX, QUAD, MODE>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grad_cube<W, TZ, TY, TX, MODE>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  k_grad_cube<W, TZ, TY, TX, QUAD, MODE><<<dim3(t.blocks()), dim3(TZ * TY * TX), sh, s>>>(a);
+  k_grad_cube<W, TZ, TY, TX, MODE><<<dim3(t.blocks()), dim3(TZ * TY * TX), sh, s>>>(a);
   return hipGetLastError();
 }
 
 template <int W>
 hipError_t grad_cube_w(const GradArgs& a, const Tiling& t, hipStream_t s) {
-  if (a.moving_quad && a.mode == 0) return grad_cube_wq<W, true, 0>(a, t, s);
-  return a.moving_quad ? grad_cube_wq<W, true>(a, t, s) : grad_cube_wq<W, false>(a, t, s);
+  switch (a.mode) {
+    case 0: return grad_cube_m<W, 0>(a, t, s);
+    case 1: return grad_cube_m<W, 1>(a, t, s);
+    default: return grad_cube_m<W, 2>(a, t, s);
+  }
 }
 
 hipError_t grad_launch_cube(const GradArgs& a, int window, const Tiling& t, hipStream_t s) {
@@ -2401,57 +2435,45 @@ hipError_t grad_launch_cube(const GradArgs& a, int window, const Tiling& t, hipS
 
 // ---- batched launches ------------------------------------------------------
 template <int W, int TY, int TX>
-hipError_t grad_batch_t(const BatchEntry<GradArgs>* E, const int* owner, int total, bool quad, bool adam,
-                        hipStream_t s) {
-  constexpr size_t sh = grad_lds<W, TY, TX>();
-  constexpr bool occ2 = (W <= 5) && TY == 16 && TX == 32;
-  const dim3 g(total), blk(TY * TX);
-  if constexpr (occ2) {
-    if (quad && adam) k_grad_o4_batch<W, TY, TX, true, 0><<<g, blk, sh, s>>>(E, owner);
-    else if (quad) k_grad_o4_batch<W, TY, TX, true><<<g, blk, sh, s>>>(E, owner);
-    else k_grad_o4_batch<W, TY, TX><<<g, blk, sh, s>>>(E, owner);
-  } else {
-    if (quad && adam) k_grad_batch<W, TY, TX, true, 0><<<g, blk, sh, s>>>(E, owner);
-    else if (quad) k_grad_batch<W, TY, TX, true><<<g, blk, sh, s>>>(E, owner);
-    else k_grad_batch<W, TY, TX><<<g, blk, sh, s>>>(E, owner);
-  }
+hipError_t grad_batch_t(const BatchEntry<GradArgs>* E, const int* owner, int total, bool adam, hipStream_t s) {
+  constexpr size_t sh = GradShape<W, TY, TX, 0>::lds_bytes;
+  const dim3 g(total);
+  if (adam) k_grad_batch<W, TY, TX, 0><<<g, dim3(GradLaunch<W, TY, TX, 0>::NT), sh, s>>>(E, owner);
+  else k_grad_batch<W, TY, TX, 1><<<g, dim3(GradLaunch<W, TY, TX, 1>::NT), sh, s>>>(E, owner);
   return hipGetLastError();
 }
 
 template <int TY, int TX>
-hipError_t grad_batch_tile(const BatchEntry<GradArgs>* E, const int* owner, int total, int window, bool quad,
-                           bool adam, hipStream_t s) {
+hipError_t grad_batch_tile(const BatchEntry<GradArgs>* E, const int* owner, int total, int window, bool adam,
+                           hipStream_t s) {
   switch (window) {
-    case 1: return grad_batch_t<1, TY, TX>(E, owner, total, quad, adam, s);
-    case 3: return grad_batch_t<3, TY, TX>(E, owner, total, quad, adam, s);
-    case 5: return grad_batch_t<5, TY, TX>(E, owner, total, quad, adam, s);
-    case 7: return grad_batch_t<7, TY, TX>(E, owner, total, quad, adam, s);
-    case 9: return grad_batch_t<9, TY, TX>(E, owner, total, quad, adam, s);
+    case 1: return grad_batch_t<1, TY, TX>(E, owner, total, adam, s);
+    case 3: return grad_batch_t<3, TY, TX>(E, owner, total, adam, s);
+    case 5: return grad_batch_t<5, TY, TX>(E, owner, total, adam, s);
+    case 7: return grad_batch_t<7, TY, TX>(E, owner, total, adam, s);
+    case 9: return grad_batch_t<9, TY, TX>(E, owner, total, adam, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-template <int W, bool QUAD, int MODE = -1>
-hipError_t grad_cube_batch_wq(const BatchEntry<GradArgs>* E, const int* owner, int total, hipStream_t s) {
+template <int W, int MODE>
+hipError_t grad_cube_batch_m(const BatchEntry<GradArgs>* E, const int* owner, int total, hipStream_t s) {
   constexpr int TZ = kCubeZ, TY = kCubeY, TX = kCubeX;
   constexpr size_t sh = GradCubeShape<W, TZ, TY, TX>::lds_bytes;
   static bool attr_set = false;   // raise the dynamic LDS limit once per process
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&k_grad_cube_batch<W, TZ, TY, TX, QUAD, MODE>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grad_cube_batch<W, TZ, TY, TX, MODE>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  k_grad_cube_batch<W, TZ, TY, TX, QUAD, MODE><<<dim3(total), dim3(TZ * TY * TX), sh, s>>>(E, owner);
+  k_grad_cube_batch<W, TZ, TY, TX, MODE><<<dim3(total), dim3(TZ * TY * TX), sh, s>>>(E, owner);
   return hipGetLastError();
 }
 
 template <int W>
-hipError_t grad_cube_batch_w(const BatchEntry<GradArgs>* E, const int* owner, int total, bool quad, bool adam,
-                             hipStream_t s) {
-  if (quad && adam) return grad_cube_batch_wq<W, true, 0>(E, owner, total, s);
-  return quad ? grad_cube_batch_wq<W, true>(E, owner, total, s) : grad_cube_batch_wq<W, false>(E, owner, total, s);
+hipError_t grad_cube_batch_w(const BatchEntry<GradArgs>* E, const int* owner, int total, bool adam, hipStream_t s) {
+  return adam ? grad_cube_batch_m<W, 0>(E, owner, total, s) : grad_cube_batch_m<W, 1>(E, owner, total, s);
 }
 
 template <int R, int TY, int TX>
@@ -2460,7 +2482,7 @@ hipError_t gauss_batch_r(const BatchEntry<GaussArgs>* E, const int* owner, int t
   const size_t sh = gauss_lds<R, TY, TX>(epi == EPI_COMPOSE_LDS);
   switch (epi) {
     case EPI_SMOOTH_MAX: k_gauss_batch<R, TY, TX, EPI_SMOOTH_MAX><<<g, blk, sh, s>>>(E, owner); break;
-    case EPI_STORE: k_gauss_batch<R, TY, TX, EPI_STORE><<<g, blk, sh, s>>>(E, owner); break;
+    case EPI_STORE_WARP: k_gauss_batch<R, TY, TX, EPI_STORE_WARP><<<g, blk, sh, s>>>(E, owner); break;
     case EPI_COMPOSE_LDS:
     case EPI_COMPOSE:
       // the composition runs with the single tap (radius 0) only
@@ -2500,7 +2522,7 @@ hipError_t gauss_cube_batch_r(const BatchEntry<GaussArgs>* E, const int* owner, 
   const dim3 g(total), blk(TZ * TY * TX);
   switch (epi) {
     case EPI_SMOOTH_MAX: k_gauss_cube_batch<R, TZ, TY, TX, EPI_SMOOTH_MAX><<<g, blk, sh, s>>>(E, owner); break;
-    case EPI_STORE: k_gauss_cube_batch<R, TZ, TY, TX, EPI_STORE><<<g, blk, sh, s>>>(E, owner); break;
+    case EPI_STORE_WARP: k_gauss_cube_batch<R, TZ, TY, TX, EPI_STORE_WARP><<<g, blk, sh, s>>>(E, owner); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -2531,19 +2553,12 @@ bool grad_cube_supported(int window) { return window == 1 || window == 3 || wind
 
 bool gauss_cube_supported(int radius, int epilogue) {
   if (epilogue == EPI_COMPOSE_LDS) return radius == 0;
-  return (epilogue == EPI_SMOOTH_MAX || epilogue == EPI_STORE) && radius >= 0 && radius <= 3;
+  return (epilogue == EPI_SMOOTH_MAX || epilogue == EPI_STORE || epilogue == EPI_STORE_WARP) && radius >= 0 &&
+         radius <= 3;
 }
 
 bool gauss_tile_supported(int ty, int tx) {
   return (ty == 16 && tx == 32) || (ty == 8 && tx == 32) || (ty == 8 && tx == 64);
-}
-
-size_t grad_lds_bytes(int window, int ty, int tx) {
-  const int R = window / 2;
-  const int GS = (R == 0) ? 1 : 2 * R;
-  const size_t base = sizeof(float) * (size_t)(5 * (ty + 4 * R) * (tx + 4 * R) + 5 * (ty + 4 * R) * (tx + 2 * R));
-  const size_t ring = sizeof(float) * (size_t)(3 * GS * ty * tx);
-  return base + ring <= 65536 ? base + ring : base;
 }
 
 size_t gauss_lds_bytes(int radius, int ty, int tx) {
@@ -2564,25 +2579,25 @@ bool grad_batch_supported(int window, const Tiling& t) {
 }
 
 bool gauss_batch_supported(int radius, int epilogue, const Tiling& t) {
-  if (t.cube) return gauss_cube_supported(radius, epilogue);
+  if (t.cube) return epilogue != EPI_STORE && gauss_cube_supported(radius, epilogue);
   if (!gauss_tile_supported(t.ty, t.tx) || radius < 0 || radius > kMaxRadius) return false;
-  if (epilogue == EPI_SMOOTH_MAX || epilogue == EPI_STORE) return true;
+  if (epilogue == EPI_SMOOTH_MAX || epilogue == EPI_STORE_WARP) return true;
   return (epilogue == EPI_COMPOSE_LDS || epilogue == EPI_COMPOSE) && radius == 0;
 }
 
 hipError_t launch_grad_batch(const BatchEntry<GradArgs>* E, const int* owner, int total, int window,
-                             const Tiling& t, bool quad, bool adam, hipStream_t s) {
+                             const Tiling& t, bool adam, hipStream_t s) {
   if (total <= 0) return hipSuccess;
   if (t.cube) {
     switch (window) {
-      case 1: return grad_cube_batch_w<1>(E, owner, total, quad, adam, s);
-      case 3: return grad_cube_batch_w<3>(E, owner, total, quad, adam, s);
-      case 5: return grad_cube_batch_w<5>(E, owner, total, quad, adam, s);
+      case 1: return grad_cube_batch_w<1>(E, owner, total, adam, s);
+      case 3: return grad_cube_batch_w<3>(E, owner, total, adam, s);
+      case 5: return grad_cube_batch_w<5>(E, owner, total, adam, s);
       default: return hipErrorInvalidValue;
     }
   }
-  if (t.ty == 16 && t.tx == 32) return grad_batch_tile<16, 32>(E, owner, total, window, quad, adam, s);
-  if (t.ty == 8 && t.tx == 32) return grad_batch_tile<8, 32>(E, owner, total, window, quad, adam, s);
+  if (t.ty == 16 && t.tx == 32) return grad_batch_tile<16, 32>(E, owner, total, window, adam, s);
+  if (t.ty == 8 && t.tx == 32) return grad_batch_tile<8, 32>(E, owner, total, window, adam, s);
   return hipErrorInvalidValue;
 }
 
@@ -2640,7 +2655,16 @@ hipError_t launch_gauss_wide(const GaussArgs& a, int radius, int epilogue, const
 }
 
 hipError_t launch_gauss(const GaussArgs& a, int radius, int epilogue, const Tiling& t, hipStream_t s) {
-  if (radius > kMaxRadius) return launch_gauss_wide(a, radius, epilogue, t, s);
+  if (epilogue == EPI_STORE_WARP && !a.moving_pairs) {
+    // a volume whose row pairs 32-bit offsets do not reach: sampled by a launch of its own
+    const hipError_t e = launch_gauss(a, radius, EPI_STORE, t, s);
+    return e != hipSuccess ? e : launch_warp_slope(a.moving, a.out, a.warped, a.slope, a.n0, a.n1, a.n2, s);
+  }
+  if (radius > kMaxRadius) {
+    if (epilogue != EPI_STORE_WARP) return launch_gauss_wide(a, radius, epilogue, t, s);
+    const hipError_t e = launch_gauss_wide(a, radius, EPI_STORE, t, s);
+    return e != hipSuccess ? e : launch_warp_slope(a.moving, a.out, a.warped, a.slope, a.n0, a.n1, a.n2, s);
+  }
   return launch_gauss_narrow(a, radius, epilogue, t, s);
 }
 
@@ -2656,10 +2680,13 @@ hipError_t launch_eulerian_adam(float* ga, const float* d, float* m, float* v, C
   return hipGetLastError();
 }
 
-hipError_t launch_pad(const float* in, float* out, int n0, int n1, int n2, hipStream_t s) {
-  const int64_t total = (int64_t)(n0 + 2 * kPad) * (n1 + 2 * kPad) * (n2 + 2 * kPad);
-  const int blocks = (int)std::min<int64_t>((total + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_pad, dim3(blocks), dim3(256), 0, s, in, out, n0, n1, n2);
+hipError_t launch_row_pairs(const float* in, float* out, int n0, int n1, int n2, hipStream_t s) {
+  const int p0 = n0 + 2 * kPad, p1 = n1 + 2 * kPad, p2 = n2 + 2 * kPad;
+  float2* o = reinterpret_cast<float2*>(out);
+  if (p0 <= 65535 && p1 <= 65535)
+    hipLaunchKernelGGL(k_row_pairs<true>, dim3(grid1(p2, 128), p1, p0), dim3(128), 0, s, in, o, n0, n1, n2);
+  else
+    hipLaunchKernelGGL(k_row_pairs<false>, dim3(grid1((int64_t)p0 * p1 * p2, 256)), dim3(256), 0, s, in, o, n0, n1, n2);
   return hipGetLastError();
 }
 
@@ -2683,14 +2710,6 @@ hipError_t blur_axis_run(const float* in, float* out, int n0, int n1, int n2, in
 template <int R>
 hipError_t blur_x(const float* in, float* out, int n0, int n1, int n2, const float* wts, hipStream_t s) {
   hipLaunchKernelGGL((k_blur_x<R>), dim3(grid1(n2, 256), n1, n0), dim3(256), 0, s, in, out, n2, wts);
-  return hipGetLastError();
-}
-
-hipError_t launch_pad_quad(const float* pad, float* quad, int n0, int n1, int n2, hipStream_t s) {
-  const int p0 = n0 + 2 * kPad, p1 = n1 + 2 * kPad, p2 = n2 + 2 * kPad;
-  const int64_t n = (int64_t)p0 * p1 * p2;
-  hipLaunchKernelGGL(k_pad_quad, dim3(grid1(n, 256)), dim3(256), 0, s, pad, reinterpret_cast<float4*>(quad), p0,
-                     p1, p2);
   return hipGetLastError();
 }
 
@@ -2737,14 +2756,27 @@ hipError_t launch_resample(const float* in, float* out, int nin0, int nin1, int 
   return hipGetLastError();
 }
 
-hipError_t launch_warp(const float* img, const float* d, float* out, int n0, int n1, int n2, hipStream_t s) {
+template <bool SLOPE>
+hipError_t warp_launch(const float* img, const float* d, float* out, float* slope, int n0, int n1, int n2,
+                       hipStream_t s) {
   if (n0 <= 65535 && n1 <= 65535) {
-    hipLaunchKernelGGL(k_warp<true>, dim3(grid1(n2, 256), n1, n0), dim3(256), 0, s, img, d, out, n0, n1, n2);
+    const int bs = n2 > 128 ? 256 : (n2 > 64 ? 128 : 64);   // a row's lanes, without a mostly idle workgroup
+    hipLaunchKernelGGL((k_warp<true, SLOPE>), dim3(grid1(n2, bs), n1, n0), dim3(bs), 0, s, img, d, out, slope, n0, n1,
+                       n2);
   } else {
     const int64_t n = (int64_t)n0 * n1 * n2;
-    hipLaunchKernelGGL(k_warp<false>, dim3(grid1(n, 256)), dim3(256), 0, s, img, d, out, n0, n1, n2);
+    hipLaunchKernelGGL((k_warp<false, SLOPE>), dim3(grid1(n, 256)), dim3(256), 0, s, img, d, out, slope, n0, n1, n2);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_warp(const float* img, const float* d, float* out, int n0, int n1, int n2, hipStream_t s) {
+  return warp_launch<false>(img, d, out, nullptr, n0, n1, n2, s);
+}
+
+hipError_t launch_warp_slope(const float* img, const float* d, float* out, float* slope, int n0, int n1, int n2,
+                             hipStream_t s) {
+  return warp_launch<true>(img, d, out, slope, n0, n1, n2, s);
 }
 
 hipError_t launch_compose_fields(const float* u, const float* d, float* out, int n0, int n1, int n2,

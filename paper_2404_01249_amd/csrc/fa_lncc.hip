@@ -1,7 +1,7 @@
 // Stateless fused LNCC cost and gradient (include/fa_lncc.h): the gradient
 // kernel of the registration iteration in its gradient-only and loss-only
-// modes, with its own control block, reduction buffers and padded copy of the
-// moving image (fa_lncc_eval), or with those in a fixed device array of the
+// modes, with its own control block, reduction buffers and warped image
+// (fa_lncc_eval), or with those in a fixed device array of the
 // library (fa_lncc_eval_noalloc).
 #include <mutex>
 #include <new>
@@ -14,8 +14,7 @@ using fa::fail;
 // ---- allocation-free evaluation (fa_lncc_eval_noalloc) ----------------------
 // Every buffer the evaluation needs besides the caller's inputs and outputs
 // lives in this array: the control block, the loss partials of the gradient
-// launch, the partials of the two mean reductions and the zero-bordered copy
-// of the moving image.  Each GPU holds its own copy, at its own address, from
+// launch, the partials of the two mean reductions and the warped image.  Each GPU holds its own copy, at its own address, from
 // the library's load until the process ends.  In host code the name is only a
 // host-side stand-in for the symbol: kernels and copies take the device
 // address kept in g_scratch_dev below, never the name.
@@ -31,8 +30,7 @@ struct fa_lncc_s {
   fa::Ctl* ctl = nullptr;
   double* partials = nullptr;   // one per workgroup of the gradient launch
   double* mean_partials = nullptr;  // kMeanBlocks doubles for the intensity means
-  float* moving_pad = nullptr;  // the moving image with a zero border, refreshed per call
-  float* moving_quad = nullptr; // the same as corner quads (NULL where quad_supported fails)
+  float* warped = nullptr;      // J = I_m(x + d), made by each call
 };
 
 namespace {
@@ -43,8 +41,7 @@ void release(fa_lncc h) {
   if (h->ctl) (void)hipFree(h->ctl);
   if (h->partials) (void)hipFree(h->partials);
   if (h->mean_partials) (void)hipFree(h->mean_partials);
-  if (h->moving_pad) (void)hipFree(h->moving_pad);
-  if (h->moving_quad) (void)hipFree(h->moving_quad);
+  if (h->warped) (void)hipFree(h->warped);
   delete h;
 }
 
@@ -73,6 +70,17 @@ fa_status scratch_address(void** out) {
   return FA_OK;
 }
 
+// J, and with a gradient the slope of the moving image in the caller's gradient
+// buffer: the gradient kernel reads it there only at the voxel it writes.
+fa_status warp_for(const float* moving, const float* d, float* warped, float* grad_dev, const fa_shape& s,
+                   hipStream_t st) {
+  if (grad_dev)
+    FA_HIP(fa::launch_warp_slope(moving, d, warped, grad_dev, s.n0, s.n1, s.n2, st));
+  else
+    FA_HIP(fa::launch_warp(moving, d, warped, s.n0, s.n1, s.n2, st));
+  return FA_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -96,17 +104,7 @@ fa_status fa_lncc_create(fa_shape shape, int window, float cc_eps, void* hip_str
   if (hipMalloc((void**)&h->ctl, sizeof(fa::Ctl)) != hipSuccess ||
       hipMalloc((void**)&h->partials, (size_t)nb * sizeof(double)) != hipSuccess ||
       hipMalloc((void**)&h->mean_partials, (size_t)fa::kMeanBlocks * sizeof(double)) != hipSuccess ||
-      hipMalloc((void**)&h->moving_pad, (size_t)fa::padded_voxels(shape.n0, shape.n1, shape.n2) * sizeof(float)) !=
-          hipSuccess) {
-    (void)hipGetLastError();
-    release(h);
-    return fail(FA_ENOMEM, "device allocation failed");
-  }
-  // the gradient kernel samples the corner quads (two 16-byte loads per
-  // trilinear sample instead of eight 4-byte gathers) where they fit
-  if (fa::quad_supported(shape.n0, shape.n1, shape.n2) &&
-      hipMalloc((void**)&h->moving_quad,
-                (size_t)4 * fa::padded_voxels(shape.n0, shape.n1, shape.n2) * sizeof(float)) != hipSuccess) {
+      hipMalloc((void**)&h->warped, (size_t)h->n * sizeof(float)) != hipSuccess) {
     (void)hipGetLastError();
     release(h);
     return fail(FA_ENOMEM, "device allocation failed");
@@ -129,14 +127,11 @@ fa_status fa_lncc_eval(fa_lncc h, const float* fixed, const float* moving, const
   // image, and removing it keeps the fp32 window variances well conditioned
   FA_HIP(fa::launch_mean(fixed, h->n, h->mean_partials, &h->ctl->shift_i, h->stream));
   FA_HIP(fa::launch_mean(moving, h->n, h->mean_partials, &h->ctl->shift_j, h->stream));
-  FA_HIP(fa::launch_pad(moving, h->moving_pad, h->shape.n0, h->shape.n1, h->shape.n2, h->stream));
-  if (h->moving_quad)
-    FA_HIP(fa::launch_pad_quad(h->moving_pad, h->moving_quad, h->shape.n0, h->shape.n1, h->shape.n2, h->stream));
+  FA_TRY(warp_for(moving, d, h->warped, grad_dev, h->shape, h->stream));
   fa::GradArgs ga{};
   ga.fixed = fixed;
-  ga.moving_pad = h->moving_pad;
-  ga.moving_quad = h->moving_quad;
-  ga.d = d;
+  ga.warped = h->warped;
+  ga.slope = grad_dev;
   ga.out = grad_dev;
   ga.gscale = grad_scale_dev;
   ga.partials = h->partials;
@@ -170,11 +165,12 @@ fa_status fa_lncc_eval_noalloc(fa_shape shape, int window, float cc_eps, const f
   const int64_t n = fa::voxels(shape);
   const fa::Tiling tg = fa::choose_tiling(shape, fa::KIND_GRAD, fa::Tuning(), fa::grad_cube_supported(window));
   const int nb = tg.blocks();
-  // layout of the scratch array: control block | loss partials | mean partials | padded moving image
+  // layout of the scratch array: control block | loss partials | mean partials | warped image (the size
+  // accepted is that of the moving image with a border of two voxels, as documented)
   const size_t off_part = align256(sizeof(fa::Ctl));
   const size_t off_mean = off_part + align256((size_t)nb * sizeof(double));
-  const size_t off_pad = off_mean + align256((size_t)fa::kMeanBlocks * sizeof(double));
-  const size_t need = off_pad + (size_t)fa::padded_voxels(shape.n0, shape.n1, shape.n2) * sizeof(float);
+  const size_t off_warp = off_mean + align256((size_t)fa::kMeanBlocks * sizeof(double));
+  const size_t need = off_warp + (size_t)fa::padded_voxels(shape.n0, shape.n1, shape.n2) * sizeof(float);
   if (need > (size_t)FA_LNCC_NOALLOC_SCRATCH_BYTES)
     return fail(FA_EINVAL, "volume too large for the allocation-free evaluation: needs " + std::to_string(need) +
                                " bytes of scratch, the library holds " +
@@ -185,19 +181,19 @@ fa_status fa_lncc_eval_noalloc(fa_shape shape, int window, float cc_eps, const f
   fa::Ctl* ctl = reinterpret_cast<fa::Ctl*>(b);
   double* partials = reinterpret_cast<double*>(b + off_part);
   double* mean_partials = reinterpret_cast<double*>(b + off_mean);
-  float* moving_pad = reinterpret_cast<float*>(b + off_pad);
+  float* warped = reinterpret_cast<float*>(b + off_warp);
   const hipStream_t st = (hipStream_t)hip_stream;
   // every scratch word the kernels read is written earlier in this call, on
   // this stream: the control block by its init kernel, the shifts by the
-  // means, the padded image by the pad kernel, each partial by its workgroup
+  // means, the warped image by the warp kernel, each partial by its workgroup
   FA_HIP(fa::launch_ctl_init(ctl, 0.9f, 0.999f, 0, 0, st));
   FA_HIP(fa::launch_mean(fixed, n, mean_partials, &ctl->shift_i, st));
   FA_HIP(fa::launch_mean(moving, n, mean_partials, &ctl->shift_j, st));
-  FA_HIP(fa::launch_pad(moving, moving_pad, shape.n0, shape.n1, shape.n2, st));
+  FA_TRY(warp_for(moving, d, warped, grad_dev, shape, st));
   fa::GradArgs ga{};
   ga.fixed = fixed;
-  ga.moving_pad = moving_pad;
-  ga.d = d;
+  ga.warped = warped;
+  ga.slope = grad_dev;
   ga.out = grad_dev;
   ga.gscale = grad_scale_dev;
   ga.partials = partials;

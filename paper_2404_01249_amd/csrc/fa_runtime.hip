@@ -90,8 +90,7 @@ struct Level {
   int iters = 0;
   float* fixed = nullptr;   // owned unless it aliases the input copy
   float* moving = nullptr;
-  float* moving_pad = nullptr;  // moving with a zero border (owned), sampled by the gradient kernel
-  float* moving_quad = nullptr; // the same as corner quads (owned; NULL where it would reach 4 GiB)
+  float* moving_pairs = nullptr; // row pairs of moving (owned; NULL where row_pairs_supported fails)
   bool owns = false;
   Tiling tg{}, tsg{}, tsc{}, tsw{};  // gradient, sigma_grad, composition and sigma_warp launches
   bool tuned[4] = {false, false, false, false};  // set by fa_pair_autotune (by KernelKind)
@@ -127,6 +126,9 @@ struct fa_pair_s {
   float* m = nullptr;
   float* v = nullptr;
   float* a = nullptr;         // Adam direction
+  float* warped = nullptr;    // J = I_m o phi at the current level, [n], and its slope dI_m/dp, [3][n]:
+  float* slope = nullptr;     // made by the warp smoothing for the next iteration
+  bool warped_ok = false;     // whether the queued work leaves them at the current d
   float* tmp = nullptr;       // smoothed direction s, then the composed d'
   float* wide = nullptr;      // [3][cap] scratch of the smoothing passes with a radius above 6
   float* blur0 = nullptr;     // pyramid scratch (input size)
@@ -179,16 +181,15 @@ void free_levels(fa_pair P) {
       (void)hipFree(L.fixed);
       (void)hipFree(L.moving);
     }
-    if (L.moving_pad) (void)hipFree(L.moving_pad);
-    if (L.moving_quad) (void)hipFree(L.moving_quad);
+    if (L.moving_pairs) (void)hipFree(L.moving_pairs);
   }
   P->levels.clear();
 }
 
 void free_all(fa_pair P) {
   free_levels(P);
-  float* fbufs[] = {P->in_fixed, P->in_moving, P->d, P->m, P->v, P->a, P->tmp, P->wide, P->blur0,
-                    P->blur1, P->loss_hist, P->wts};
+  float* fbufs[] = {P->in_fixed, P->in_moving, P->d, P->m, P->v, P->a, P->warped, P->slope, P->tmp,
+                    P->wide, P->blur0, P->blur1, P->loss_hist, P->wts};
   for (float* b : fbufs)
     if (b) (void)hipFree(b);
   if (P->ctl) (void)hipFree(P->ctl);
@@ -280,9 +281,8 @@ void plan_iteration(fa_pair P, const Level& L, IterPlan& it, const float* fixed 
   fa::GradArgs& ga = it.ga;
   ga = fa::GradArgs{};
   ga.fixed = fixed ? fixed : (P->fixed_override ? P->fixed_override : L.fixed);
-  ga.moving_pad = L.moving_pad;
-  ga.moving_quad = L.moving_quad;
-  ga.d = P->d;
+  ga.warped = P->warped;
+  ga.slope = P->slope;
   ga.m = P->m;
   ga.v = P->v;
   ga.out = P->a;
@@ -347,6 +347,10 @@ void plan_iteration(fa_pair P, const Level& L, IterPlan& it, const float* fixed 
   g3 = gs;
   g3.in = P->tmp;
   g3.out = P->d;
+  g3.moving = L.moving;
+  g3.moving_pairs = L.moving_pairs;
+  g3.warped = P->warped;
+  g3.slope = P->slope;
   g3.wts = P->wts + P->off_w;
   g3.wide_tmp = P->wide;
   g3.zc = L.tsw.zc;
@@ -354,7 +358,7 @@ void plan_iteration(fa_pair P, const Level& L, IterPlan& it, const float* fixed 
   g3.tiles_x = L.tsw.tiles_x;
   it.tgs[2] = L.tsw;
   it.radius[2] = P->rw;
-  it.epi[2] = fa::EPI_STORE;
+  it.epi[2] = fa::EPI_STORE_WARP;
 
   // the loss record and step count
   fa::GaussArgs& gr = it.g[record_launch(L.tsw)];
@@ -362,6 +366,15 @@ void plan_iteration(fa_pair P, const Level& L, IterPlan& it, const float* fixed 
   gr.n_partials = L.tg.blocks();
   gr.loss_hist = P->loss_hist;
   gr.loss_cap = P->loss_cap;
+}
+
+// J = I_m o phi and its slope at the pair's current d, unless the last
+// iteration's warp smoothing has made them.
+fa_status ensure_warped(fa_pair P, const Level& L) {
+  if (!P->warped_ok)
+    FA_HIP(fa::launch_warp_slope(L.moving, P->d, P->warped, P->slope, L.shape.n0, L.shape.n1, L.shape.n2, P->stream));
+  P->warped_ok = true;
+  return FA_OK;
 }
 
 fa_status launch_eulerian(fa_pair P, const Level& L) {
@@ -379,13 +392,19 @@ fa_status launch_iteration(fa_pair P, const Level& L, const float* fixed = nullp
   }
   IterPlan it;
   plan_iteration(P, L, it, fixed);
+  // a level's last iteration leaves no J: the next level's differs
+  const bool last = P->cur_iter + 1 >= L.iters;
+  if (last) it.epi[2] = fa::EPI_STORE;
+  FA_TRY(ensure_warped(P, L));
   FA_HIP(fa::launch_grad(it.ga, it.window, it.tg, P->stream));
+  P->warped_ok = false;
   if (P->p.use_jac) FA_TRY(launch_eulerian(P, L));
   if (P->profiling) FA_HIP(hipEventRecord(pe.e[1], P->stream));
   for (int k = 0; k < 3; ++k) {
     FA_HIP(fa::launch_gauss(it.g[k], it.radius[k], it.epi[k], it.tgs[k], P->stream));
     if (P->profiling) FA_HIP(hipEventRecord(pe.e[2 + k], P->stream));
   }
+  P->warped_ok = !last;
   if (P->profiling) {
     P->pending.push_back(pe);
     if (P->pending.size() >= 4096) FA_TRY(drain_profile(P));
@@ -415,6 +434,7 @@ fa_status transition(fa_pair P) {
   P->v = old_m;
   P->a = old_d;
   P->tmp = old_v;
+  P->warped_ok = false;
   return FA_OK;
 }
 
@@ -449,9 +469,8 @@ struct BatchLaunch {
   size_t ent_off;  // byte offsets of the entries and the owner array
   size_t own_off;
   int total;       // workgroups of the launch
-  bool quad = false;   // gradient: the entries gather from corner quads
   bool adam = false;   // gradient: every entry runs mode 0 (gradient and Adam)
-  // radius above 6: no batched form; each entry's launches run one after
+  // radius above 6, or no row pairs: no batched form; each entry's launches run one after
   // another from these host-side arguments instead
   std::vector<fa::GaussArgs> singles;
   std::vector<Tiling> single_t;
@@ -512,7 +531,6 @@ fa_status build_batch_tables(const std::vector<fa_pair>& live, BatchTables& bt) 
     std::vector<size_t> mem;
     for (size_t j = i; j < n; ++j) {
       if (taken[j] || its[j].window != its[i].window || !same_form(its[j].tg, its[i].tg) ||
-          (its[j].ga.moving_quad != nullptr) != (its[i].ga.moving_quad != nullptr) ||
           (its[j].ga.mode == 0) != (its[i].ga.mode == 0))
         continue;
       taken[j] = 1;
@@ -547,10 +565,13 @@ fa_status build_batch_tables(const std::vector<fa_pair>& live, BatchTables& bt) 
       nb.push_back(its[j].tg.blocks());
     }
     append_launch(bt, 0, its[i].tg, its[i].window, 0, args, nb);
-    bt.launches.back().quad = its[i].ga.moving_quad != nullptr;
     bt.launches.back().adam = its[i].ga.mode == 0;
   }
-  // stages 1 to 3, grouped by radius, epilogue and tiling form
+  // stages 1 to 3, grouped by radius, epilogue and tiling form; a warp
+  // smoothing without row pairs to sample runs per pair, as a wide one
+  auto unpaired = [](const IterPlan& it, int k) {
+    return it.epi[k] == fa::EPI_STORE_WARP && !it.g[k].moving_pairs;
+  };
   static const fa::KernelKind kinds[3] = {fa::KIND_SMOOTH_MAX, fa::KIND_COMPOSE, fa::KIND_WARP_SMOOTH};
   for (int k = 0; k < 3; ++k) {
     std::fill(taken.begin(), taken.end(), 0);
@@ -559,12 +580,13 @@ fa_status build_batch_tables(const std::vector<fa_pair>& live, BatchTables& bt) 
       std::vector<size_t> mem;
       for (size_t j = i; j < n; ++j) {
         if (taken[j] || its[j].radius[k] != its[i].radius[k] || its[j].epi[k] != its[i].epi[k] ||
+            unpaired(its[j], k) != unpaired(its[i], k) ||
             !same_form(its[j].tgs[k], its[i].tgs[k]))
           continue;
         taken[j] = 1;
         mem.push_back(j);
       }
-      if (its[i].radius[k] > fa::kMaxRadius) {
+      if (its[i].radius[k] > fa::kMaxRadius || unpaired(its[i], k)) {
         BatchLaunch bl{k + 1, its[i].tgs[k], its[i].radius[k], its[i].epi[k], 0, 0, 0};
         for (size_t j : mem) {
           bl.singles.push_back(its[j].g[k]);
@@ -619,6 +641,10 @@ fa_status upload_batch_tables(BatchTables& bt, hipStream_t s) {
 fa_status launch_batch_iteration(const std::vector<fa_pair>& live, const BatchTables& bt, hipStream_t s) {
   const unsigned char* base = static_cast<const unsigned char*>(bt.dev);
   bool jac_done = false;
+  // every pair's warped image first: in a symmetric registration each half's
+  // gradient reads the other half's
+  for (fa_pair P : live) FA_TRY(ensure_warped(P, P->levels[P->cur_level]));
+  for (fa_pair P : live) P->warped_ok = false;
   for (const BatchLaunch& bl : bt.launches) {
     if (bl.stage >= 1 && !jac_done) {
       for (int j : bt.jac) FA_TRY(launch_eulerian(live[j], live[j]->levels[live[j]->cur_level]));
@@ -632,12 +658,13 @@ fa_status launch_batch_iteration(const std::vector<fa_pair>& live, const BatchTa
     const int* own = reinterpret_cast<const int*>(base + bl.own_off);
     if (bl.stage == 0) {
       const auto* E = reinterpret_cast<const fa::BatchEntry<fa::GradArgs>*>(base + bl.ent_off);
-      FA_HIP(fa::launch_grad_batch(E, own, bl.total, bl.param, bl.t, bl.quad, bl.adam, s));
+      FA_HIP(fa::launch_grad_batch(E, own, bl.total, bl.param, bl.t, bl.adam, s));
     } else {
       const auto* E = reinterpret_cast<const fa::BatchEntry<fa::GaussArgs>*>(base + bl.ent_off);
       FA_HIP(fa::launch_gauss_batch(E, own, bl.total, bl.param, bl.epi, bl.t, s));
     }
   }
+  for (fa_pair P : live) P->warped_ok = true;
   return FA_OK;
 }
 
@@ -762,7 +789,6 @@ fa_status check_shape(const fa_shape& s) {
   // gathers address one volume with 32-bit signed byte offsets
   if ((double)s.n0 * s.n1 * s.n2 > 536870911.0)
     return fail(FA_ESHAPE, "volume too large: n0*n1*n2 must be < 2^29");
-  // the gradient kernel addresses the padded moving image with 32-bit byte offsets
   if ((double)(s.n0 + 2 * kPad) * (s.n1 + 2 * kPad) * (s.n2 + 2 * kPad) > 1073741823.0)
     return fail(FA_ESHAPE, "volume too large: the padded volume (n+4 per axis) must hold < 2^30 voxels");
   return FA_OK;
@@ -808,7 +834,6 @@ Tiling choose_tiling(const fa_shape& s, KernelKind kind, const Tuning& tu, bool 
     t.ty = tu.ty;
     t.tx = tu.tx;
   }
-  t.variant = tu.variant;
   t.tiles_y = (s.n1 + t.ty - 1) / t.ty;
   t.tiles_x = (s.n2 + t.tx - 1) / t.tx;
   const int plane_tiles = t.tiles_y * t.tiles_x;
@@ -939,7 +964,7 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
     lv[i].tsg = choose_tiling(lv[i].shape, fa::KIND_SMOOTH_MAX, P->tune[1],
                               fa::gauss_cube_supported(P->rg, fa::EPI_SMOOTH_MAX));
     lv[i].tsw = choose_tiling(lv[i].shape, fa::KIND_WARP_SMOOTH, P->tune[2],
-                              fa::gauss_cube_supported(P->rw, fa::EPI_STORE));
+                              fa::gauss_cube_supported(P->rw, fa::EPI_STORE_WARP));
     lv[i].tsc = choose_tiling(lv[i].shape, fa::KIND_COMPOSE, P->tune[3],
                               P->p.eta <= 2.0f && fa::gauss_cube_supported(0, fa::EPI_COMPOSE_LDS));
     {
@@ -979,8 +1004,7 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
       lv[i].fixed = o.fixed;
       lv[i].moving = o.moving;
       lv[i].owns = o.owns;
-      lv[i].moving_pad = o.moving_pad;
-      lv[i].moving_quad = o.moving_quad;
+      lv[i].moving_pairs = o.moving_pairs;
     }
     P->levels = lv;   // owned by the pair while the rest of the call may fail
   } else {
@@ -1021,14 +1045,17 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
   const bool wide = P->rg > fa::kMaxRadius || P->rw > fa::kMaxRadius;
   if (nmax > P->cap || (wide && !P->wide)) {
     (void)hipStreamSynchronize(P->stream);
-    float** bufs[] = {&P->d, &P->m, &P->v, &P->a, &P->tmp, &P->wide};
+    if (P->warped) (void)hipFree(P->warped);
+    P->warped = nullptr;
+    float** bufs[] = {&P->d, &P->m, &P->v, &P->a, &P->tmp, &P->slope, &P->wide};
     for (float** b : bufs) {
       if (*b) (void)hipFree(*b);
       *b = nullptr;
     }
     P->cap = 0;
-    const int nb = wide ? 6 : 5;
+    const int nb = wide ? 7 : 6;
     for (int k = 0; k < nb; ++k) FA_TRY(dalloc(bufs[k], (size_t)3 * nmax, "state"));
+    FA_TRY(dalloc(&P->warped, (size_t)nmax, "warped image"));
     P->cap = nmax;
   }
   if (total_iters > P->loss_cap) {
@@ -1077,17 +1104,13 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
     FA_TRY(build_level_image(P, P->in_fixed, L.fixed, L, P->off_blur[i]));
     FA_TRY(build_level_image(P, P->in_moving, L.moving, L, P->off_blur[i]));
   }
+
   for (auto& L : P->levels) {
-    if (!L.moving_pad)
-      FA_TRY(dalloc(&L.moving_pad, (size_t)fa::padded_voxels(L.shape.n0, L.shape.n1, L.shape.n2),
-                    "padded moving"));
-    FA_HIP(fa::launch_pad(L.moving, L.moving_pad, L.shape.n0, L.shape.n1, L.shape.n2, P->stream));
-    if (fa::quad_supported(L.shape.n0, L.shape.n1, L.shape.n2)) {
-      if (!L.moving_quad)
-        FA_TRY(dalloc(&L.moving_quad, (size_t)4 * fa::padded_voxels(L.shape.n0, L.shape.n1, L.shape.n2),
-                      "padded moving quads"));
-      FA_HIP(fa::launch_pad_quad(L.moving_pad, L.moving_quad, L.shape.n0, L.shape.n1, L.shape.n2, P->stream));
-    }
+    if (!fa::row_pairs_supported(L.shape.n0, L.shape.n1, L.shape.n2)) continue;
+    if (!L.moving_pairs)
+      FA_TRY(dalloc(&L.moving_pairs, (size_t)2 * fa::padded_voxels(L.shape.n0, L.shape.n1, L.shape.n2),
+                    "moving row pairs"));
+    FA_HIP(fa::launch_row_pairs(L.moving, L.moving_pairs, L.shape.n0, L.shape.n1, L.shape.n2, P->stream));
   }
 
   // State: phi = id, m = v = 0, t = 0.
@@ -1104,6 +1127,7 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
   P->t_done = 0;
   P->iters_done = 0;
   P->scheduled = true;
+  P->warped_ok = false;
   return FA_OK;
 }
 
@@ -1268,6 +1292,7 @@ fa_status fa_pair_set_state(fa_pair P, const float* d, const float* m, const flo
   if (v) FA_HIP(hipMemcpyAsync(P->v, v, bytes, hipMemcpyDeviceToDevice, P->stream));
   FA_HIP(fa::launch_ctl_init(P->ctl, P->p.adam_beta1, P->p.adam_beta2, t_done, -1, P->stream));
   P->t_done = t_done;
+  if (d) P->warped_ok = false;
   return FA_OK;
 }
 
@@ -1288,10 +1313,9 @@ fa_status fa_pair_eval_gradient(fa_pair P, float* g_dev, float* loss_host) {
   const Level& L = P->levels[P->cur_level];
   fa::GradArgs ga{};
   ga.fixed = L.fixed;
-  ga.moving_pad = L.moving_pad;
-  ga.moving_quad = L.moving_quad;
-  ga.d = P->d;
+  ga.warped = P->warped;
   ga.out = g_dev ? g_dev : P->tmp;
+  ga.slope = P->slope;
   ga.partials = P->partials;
   ga.ctl = P->ctl;
   ga.n0 = L.shape.n0;
@@ -1303,6 +1327,7 @@ fa_status fa_pair_eval_gradient(fa_pair P, float* g_dev, float* loss_host) {
   ga.eps_cc = P->p.cc_eps;
   ga.inv_n = (float)(1.0 / (double)L.n);
   ga.mode = 1;
+  FA_TRY(ensure_warped(P, L));
   FA_HIP(fa::launch_grad(ga, P->p.cc_window, L.tg, P->stream));
   if (loss_host) {
     FA_HIP(fa::launch_sum_partials(P->partials, L.tg.blocks(), P->scratch + fa::kMeanBlocks, P->stream));
@@ -1534,7 +1559,7 @@ fa_status fa_pair_autotune(fa_pair P, int trials) {
     for (int k = 0; k < 3 && st == FA_OK; ++k) {
       const bool cube_ok = k == 0   ? fa::gauss_cube_supported(P->rg, fa::EPI_SMOOTH_MAX)
                            : k == 1 ? (P->p.eta <= 2.0f && fa::gauss_cube_supported(0, fa::EPI_COMPOSE_LDS))
-                                    : fa::gauss_cube_supported(P->rw, fa::EPI_STORE);
+                                    : fa::gauss_cube_supported(P->rw, fa::EPI_STORE_WARP);
       std::vector<Tiling> cs = tiling_candidates(L.shape, kinds[k], *slots[k], cube_ok);
       fa::GaussArgs g = it.g[k];
       g.ctl = sctl;
@@ -1546,6 +1571,7 @@ fa_status fa_pair_autotune(fa_pair P, int trials) {
       } else {
         g.in = P->tmp;
         g.out = P->a;
+        P->warped_ok = false;   // the timed launches leave J and its slope at another field
       }
       if (g.partials) {   // the record runs (on the scratch control block) but stores no loss
         g.loss_hist = nullptr;
@@ -1606,13 +1632,10 @@ fa_status fa_pair_get_tiling(fa_pair P, int level, int kind, int* ty, int* tx, i
 // Two pairs share the handle's stream: M registers I_M (its moving image)
 // toward I_F o phi_F, F registers I_F toward I_M o phi_M.  Each pair's
 // level-l fixed image is the other side's level-l image; the warped images
-// replace it as the fixed image of every iteration.
+// (each pair's `warped`) replace it as the fixed image of every iteration.
 struct fa_sym_s {
   fa_pair F = nullptr;
   fa_pair M = nullptr;
-  float* wf = nullptr;   // I_F o phi_F at the current level
-  float* wm = nullptr;   // I_M o phi_M
-  int64_t wcap = 0;
   hipStream_t stream = nullptr;
   fa_shape shape{};
 };
@@ -1642,18 +1665,6 @@ fa_status fa_sym_set_schedule(fa_sym H, int n_levels, const float* scales, const
   if (!H) return fail(FA_EINVAL, "handle is NULL");
   FA_TRY(fa_pair_set_schedule(H->F, n_levels, scales, iters));
   FA_TRY(fa_pair_set_schedule(H->M, n_levels, scales, iters));
-  int64_t nmax = 0;
-  for (const Level& L : H->M->levels) nmax = std::max(nmax, L.n);
-  if (nmax > H->wcap) {
-    FA_HIP(hipStreamSynchronize(H->stream));
-    if (H->wf) (void)hipFree(H->wf);
-    if (H->wm) (void)hipFree(H->wm);
-    H->wf = H->wm = nullptr;
-    H->wcap = 0;
-    FA_TRY(dalloc(&H->wf, (size_t)nmax, "warped image"));
-    FA_TRY(dalloc(&H->wm, (size_t)nmax, "warped image"));
-    H->wcap = nmax;
-  }
   return FA_OK;
 }
 
@@ -1664,8 +1675,8 @@ fa_status fa_sym_step(fa_sym H, int max_iters, int* iters_done, int* finished) {
   if (!H->F->scheduled || !H->M->scheduled) return fail(FA_ESTATE, "fa_sym_set_schedule has not been called");
   if (max_iters < 0) return fail(FA_EINVAL, "max_iters must be >= 0");
   fa_pair F = H->F, M = H->M;
-  M->fixed_override = H->wf;
-  F->fixed_override = H->wm;
+  M->fixed_override = F->warped;
+  F->fixed_override = M->warped;
   // the two halves share every template parameter: each kernel of an
   // iteration is one batched launch over both
   const std::vector<fa_pair> both = {M, F};
@@ -1680,16 +1691,6 @@ fa_status fa_sym_step(fa_sym H, int max_iters, int* iters_done, int* finished) {
       if ((st = build_batch_tables(both, bt)) != FA_OK) break;
       if ((st = upload_batch_tables(bt, H->stream)) != FA_OK) break;
       level = M->cur_level;
-    }
-    const Level& LF = F->levels[F->cur_level];
-    const Level& LM = M->levels[M->cur_level];
-    const fa_shape& s = LM.shape;
-    // both warped images first: the two halves step from the same pair of warps
-    hipError_t he = fa::launch_warp(LF.moving, F->d, H->wf, s.n0, s.n1, s.n2, H->stream);
-    if (he == hipSuccess) he = fa::launch_warp(LM.moving, M->d, H->wm, s.n0, s.n1, s.n2, H->stream);
-    if (he != hipSuccess) {
-      st = fail(FA_EHIP, std::string("warp: ") + hipGetErrorString(he));
-      break;
     }
     if ((st = launch_batch_iteration(both, bt, H->stream)) != FA_OK) break;
     for (fa_pair P : both) {
@@ -1768,8 +1769,6 @@ fa_status fa_sym_finish(fa_sym H, const fa_params* inv_params, int n_levels, con
 void fa_sym_destroy(fa_sym H) {
   if (!H) return;
   (void)hipStreamSynchronize(H->stream);
-  if (H->wf) (void)hipFree(H->wf);
-  if (H->wm) (void)hipFree(H->wm);
   fa_pair_destroy(H->F);
   fa_pair_destroy(H->M);
   delete H;
