@@ -160,10 +160,16 @@ hipError_t launch_fill(float* p, float value, int64_t n, hipStream_t s);
 // Row pairs of the moving image with a zero border (2 * padded_voxels floats,
 // 8-byte aligned; row_pairs_supported must hold).
 hipError_t launch_row_pairs(const float* in, float* out, int n0, int n1, int n2, hipStream_t s);
-hipError_t launch_blur_axis(const float* in, float* out, int n0, int n1, int n2, int axis,
-                            const float* wts, int radius, hipStream_t s);
+// Level images of `count` (1 to 3) volumes [n0][n1][n2]: blurred along n0, n1,
+// n2 with the 2R + 1 taps wts (replicate boundary, R >= 1), sampled trilinearly
+// at the corner-aligned positions of the m0 x m1 x m2 grid, times rho[i].  tmp0
+// and tmp1: scratch of count * n0 * n1 * n2 floats each, distinct from the rest.
+hipError_t launch_level_images(const float* const* src, float* const* dst, const float* rho, int count, float* tmp0,
+                               float* tmp1, int n0, int n1, int n2, int m0, int m1, int m2, const float* wts, int R,
+                               hipStream_t s);
+// Trilinear samples of a [3][N] field at corner-aligned positions, component c times rho_c.
 hipError_t launch_resample(const float* in, float* out, int nin0, int nin1, int nin2,
-                           int nout0, int nout1, int nout2, int nch,
+                           int nout0, int nout1, int nout2,
                            float rho0, float rho1, float rho2, hipStream_t s);
 hipError_t launch_warp(const float* img, const float* d, float* out, int n0, int n1, int n2,
                        hipStream_t s);

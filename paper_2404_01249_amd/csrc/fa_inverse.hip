@@ -406,10 +406,10 @@ fa_status transition(fa_inverse H) {
   auto rho = [](int nf, int nc) { return nc > 1 ? (float)((double)(nf - 1) / (double)(nc - 1)) : 1.0f; };
   const fa_shape& c = C.shape;
   const fa_shape& f = F.shape;
-  FA_HIP(fa::launch_resample(H->e, H->tmp, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 3, rho(f.n0, c.n0),
+  FA_HIP(fa::launch_resample(H->e, H->tmp, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, rho(f.n0, c.n0),
                              rho(f.n1, c.n1), rho(f.n2, c.n2), H->stream));
-  FA_HIP(fa::launch_resample(H->m, H->a, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 3, 1.f, 1.f, 1.f, H->stream));
-  FA_HIP(fa::launch_resample(H->v, H->m, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 3, 1.f, 1.f, 1.f, H->stream));
+  FA_HIP(fa::launch_resample(H->m, H->a, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 1.f, 1.f, 1.f, H->stream));
+  FA_HIP(fa::launch_resample(H->v, H->m, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 1.f, 1.f, 1.f, H->stream));
   // the fine e, m, v now sit in tmp, a, m; the coarse e and v buffers are free
   float* old_e = H->e;
   float* old_m = H->m;
@@ -583,7 +583,7 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
   FA_HIP(hipMemcpyAsync(H->wts, host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice, H->stream));
 
   // state (sized for the largest level) and the splat accumulator
-  const int64_t need = std::max(nmax, H->n);   // the blur scratch below spans 5 input-sized volumes
+  const int64_t need = std::max(nmax, H->n);   // m and e hold three input volumes each below
   const bool wide = H->rg > fa::kMaxRadius || H->rw > fa::kMaxRadius;
   if (need > H->cap || (wide && !H->wide)) {
     float** bufs[] = {&H->e, &H->m, &H->v, &H->a, &H->tmp, &H->wide};
@@ -610,7 +610,7 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
     H->loss_cap = (int)total;
   }
 
-  // pyramid of the warp's field; e, m, v, a serve as blur scratch before the state is set
+  // pyramid of the warp's field; m and e serve as scratch before the state is set
   H->levels = lv;
   for (int i = 0; i < n_levels; ++i) {
     ILevel& L = H->levels[i];
@@ -621,22 +621,17 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
     }
     FA_TRY(ialloc(&L.d, (size_t)(3 * L.n), "level field"));
     L.owns = true;
-    // blur scratch: two volumes in m, the blurred field in e (both hold 3 input-sized volumes)
-    float* p0p1 = H->m;
-    float* blurred = H->e;
     const fa_shape& s = H->shape;
-    const int64_t n = H->n;
-    const int rad = fa::tap_radius(L.scale / 2.0f);
-    const float* w = H->wts + off_blur[i];
+    const float* src[3];
+    float* dst[3];
     for (int c = 0; c < 3; ++c) {
-      FA_HIP(fa::launch_blur_axis(H->in_d + c * n, p0p1, s.n0, s.n1, s.n2, 0, w, rad, H->stream));
-      FA_HIP(fa::launch_blur_axis(p0p1, p0p1 + n, s.n0, s.n1, s.n2, 1, w, rad, H->stream));
-      FA_HIP(fa::launch_blur_axis(p0p1 + n, blurred + c * n, s.n0, s.n1, s.n2, 2, w, rad, H->stream));
+      src[c] = H->in_d + c * H->n;
+      dst[c] = L.d + c * L.n;
     }
     auto inv_rho = [](int nf, int nc) { return nc > 1 ? (float)((double)(nc - 1) / (double)(nf - 1)) : 1.0f; };
-    FA_HIP(fa::launch_resample(blurred, L.d, s.n0, s.n1, s.n2, L.shape.n0, L.shape.n1, L.shape.n2, 3,
-                               inv_rho(s.n0, L.shape.n0), inv_rho(s.n1, L.shape.n1), inv_rho(s.n2, L.shape.n2),
-                               H->stream));
+    const float rho[3] = {inv_rho(s.n0, L.shape.n0), inv_rho(s.n1, L.shape.n1), inv_rho(s.n2, L.shape.n2)};
+    FA_HIP(fa::launch_level_images(src, dst, rho, 3, H->m, H->e, s.n0, s.n1, s.n2, L.shape.n0, L.shape.n1, L.shape.n2,
+                                   H->wts + off_blur[i], fa::tap_radius(L.scale / 2.0f), H->stream));
   }
 
   // psi = id, m = v = 0, t = 0

@@ -2112,31 +2112,96 @@ __global__ void __launch_bounds__(kWideThreads) k_field_wide_yz(const float* __r
   }
 }
 
-__global__ void k_blur_axis(const float* __restrict__ in, float* __restrict__ out, int n0, int n1,
-                            int n2, int axis, const float* __restrict__ w, int R) {
-  const int N = n0 * n1 * n2;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  const int x = i % n2, y = (i / n2) % n1, z = i / (n1 * n2);
-  const int pos = axis == 0 ? z : (axis == 1 ? y : x);
-  const int n = axis == 0 ? n0 : (axis == 1 ? n1 : n2);
-  const int stride = axis == 0 ? n1 * n2 : (axis == 1 ? n2 : 1);
-  float s = 0.0f;
-  for (int k = -R; k <= R; ++k) {
-    const int q = min(max(pos + k, 0), n - 1);
-    s += w[k + R] * in[i + (q - pos) * stride];
-  }
-  out[i] = s;
+__device__ __forceinline__ float aligned_pos(int i, int nin, int nout) {
+  return nout > 1 ? (float)(i * (nin - 1)) / (float)(nout - 1) : 0.0f;
 }
 
-// The same blur along n0 or n1 with T consecutive outputs per thread: the
+// ---- level images ------------------------------------------------------------
+// A level's image is the input blurred along n0, n1, n2 and sampled trilinearly
+// at corner-aligned positions.  Along an axis of n inputs and m samples only
+// the 2m entries floor(pos) and floor(pos) + 1 of the blurred input are read,
+// so where 2m < n ("compact", and wherever the radius is above 3) the passes along n0 and n1 form only those, entry
+// 2k + b at input floor(pos(k)) + b, and the last pass blurs along n2 just the
+// eight corners it samples.  The taps, their order and the sample are those of
+// the full blur, so the values are the same.  At scale 8 the first pass writes
+// a quarter of the volume and the second a sixteenth.  (512^3, scales 8, 4, 2,
+// two images: 2.7 ms; 13.9 when every entry was blurred and then resampled, the
+// radius-12 passes 10.3 of them.)  Up to three images go through one launch per pass.
+struct Images {
+  const float* in[3];
+  float* out[3];
+};
+
+// Splits a launch over `outer` rows of `inner` consecutive items: whole
+// workgroups per row (BLK), so that everything but the item is uniform, or flat
+// over all items where a row is too short to fill a wavefront.
+template <bool BLK>
+__device__ __forceinline__ bool row_item(unsigned inner, unsigned outer, unsigned& row, unsigned& item) {
+  if constexpr (BLK) {
+    const unsigned nb = (inner + blockDim.x - 1) / blockDim.x;
+    row = blockIdx.x / nb;
+    item = (blockIdx.x - row * nb) * blockDim.x + threadIdx.x;
+    return item < inner;
+  } else {
+    const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
+    row = t / inner;
+    item = t - row * inner;
+    return row < outer;
+  }
+}
+
+// floor of the position of sample k
+__device__ __forceinline__ int aligned_cell(int k, int nin, int nout) {
+  int i;
+  float t;
+  bool lo, hi;
+  cell(aligned_pos(k, nin, nout), nin, i, t, lo, hi);
+  return i;
+}
+
+// Entries 2k and 2k + 1 (inputs floor(pos(k)) and the next) of the blur along
+// n0 (AX 0) or n1 (AX 1) of `count` images [n0][n1][n2]: na is the blurred axis'
+// inputs, nm its samples, n_other the other of the two axes.  Both entries take
+// the 2R + 2 inputs they share; radius RT, or R at run time (RT = 0).  A thread
+// takes kg consecutive k, so that the inputs that neighbouring k share (26 - 8
+// of 26 at scale 8) come from the caches.
+template <int AX, int RT, bool BLK>
+__global__ void __launch_bounds__(256) k_blur_pairs(const Images im, unsigned count, int na, int nm, int n_other,
+                                                    int n2, const float* __restrict__ w, int Rr, int kg) {
+  const int R = RT ? RT : Rr;
+  // a row: the items [n_other][n2] (AX 0) or [n2] at one n0 (AX 1) of one image and one group of k
+  const unsigned inner = AX == 0 ? (unsigned)n_other * n2 : (unsigned)n2;
+  const unsigned groups = (unsigned)(nm + kg - 1) / kg;
+  const unsigned per_image = AX == 0 ? groups : n_other * groups;
+  unsigned row, item;
+  if (!row_item<BLK>(inner, per_image * count, row, item)) return;
+  const unsigned img = row / per_image, r = row - img * per_image, z = AX == 0 ? 0u : r / groups;
+  const int k0 = (int)(r - z * groups) * kg;
+  const size_t stride = inner;
+  const float* src = im.in[img] + (size_t)z * na * stride + item;
+  float* dst = im.out[img] + ((size_t)z * (2 * nm) + 2 * k0) * stride + item;
+  for (int k = k0; k < min(k0 + kg, nm); ++k, dst += 2 * stride) {
+    const int f = aligned_cell(k, na, nm);
+    float s0 = 0.0f, s1 = 0.0f;
+    float x = src[(size_t)min(max(f - R, 0), na - 1) * stride];
+#pragma unroll(RT ? 2 * RT + 1 : 4)
+    for (int j = 0; j <= 2 * R; ++j) {
+      const float y = src[(size_t)min(max(f - R + 1 + j, 0), na - 1) * stride];
+      s0 += w[j] * x;
+      s1 += w[j] * y;
+      x = y;
+    }
+    dst[0] = s0;
+    dst[stride] = s1;
+  }
+}
+
+// The blur along n0 or n1 of every entry, T consecutive outputs per thread: the
 // T + 2R inputs of a run are loaded once into registers instead of 2R + 1
 // times per output through the caches.  Consecutive threads take consecutive
-// lines (x fastest), so every load is coalesced.  Each output sums the same
-// taps in the same order as k_blur_axis, so the results are bitwise equal.
+// lines (x fastest), so every load is coalesced.
 template <int R, int T>
-__global__ void __launch_bounds__(256) k_blur_axis_run(const float* __restrict__ in, float* __restrict__ out,
-                                                       int n0, int n1, int n2, int axis,
+__global__ void __launch_bounds__(256) k_blur_axis_run(const Images im, int n0, int n1, int n2, int axis,
                                                        const float* __restrict__ w) {
   const int n = axis == 0 ? n0 : n1;
   const int stride = axis == 0 ? n1 * n2 : n2;
@@ -2144,6 +2209,8 @@ __global__ void __launch_bounds__(256) k_blur_axis_run(const float* __restrict__
   const int runs = (n + T - 1) / T;
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= lines * runs) return;
+  const float* __restrict__ in = im.in[blockIdx.y];
+  float* __restrict__ out = im.out[blockIdx.y];
   const int l = t % lines, r = t / lines;
   const int base = axis == 0 ? l : (l / n2) * (n1 * n2) + l % n2;
   const int p0 = r * T;
@@ -2164,30 +2231,55 @@ __global__ void __launch_bounds__(256) k_blur_axis_run(const float* __restrict__
   }
 }
 
-// The same blur along n2 on a (n2 / 256, n1, n0) grid: the voxel comes from
-// the block indices, with none of the runtime integer divisions of the flat
-// form, and each lane's 2R + 1 taps are neighbouring floats.  Same taps and
-// order as k_blur_axis (bitwise equal).
-template <int R>
-__global__ void __launch_bounds__(256) k_blur_x(const float* __restrict__ in, float* __restrict__ out, int n2,
-                                                const float* __restrict__ w) {
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  if (x >= n2) return;
-  const size_t row = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * (size_t)n2;
-  float s = 0.0f;
+// The blur along n2 of the eight corners of each sample, and the sample, times
+// rho[image].  im.in holds the images after the passes along n0 and n1,
+// [p0][p1][n2] (p0 = 2 m0 where compact, else n0; p1 likewise).
+template <int RT, bool BLK>
+__global__ void __launch_bounds__(256) k_level_sample(const Images im, unsigned count, int n0, int n1, int n2, int m0, int m1, int m2,
+                                                      bool c0, bool c1, float rho0, float rho1, float rho2,
+                                                      const float* __restrict__ w, int Rr) {
+  const int R = RT ? RT : Rr;
+  unsigned row, item;
+  const unsigned per_image = (unsigned)m0 * m1;
+  if (!row_item<BLK>((unsigned)m2, per_image * count, row, item)) return;
+  const unsigned img = row / per_image, r = row - img * per_image;
+  const int k1 = (int)(r % m1), k0 = (int)(r / m1), k2 = (int)item;
+  Corners c = make_corners(n0, n1, n2, aligned_pos(k0, n0, m0), aligned_pos(k1, n1, m1), aligned_pos(k2, n2, m2));
+  const int i0 = aligned_cell(k0, n0, m0), i1 = aligned_cell(k1, n1, m1), i2 = aligned_cell(k2, n2, m2);
+  const int p1 = c1 ? 2 * m1 : n1;
+  float v[8];
 #pragma unroll
-  for (int k = -R; k <= R; ++k) s += w[k + R] * in[row + min(max(x + k, 0), n2 - 1)];
-  out[row + x] = s;
-}
-
-__device__ __forceinline__ float aligned_pos(int i, int nin, int nout) {
-  return nout > 1 ? (float)(i * (nin - 1)) / (float)(nout - 1) : 0.0f;
+  for (int b = 0; b < 4; ++b) {
+    const int b0 = b >> 1, b1 = b & 1;
+    const int z = c0 ? 2 * k0 + b0 : min(max(i0 + b0, 0), n0 - 1);
+    const int y = c1 ? 2 * k1 + b1 : min(max(i1 + b1, 0), n1 - 1);
+    const float* src = im.in[img] + ((size_t)z * p1 + y) * n2;
+    float s0 = 0.0f, s1 = 0.0f;
+    float x = src[min(max(i2 - R, 0), n2 - 1)];
+#pragma unroll(RT ? 2 * RT + 1 : 4)
+    for (int j = 0; j <= 2 * R; ++j) {
+      const float t = src[min(max(i2 - R + 1 + j, 0), n2 - 1)];
+      s0 += w[j] * x;
+      s1 += w[j] * t;
+      x = t;
+    }
+    const bool in0 = b0 ? c.b0 : c.a0, in1 = b1 ? c.b1 : c.a1;
+    v[2 * b] = in0 & in1 & c.a2 ? s0 : 0.0f;
+    v[2 * b + 1] = in0 & in1 & c.b2 ? s1 : 0.0f;
+  }
+  const float e00 = v[0] + c.t2 * (v[1] - v[0]);
+  const float e01 = v[2] + c.t2 * (v[3] - v[2]);
+  const float e10 = v[4] + c.t2 * (v[5] - v[4]);
+  const float e11 = v[6] + c.t2 * (v[7] - v[6]);
+  const float f0 = e00 + c.t1 * (e01 - e00);
+  const float f1 = e10 + c.t1 * (e11 - e10);
+  const float rho = img == 0 ? rho0 : (img == 1 ? rho1 : rho2);
+  im.out[img][(size_t)r * m2 + k2] = rho * (f0 + c.t0 * (f1 - f0));
 }
 
 template <bool G3>
 __global__ void k_resample(const float* __restrict__ in, float* __restrict__ out, int ni0, int ni1,
-                           int ni2, int no0, int no1, int no2, int nch, float rho0, float rho1,
-                           float rho2) {
+                           int ni2, int no0, int no1, int no2, float rho0, float rho1, float rho2) {
   const int No = no0 * no1 * no2;
   const int Ni = ni0 * ni1 * ni2;
   int z, y, x, i;
@@ -2195,10 +2287,8 @@ __global__ void k_resample(const float* __restrict__ in, float* __restrict__ out
   const Corners c = make_corners(ni0, ni1, ni2, aligned_pos(z, ni0, no0), aligned_pos(y, ni1, no1),
                                  aligned_pos(x, ni2, no2));
   out[i] = rho0 * tri(in, c);
-  if (nch > 1) {
-    out[No + i] = rho1 * tri(in + Ni, c);
-    out[2 * No + i] = rho2 * tri(in + 2 * Ni, c);
-  }
+  out[No + i] = rho1 * tri(in + Ni, c);
+  out[2 * No + i] = rho2 * tri(in + 2 * Ni, c);
 }
 
 // J = I_m(x + d) and, with SLOPE, its position derivative ([3][N]): one
@@ -2696,62 +2786,108 @@ hipError_t launch_fill(float* p, float value, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Workgroup size for rows of n items: whole workgroups per row (0: too short,
+// take the flat form).
+static inline int row_block(int64_t n) { return n >= 192 ? 256 : (n >= 96 ? 128 : (n >= 32 ? 64 : 0)); }
+
 template <int R>
-hipError_t blur_axis_run(const float* in, float* out, int n0, int n1, int n2, int axis, const float* wts,
+hipError_t blur_axis_run(const Images& im, int count, int n0, int n1, int n2, int axis, const float* wts,
                          hipStream_t s) {
   constexpr int T = 8;
   const int n = axis == 0 ? n0 : n1;
   const int64_t threads = (int64_t)n0 * n1 * n2 / n * ((n + T - 1) / T);
-  hipLaunchKernelGGL((k_blur_axis_run<R, T>), dim3(grid1(threads, 256)), dim3(256), 0, s, in, out, n0, n1, n2,
-                     axis, wts);
+  hipLaunchKernelGGL((k_blur_axis_run<R, T>), dim3(grid1(threads, 256), count), dim3(256), 0, s, im, n0, n1, n2, axis,
+                     wts);
   return hipGetLastError();
 }
 
-template <int R>
-hipError_t blur_x(const float* in, float* out, int n0, int n1, int n2, const float* wts, hipStream_t s) {
-  hipLaunchKernelGGL((k_blur_x<R>), dim3(grid1(n2, 256), n1, n0), dim3(256), 0, s, in, out, n2, wts);
+template <int AX, int RT>
+hipError_t blur_pairs(const Images& im, int count, int na, int nm, int n_other, int n2, const float* wts, int R,
+                      hipStream_t s) {
+  const int64_t inner = AX == 0 ? (int64_t)n_other * n2 : n2;
+  const int64_t rows = (int64_t)count * (AX == 0 ? 1 : n_other);   // times the groups of k
+  // a thread takes up to eight k while that leaves every CU its 2048 threads
+  const int kg = (int)std::min<int64_t>(8, std::max<int64_t>(1, rows * inner * nm / (256 * 2048)));
+  const int64_t all = rows * ((nm + kg - 1) / kg);
+  if (const int bs = row_block(inner))
+    hipLaunchKernelGGL((k_blur_pairs<AX, RT, true>), dim3((unsigned)(all * ((inner + bs - 1) / bs))), dim3(bs), 0, s,
+                       im, count, na, nm, n_other, n2, wts, R, kg);
+  else
+    hipLaunchKernelGGL((k_blur_pairs<AX, RT, false>), dim3(grid1(all * inner, 256)), dim3(256), 0, s, im, count, na,
+                       nm, n_other, n2, wts, R, kg);
   return hipGetLastError();
 }
 
-hipError_t launch_blur_axis(const float* in, float* out, int n0, int n1, int n2, int axis,
-                            const float* wts, int radius, hipStream_t s) {
-  if (axis == 2 && n0 <= 65535 && n1 <= 65535) {   // grid y and z hold n1 and n0
-    switch (radius) {
-      case 1: return blur_x<1>(in, out, n0, n1, n2, wts, s);
-      case 2: return blur_x<2>(in, out, n0, n1, n2, wts, s);
-      case 3: return blur_x<3>(in, out, n0, n1, n2, wts, s);
-      case 4: return blur_x<4>(in, out, n0, n1, n2, wts, s);
-      case 5: return blur_x<5>(in, out, n0, n1, n2, wts, s);
-      case 6: return blur_x<6>(in, out, n0, n1, n2, wts, s);
-      default: break;
+// One pass of the blur along n0 or n1: the entries that are sampled (compact) or all.
+template <int AX>
+hipError_t blur_pass(const Images& im, int count, int n0, int n1, int n2, int nm, bool compact, const float* wts, int R,
+                     hipStream_t s) {
+  const int na = AX == 0 ? n0 : n1, other = AX == 0 ? n1 : n0;
+  if (compact) {
+    switch (R) {   // radii of the usual scales (4 and 8) unrolled
+      case 6: return blur_pairs<AX, 6>(im, count, na, nm, other, n2, wts, R, s);
+      case 12: return blur_pairs<AX, 12>(im, count, na, nm, other, n2, wts, R, s);
+      default: return blur_pairs<AX, 0>(im, count, na, nm, other, n2, wts, R, s);
     }
   }
-  if (axis != 2) {   // the run form for strided axes (radii of the pyramid's usual scales)
-    switch (radius) {
-      case 1: return blur_axis_run<1>(in, out, n0, n1, n2, axis, wts, s);
-      case 2: return blur_axis_run<2>(in, out, n0, n1, n2, axis, wts, s);
-      case 3: return blur_axis_run<3>(in, out, n0, n1, n2, axis, wts, s);
-      case 4: return blur_axis_run<4>(in, out, n0, n1, n2, axis, wts, s);
-      case 5: return blur_axis_run<5>(in, out, n0, n1, n2, axis, wts, s);
-      case 6: return blur_axis_run<6>(in, out, n0, n1, n2, axis, wts, s);
-      default: break;
-    }
+  switch (R) {   // compact where R > 3
+    case 1: return blur_axis_run<1>(im, count, n0, n1, n2, AX, wts, s);
+    case 2: return blur_axis_run<2>(im, count, n0, n1, n2, AX, wts, s);
+    case 3: return blur_axis_run<3>(im, count, n0, n1, n2, AX, wts, s);
+    default: return hipErrorInvalidValue;
   }
-  const int64_t n = (int64_t)n0 * n1 * n2;
-  hipLaunchKernelGGL(k_blur_axis, dim3(grid1(n, 256)), dim3(256), 0, s, in, out, n0, n1, n2, axis, wts, radius);
+}
+
+template <int RT>
+hipError_t level_sample(const Images& im, int count, int n0, int n1, int n2, int m0, int m1, int m2, bool c0, bool c1,
+                        const float* rho, const float* wts, int R, hipStream_t s) {
+  const int64_t rows = (int64_t)count * m0 * m1;
+  if (const int bs = row_block(m2))
+    hipLaunchKernelGGL((k_level_sample<RT, true>), dim3((unsigned)(rows * ((m2 + bs - 1) / bs))), dim3(bs), 0, s, im,
+                       count, n0, n1, n2, m0, m1, m2, c0, c1, rho[0], rho[1], rho[2], wts, R);
+  else
+    hipLaunchKernelGGL((k_level_sample<RT, false>), dim3(grid1(rows * m2, 256)), dim3(256), 0, s, im, count, n0, n1,
+                       n2, m0, m1, m2, c0, c1, rho[0], rho[1], rho[2], wts, R);
   return hipGetLastError();
+}
+
+hipError_t launch_level_images(const float* const* src, float* const* dst, const float* rho, int count, float* tmp0,
+                               float* tmp1, int n0, int n1, int n2, int m0, int m1, int m2, const float* wts, int R,
+                               hipStream_t s) {
+  if (count < 1 || count > 3 || R < 1) return hipErrorInvalidValue;
+  // Scale 2 and below (2m >= n, radius at most 3) leave out so little that the
+  // run form's shared loads win; a larger radius always has 2m <= n.
+  const bool c0 = 2 * m0 < n0 || R > 3, c1 = 2 * m1 < n1 || R > 3;
+  const int p0 = c0 ? 2 * m0 : n0, p1 = c1 ? 2 * m1 : n1;
+  Images a{}, b{}, c{};
+  for (int i = 0; i < count; ++i) {
+    a.in[i] = src[i];
+    a.out[i] = tmp0 + (size_t)i * p0 * n1 * n2;
+    b.in[i] = a.out[i];
+    b.out[i] = tmp1 + (size_t)i * p0 * p1 * n2;
+    c.in[i] = b.out[i];
+    c.out[i] = dst[i];
+  }
+  hipError_t e = blur_pass<0>(a, count, n0, n1, n2, m0, c0, wts, R, s);
+  if (e == hipSuccess) e = blur_pass<1>(b, count, p0, n1, n2, m1, c1, wts, R, s);
+  if (e != hipSuccess) return e;
+  switch (R) {   // scales 2, 4 and 8 unrolled
+    case 3: return level_sample<3>(c, count, n0, n1, n2, m0, m1, m2, c0, c1, rho, wts, R, s);
+    case 6: return level_sample<6>(c, count, n0, n1, n2, m0, m1, m2, c0, c1, rho, wts, R, s);
+    case 12: return level_sample<12>(c, count, n0, n1, n2, m0, m1, m2, c0, c1, rho, wts, R, s);
+    default: return level_sample<0>(c, count, n0, n1, n2, m0, m1, m2, c0, c1, rho, wts, R, s);
+  }
 }
 
 hipError_t launch_resample(const float* in, float* out, int nin0, int nin1, int nin2, int nout0,
-                           int nout1, int nout2, int nch, float rho0, float rho1, float rho2,
-                           hipStream_t s) {
+                           int nout1, int nout2, float rho0, float rho1, float rho2, hipStream_t s) {
   if (nout0 <= 65535 && nout1 <= 65535) {   // grid z and y hold n0 and n1
     hipLaunchKernelGGL(k_resample<true>, dim3(grid1(nout2, 256), nout1, nout0), dim3(256), 0, s, in, out, nin0,
-                       nin1, nin2, nout0, nout1, nout2, nch, rho0, rho1, rho2);
+                       nin1, nin2, nout0, nout1, nout2, rho0, rho1, rho2);
   } else {
     const int64_t n = (int64_t)nout0 * nout1 * nout2;
     hipLaunchKernelGGL(k_resample<false>, dim3(grid1(n, 256)), dim3(256), 0, s, in, out, nin0, nin1, nin2,
-                       nout0, nout1, nout2, nch, rho0, rho1, rho2);
+                       nout0, nout1, nout2, rho0, rho1, rho2);
   }
   return hipGetLastError();
 }

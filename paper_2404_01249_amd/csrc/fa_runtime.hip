@@ -131,8 +131,7 @@ struct fa_pair_s {
   bool warped_ok = false;     // whether the queued work leaves them at the current d
   float* tmp = nullptr;       // smoothed direction s, then the composed d'
   float* wide = nullptr;      // [3][cap] scratch of the smoothing passes with a radius above 6
-  float* blur0 = nullptr;     // pyramid scratch (input size)
-  float* blur1 = nullptr;
+  float* blur = nullptr;      // pyramid scratch (two input volumes), where the state's buffers are too small for it
   Ctl* ctl = nullptr;
   float* loss_hist = nullptr;
   int loss_cap = 0;
@@ -189,7 +188,7 @@ void free_levels(fa_pair P) {
 void free_all(fa_pair P) {
   free_levels(P);
   float* fbufs[] = {P->in_fixed, P->in_moving, P->d, P->m, P->v, P->a, P->warped, P->slope, P->tmp,
-                    P->wide, P->blur0, P->blur1, P->loss_hist, P->wts};
+                    P->wide, P->blur, P->loss_hist, P->wts};
   for (float* b : fbufs)
     if (b) (void)hipFree(b);
   if (P->ctl) (void)hipFree(P->ctl);
@@ -214,16 +213,16 @@ fa_status dalloc(T** out, size_t count, const char* what) {
 
 
 
-// Blur (sigma = scale/2, replicate) then resample at corner-aligned positions.
-fa_status build_level_image(fa_pair P, const float* src, float* dst, const Level& L, int off) {
+// Both level images: blur (sigma = scale/2, replicate), then samples at
+// corner-aligned positions.
+fa_status build_level_images(fa_pair P, const Level& L, int off, float* tmp0, float* tmp1, int together) {
   const fa_shape& s = P->shape;
-  const int rad = tap_radius(L.scale / 2.0f);
-  const float* w = P->wts + off;
-  FA_HIP(fa::launch_blur_axis(src, P->blur0, s.n0, s.n1, s.n2, 0, w, rad, P->stream));
-  FA_HIP(fa::launch_blur_axis(P->blur0, P->blur1, s.n0, s.n1, s.n2, 1, w, rad, P->stream));
-  FA_HIP(fa::launch_blur_axis(P->blur1, P->blur0, s.n0, s.n1, s.n2, 2, w, rad, P->stream));
-  FA_HIP(fa::launch_resample(P->blur0, dst, s.n0, s.n1, s.n2, L.shape.n0, L.shape.n1, L.shape.n2, 1,
-                             1.0f, 1.0f, 1.0f, P->stream));
+  const float* src[2] = {P->in_fixed, P->in_moving};
+  float* dst[2] = {L.fixed, L.moving};
+  const float rho[3] = {1.0f, 1.0f, 1.0f};
+  for (int i = 0; i < 2; i += together)
+    FA_HIP(fa::launch_level_images(src + i, dst + i, rho, together, tmp0, tmp1, s.n0, s.n1, s.n2, L.shape.n0,
+                                   L.shape.n1, L.shape.n2, P->wts + off, tap_radius(L.scale / 2.0f), P->stream));
   return FA_OK;
 }
 
@@ -420,10 +419,10 @@ fa_status transition(fa_pair P) {
   const float r0 = rho(F.shape.n0, C.shape.n0), r1 = rho(F.shape.n1, C.shape.n1), r2 = rho(F.shape.n2, C.shape.n2);
   const fa_shape& c = C.shape;
   const fa_shape& f = F.shape;
-  FA_HIP(fa::launch_resample(P->d, P->tmp, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 3, r0, r1, r2, P->stream));
-  FA_HIP(fa::launch_resample(P->m, P->a, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 3, 1.f, 1.f, 1.f, P->stream));
+  FA_HIP(fa::launch_resample(P->d, P->tmp, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, r0, r1, r2, P->stream));
+  FA_HIP(fa::launch_resample(P->m, P->a, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 1.f, 1.f, 1.f, P->stream));
   // v's coarse data moves into the buffer that held m (already consumed).
-  FA_HIP(fa::launch_resample(P->v, P->m, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 3, 1.f, 1.f, 1.f, P->stream));
+  FA_HIP(fa::launch_resample(P->v, P->m, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 1.f, 1.f, 1.f, P->stream));
   float* old_d = P->d;
   float* old_m = P->m;
   float* old_v = P->v;
@@ -1078,10 +1077,14 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
   // Pyramid.
   bool need_blur = false;
   for (auto& L : lv) need_blur |= !(L.scale == 1.0f);
-  if (need_blur && !P->blur0) {
-    FA_TRY(dalloc(&P->blur0, (size_t)P->n, "pyramid scratch"));
-    FA_TRY(dalloc(&P->blur1, (size_t)P->n, "pyramid scratch"));
-  }
+  // Pyramid scratch: the moments' buffers (reset below) where each holds two
+  // input volumes, as with a level near the input's size; else two volumes of
+  // its own, and the images one after the other.
+  const bool state_holds = 3 * P->cap >= 2 * P->n;
+  if (need_blur && !state_holds && !P->blur) FA_TRY(dalloc(&P->blur, (size_t)(2 * P->n), "pyramid scratch"));
+  float* const tmp0 = state_holds ? P->m : P->blur;
+  float* const tmp1 = state_holds ? P->v : (P->blur ? P->blur + P->n : nullptr);
+  const int together = state_holds ? 2 : 1;
   P->levels = lv;
   for (int i = 0; i < n_levels; ++i) {
     Level& L = P->levels[i];
@@ -1101,8 +1104,7 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
       }
       L.owns = true;
     }
-    FA_TRY(build_level_image(P, P->in_fixed, L.fixed, L, P->off_blur[i]));
-    FA_TRY(build_level_image(P, P->in_moving, L.moving, L, P->off_blur[i]));
+    FA_TRY(build_level_images(P, L, P->off_blur[i], tmp0, tmp1, together));
   }
 
   for (auto& L : P->levels) {
