@@ -16,12 +16,12 @@
  * trilinear resampling, each component divided by (n_fine - 1)/(n_coarse - 1)).
  * Displacements are in voxels, sampled trilinearly, zero outside the grid.
  *
- * Every step of an iteration runs on the GPU on the handle's stream: a splat
- * kernel (the derivative of |psi(phi(x)) - x|^2, scattered with 64-bit
- * fixed-point atomics, so results do not depend on the order of the atomics
- * and are bitwise reproducible), a kernel for the derivative of
- * |phi(psi(x)) - x|^2 plus Adam, and the registration's smoothing and
- * composition kernels.  The splat accumulates in units of 2^-32 and holds
+ * Every step of an iteration runs on the GPU on the handle's stream: a kernel
+ * for the direction (the derivative of |psi(phi(x)) - x|^2, a splat summed in
+ * 64-bit fixed point, so that results do not depend on the order of the
+ * summation and are bitwise reproducible; that of |phi(psi(x)) - x|^2; Adam),
+ * and the registration's smoothing and composition kernels.  The first
+ * iteration of a level lists the level's voxels by the cell they map into.  The splat accumulates in units of 2^-32 and holds
  * sums of magnitude below 2^31, which bounds |d| and |e| far beyond any
  * volume's size.
  */
@@ -75,10 +75,11 @@ fa_status fa_inverse_get_loss(fa_inverse h, float* host_out, int capacity, int* 
  * given).  Changes no state.  FA_EINVAL, FA_ESTATE, FA_EHIP. */
 fa_status fa_inverse_eval_gradient(fa_inverse h, float* g_dev, float* loss_host);
 
-/* Splat form (a tuning and test switch): 0 (default) sums each brick's
- * contributions in LDS and adds each touched node once; 1 adds every
- * contribution with its own global atomic.  Both add the same fixed-point
- * integers, so results are bitwise equal.  FA_EINVAL. */
+/* Splat form (a tuning and test switch): 0 (default) sums the contributions to
+ * each tile of nodes in LDS; 1 adds every contribution with its own global
+ * atomic (and holds an accumulator of 24 bytes per voxel).  Both add the same
+ * fixed-point integers, so results are bitwise equal.  FA_EINVAL, FA_ENOMEM,
+ * FA_EHIP. */
 fa_status fa_inverse_set_splat(fa_inverse h, int direct);
 
 /* Releases the handle (synchronises with its stream first).  NULL is a

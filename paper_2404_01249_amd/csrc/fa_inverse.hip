@@ -30,6 +30,8 @@ constexpr double kFixUnit = 1.0 / 4294967296.0;
 constexpr float kFixClamp = 1073741824.0f;
 constexpr int kInvThreads = 256;
 constexpr int kInvMaxBlocks = 4096;
+constexpr int64_t kSmallTileVoxels = 300000;
+constexpr int kDirMaxBlocks = 2 * kInvMaxBlocks;   // loss partials of k_inv_direction
 
 // Trilinear cell of position p on an n0 x n1 x n2 grid: flat corner indices
 // and weights in the order (b0, b1, b2) = 000, 001, ..., 111; corners off the
@@ -71,31 +73,81 @@ __device__ __forceinline__ float sample(const float* __restrict__ f, const Cell&
   return s;
 }
 
+// The same cell as four rows of two neighbouring corners: where the pair starts
+// (clamped onto the grid, so that both of its loads are in bounds), and which
+// corners are on the grid.
+struct PairCell {
+  int off[4];          // rows (b0, b1) = 00, 01, 10, 11
+  bool upper, lower;   // the pair was clamped: its second (first) value is the first (second) corner's
+  unsigned ok;
+  float t0, t1, t2;
+};
+
+__device__ __forceinline__ PairCell pair_cell(float p0, float p1, float p2, int n0, int n1, int n2) {
+  PairCell c;
+  const float f0 = floorf(p0), f1 = floorf(p1), f2 = floorf(p2);
+  c.t0 = p0 - f0;
+  c.t1 = p1 - f1;
+  c.t2 = p2 - f2;
+  const int i0 = (int)clamp_med3(f0, -2.0f, (float)n0);
+  const int i1 = (int)clamp_med3(f1, -2.0f, (float)n1);
+  const int i2 = (int)clamp_med3(f2, -2.0f, (float)n2);
+  const int xb = min(max(i2, 0), n2 - 2);
+  c.upper = i2 > xb;
+  c.lower = i2 < xb;
+  const unsigned mx = ((unsigned)i2 < (unsigned)n2 ? 0x55u : 0u) | ((unsigned)(i2 + 1) < (unsigned)n2 ? 0xAAu : 0u);
+  const unsigned my = ((unsigned)i1 < (unsigned)n1 ? 0x33u : 0u) | ((unsigned)(i1 + 1) < (unsigned)n1 ? 0xCCu : 0u);
+  const unsigned mz = ((unsigned)i0 < (unsigned)n0 ? 0x0Fu : 0u) | ((unsigned)(i0 + 1) < (unsigned)n0 ? 0xF0u : 0u);
+  c.ok = mx & my & mz;
+  const int z0 = min(max(i0, 0), n0 - 1), z1 = min(max(i0 + 1, 0), n0 - 1);
+  const int y0 = min(max(i1, 0), n1 - 1), y1 = min(max(i1 + 1, 0), n1 - 1);
+  c.off[0] = (z0 * n1 + y0) * n2 + xb;
+  c.off[1] = (z0 * n1 + y1) * n2 + xb;
+  c.off[2] = (z1 * n1 + y0) * n2 + xb;
+  c.off[3] = (z1 * n1 + y1) * n2 + xb;
+  return c;
+}
+
+typedef float float2_any __attribute__((ext_vector_type(2), aligned(4)));
+
 // Value and position derivative of the trilinear sample (the derivative from
 // the right at an integer coordinate, as the cell is chosen by floor).
-__device__ __forceinline__ float sample_grad(const float* __restrict__ f, const Cell& c, float& g0, float& g1,
+__device__ __forceinline__ float sample_grad(const float* __restrict__ f, const PairCell& c, float& g0, float& g1,
                                              float& g2) {
   float v[8];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) v[k] = ((c.ok >> k) & 1u) ? f[c.idx[k]] : 0.0f;
+  for (int k = 0; k < 4; ++k) {
+    const float2_any p = *reinterpret_cast<const float2_any*>(f + c.off[k]);
+    v[2 * k] = (c.ok >> (2 * k)) & 1u ? (c.upper ? p.y : p.x) : 0.0f;
+    v[2 * k + 1] = (c.ok >> (2 * k + 1)) & 1u ? (c.lower ? p.x : p.y) : 0.0f;
+  }
   const float dx00 = v[1] - v[0], dx01 = v[3] - v[2], dx10 = v[5] - v[4], dx11 = v[7] - v[6];
-  const float e00 = v[0] + c.t2 * dx00, e01 = v[2] + c.t2 * dx01;
-  const float e10 = v[4] + c.t2 * dx10, e11 = v[6] + c.t2 * dx11;
+  const float e00 = __builtin_fmaf(c.t2, dx00, v[0]), e01 = __builtin_fmaf(c.t2, dx01, v[2]);
+  const float e10 = __builtin_fmaf(c.t2, dx10, v[4]), e11 = __builtin_fmaf(c.t2, dx11, v[6]);
   const float dy0 = e01 - e00, dy1 = e11 - e10;
-  const float f0 = e00 + c.t1 * dy0, f1 = e10 + c.t1 * dy1;
-  const float dxy0 = dx00 + c.t1 * (dx01 - dx00), dxy1 = dx10 + c.t1 * (dx11 - dx10);
+  const float f0 = __builtin_fmaf(c.t1, dy0, e00), f1 = __builtin_fmaf(c.t1, dy1, e10);
+  const float dxy0 = __builtin_fmaf(c.t1, dx01 - dx00, dx00), dxy1 = __builtin_fmaf(c.t1, dx11 - dx10, dx10);
   g0 = f1 - f0;
-  g1 = dy0 + c.t0 * (dy1 - dy0);
-  g2 = dxy0 + c.t0 * (dxy1 - dxy0);
-  return f0 + c.t0 * (f1 - f0);
+  g1 = __builtin_fmaf(c.t0, dy1 - dy0, dy0);
+  g2 = __builtin_fmaf(c.t0, dxy1 - dxy0, dxy0);
+  return __builtin_fmaf(c.t0, f1 - f0, f0);
 }
 
+// v in units of 2^-32, rounded to nearest (ties to even).  |v| = hi + lo with hi
+// its integer part and lo exact in fp32, so the two 32-bit halves convert
+// separately: 12 full-rate instructions; the conversion through fp64 takes about
+// as many at half the rate.
 __device__ __forceinline__ unsigned long long to_fixed(float v) {
   const float vc = clamp_med3(v, -kFixClamp, kFixClamp);
-  return (unsigned long long)__double2ll_rn((double)vc * kFixScale);
+  const float a = fabsf(vc);
+  const unsigned hi = (unsigned)a;
+  const unsigned lo = (unsigned)rintf((a - (float)hi) * 4294967296.0f);
+  const unsigned long long u = ((unsigned long long)hi << 32) | lo;
+  return vc < 0.0f ? 0ull - u : u;
 }
 
-__device__ __forceinline__ double block_sum256(double v, double* red) {
+template <int NT>
+__device__ __forceinline__ double block_sum(double v, double* red) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -104,7 +156,7 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
   __syncthreads();
   double s = 0.0;
   if (threadIdx.x == 0)
-    for (int i = 0; i < kInvThreads / 64; ++i) s += red[i];
+    for (int i = 0; i < NT / 64; ++i) s += red[i];
   return s;
 }
 
@@ -135,192 +187,332 @@ k_inv_splat(const float* __restrict__ d, const float* __restrict__ e, unsigned l
       }
     }
   }
-  const double s = block_sum256(loss, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = -s;
-}
-
-// The same splat by bricks of 4 x 8 x 16 voxels (two per thread).  A smooth
-// warp sends a brick's samples into a box of nodes little larger than the
-// brick: the workgroup sums its contributions there with LDS atomics (the
-// same fixed-point integers, so the result is bitwise that of the direct
-// form), then adds each non-zero box node to acc with one global atomic per
-// component.  A brick whose box exceeds kBoxNodes (a folded or wildly varying
-// warp) scatters directly.
-constexpr int kBZ = 4, kBY = 8, kBX = 16;
-constexpr int kBoxNodes = 2048;   // 3 x 2048 x 8 B = 48 KiB of LDS
-
-__global__ void __launch_bounds__(kInvThreads)
-k_inv_splat_lds(const float* __restrict__ d, const float* __restrict__ e, unsigned long long* __restrict__ acc,
-                double* __restrict__ part, int n0, int n1, int n2) {
-  __shared__ unsigned long long box[3 * kBoxNodes];
-  __shared__ int bb[6];   // box: lo0, lo1, lo2, hi0, hi1, hi2 (inclusive)
-  __shared__ double red[kInvThreads / 64];
-  constexpr int VPT = kBZ * kBY * kBX / kInvThreads;
-  const int N = n0 * n1 * n2;
-  const int tz = (n0 + kBZ - 1) / kBZ, ty = (n1 + kBY - 1) / kBY, tx = (n2 + kBX - 1) / kBX;
-  const int nbricks = tz * ty * tx;
-  const int tid = threadIdx.x;
-  double loss = 0.0;
-  for (int b = blockIdx.x; b < nbricks; b += gridDim.x) {
-    const int bx = b % tx, by = (b / tx) % ty, bz = b / (tx * ty);
-    int cz[VPT], cy[VPT], cx[VPT];
-    float t0[VPT], t1[VPT], t2[VPT], r[VPT][3];
-    bool valid[VPT];
-    int lo0 = 1 << 30, lo1 = 1 << 30, lo2 = 1 << 30, hi0 = -(1 << 30), hi1 = -(1 << 30), hi2 = -(1 << 30);
-#pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-      const int l = tid + k * kInvThreads;
-      const int z = bz * kBZ + l / (kBY * kBX), y = by * kBY + (l / kBX) % kBY, x = bx * kBX + l % kBX;
-      valid[k] = z < n0 && y < n1 && x < n2;
-      cz[k] = cy[k] = cx[k] = 0;
-      t0[k] = t1[k] = t2[k] = 0.0f;
-      r[k][0] = r[k][1] = r[k][2] = 0.0f;
-      if (valid[k]) {
-        const int i = (z * n1 + y) * n2 + x;
-        const float d0 = d[i], d1 = d[N + i], d2 = d[2 * N + i];
-        const Cell c = cell_of((float)z + d0, (float)y + d1, (float)x + d2, n0, n1, n2);
-        r[k][0] = d0 + sample(e, c);
-        r[k][1] = d1 + sample(e + N, c);
-        r[k][2] = d2 + sample(e + 2 * N, c);
-        loss += (double)(r[k][0] * r[k][0] + r[k][1] * r[k][1] + r[k][2] * r[k][2]);
-        t0[k] = c.t0;
-        t1[k] = c.t1;
-        t2[k] = c.t2;
-        // the cell's lower corner (clamped as in cell_of: off-grid corners are dropped below)
-        cz[k] = (int)clamp_med3(floorf((float)z + d0), -2.0f, (float)n0);
-        cy[k] = (int)clamp_med3(floorf((float)y + d1), -2.0f, (float)n1);
-        cx[k] = (int)clamp_med3(floorf((float)x + d2), -2.0f, (float)n2);
-        lo0 = min(lo0, cz[k]);
-        lo1 = min(lo1, cy[k]);
-        lo2 = min(lo2, cx[k]);
-        hi0 = max(hi0, cz[k] + 1);
-        hi1 = max(hi1, cy[k] + 1);
-        hi2 = max(hi2, cx[k] + 1);
-      }
-    }
-    if (tid == 0) {
-      bb[0] = bb[1] = bb[2] = 1 << 30;
-      bb[3] = bb[4] = bb[5] = -(1 << 30);
-    }
-    __syncthreads();
-    atomicMin(&bb[0], lo0);
-    atomicMin(&bb[1], lo1);
-    atomicMin(&bb[2], lo2);
-    atomicMax(&bb[3], hi0);
-    atomicMax(&bb[4], hi1);
-    atomicMax(&bb[5], hi2);
-    __syncthreads();
-    // the box clipped to the grid (nodes off the grid receive nothing)
-    const int b0 = max(bb[0], 0), b1 = max(bb[1], 0), b2 = max(bb[2], 0);
-    const int e0 = min(bb[3], n0 - 1), e1 = min(bb[4], n1 - 1), e2 = min(bb[5], n2 - 1);
-    const int s0 = e0 - b0 + 1, s1 = e1 - b1 + 1, s2 = e2 - b2 + 1;
-    const bool empty = s0 <= 0 || s1 <= 0 || s2 <= 0;
-    const int nb = empty ? 0 : s0 * s1 * s2;
-    if (nb <= kBoxNodes) {
-      for (int q = tid; q < 3 * nb; q += kInvThreads) box[q] = 0ull;
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < VPT; ++k) {
-        if (!valid[k]) continue;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int o0 = (j >> 2) & 1, o1 = (j >> 1) & 1, o2 = j & 1;
-          const int z = cz[k] + o0, y = cy[k] + o1, x = cx[k] + o2;
-          if (z < 0 || z >= n0 || y < 0 || y >= n1 || x < 0 || x >= n2) continue;
-          const float w = (o0 ? t0[k] : 1.0f - t0[k]) * (o1 ? t1[k] : 1.0f - t1[k]) * (o2 ? t2[k] : 1.0f - t2[k]);
-          if (w == 0.0f) continue;
-          const int q = ((z - b0) * s1 + (y - b1)) * s2 + (x - b2);
-          const float w2 = 2.0f * w;
-          atomicAdd(&box[q], to_fixed(w2 * r[k][0]));
-          atomicAdd(&box[nb + q], to_fixed(w2 * r[k][1]));
-          atomicAdd(&box[2 * nb + q], to_fixed(w2 * r[k][2]));
-        }
-      }
-      __syncthreads();
-      for (int q = tid; q < nb; q += kInvThreads) {
-        const int x = b2 + q % s2, y = b1 + (q / s2) % s1, z = b0 + q / (s1 * s2);
-        const int gi = (z * n1 + y) * n2 + x;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const unsigned long long v = box[c * nb + q];
-          if (v != 0ull) atomicAdd(&acc[c * N + gi], v);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < VPT; ++k) {
-        if (!valid[k]) continue;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int o0 = (j >> 2) & 1, o1 = (j >> 1) & 1, o2 = j & 1;
-          const int z = cz[k] + o0, y = cy[k] + o1, x = cx[k] + o2;
-          if (z < 0 || z >= n0 || y < 0 || y >= n1 || x < 0 || x >= n2) continue;
-          const float w = (o0 ? t0[k] : 1.0f - t0[k]) * (o1 ? t1[k] : 1.0f - t1[k]) * (o2 ? t2[k] : 1.0f - t2[k]);
-          if (w == 0.0f) continue;
-          const int gi = (z * n1 + y) * n2 + x;
-          const float w2 = 2.0f * w;
-          atomicAdd(&acc[gi], to_fixed(w2 * r[k][0]));
-          atomicAdd(&acc[N + gi], to_fixed(w2 * r[k][1]));
-          atomicAdd(&acc[2 * N + gi], to_fixed(w2 * r[k][2]));
-        }
-      }
-    }
-    __syncthreads();   // box and bb are reused by the next brick
-  }
-  const double s = block_sum256(loss, red);
+  const double s = block_sum<kInvThreads>(loss, red);
   if (threadIdx.x == 0) part[blockIdx.x] = -s;
 }
 
 // r2(x) = e(x) + d(x + e(x)), the residual of phi o psi, whose derivative in
-// e(x) is 2 (I + grad d)^T r2; with the splat's sum (acc, cleared here for the
-// next iteration) and the 1/N of the mean this is dU/de.  grad_only: write it
-// to out.  Otherwise Adam on it (moments m, v; bias corrections from ctl):
-// out = the direction; block 0 also clears M for the iteration's smoothing.
-// part[block] = -sum of |r2|^2.
-__global__ void __launch_bounds__(kInvThreads)
-k_inv_dir(const float* __restrict__ d, const float* __restrict__ e, unsigned long long* __restrict__ acc,
-          float* __restrict__ m, float* __restrict__ v, float* __restrict__ out, Ctl* __restrict__ ctl,
-          double* __restrict__ part, int n0, int n1, int n2, float inv_n, float beta1, float beta2,
-          float adam_eps, int grad_only) {
+// e(x) is 2 (I + grad d)^T r2; with the splat's sum sp at x and the 1/N of the
+// mean this is dU/de.  grad_only: write it to out.  Otherwise Adam on it
+// (moments m, v; reciprocal bias corrections ibc1, ibc2): out = the direction.
+// Returns |r2|^2.
+struct DirArgs {
+  const float* d;
+  const float* e;
+  float* m;
+  float* v;
+  float* out;
+  Ctl* ctl;
+  double* part;   // per-workgroup loss partials (minus the sum)
+  int n0, n1, n2;
+  float inv_n, beta1, beta2, adam_eps;
+  int grad_only;
+};
+
+__device__ __forceinline__ float node_direction(const DirArgs& A, int z, int y, int x, const float sp[3], float e0,
+                                                float e1, float e2, float ibc1, float ibc2) {
+  const int N = A.n0 * A.n1 * A.n2, i = (z * A.n1 + y) * A.n2 + x;
+  const PairCell c = pair_cell((float)z + e0, (float)y + e1, (float)x + e2, A.n0, A.n1, A.n2);
+  float J[3][3];   // J[q][a] = d d_q / d p_a at x + e(x)
+  const float v0 = sample_grad(A.d, c, J[0][0], J[0][1], J[0][2]);
+  const float v1 = sample_grad(A.d + N, c, J[1][0], J[1][1], J[1][2]);
+  const float v2 = sample_grad(A.d + 2 * N, c, J[2][0], J[2][1], J[2][2]);
+  const float r[3] = {e0 + v0, e1 + v1, e2 + v2};
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float g =
+        __builtin_fmaf(2.0f, __builtin_fmaf(J[2][a], r[2], __builtin_fmaf(J[1][a], r[1], __builtin_fmaf(J[0][a], r[0], r[a]))),
+                       sp[a]) *
+        A.inv_n;
+    const int ia = a * N + i;
+    if (A.grad_only) {
+      A.out[ia] = g;
+    } else {
+      const float mm = __builtin_fmaf(A.beta1, A.m[ia], (1.0f - A.beta1) * g);
+      const float vv = __builtin_fmaf(A.beta2, A.v[ia], (1.0f - A.beta2) * g * g);
+      A.m[ia] = mm;
+      A.v[ia] = vv;
+      A.out[ia] = fa::adam_direction(mm, vv, ibc1, ibc2, A.adam_eps);
+    }
+  }
+  return r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
+}
+
+__device__ __forceinline__ float from_fixed(unsigned long long s) {
+  return (float)((double)(long long)s * kFixUnit);
+}
+
+// The direction from the splat of k_inv_splat (acc, cleared here for the next iteration).
+__global__ void __launch_bounds__(kInvThreads) k_inv_dir(const DirArgs A, unsigned long long* __restrict__ acc) {
   __shared__ double red[kInvThreads / 64];
-  const int N = n0 * n1 * n2;
-  if (!grad_only && blockIdx.x == 0 && threadIdx.x < fa::kMSlots) ctl->mslot[threadIdx.x * fa::kMStride] = 0u;
-  const float ibc1 = grad_only ? 1.0f : 1.0f / ctl->bc1;
-  const float ibc2 = grad_only ? 1.0f : 1.0f / ctl->bc2;
+  const int N = A.n0 * A.n1 * A.n2;
+  if (!A.grad_only && blockIdx.x == 0 && threadIdx.x < fa::kMSlots) A.ctl->mslot[threadIdx.x * fa::kMStride] = 0u;
+  const float ibc1 = A.grad_only ? 1.0f : 1.0f / A.ctl->bc1;
+  const float ibc2 = A.grad_only ? 1.0f : 1.0f / A.ctl->bc2;
   double loss = 0.0;
   for (int i = blockIdx.x * kInvThreads + threadIdx.x; i < N; i += gridDim.x * kInvThreads) {
-    const int x = i % n2, y = (i / n2) % n1, z = i / (n1 * n2);
+    const int x = i % A.n2, y = (i / A.n2) % A.n1, z = i / (A.n1 * A.n2);
     float s[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      s[q] = (float)((double)(long long)acc[q * N + i] * kFixUnit);
+      s[q] = from_fixed(acc[q * N + i]);
       acc[q * N + i] = 0ull;
     }
-    const float e0 = e[i], e1 = e[N + i], e2 = e[2 * N + i];
-    const Cell c = cell_of((float)z + e0, (float)y + e1, (float)x + e2, n0, n1, n2);
-    float J[3][3];   // J[q][a] = d d_q / d p_a at x + e(x)
-    const float v0 = sample_grad(d, c, J[0][0], J[0][1], J[0][2]);
-    const float v1 = sample_grad(d + N, c, J[1][0], J[1][1], J[1][2]);
-    const float v2 = sample_grad(d + 2 * N, c, J[2][0], J[2][1], J[2][2]);
-    const float r[3] = {e0 + v0, e1 + v1, e2 + v2};
-    loss += (double)(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+    loss += (double)node_direction(A, z, y, x, s, A.e[i], A.e[N + i], A.e[2 * N + i], ibc1, ibc2);
+  }
+  const double t = block_sum<kInvThreads>(loss, red);
+  if (threadIdx.x == 0) A.part[blockIdx.x] = -t;
+}
+
+// ---- the splat by owner ------------------------------------------------------
+// d is the same in every iteration of a level, so the cell that x + d(x) falls
+// into is listed once per level (k_inv_plan): up to kSlots voxels per cell of
+// the grid extended by one cell below, in `slots` ([2][cells] int4), and their
+// number in `count`.  k_inv_direction then gives each tile of nodes to one
+// workgroup, which takes every voxel listed in the tile's cells, sums its
+// contributions in LDS and goes on to the direction: no global atomics and no
+// accumulator in memory.  (Gradient at 160x192x224: 904 us when bricks of
+// voxels were summed in LDS and added to memory with one 64-bit atomic per
+// touched node and component, six per voxel, and a second kernel read the sums;
+// 297 us here.  96x112x112: 174 -> 64; 40x48x56: 35 -> 25.)
+//
+// A cell with more than kSlots voxels (a strongly contracting or wild warp) is
+// not walked through its list: its tile goes over the bricks of voxels whose
+// box of cells meets the tile.
+constexpr int kSlots = 8;
+constexpr int kBZ = 4, kBY = 8, kBX = 16, kBrick = kBZ * kBY * kBX;
+
+struct Plan {
+  unsigned* count;      // [cells]
+  int4* slots;          // [2][cells]
+  int4* box;            // [2][bricks]: lowest cell, highest cell (+1 each), empty where low > high
+  double* outside;      // [blocks]: sum of |d|^2 over voxels whose sample has no corner on the grid
+  size_t cells;
+  int bricks;
+};
+
+// Cells are numbered -1 .. n-1 per axis; cell index of (c0, c1, c2).
+__device__ __forceinline__ size_t cell_index(int c0, int c1, int c2, int n1, int n2) {
+  return ((size_t)(c0 + 1) * (n1 + 1) + (c1 + 1)) * (n2 + 1) + (c2 + 1);
+}
+
+// Cell of position p; false if no corner is on the grid (or p is not a number).
+__device__ __forceinline__ bool plan_cell(float p0, float p1, float p2, int n0, int n1, int n2, int& c0, int& c1,
+                                          int& c2) {
+  c0 = (int)clamp_med3(floorf(p0), -2.0f, (float)n0);
+  c1 = (int)clamp_med3(floorf(p1), -2.0f, (float)n1);
+  c2 = (int)clamp_med3(floorf(p2), -2.0f, (float)n2);
+  return c0 >= -1 && c0 < n0 && c1 >= -1 && c1 < n1 && c2 >= -1 && c2 < n2;
+}
+
+__global__ void __launch_bounds__(kInvThreads) k_inv_plan(const float* __restrict__ d, const Plan P, int n0, int n1,
+                                                          int n2) {
+  __shared__ int bb[kInvThreads / 64][6];
+  __shared__ double red[kInvThreads / 64];
+  const int N = n0 * n1 * n2;
+  const int ty = (n1 + kBY - 1) / kBY, tx = (n2 + kBX - 1) / kBX;
+  const int tid = threadIdx.x;
+  double outside = 0.0;
+  for (int b = blockIdx.x; b < P.bricks; b += gridDim.x) {
+    const int bx = b % tx, by = (b / tx) % ty, bz = b / (tx * ty);
+    int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {-1, -1, -1};
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const float g = (s[a] + 2.0f * (r[a] + J[0][a] * r[0] + J[1][a] * r[1] + J[2][a] * r[2])) * inv_n;
-      const int ia = a * N + i;
-      if (grad_only) {
-        out[ia] = g;
-      } else {
-        const float mm = beta1 * m[ia] + (1.0f - beta1) * g;
-        const float vv = beta2 * v[ia] + (1.0f - beta2) * g * g;
-        m[ia] = mm;
-        v[ia] = vv;
-        out[ia] = fa::adam_direction(mm, vv, ibc1, ibc2, adam_eps);
+    for (int l = tid; l < kBrick; l += kInvThreads) {
+      const int z = bz * kBZ + l / (kBY * kBX), y = by * kBY + (l / kBX) % kBY, x = bx * kBX + l % kBX;
+      if (z >= n0 || y >= n1 || x >= n2) continue;
+      const int i = (z * n1 + y) * n2 + x;
+      const float d0 = d[i], d1 = d[N + i], d2 = d[2 * N + i];
+      int c[3];
+      if (!plan_cell((float)z + d0, (float)y + d1, (float)x + d2, n0, n1, n2, c[0], c[1], c[2])) {
+        outside += (double)(d0 * d0 + d1 * d1 + d2 * d2);
+        continue;
+      }
+      const size_t ci = cell_index(c[0], c[1], c[2], n1, n2);
+      const unsigned r = atomicAdd(&P.count[ci], 1u);
+      if (r < kSlots) reinterpret_cast<int*>(P.slots + (r < 4 ? 0 : P.cells) + ci)[r & 3] = i;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        lo[a] = min(lo[a], c[a] + 1);
+        hi[a] = max(hi[a], c[a] + 1);
       }
     }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        lo[a] = min(lo[a], __shfl_xor(lo[a], o, 64));
+        hi[a] = max(hi[a], __shfl_xor(hi[a], o, 64));
+      }
+    if ((tid & 63) == 0)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        bb[tid >> 6][a] = lo[a];
+        bb[tid >> 6][3 + a] = hi[a];
+      }
+    __syncthreads();
+    if (tid < 2) {   // thread 0: lowest cell, thread 1: highest
+      int v[3] = {bb[0][3 * tid], bb[0][3 * tid + 1], bb[0][3 * tid + 2]};
+      for (int w = 1; w < kInvThreads / 64; ++w)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) v[a] = tid == 0 ? min(v[a], bb[w][a]) : max(v[a], bb[w][3 + a]);
+      P.box[(size_t)tid * P.bricks + b] = make_int4(v[0], v[1], v[2], 0);
+    }
+    __syncthreads();
   }
-  const double t = block_sum256(loss, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = -t;
+  const double s = block_sum<kInvThreads>(outside, red);
+  if (tid == 0) P.outside[blockIdx.x] = s;
+}
+
+// Exact i / dv for 0 <= i < 2^31 (launch: mul = floor(2^(31 + s) / dv) + 1, s = ceil(log2 dv)).
+struct FastDiv {
+  unsigned mul, shift;
+};
+__device__ __forceinline__ int fast_div(int i, FastDiv f) { return (int)(__umulhi((unsigned)i, f.mul) >> f.shift); }
+
+// Per tile: 24 B per node of accumulators and 12 B per node of the tile and its
+// one-node border (e) in LDS, 46 KB at 8 x 8 x 16 nodes.  Bound by latency and
+// VALU work rather than by memory: each listed voxel takes 24 LDS reads, 24
+// conversions and up to 24 LDS atomics, and the tile's lower border cells (a
+// third of its cells) are also taken by its neighbours.  At 160x192x224, of 297
+// us: 80 the lists and d, 86 the contributions, 90 the nodes.  Six wavefronts
+// per SIMD (80 VGPRs, a few spilled) hide more of the latency than the five of
+// an unbounded allocation (322 us); 4 x 8 x 16 tiles take 355, 8 x 8 x 32 575.
+template <int TZ, int TY, int TX, int NT>
+__global__ void __launch_bounds__(NT, 6) k_inv_direction(const DirArgs A, const Plan P, FastDiv by_row, FastDiv by_plane) {
+  constexpr int CY = TY + 1, CX = TX + 1, CELLS = (TZ + 1) * CY * CX, NODES = TZ * TY * TX;
+  constexpr int SY = TY + 2, SX = TX + 2, SN = (TZ + 2) * SY * SX;
+  __shared__ unsigned long long acc[3 * NODES];
+  __shared__ float es[3 * SN];
+  __shared__ double red[NT / 64];
+  __shared__ unsigned long long hit[NT / 64];
+  __shared__ int crowded;
+  const int n0 = A.n0, n1 = A.n1, n2 = A.n2, N = n0 * n1 * n2;
+  const int tid = threadIdx.x;
+  if (!A.grad_only && blockIdx.x == 0 && tid < fa::kMSlots) A.ctl->mslot[tid * fa::kMStride] = 0u;
+  const float ibc1 = A.grad_only ? 1.0f : 1.0f / A.ctl->bc1;
+  const float ibc2 = A.grad_only ? 1.0f : 1.0f / A.ctl->bc2;
+  const int ty = (n1 + TY - 1) / TY, tx = (n2 + TX - 1) / TX, tiles = (n0 + TZ - 1) / TZ * ty * tx;
+  double loss = tid == 0 ? P.outside[blockIdx.x] : 0.0;
+  // every XCD takes a contiguous range of tiles (neighbours share border cells and gathers in its L2)
+  const int G = gridDim.x, xq = G / 8, xr = G % 8, xb = blockIdx.x % 8;
+  for (int t = xb * xq + min(xb, xr) + blockIdx.x / 8; t < tiles; t += G) {
+    const int x0 = t % tx * TX, y0 = t / tx % ty * TY, z0 = t / (tx * ty) * TZ;
+    for (int q = tid; q < 3 * NODES; q += NT) acc[q] = 0ull;
+    for (int q = tid; q < SN; q += NT) {
+      const int z = z0 - 1 + q / (SY * SX), y = y0 - 1 + q / SX % SY, x = x0 - 1 + q % SX;
+      const bool in = (unsigned)z < (unsigned)n0 && (unsigned)y < (unsigned)n1 && (unsigned)x < (unsigned)n2;
+      const int i = in ? (z * n1 + y) * n2 + x : 0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) es[c * SN + q] = in ? A.e[c * N + i] : 0.0f;
+    }
+    if (tid == 0) crowded = 0;
+    __syncthreads();
+
+    // voxel with displacement (d0, d1, d2) to position p in the tile's cell (lz, ly, lx), 0 = the border
+    auto take = [&](float d0, float d1, float d2, float p0, float p1, float p2, int lz, int ly, int lx) {
+      const float t0 = p0 - floorf(p0), t1 = p1 - floorf(p1), t2 = p2 - floorf(p2);
+      const int base = (lz * SY + ly) * SX + lx;
+      float w[8], r[3];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        w[k] = ((k >> 2) & 1 ? t0 : 1.0f - t0) * ((k >> 1) & 1 ? t1 : 1.0f - t1) * (k & 1 ? t2 : 1.0f - t2);
+      const float dd[3] = {d0, d1, d2};
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+#pragma clang fp contract(off)
+        float s = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += w[k] * es[c * SN + base + ((k >> 2) * SY + ((k >> 1) & 1)) * SX + (k & 1)];
+        r[c] = dd[c] + s;
+      }
+      // a border cell's voxels count where that cell is not another tile's own
+      if ((lz > 0 || z0 == 0) && (ly > 0 || y0 == 0) && (lx > 0 || x0 == 0))
+        loss += (double)(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int z = lz - 1 + (k >> 2), y = ly - 1 + ((k >> 1) & 1), x = lx - 1 + (k & 1);
+        if ((unsigned)z < (unsigned)TZ && (unsigned)y < (unsigned)TY && (unsigned)x < (unsigned)TX && w[k] != 0.0f) {
+          const int q = (z * TY + y) * TX + x;
+          const float w2 = 2.0f * w[k];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) atomicAdd(&acc[c * NODES + q], to_fixed(w2 * r[c]));
+        }
+      }
+    };
+
+    for (int q = tid; q < CELLS; q += NT) {
+      const int lz = q / (CY * CX), ly = q / CX % CY, lx = q % CX;
+      const int cz = z0 - 1 + lz, cy = y0 - 1 + ly, cx = x0 - 1 + lx;
+      if (cz >= n0 || cy >= n1 || cx >= n2) continue;
+      const size_t ci = cell_index(cz, cy, cx, n1, n2);
+      const int4 a = P.slots[ci];   // not waiting for the count: entries past it are ignored
+      const int n = (int)min(P.count[ci], (unsigned)kSlots + 1u);
+      if (n == 0) continue;
+      if (n > kSlots) {
+        crowded = 1;
+        continue;
+      }
+      // in the order of the voxels, so that the loss does not depend on the order of the listing
+      int i = -1;
+      for (int j = 0; j < n; ++j) {
+        int next = 0x7fffffff;
+        auto after = [&](int v, int k) { next = k < n && v > i ? min(next, v) : next; };
+        after(a.x, 0), after(a.y, 1), after(a.z, 2), after(a.w, 3);
+        if (n > 4) {
+          const int4 b = P.slots[P.cells + ci];
+          after(b.x, 4), after(b.y, 5), after(b.z, 6), after(b.w, 7);
+        }
+        i = next;
+        const int z = fast_div(i, by_plane), yx = i - z * (n1 * n2), y = fast_div(yx, by_row), x = yx - y * n2;
+        const float d0 = A.d[i], d1 = A.d[N + i], d2 = A.d[2 * N + i];
+        take(d0, d1, d2, (float)z + d0, (float)y + d1, (float)x + d2, lz, ly, lx);
+      }
+    }
+    __syncthreads();
+    if (crowded) {
+      const int bty = (n1 + kBY - 1) / kBY, btx = (n2 + kBX - 1) / kBX;
+      for (int b0 = 0; b0 < P.bricks; b0 += NT) {
+        bool meets = false;
+        if (b0 + tid < P.bricks) {
+          const int4 lo = P.box[b0 + tid], hi = P.box[(size_t)P.bricks + b0 + tid];   // cells + 1
+          meets = lo.x <= z0 + TZ && hi.x >= z0 && lo.y <= y0 + TY && hi.y >= y0 && lo.z <= x0 + TX && hi.z >= x0;
+        }
+        const unsigned long long mask = __ballot(meets);
+        if ((tid & 63) == 0) hit[tid >> 6] = mask;
+        __syncthreads();
+        for (int w = 0; w < NT / 64; ++w)
+          for (unsigned long long bits = hit[w]; bits; bits &= bits - 1) {
+            const int b = b0 + 64 * w + __ffsll(bits) - 1;
+            const int bx = b % btx, by = b / btx % bty, bz = b / (btx * bty);
+            for (int l = tid; l < kBrick; l += NT) {
+              const int z = bz * kBZ + l / (kBY * kBX), y = by * kBY + (l / kBX) % kBY, x = bx * kBX + l % kBX;
+              if (z >= n0 || y >= n1 || x >= n2) continue;
+              const int i = (z * n1 + y) * n2 + x;
+              const float d0 = A.d[i], d1 = A.d[N + i], d2 = A.d[2 * N + i];
+              const float p0 = (float)z + d0, p1 = (float)y + d1, p2 = (float)x + d2;
+              int cz, cy, cx;
+              if (!plan_cell(p0, p1, p2, n0, n1, n2, cz, cy, cx)) continue;
+              const int lz = cz - z0 + 1, ly = cy - y0 + 1, lx = cx - x0 + 1;
+              if ((unsigned)lz > (unsigned)TZ || (unsigned)ly > (unsigned)TY || (unsigned)lx > (unsigned)TX) continue;
+              if (P.count[cell_index(cz, cy, cx, n1, n2)] > (unsigned)kSlots) take(d0, d1, d2, p0, p1, p2, lz, ly, lx);
+            }
+          }
+        __syncthreads();   // hit is written again
+      }
+      // (the last barrier also ends the accumulation)
+    }
+    for (int q = tid; q < NODES; q += NT) {
+      const int lz = q / (TY * TX), ly = q / TX % TY, lx = q % TX;
+      const int z = z0 + lz, y = y0 + ly, x = x0 + lx;
+      if (z >= n0 || y >= n1 || x >= n2) continue;
+      const float s[3] = {from_fixed(acc[q]), from_fixed(acc[NODES + q]), from_fixed(acc[2 * NODES + q])};
+      const int u = ((lz + 1) * SY + ly + 1) * SX + lx + 1;
+      loss += (double)node_direction(A, z, y, x, s, es[u], es[SN + u], es[2 * SN + u], ibc1, ibc2);
+    }
+    __syncthreads();   // acc and es are written again
+  }
+  const double s = block_sum<NT>(loss, red);
+  if (tid == 0) A.part[blockIdx.x] = -s;
 }
 
 int inv_blocks(int64_t n) {
@@ -367,7 +559,11 @@ struct fa_inverse_s {
   float* a = nullptr;      // Adam direction
   float* tmp = nullptr;    // smoothed direction, then the composed field
   float* wide = nullptr;   // [3][cap] scratch of the smoothing passes with a radius above 6
-  unsigned long long* acc = nullptr;   // splat accumulator [3][n], zero between iterations
+  unsigned long long* acc = nullptr;   // accumulator of the direct splat [3][cap], zero between iterations
+  Plan plan{};             // voxels by cell of level plan_level
+  size_t plan_cells = 0;   // capacities of its buffers
+  int plan_bricks = 0;
+  int plan_level = -1;
   Ctl* ctl = nullptr;
   float* loss_hist = nullptr;
   int loss_cap = 0;
@@ -388,11 +584,36 @@ void free_levels(fa_inverse H) {
   H->levels.clear();
 }
 
+void free_plan(fa_inverse H) {
+  if (H->plan.count) (void)hipFree(H->plan.count);
+  if (H->plan.slots) (void)hipFree(H->plan.slots);
+  if (H->plan.box) (void)hipFree(H->plan.box);
+  if (H->plan.outside) (void)hipFree(H->plan.outside);
+  H->plan = Plan{};
+  H->plan_cells = 0;
+  H->plan_bricks = 0;
+  H->plan_level = -1;
+}
+
+int64_t cells_of(const fa_shape& s) { return (int64_t)(s.n0 + 1) * (s.n1 + 1) * (s.n2 + 1); }
+int bricks_of(const fa_shape& s) {
+  return (s.n0 + kBZ - 1) / kBZ * ((s.n1 + kBY - 1) / kBY) * ((s.n2 + kBX - 1) / kBX);
+}
+
+// The direct splat's accumulator, zeroed.
+fa_status ensure_acc(fa_inverse H) {
+  if (H->acc) return FA_OK;
+  FA_TRY(ialloc(&H->acc, (size_t)(3 * H->cap), "splat accumulator"));
+  FA_HIP(hipMemsetAsync(H->acc, 0, (size_t)(3 * H->cap) * sizeof(unsigned long long), H->stream));
+  return FA_OK;
+}
+
 void free_all(fa_inverse H) {
   free_levels(H);
   float* fb[] = {H->in_d, H->e, H->m, H->v, H->a, H->tmp, H->wide, H->loss_hist, H->scalar, H->wts};
   for (float* b : fb)
     if (b) (void)hipFree(b);
+  free_plan(H);
   if (H->acc) (void)hipFree(H->acc);
   if (H->ctl) (void)hipFree(H->ctl);
   if (H->partials) (void)hipFree(H->partials);
@@ -428,20 +649,72 @@ bool schedule_done(const fa_inverse H) {
   return H->cur_level == (int)H->levels.size() - 1 && H->cur_iter >= H->levels.back().iters;
 }
 
+// Tiles of k_inv_direction: 8 x 8 x 16 nodes, or 4 x 4 x 16 below
+// kSmallTileVoxels, where the larger ones give a CU less than one workgroup
+// (40x48x56: 25 us against 30 with the larger; 80x96x112, 860,000 voxels: 58
+// with either).
+bool small_tiles(const fa_shape& s) { return fa::voxels(s) < kSmallTileVoxels; }
+
+int dir_blocks(const fa_shape& s) {
+  const int t = small_tiles(s) ? 4 : 8;
+  const int64_t tiles = (int64_t)((s.n0 + t - 1) / t) * ((s.n1 + t - 1) / t) * ((s.n2 + 15) / 16);
+  return (int)std::min<int64_t>(tiles, kDirMaxBlocks);
+}
+
+// Loss partials of one direction (launch_direction).
+int direction_partials(const fa_inverse H, const ILevel& L) {
+  return H->splat_direct ? 2 * inv_blocks(L.n) : dir_blocks(L.shape);
+}
+
+FastDiv fast_divisor(unsigned dv) {   // dv >= 2
+  unsigned s = 0;
+  while ((1ull << s) < dv) ++s;
+  return {(unsigned)((1ull << (31 + s)) / dv + 1), s - 1};
+}
+
 fa_status launch_direction(fa_inverse H, const ILevel& L, float* out, int grad_only) {
   const fa_shape& s = L.shape;
-  const int b = inv_blocks(L.n);
+  DirArgs A{};
+  A.d = L.d;
+  A.e = H->e;
+  A.m = H->m;
+  A.v = H->v;
+  A.out = out;
+  A.ctl = H->ctl;
+  A.part = H->partials;
+  A.n0 = s.n0;
+  A.n1 = s.n1;
+  A.n2 = s.n2;
+  A.inv_n = (float)(1.0 / (double)L.n);
+  A.beta1 = H->p.adam_beta1;
+  A.beta2 = H->p.adam_beta2;
+  A.adam_eps = H->p.adam_eps;
+  A.grad_only = grad_only;
   if (H->splat_direct) {
+    const int b = inv_blocks(L.n);
     hipLaunchKernelGGL(k_inv_splat, dim3(b), dim3(kInvThreads), 0, H->stream, L.d, H->e, H->acc, H->partials,
                        s.n0, s.n1, s.n2);
-  } else {
-    hipLaunchKernelGGL(k_inv_splat_lds, dim3(b), dim3(kInvThreads), 0, H->stream, L.d, H->e, H->acc,
-                       H->partials, s.n0, s.n1, s.n2);
+    FA_HIP(hipGetLastError());
+    A.part = H->partials + b;
+    hipLaunchKernelGGL(k_inv_dir, dim3(b), dim3(kInvThreads), 0, H->stream, A, H->acc);
+    FA_HIP(hipGetLastError());
+    return FA_OK;
   }
-  FA_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_inv_dir, dim3(b), dim3(kInvThreads), 0, H->stream, L.d, H->e, H->acc, H->m, H->v, out,
-                     H->ctl, H->partials + b, s.n0, s.n1, s.n2, (float)(1.0 / (double)L.n), H->p.adam_beta1,
-                     H->p.adam_beta2, H->p.adam_eps, grad_only);
+  const int b = dir_blocks(s);
+  Plan P = H->plan;
+  P.cells = (size_t)cells_of(s);
+  P.bricks = bricks_of(s);
+  if (H->plan_level != H->cur_level) {
+    FA_HIP(fa::launch_fill(reinterpret_cast<float*>(P.count), 0.0f, (int64_t)P.cells, H->stream));
+    hipLaunchKernelGGL(k_inv_plan, dim3(b), dim3(kInvThreads), 0, H->stream, L.d, P, s.n0, s.n1, s.n2);
+    FA_HIP(hipGetLastError());
+    H->plan_level = H->cur_level;
+  }
+  const FastDiv by_row = fast_divisor(s.n2), by_plane = fast_divisor((unsigned)(s.n1 * s.n2));
+  if (small_tiles(s))
+    hipLaunchKernelGGL((k_inv_direction<4, 4, 16, 256>), dim3(b), dim3(256), 0, H->stream, A, P, by_row, by_plane);
+  else
+    hipLaunchKernelGGL((k_inv_direction<8, 8, 16, 512>), dim3(b), dim3(512), 0, H->stream, A, P, by_row, by_plane);
   FA_HIP(hipGetLastError());
   return FA_OK;
 }
@@ -487,7 +760,7 @@ fa_status launch_iteration(fa_inverse H, const ILevel& L) {
   // the cost record and step count, in the launch the registration uses
   fa::GaussArgs& gr = fa::record_launch(L.tsw) == 2 ? g3 : g2;
   gr.partials = H->partials;
-  gr.n_partials = 2 * inv_blocks(L.n);
+  gr.n_partials = direction_partials(H, L);
   gr.loss_hist = H->loss_hist;
   gr.loss_cap = H->loss_cap;
 
@@ -597,11 +870,29 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
     H->partials = nullptr;
     H->cap = 0;
     for (int k = 0; k < (wide ? 6 : 5); ++k) FA_TRY(ialloc(bufs[k], (size_t)(3 * need), "state"));
-    FA_TRY(ialloc(&H->acc, (size_t)(3 * need), "splat accumulator"));
-    FA_TRY(ialloc(&H->partials, (size_t)(2 * kInvMaxBlocks), "cost partials"));
+    FA_TRY(ialloc(&H->partials, (size_t)kDirMaxBlocks, "cost partials"));
     H->cap = need;
   }
-  FA_HIP(hipMemsetAsync(H->acc, 0, (size_t)(3 * H->cap) * sizeof(unsigned long long), H->stream));
+  size_t cells = 0;
+  int bricks = 0;
+  for (auto& L : lv) {
+    cells = std::max(cells, (size_t)cells_of(L.shape));
+    bricks = std::max(bricks, bricks_of(L.shape));
+  }
+  if (cells > H->plan_cells || bricks > H->plan_bricks) {
+    free_plan(H);
+    FA_TRY(ialloc(&H->plan.count, cells, "cell counts"));
+    FA_TRY(ialloc(&H->plan.slots, 2 * cells, "voxels by cell"));
+    FA_TRY(ialloc(&H->plan.box, (size_t)(2 * bricks), "brick boxes"));
+    FA_TRY(ialloc(&H->plan.outside, (size_t)kDirMaxBlocks, "cost partials"));
+    H->plan_cells = cells;
+    H->plan_bricks = bricks;
+  }
+  H->plan_level = -1;
+  if (H->splat_direct) {
+    FA_TRY(ensure_acc(H));
+    FA_HIP(hipMemsetAsync(H->acc, 0, (size_t)(3 * H->cap) * sizeof(unsigned long long), H->stream));
+  }
   if (total > H->loss_cap) {
     if (H->loss_hist) (void)hipFree(H->loss_hist);
     H->loss_hist = nullptr;
@@ -702,7 +993,7 @@ fa_status fa_inverse_eval_gradient(fa_inverse H, float* g_dev, float* loss_host)
   if (!H->scheduled) return fail(FA_ESTATE, "fa_inverse_set_schedule has not been called");
   const ILevel& L = H->levels[H->cur_level];
   FA_TRY(launch_direction(H, L, g_dev, 1));
-  FA_HIP(fa::launch_partials_ratio(H->partials, 2 * inv_blocks(L.n), -(double)L.n, H->scalar, H->stream));
+  FA_HIP(fa::launch_partials_ratio(H->partials, direction_partials(H, L), -(double)L.n, H->scalar, H->stream));
   if (loss_host) {
     FA_HIP(hipMemcpyAsync(loss_host, H->scalar, sizeof(float), hipMemcpyDeviceToHost, H->stream));
     FA_HIP(hipStreamSynchronize(H->stream));
@@ -713,6 +1004,7 @@ fa_status fa_inverse_eval_gradient(fa_inverse H, float* g_dev, float* loss_host)
 fa_status fa_inverse_set_splat(fa_inverse H, int direct) {
   if (!H) return fail(FA_EINVAL, "handle is NULL");
   if (direct != 0 && direct != 1) return fail(FA_EINVAL, "direct must be 0 or 1");
+  if (direct && H->scheduled) FA_TRY(ensure_acc(H));   // else set_schedule allocates it
   H->splat_direct = direct != 0;
   return FA_OK;
 }
