@@ -688,7 +688,9 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
   // oldest first.
   constexpr int UNZ = (W == 7 && TY == 16) ? W : 1;   // not the 8-row tiles of thin volumes
   constexpr bool SWAP = W >= 7 && TY == 16;
-  int wphase = 0;   // plane step modulo W (rolled march)
+  // phase of the first step: a loss-only march starts W / 2 planes later
+  constexpr int PH0 = H1 == 2 * (W / 2) ? 0 : W / 2;
+  int wphase = PH0;   // plane step modulo W (rolled march)
   auto step = [&](const int zin, auto PH) __attribute__((always_inline)) {
     constexpr int ph = decltype(PH)::value;
     // slot of the j-th oldest entry of the I/J rings
@@ -725,7 +727,7 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
           // 16-row marches, so that every window's results stay the same.
           if constexpr (W > 1) {
             const float i1 = ringI[k][ri(1)], j1 = ringJ[k][ri(1)];
-            const bool sw = SWAP && (UNZ == 1 ? wphase >= W - 2 : ph >= W - 2);
+            const bool sw = SWAP && (UNZ == 1 ? wphase : (ph + PH0) % W) >= W - 2;
             const float ia = sw ? i1 : i0, ib = sw ? i0 : i1, ja = sw ? j1 : j0, jb = sw ? j0 : j1;
             s0 += i1;
             s1 += j1;
