@@ -11,6 +11,8 @@
 #include "fa.h"
 #include "fa_internal.h"
 
+struct fa_inverse_s;
+
 namespace fa {
 
 // Records msg as the calling thread's last error (returned by fa_last_error)
@@ -53,6 +55,10 @@ fa_shape level_shape(const fa_shape& s, float scale);
 // their chunk.  Brick tilings are left as they are.
 void batch_chunks(KernelKind kind, int halo, const std::vector<Tiling*>& ts, const std::vector<int>& n0s,
                   const std::vector<char>& pinned);
+
+// Gives H another warp of the same shape (device pointer, copied) and other
+// parameters; its buffers stay.  A schedule has to be set next.
+fa_status inverse_restart(fa_inverse_s* H, const float* d, const fa_params* params);
 
 }  // namespace fa
 

@@ -570,6 +570,7 @@ struct fa_inverse_s {
   double* partials = nullptr;
   float* scalar = nullptr;  // device float (eval_gradient's cost)
   float* wts = nullptr;
+  std::vector<float> wts_host;   // what wts holds
   int rg = 0, rw = 0, off_g = 0, off_w = 0, off_one = 0;
   int cur_level = 0, cur_iter = 0, t_done = 0, iters_done = 0;
   bool scheduled = false;
@@ -772,6 +773,18 @@ fa_status launch_iteration(fa_inverse H, const ILevel& L) {
 
 }  // namespace
 
+namespace fa {
+
+fa_status inverse_restart(fa_inverse H, const float* d, const fa_params* params) {
+  FA_TRY(check_params(params));
+  H->p = *params;
+  H->scheduled = false;
+  FA_HIP(hipMemcpyAsync(H->in_d, d, (size_t)(3 * H->n) * sizeof(float), hipMemcpyDeviceToDevice, H->stream));
+  return FA_OK;
+}
+
+}  // namespace fa
+
 extern "C" {
 
 fa_status fa_inverse_create(const float* d, fa_shape shape, const fa_params* params, void* stream,
@@ -833,9 +846,25 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
   }
   if (total > (int64_t)1 << 30) return fail(FA_EINVAL, "too many iterations");
 
-  FA_HIP(hipStreamSynchronize(H->stream));
-  free_levels(H);
+  // the level fields of an earlier schedule over the same grids are used again
   H->scheduled = false;
+  auto full = [&](const fa_shape& a) { return a.n0 == H->shape.n0 && a.n1 == H->shape.n1 && a.n2 == H->shape.n2; };
+  bool same = (int)H->levels.size() == n_levels;
+  for (int i = 0; same && i < n_levels; ++i) {
+    const ILevel& o = H->levels[i];
+    same = o.d && o.owns == !(lv[i].scale == 1.0f && full(lv[i].shape)) && o.shape.n0 == lv[i].shape.n0 &&
+           o.shape.n1 == lv[i].shape.n1 && o.shape.n2 == lv[i].shape.n2;
+  }
+  if (same) {
+    for (int i = 0; i < n_levels; ++i) {
+      lv[i].d = H->levels[i].d;
+      lv[i].owns = H->levels[i].owns;
+    }
+    H->levels = lv;
+  } else {
+    FA_HIP(hipStreamSynchronize(H->stream));
+    free_levels(H);
+  }
 
   // tap tables: sigma_grad, sigma_warp, the single tap, then one blur per level
   std::vector<float> host;
@@ -850,15 +879,20 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
   H->off_one = push(std::vector<float>{1.0f});
   std::vector<int> off_blur(n_levels);
   for (int i = 0; i < n_levels; ++i) off_blur[i] = push(fa::gaussian_taps(lv[i].scale / 2.0f));
-  if (H->wts) (void)hipFree(H->wts);
-  H->wts = nullptr;
-  FA_TRY(ialloc(&H->wts, host.size(), "tap tables"));
-  FA_HIP(hipMemcpyAsync(H->wts, host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice, H->stream));
+  if (!H->wts || host != H->wts_host) {
+    FA_HIP(hipStreamSynchronize(H->stream));
+    if (H->wts) (void)hipFree(H->wts);
+    H->wts = nullptr;
+    FA_TRY(ialloc(&H->wts, host.size(), "tap tables"));
+    H->wts_host = host;
+    FA_HIP(hipMemcpyAsync(H->wts, H->wts_host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice, H->stream));
+  }
 
   // state (sized for the largest level) and the splat accumulator
   const int64_t need = std::max(nmax, H->n);   // m and e hold three input volumes each below
   const bool wide = H->rg > fa::kMaxRadius || H->rw > fa::kMaxRadius;
   if (need > H->cap || (wide && !H->wide)) {
+    FA_HIP(hipStreamSynchronize(H->stream));
     float** bufs[] = {&H->e, &H->m, &H->v, &H->a, &H->tmp, &H->wide};
     for (float** b : bufs) {
       if (*b) (void)hipFree(*b);
@@ -880,6 +914,7 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
     bricks = std::max(bricks, bricks_of(L.shape));
   }
   if (cells > H->plan_cells || bricks > H->plan_bricks) {
+    FA_HIP(hipStreamSynchronize(H->stream));
     free_plan(H);
     FA_TRY(ialloc(&H->plan.count, cells, "cell counts"));
     FA_TRY(ialloc(&H->plan.slots, 2 * cells, "voxels by cell"));
@@ -894,6 +929,7 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
     FA_HIP(hipMemsetAsync(H->acc, 0, (size_t)(3 * H->cap) * sizeof(unsigned long long), H->stream));
   }
   if (total > H->loss_cap) {
+    FA_HIP(hipStreamSynchronize(H->stream));
     if (H->loss_hist) (void)hipFree(H->loss_hist);
     H->loss_hist = nullptr;
     H->loss_cap = 0;
@@ -902,15 +938,15 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
   }
 
   // pyramid of the warp's field; m and e serve as scratch before the state is set
-  H->levels = lv;
+  if (!same) H->levels = lv;
   for (int i = 0; i < n_levels; ++i) {
     ILevel& L = H->levels[i];
-    if (L.scale == 1.0f && L.shape.n0 == H->shape.n0 && L.shape.n1 == H->shape.n1 && L.shape.n2 == H->shape.n2) {
+    if (L.scale == 1.0f && full(L.shape)) {
       L.d = H->in_d;
       L.owns = false;
       continue;
     }
-    FA_TRY(ialloc(&L.d, (size_t)(3 * L.n), "level field"));
+    if (!L.d) FA_TRY(ialloc(&L.d, (size_t)(3 * L.n), "level field"));
     L.owns = true;
     const fa_shape& s = H->shape;
     const float* src[3];

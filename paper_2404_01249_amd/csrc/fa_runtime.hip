@@ -479,9 +479,23 @@ struct BatchTables {
   std::vector<BatchLaunch> launches;
   std::vector<unsigned char> host;
   std::vector<int> jac;   // live pairs with use_jac (their Eulerian launch follows stage 0)
-  void* dev = nullptr;
-  size_t dev_cap = 0;
+  void* dev = nullptr;    // the uploaded copy of host, within the current chunk
+  // Every upload of a call takes a region of its own, and its host copy is
+  // kept, so that neither waits for the launches already queued; the call's
+  // closing synchronisation makes them all free again (recycle).
+  struct Chunk {
+    unsigned char* base;
+    size_t cap;
+  };
+  std::vector<Chunk> chunks;
+  size_t chunk = 0, used = 0;   // current chunk and what is taken of it
+  std::vector<std::vector<unsigned char>> sent;
+  void recycle() {
+    chunk = used = 0;
+    sent.clear();
+  }
 };
+constexpr size_t kTableChunk = 1 << 18;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -622,19 +636,35 @@ fa_status build_batch_tables(const std::vector<fa_pair>& live, BatchTables& bt) 
 // Copies the host image to the device.  Synchronises: the launches already
 // queued read the previous tables, and the host image may change after this.
 fa_status upload_batch_tables(BatchTables& bt, hipStream_t s) {
-  const size_t need = std::max<size_t>(bt.host.size(), 256);
-  FA_HIP(hipStreamSynchronize(s));
-  if (need > bt.dev_cap) {
-    if (bt.dev) FA_HIP(hipFree(bt.dev));
-    bt.dev = nullptr;
-    bt.dev_cap = 0;
-    FA_TRY(dalloc((unsigned char**)&bt.dev, need, "batch tables"));
-    bt.dev_cap = need;
+  const size_t need = align256(std::max<size_t>(bt.host.size(), 256));
+  while (bt.chunk < bt.chunks.size() && need > bt.chunks[bt.chunk].cap - bt.used) {
+    ++bt.chunk;
+    bt.used = 0;
   }
-  if (!bt.host.empty())
-    FA_HIP(hipMemcpyAsync(bt.dev, bt.host.data(), bt.host.size(), hipMemcpyHostToDevice, s));
-  FA_HIP(hipStreamSynchronize(s));
+  if (bt.chunk == bt.chunks.size()) {
+    BatchTables::Chunk c{nullptr, std::max(need, kTableChunk)};
+    FA_TRY(dalloc(&c.base, c.cap, "batch tables"));
+    bt.chunks.push_back(c);
+  }
+  bt.dev = bt.chunks[bt.chunk].base + bt.used;
+  bt.used += need;
+  if (!bt.host.empty()) {
+    bt.sent.push_back(bt.host);
+    FA_HIP(hipMemcpyAsync(bt.dev, bt.sent.back().data(), bt.host.size(), hipMemcpyHostToDevice, s));
+  }
   return FA_OK;
+}
+
+fa_status free_batch_tables(BatchTables& bt) {
+  fa_status st = FA_OK;
+  for (auto& c : bt.chunks) {
+    const hipError_t e = hipFree(c.base);
+    if (st == FA_OK && e != hipSuccess) st = fail(FA_EHIP, std::string("hipFree: ") + hipGetErrorString(e));
+  }
+  bt.chunks.clear();
+  bt.dev = nullptr;
+  bt.recycle();
+  return st;
 }
 
 fa_status launch_batch_iteration(const std::vector<fa_pair>& live, const BatchTables& bt, hipStream_t s) {
@@ -718,7 +748,7 @@ fa_status run_batch_fused(fa_pair* pairs, int n, int max_iters, hipStream_t s) {
     if (st != FA_OK || live.empty()) break;
     if (sig != last) {
       if (gexec) {
-        // the replays already queued use the old tables: upload_batch_tables synchronises first
+        (void)hipStreamSynchronize(s);   // replays may still be queued
         (void)hipGraphExecDestroy(gexec);
         gexec = nullptr;
       }
@@ -763,12 +793,12 @@ fa_status run_batch_fused(fa_pair* pairs, int n, int max_iters, hipStream_t s) {
       P->iters_done += 1;
     }
   }
-  if (bt.dev) {
+  if (!bt.chunks.empty()) {
     // the queued launches read the tables
     const hipError_t e1 = hipStreamSynchronize(s);
-    const hipError_t e2 = hipFree(bt.dev);
+    const fa_status st2 = free_batch_tables(bt);
     if (st == FA_OK && e1 != hipSuccess) st = fail(FA_EHIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(e1));
-    if (st == FA_OK && e2 != hipSuccess) st = fail(FA_EHIP, std::string("hipFree: ") + hipGetErrorString(e2));
+    if (st == FA_OK) st = st2;
   }
   if (gexec) (void)hipGraphExecDestroy(gexec);
   return st;
@@ -1640,6 +1670,10 @@ struct fa_sym_s {
   fa_pair M = nullptr;
   hipStream_t stream = nullptr;
   fa_shape shape{};
+  BatchTables tables;          // its device memory is kept between calls
+  // The inversion of finish, kept for the next one: allocating and releasing its
+  // twenty buffers and the tables took 1.1 ms of a 2.8 ms registration at 96x112x112.
+  fa_inverse inv = nullptr;
 };
 
 extern "C" {
@@ -1682,7 +1716,7 @@ fa_status fa_sym_step(fa_sym H, int max_iters, int* iters_done, int* finished) {
   // the two halves share every template parameter: each kernel of an
   // iteration is one batched launch over both
   const std::vector<fa_pair> both = {M, F};
-  BatchTables bt;
+  BatchTables& bt = H->tables;
   int level = -1;
   int done = 0;
   fa_status st = FA_OK;
@@ -1702,11 +1736,11 @@ fa_status fa_sym_step(fa_sym H, int max_iters, int* iters_done, int* finished) {
     }
     done += 1;
   }
-  if (bt.dev) {
+  if (!bt.sent.empty()) {
+    // the queued launches read the tables
     const hipError_t e1 = hipStreamSynchronize(H->stream);
-    const hipError_t e2 = hipFree(bt.dev);
     if (st == FA_OK && e1 != hipSuccess) st = fail(FA_EHIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(e1));
-    if (st == FA_OK && e2 != hipSuccess) st = fail(FA_EHIP, std::string("hipFree: ") + hipGetErrorString(e2));
+    bt.recycle();
   }
   if (st != FA_OK) return st;
   if (iters_done) *iters_done = done;
@@ -1735,8 +1769,12 @@ fa_status fa_sym_finish(fa_sym H, const fa_params* inv_params, int n_levels, con
   const Level& L = H->M->levels[H->M->cur_level];
   if (L.shape.n0 != H->shape.n0 || L.shape.n1 != H->shape.n1 || L.shape.n2 != H->shape.n2)
     return fail(FA_ESTATE, "the schedule's last level must be the input grid (scale 1)");
-  fa_inverse inv = nullptr;
-  FA_TRY(fa_inverse_create(H->F->d, H->shape, inv_params, H->stream, &inv));
+  if (H->inv) {
+    FA_TRY(fa::inverse_restart(H->inv, H->F->d, inv_params));
+  } else {
+    FA_TRY(fa_inverse_create(H->F->d, H->shape, inv_params, H->stream, &H->inv));
+  }
+  fa_inverse const inv = H->inv;
   fa_status st = fa_inverse_set_schedule(inv, n_levels, scales, iters);
   if (st == FA_OK) st = fa_inverse_step(inv, 1 << 30, nullptr, nullptr);
   int lvl = 0;
@@ -1760,10 +1798,11 @@ fa_status fa_sym_finish(fa_sym H, const fa_params* inv_params, int n_levels, con
     st = fa_inverse_get_loss(inv, hist.data(), total, &got);
     *inv_cost = got > 0 ? hist[(size_t)got - 1] : 0.0f;
   }
-  fa_inverse_destroy(inv);
-  if (st == FA_OK) {
-    const hipError_t he = hipStreamSynchronize(H->stream);
-    if (he != hipSuccess) st = fail(FA_EHIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(he));
+  const hipError_t he = hipStreamSynchronize(H->stream);
+  if (st == FA_OK && he != hipSuccess) st = fail(FA_EHIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(he));
+  if (st != FA_OK) {   // nothing is kept from a failed call
+    fa_inverse_destroy(H->inv);
+    H->inv = nullptr;
   }
   return st;
 }
@@ -1771,6 +1810,8 @@ fa_status fa_sym_finish(fa_sym H, const fa_params* inv_params, int n_levels, con
 void fa_sym_destroy(fa_sym H) {
   if (!H) return;
   (void)hipStreamSynchronize(H->stream);
+  fa_inverse_destroy(H->inv);
+  (void)free_batch_tables(H->tables);
   fa_pair_destroy(H->F);
   fa_pair_destroy(H->M);
   delete H;
