@@ -167,10 +167,11 @@ hipError_t launch_row_pairs(const float* in, float* out, int n0, int n1, int n2,
 hipError_t launch_level_images(const float* const* src, float* const* dst, const float* rho, int count, float* tmp0,
                                float* tmp1, int n0, int n1, int n2, int m0, int m1, int m2, const float* wts, int R,
                                hipStream_t s);
-// Trilinear samples of a [3][N] field at corner-aligned positions, component c times rho_c.
-hipError_t launch_resample(const float* in, float* out, int nin0, int nin1, int nin2,
-                           int nout0, int nout1, int nout2,
-                           float rho0, float rho1, float rho2, hipStream_t s);
+// Trilinear samples of `fields` (1 to 3) [3][N] fields at corner-aligned
+// positions, from grid ni to grid no ; the first
+// field's component c times rho[c].  No output may be an input.
+hipError_t launch_resample(const float* const* in, float* const* out, int fields, const int ni[3], const int no[3],
+                           const float rho[3], hipStream_t s);
 hipError_t launch_warp(const float* img, const float* d, float* out, int n0, int n1, int n2,
                        hipStream_t s);
 // The same with the position derivative of the sample ([3][N]).

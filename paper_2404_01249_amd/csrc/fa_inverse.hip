@@ -626,23 +626,17 @@ fa_status transition(fa_inverse H) {
   const ILevel& C = H->levels[H->cur_level];
   const ILevel& F = H->levels[H->cur_level + 1];
   auto rho = [](int nf, int nc) { return nc > 1 ? (float)((double)(nf - 1) / (double)(nc - 1)) : 1.0f; };
-  const fa_shape& c = C.shape;
-  const fa_shape& f = F.shape;
-  FA_HIP(fa::launch_resample(H->e, H->tmp, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, rho(f.n0, c.n0),
-                             rho(f.n1, c.n1), rho(f.n2, c.n2), H->stream));
-  FA_HIP(fa::launch_resample(H->m, H->a, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 1.f, 1.f, 1.f, H->stream));
-  FA_HIP(fa::launch_resample(H->v, H->m, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 1.f, 1.f, 1.f, H->stream));
-  // the fine e, m, v now sit in tmp, a, m; the coarse e and v buffers are free
-  float* old_e = H->e;
-  float* old_m = H->m;
-  float* old_v = H->v;
-  float* old_a = H->a;
-  float* old_t = H->tmp;
-  H->e = old_t;
-  H->m = old_a;
-  H->v = old_m;
-  H->a = old_e;
-  H->tmp = old_v;
+  const int c[3] = {C.shape.n0, C.shape.n1, C.shape.n2}, f[3] = {F.shape.n0, F.shape.n1, F.shape.n2};
+  const float r[3] = {rho(f[0], c[0]), rho(f[1], c[1]), rho(f[2], c[2])}, one[3] = {1.0f, 1.0f, 1.0f};
+  const float* in[2] = {H->e, H->m};
+  float* out[2] = {H->tmp, H->a};
+  FA_HIP(fa::launch_resample(in, out, 2, c, f, r, H->stream));
+  std::swap(H->e, H->tmp);
+  std::swap(H->m, H->a);
+  // v goes to the buffer that held the coarse e
+  const float* in_v = H->v;
+  FA_HIP(fa::launch_resample(&in_v, &H->tmp, 1, c, f, one, H->stream));
+  std::swap(H->v, H->tmp);
   return FA_OK;
 }
 

@@ -63,12 +63,6 @@ __device__ __forceinline__ void cell(float p, int n, int& i, float& t, bool& lo,
   hi = (i >= -1) & (i + 1 < n);
 }
 
-// Load with per-corner zero padding; the address is always in bounds.
-__device__ __forceinline__ float ldz(const float* __restrict__ f, int idx, bool ok) {
-  const float v = f[ok ? idx : 0];
-  return ok ? v : 0.0f;
-}
-
 // The same for a sample at grid point x displaced by dd.  The cell index is
 // x + floor(dd) and the fraction dd - floor(dd), so no precision is lost to
 // forming x + dd in fp32: the cell is exactly the cell of the exact position
@@ -84,83 +78,31 @@ __device__ __forceinline__ void cell_at(int x, float dd, int n, int& i, float& t
 }
 
 struct Corners {
-  int base, s0, s1;
+  int i0, i1, i2;
   bool a0, b0, a1, b1, a2, b2;
   float t0, t1, t2;
 };
 
-// Corners of the sample at grid point (z, y, x) + (d0, d1, d2).
-__device__ __forceinline__ Corners corners_at(int n0, int n1, int n2, int z, int y, int x, float d0,
-                                              float d1, float d2) {
-  Corners c;
-  int i0, i1, i2;
-  cell_at(z, d0, n0, i0, c.t0, c.a0, c.b0);
-  cell_at(y, d1, n1, i1, c.t1, c.a1, c.b1);
-  cell_at(x, d2, n2, i2, c.t2, c.a2, c.b2);
-  c.s1 = n2;
-  c.s0 = n1 * n2;
-  c.base = (i0 * n1 + i1) * n2 + i2;
-  return c;
-}
-
 __device__ __forceinline__ Corners make_corners(int n0, int n1, int n2, float p0, float p1, float p2) {
   Corners c;
-  int i0, i1, i2;
-  cell(p0, n0, i0, c.t0, c.a0, c.b0);
-  cell(p1, n1, i1, c.t1, c.a1, c.b1);
-  cell(p2, n2, i2, c.t2, c.a2, c.b2);
-  c.s1 = n2;
-  c.s0 = n1 * n2;
-  c.base = (i0 * n1 + i1) * n2 + i2;
+  cell(p0, n0, c.i0, c.t0, c.a0, c.b0);
+  cell(p1, n1, c.i1, c.t1, c.a1, c.b1);
+  cell(p2, n2, c.i2, c.t2, c.a2, c.b2);
   return c;
 }
 
-// Trilinear sample T(f, p), zero outside the grid (per corner).
-__device__ __forceinline__ float tri(const float* __restrict__ f, const Corners& c) {
-  const float c000 = ldz(f, c.base, c.a0 & c.a1 & c.a2);
-  const float c001 = ldz(f, c.base + 1, c.a0 & c.a1 & c.b2);
-  const float c010 = ldz(f, c.base + c.s1, c.a0 & c.b1 & c.a2);
-  const float c011 = ldz(f, c.base + c.s1 + 1, c.a0 & c.b1 & c.b2);
-  const float c100 = ldz(f, c.base + c.s0, c.b0 & c.a1 & c.a2);
-  const float c101 = ldz(f, c.base + c.s0 + 1, c.b0 & c.a1 & c.b2);
-  const float c110 = ldz(f, c.base + c.s0 + c.s1, c.b0 & c.b1 & c.a2);
-  const float c111 = ldz(f, c.base + c.s0 + c.s1 + 1, c.b0 & c.b1 & c.b2);
-  const float e00 = c000 + c.t2 * (c001 - c000);
-  const float e01 = c010 + c.t2 * (c011 - c010);
-  const float e10 = c100 + c.t2 * (c101 - c100);
-  const float e11 = c110 + c.t2 * (c111 - c110);
+// Trilinear sample from its corners' values in the order 000, 001, ..., 111
+// (zero where a corner is off the grid).
+__device__ __forceinline__ float tri(const float v[8], const Corners& c) {
+  const float e00 = v[0] + c.t2 * (v[1] - v[0]);
+  const float e01 = v[2] + c.t2 * (v[3] - v[2]);
+  const float e10 = v[4] + c.t2 * (v[5] - v[4]);
+  const float e11 = v[6] + c.t2 * (v[7] - v[6]);
   const float f0 = e00 + c.t1 * (e01 - e00);
   const float f1 = e10 + c.t1 * (e11 - e10);
   return f0 + c.t0 * (f1 - f0);
 }
 
-// T(f, p) and dT/dp (the trilinear weight along one axis replaced by -1/+1;
-// at integer coordinates this is the derivative from the right).
-__device__ __forceinline__ float tri_grad(const float* __restrict__ f, const Corners& c,
-                                          float& g0, float& g1, float& g2) {
-  const float c000 = ldz(f, c.base, c.a0 & c.a1 & c.a2);
-  const float c001 = ldz(f, c.base + 1, c.a0 & c.a1 & c.b2);
-  const float c010 = ldz(f, c.base + c.s1, c.a0 & c.b1 & c.a2);
-  const float c011 = ldz(f, c.base + c.s1 + 1, c.a0 & c.b1 & c.b2);
-  const float c100 = ldz(f, c.base + c.s0, c.b0 & c.a1 & c.a2);
-  const float c101 = ldz(f, c.base + c.s0 + 1, c.b0 & c.a1 & c.b2);
-  const float c110 = ldz(f, c.base + c.s0 + c.s1, c.b0 & c.b1 & c.a2);
-  const float c111 = ldz(f, c.base + c.s0 + c.s1 + 1, c.b0 & c.b1 & c.b2);
-  const float dx00 = c001 - c000, dx01 = c011 - c010, dx10 = c101 - c100, dx11 = c111 - c110;
-  const float e00 = c000 + c.t2 * dx00;
-  const float e01 = c010 + c.t2 * dx01;
-  const float e10 = c100 + c.t2 * dx10;
-  const float e11 = c110 + c.t2 * dx11;
-  const float dy0 = e01 - e00, dy1 = e11 - e10;
-  const float f0 = e00 + c.t1 * dy0;
-  const float f1 = e10 + c.t1 * dy1;
-  const float dxy0 = dx00 + c.t1 * (dx01 - dx00);
-  const float dxy1 = dx10 + c.t1 * (dx11 - dx10);
-  g0 = f1 - f0;
-  g1 = dy0 + c.t0 * (dy1 - dy0);
-  g2 = dxy0 + c.t0 * (dxy1 - dxy0);
-  return f0 + c.t0 * (f1 - f0);
-}
 
 // Number of grid points of [i - r, i + r] inside [0, n).
 __device__ __forceinline__ float clipped_count(int i, int n, int r) {
@@ -2138,14 +2080,15 @@ struct Images {
 // workgroups per row (BLK), so that everything but the item is uniform, or flat
 // over all items where a row is too short to fill a wavefront.
 template <bool BLK>
-__device__ __forceinline__ bool row_item(unsigned inner, unsigned outer, unsigned& row, unsigned& item) {
+__device__ __forceinline__ bool row_item(unsigned block, unsigned inner, unsigned outer, unsigned& row,
+                                         unsigned& item) {
   if constexpr (BLK) {
     const unsigned nb = (inner + blockDim.x - 1) / blockDim.x;
-    row = blockIdx.x / nb;
-    item = (blockIdx.x - row * nb) * blockDim.x + threadIdx.x;
+    row = block / nb;
+    item = (block - row * nb) * blockDim.x + threadIdx.x;
     return item < inner;
   } else {
-    const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned t = block * blockDim.x + threadIdx.x;
     row = t / inner;
     item = t - row * inner;
     return row < outer;
@@ -2176,7 +2119,7 @@ __global__ void __launch_bounds__(256) k_blur_pairs(const Images im, unsigned co
   const unsigned groups = (unsigned)(nm + kg - 1) / kg;
   const unsigned per_image = AX == 0 ? groups : n_other * groups;
   unsigned row, item;
-  if (!row_item<BLK>(inner, per_image * count, row, item)) return;
+  if (!row_item<BLK>(blockIdx.x, inner, per_image * count, row, item)) return;
   const unsigned img = row / per_image, r = row - img * per_image, z = AX == 0 ? 0u : r / groups;
   const int k0 = (int)(r - z * groups) * kg;
   const size_t stride = inner;
@@ -2243,24 +2186,23 @@ __global__ void __launch_bounds__(256) k_level_sample(const Images im, unsigned 
   const int R = RT ? RT : Rr;
   unsigned row, item;
   const unsigned per_image = (unsigned)m0 * m1;
-  if (!row_item<BLK>((unsigned)m2, per_image * count, row, item)) return;
+  if (!row_item<BLK>(blockIdx.x, (unsigned)m2, per_image * count, row, item)) return;
   const unsigned img = row / per_image, r = row - img * per_image;
   const int k1 = (int)(r % m1), k0 = (int)(r / m1), k2 = (int)item;
   Corners c = make_corners(n0, n1, n2, aligned_pos(k0, n0, m0), aligned_pos(k1, n1, m1), aligned_pos(k2, n2, m2));
-  const int i0 = aligned_cell(k0, n0, m0), i1 = aligned_cell(k1, n1, m1), i2 = aligned_cell(k2, n2, m2);
   const int p1 = c1 ? 2 * m1 : n1;
   float v[8];
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
     const int b0 = b >> 1, b1 = b & 1;
-    const int z = c0 ? 2 * k0 + b0 : min(max(i0 + b0, 0), n0 - 1);
-    const int y = c1 ? 2 * k1 + b1 : min(max(i1 + b1, 0), n1 - 1);
+    const int z = c0 ? 2 * k0 + b0 : min(max(c.i0 + b0, 0), n0 - 1);
+    const int y = c1 ? 2 * k1 + b1 : min(max(c.i1 + b1, 0), n1 - 1);
     const float* src = im.in[img] + ((size_t)z * p1 + y) * n2;
     float s0 = 0.0f, s1 = 0.0f;
-    float x = src[min(max(i2 - R, 0), n2 - 1)];
+    float x = src[min(max(c.i2 - R, 0), n2 - 1)];
 #pragma unroll(RT ? 2 * RT + 1 : 4)
     for (int j = 0; j <= 2 * R; ++j) {
-      const float t = src[min(max(i2 - R + 1 + j, 0), n2 - 1)];
+      const float t = src[min(max(c.i2 - R + 1 + j, 0), n2 - 1)];
       s0 += w[j] * x;
       s1 += w[j] * t;
       x = t;
@@ -2269,28 +2211,89 @@ __global__ void __launch_bounds__(256) k_level_sample(const Images im, unsigned 
     v[2 * b] = in0 & in1 & c.a2 ? s0 : 0.0f;
     v[2 * b + 1] = in0 & in1 & c.b2 ? s1 : 0.0f;
   }
-  const float e00 = v[0] + c.t2 * (v[1] - v[0]);
-  const float e01 = v[2] + c.t2 * (v[3] - v[2]);
-  const float e10 = v[4] + c.t2 * (v[5] - v[4]);
-  const float e11 = v[6] + c.t2 * (v[7] - v[6]);
-  const float f0 = e00 + c.t1 * (e01 - e00);
-  const float f1 = e10 + c.t1 * (e11 - e10);
   const float rho = img == 0 ? rho0 : (img == 1 ? rho1 : rho2);
-  im.out[img][(size_t)r * m2 + k2] = rho * (f0 + c.t0 * (f1 - f0));
+  im.out[img][(size_t)r * m2 + k2] = rho * tri(v, c);
 }
 
-template <bool G3>
-__global__ void k_resample(const float* __restrict__ in, float* __restrict__ out, int ni0, int ni1,
-                           int ni2, int no0, int no1, int no2, float rho0, float rho1, float rho2) {
-  const int No = no0 * no1 * no2;
-  const int Ni = ni0 * ni1 * ni2;
-  int z, y, x, i;
-  if (!grid_voxel<G3>(no0, no1, no2, z, y, x, i)) return;
-  const Corners c = make_corners(ni0, ni1, ni2, aligned_pos(z, ni0, no0), aligned_pos(y, ni1, no1),
-                                 aligned_pos(x, ni2, no2));
-  out[i] = rho0 * tri(in, c);
-  out[No + i] = rho1 * tri(in + Ni, c);
-  out[2 * No + i] = rho2 * tri(in + 2 * Ni, c);
+// Trilinear samples at corner-aligned positions of up to three [3][N] fields
+// (displacement and Adam moments at a level's end).  A thread takes one field's
+// three components along a run of zc samples in n0: the sample in a plane
+// (along n2, then n1) is the same for every sample between two planes, so it is
+// formed once per input plane and a sample costs one more interpolation and its
+// store.  Forming each sample by itself takes some 150 instructions a wavefront,
+// 1.5 times what the stores cost.  (Three fields, 64^3 to 512^3 in three steps:
+// 1.69 ms; a launch per field and a thread per sample 2.80.  Eight pairs,
+// 48x56x52 to 96x112x104: 125 us against 307.)
+struct Resample {
+  const float* in[3];
+  float* out[3];
+  float rho[3];   // of the first field's components; the others' are 1
+};
+
+template <bool BLK>
+__global__ void __launch_bounds__(256) k_resample(const Resample A, unsigned fields, int ni0, int ni1, int ni2,
+                                                  int no0, int no1, int no2, int zc) {
+  unsigned row, item;   // a row: one field, one run along n0, one y
+  const unsigned runs = (unsigned)(no0 + zc - 1) / zc;
+  if (!row_item<BLK>(xcd_tile(blockIdx.x, gridDim.x), (unsigned)no2, fields * runs * no1, row, item)) return;
+  const unsigned f = row / (runs * no1), run = row / no1 % runs;
+  const int y = (int)(row % no1), x = (int)item;
+  int iy, ix;
+  float ty, tx;
+  bool a1, b1, a2, b2;
+  cell(aligned_pos(y, ni1, no1), ni1, iy, ty, a1, b1);
+  cell(aligned_pos(x, ni2, no2), ni2, ix, tx, a2, b2);
+  const int ya = min(max(iy, 0), ni1 - 1) * ni2, yb = min(max(iy + 1, 0), ni1 - 1) * ni2;
+  const int xa = min(max(ix, 0), ni2 - 1), xb = min(max(ix + 1, 0), ni2 - 1);
+  const int off[4] = {ya + xa, ya + xb, yb + xa, yb + xb};
+  const bool ok[4] = {a1 && a2, a1 && b2, b1 && a2, b1 && b2};
+  const float* const in = f == 0 ? A.in[0] : (f == 1 ? A.in[1] : A.in[2]);
+  float* const out = (f == 0 ? A.out[0] : (f == 1 ? A.out[1] : A.out[2])) + (size_t)y * no2 + x;
+  const size_t Ni = (size_t)ni0 * ni1 * ni2, No = (size_t)no0 * no1 * no2;
+
+  float lo[3], hi[3];   // the samples in planes at and at + 1
+  auto plane = [&](int z, float p[3]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) p[q] = 0.0f;
+    if (z < 0 || z >= ni0) return;
+    const float* g = in + (size_t)z * ni1 * ni2;
+    float v[3][4];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[q][k] = g[q * Ni + off[k]];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[q][k] = ok[k] ? v[q][k] : 0.0f;
+      const float e0 = v[q][0] + tx * (v[q][1] - v[q][0]);
+      const float e1 = v[q][2] + tx * (v[q][3] - v[q][2]);
+      p[q] = e0 + ty * (e1 - e0);
+    }
+  };
+  int at = -100;   // no plane yet
+  const int z1 = min((int)(run + 1) * zc, no0);
+  for (int z = (int)run * zc; z < z1; ++z) {
+    int iz;
+    float tz;
+    bool a0, b0;
+    cell(aligned_pos(z, ni0, no0), ni0, iz, tz, a0, b0);
+    if (iz != at) {
+      if (iz == at + 1)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) lo[q] = hi[q];
+      else
+        plane(iz, lo);
+      plane(iz + 1, hi);
+      at = iz;
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const float s = lo[q] + tz * (hi[q] - lo[q]);
+      // written once and far more than the L2 holds: past it (1.82 -> 1.69 ms)
+      __builtin_nontemporal_store((f == 0 ? A.rho[q] : 1.0f) * s, &out[q * No + (size_t)z * no1 * no2]);
+    }
+  }
 }
 
 // J = I_m(x + d) and, with SLOPE, its position derivative ([3][N]): one
@@ -2881,16 +2884,25 @@ hipError_t launch_level_images(const float* const* src, float* const* dst, const
   }
 }
 
-hipError_t launch_resample(const float* in, float* out, int nin0, int nin1, int nin2, int nout0,
-                           int nout1, int nout2, float rho0, float rho1, float rho2, hipStream_t s) {
-  if (nout0 <= 65535 && nout1 <= 65535) {   // grid z and y hold n0 and n1
-    hipLaunchKernelGGL(k_resample<true>, dim3(grid1(nout2, 256), nout1, nout0), dim3(256), 0, s, in, out, nin0,
-                       nin1, nin2, nout0, nout1, nout2, rho0, rho1, rho2);
-  } else {
-    const int64_t n = (int64_t)nout0 * nout1 * nout2;
-    hipLaunchKernelGGL(k_resample<false>, dim3(grid1(n, 256)), dim3(256), 0, s, in, out, nin0, nin1, nin2,
-                       nout0, nout1, nout2, rho0, rho1, rho2);
+hipError_t launch_resample(const float* const* in, float* const* out, int fields, const int ni[3], const int no[3],
+                           const float rho[3], hipStream_t s) {
+  if (fields < 1 || fields > 3) return hipErrorInvalidValue;
+  Resample A{};
+  for (int f = 0; f < fields; ++f) {
+    A.in[f] = in[f];
+    A.out[f] = out[f];
   }
+  for (int q = 0; q < 3; ++q) A.rho[q] = rho[q];
+  // runs of 4 to 16 samples: as long as every CU keeps its 2048 threads
+  const int64_t threads = (int64_t)fields * no[0] * no[1] * no[2];
+  const int zc = (int)std::min<int64_t>(16, std::max<int64_t>(4, threads / (256 * 2048)));
+  const int64_t rows = (int64_t)fields * no[1] * ((no[0] + zc - 1) / zc);
+  if (const int bs = row_block(no[2]))
+    hipLaunchKernelGGL(k_resample<true>, dim3((unsigned)(rows * ((no[2] + bs - 1) / bs))), dim3(bs), 0, s, A, fields,
+                       ni[0], ni[1], ni[2], no[0], no[1], no[2], zc);
+  else
+    hipLaunchKernelGGL(k_resample<false>, dim3(grid1(rows * no[2], 256)), dim3(256), 0, s, A, fields, ni[0], ni[1],
+                       ni[2], no[0], no[1], no[2], zc);
   return hipGetLastError();
 }
 

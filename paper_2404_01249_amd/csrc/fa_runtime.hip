@@ -416,23 +416,14 @@ fa_status transition(fa_pair P) {
   const Level& C = P->levels[P->cur_level];
   const Level& F = P->levels[P->cur_level + 1];
   auto rho = [](int nf, int nc) { return nc > 1 ? (float)((double)(nf - 1) / (double)(nc - 1)) : 1.0f; };
-  const float r0 = rho(F.shape.n0, C.shape.n0), r1 = rho(F.shape.n1, C.shape.n1), r2 = rho(F.shape.n2, C.shape.n2);
-  const fa_shape& c = C.shape;
-  const fa_shape& f = F.shape;
-  FA_HIP(fa::launch_resample(P->d, P->tmp, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, r0, r1, r2, P->stream));
-  FA_HIP(fa::launch_resample(P->m, P->a, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 1.f, 1.f, 1.f, P->stream));
-  // v's coarse data moves into the buffer that held m (already consumed).
-  FA_HIP(fa::launch_resample(P->v, P->m, c.n0, c.n1, c.n2, f.n0, f.n1, f.n2, 1.f, 1.f, 1.f, P->stream));
-  float* old_d = P->d;
-  float* old_m = P->m;
-  float* old_v = P->v;
-  float* old_a = P->a;
-  float* old_t = P->tmp;
-  P->d = old_t;
-  P->m = old_a;
-  P->v = old_m;
-  P->a = old_d;
-  P->tmp = old_v;
+  const int c[3] = {C.shape.n0, C.shape.n1, C.shape.n2}, f[3] = {F.shape.n0, F.shape.n1, F.shape.n2};
+  const float r[3] = {rho(f[0], c[0]), rho(f[1], c[1]), rho(f[2], c[2])};
+  const float* in[3] = {P->d, P->m, P->v};
+  float* out[3] = {P->tmp, P->a, P->slope};   // the slope at the coarse grid has no further use
+  FA_HIP(fa::launch_resample(in, out, 3, c, f, r, P->stream));
+  std::swap(P->d, P->tmp);
+  std::swap(P->m, P->a);
+  std::swap(P->v, P->slope);
   P->warped_ok = false;
   return FA_OK;
 }
