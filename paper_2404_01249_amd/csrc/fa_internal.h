@@ -182,10 +182,26 @@ hipError_t launch_soa_to_aos(const float* in, float* out, int64_t n, hipStream_t
 hipError_t launch_compose_fields(const float* u, const float* d, float* out, int n0, int n1, int n2,
                                  hipStream_t s);
 // Sets the Adam step count to t_done + 1 (bias corrections in double), clears
-// M; iter >= 0 also resets the iteration counter.
-hipError_t launch_ctl_init(Ctl* ctl, float beta1, float beta2, int t_done, int iter, hipStream_t s);
-// Mean of x (n values) into *dst (device float), via `scratch` (kMeanBlocks doubles).
-hipError_t launch_mean(const float* x, int64_t n, double* scratch, float* dst, hipStream_t s);
+// M and tickets (may be NULL); iter >= 0 also resets the iteration counter.
+hipError_t launch_ctl_init(Ctl* ctl, float beta1, float beta2, int t_done, int iter, unsigned* tickets,
+                           hipStream_t s);
+// The same for t_done = iter = 0, and clears four arrays of n floats each
+// (16-byte aligned).
+hipError_t launch_start(float* const p[4], int64_t n, Ctl* ctl, float beta1, float beta2, unsigned* tickets,
+                        hipStream_t s);
+// Means of two images of n values each into *dst (device floats).  part: 2 *
+// kMeanBlocks doubles; tickets: kTicketWords words, zero, and left at zero.
+struct Means {
+  const float* x[2];
+  float* dst[2];
+  int64_t n;
+  double* part;
+  unsigned* tickets;
+};
+hipError_t launch_means(const Means& A, hipStream_t s);
+// launch_means and launch_warp (slope NULL) or launch_warp_slope in one launch.
+hipError_t launch_means_warp(const Means& A, const float* img, const float* d, float* out, float* slope, int n0, int n1,
+                             int n2, hipStream_t s);
 hipError_t launch_sum_partials(const double* partials, int n, double* dst, hipStream_t s);
 // (float)(sum of n partials / denom) into *dst (device float).
 hipError_t launch_partials_ratio(const double* partials, int n, double denom, float* dst, hipStream_t s);
@@ -193,6 +209,10 @@ hipError_t launch_partials_ratio(const double* partials, int n, double denom, fl
 // of each thread (a few per thread at 160x192x224) are not latency-bound
 // (256 workgroups took 33 us for 6.9 M values, 2048 take 9 us).
 constexpr int kMeanBlocks = 2048;
+// Counters of the means' workgroups, each in a 128-byte line: per image one and
+// kTicketSlots below it.
+constexpr int kTicketSlots = 32, kTicketStride = 32, kTicketCount = 2 * (kTicketSlots + 1);
+constexpr size_t kTicketWords = (size_t)kTicketCount * kTicketStride;
 
 bool grad_tile_supported(int ty, int tx);
 bool gauss_tile_supported(int ty, int tx);

@@ -957,11 +957,8 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
 
   // psi = id, m = v = 0, t = 0
   const int64_t n0 = H->levels[0].n;
-  FA_HIP(fa::launch_fill(H->e, 0.0f, 3 * n0, H->stream));
-  FA_HIP(fa::launch_fill(H->m, 0.0f, 3 * n0, H->stream));
-  FA_HIP(fa::launch_fill(H->v, 0.0f, 3 * n0, H->stream));
-  FA_HIP(fa::launch_fill(H->a, 0.0f, 3 * n0, H->stream));
-  FA_HIP(fa::launch_ctl_init(H->ctl, H->p.adam_beta1, H->p.adam_beta2, 0, 0, H->stream));
+  float* const zeroed[4] = {H->e, H->m, H->v, H->a};
+  FA_HIP(fa::launch_start(zeroed, 3 * n0, H->ctl, H->p.adam_beta1, H->p.adam_beta2, nullptr, H->stream));
   H->cur_level = 0;
   H->cur_iter = 0;
   H->t_done = 0;

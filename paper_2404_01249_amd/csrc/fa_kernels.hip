@@ -2298,13 +2298,12 @@ __global__ void __launch_bounds__(256) k_resample(const Resample A, unsigned fie
 
 // J = I_m(x + d) and, with SLOPE, its position derivative ([3][N]): one
 // trilinear sample per voxel, zero outside the grid.
-template <bool G3, bool SLOPE>
-__global__ void k_warp(const float* __restrict__ img, const float* __restrict__ d, float* __restrict__ out,
-                       float* __restrict__ slope, int n0, int n1, int n2) {
+template <bool SLOPE>
+__device__ __forceinline__ void warp_voxel(const float* __restrict__ img, const float* __restrict__ d,
+                                           float* __restrict__ out, float* __restrict__ slope, int n0, int n1, int n2,
+                                           int z, int y, int x) {
   const int N = n0 * n1 * n2;
-  int z, y, x, i;
-  if (!grid_voxel<G3>(n0, n1, n2, z, y, x, i)) return;
-  const unsigned off = (unsigned)i * 4u;
+  const unsigned off = (unsigned)((z * n1 + y) * n2 + x) * 4u;
   const Cell8 c = cell8_at(n0, n1, n2, z, y, x, load_at(d, off), load_at(d + N, off), load_at(d + 2 * N, off));
   Gather g;
   gather_issue(img, c, g);
@@ -2317,6 +2316,14 @@ __global__ void k_warp(const float* __restrict__ img, const float* __restrict__ 
   } else {
     store_at(out, off, gather_value(g));
   }
+}
+
+template <bool G3, bool SLOPE>
+__global__ void k_warp(const float* __restrict__ img, const float* __restrict__ d, float* __restrict__ out,
+                       float* __restrict__ slope, int n0, int n1, int n2) {
+  int z, y, x, i;
+  if (!grid_voxel<G3>(n0, n1, n2, z, y, x, i)) return;
+  warp_voxel<SLOPE>(img, d, out, slope, n0, n1, n2, z, y, x);
 }
 
 // out = u + d(x + u): the displacement of phi o (id + u) for phi = id + d,
@@ -2346,28 +2353,121 @@ __global__ void k_soa_to_aos(const float* __restrict__ in, float* __restrict__ o
   out[3 * i + 2] = in[2 * n + i];
 }
 
-__global__ void k_ctl_init(Ctl* ctl, float beta1, float beta2, int t_done, int iter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    const int t = t_done + 1;
-    ctl->t = t;
-    if (iter >= 0) ctl->iter = iter;
-    ctl->beta1 = beta1;
-    ctl->beta2 = beta2;
-    ctl->bp1 = pow((double)beta1, (double)t);
-    ctl->bp2 = pow((double)beta2, (double)t);
-    ctl->bc1 = (float)(1.0 - ctl->bp1);
-    ctl->bc2 = (float)(1.0 - ctl->bp2);
-    for (int j = 0; j < kMSlots; ++j) ctl->mslot[j * kMStride] = 0u;
+__device__ __forceinline__ void ctl_init(Ctl* ctl, float beta1, float beta2, int t_done, int iter) {
+  const int t = t_done + 1;
+  ctl->t = t;
+  if (iter >= 0) ctl->iter = iter;
+  ctl->beta1 = beta1;
+  ctl->beta2 = beta2;
+  ctl->bp1 = pow((double)beta1, (double)t);
+  ctl->bp2 = pow((double)beta2, (double)t);
+  ctl->bc1 = (float)(1.0 - ctl->bp1);
+  ctl->bc2 = (float)(1.0 - ctl->bp2);
+  for (int j = 0; j < kMSlots; ++j) ctl->mslot[j * kMStride] = 0u;
+}
+
+__global__ void k_ctl_init(Ctl* ctl, float beta1, float beta2, int t_done, int iter, unsigned* tickets) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) ctl_init(ctl, beta1, beta2, t_done, iter);
+  if (tickets && threadIdx.x < kTicketCount) tickets[threadIdx.x * kTicketStride] = 0u;
+}
+
+// The start of a schedule in one launch: four arrays of n floats cleared (y
+// picks one, four values per thread), the control block and the means' tickets.
+struct Clear4 {
+  float* p[4];
+};
+__global__ void __launch_bounds__(256) k_start(const Clear4 A, int64_t n, Ctl* ctl, float beta1, float beta2,
+                                               unsigned* tickets) {
+  const unsigned a = blockIdx.y;
+  float* p = a == 0 ? A.p[0] : (a == 1 ? A.p[1] : (a == 2 ? A.p[2] : A.p[3]));
+  const int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+  if (i + 4 <= n) {
+    *reinterpret_cast<float4*>(p + i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  } else {
+    for (int64_t j = i; j < n; ++j) p[j] = 0.0f;
+  }
+  if (a == 0 && blockIdx.x == 0) {
+    if (threadIdx.x == 255) ctl_init(ctl, beta1, beta2, 0, 0);
+    if (tickets && threadIdx.x < kTicketCount) tickets[threadIdx.x * kTicketStride] = 0u;
   }
 }
 
-__global__ void k_sum_partial(const float* __restrict__ x, int64_t n, double* __restrict__ part) {
+// The means of two images in one launch: the sums of each image's workgroups go
+// to memory, and the last workgroup to finish adds them up, in the order of the
+// workgroups.  A counter takes about 10 ns per workgroup, so an image's 2048
+// count on kTicketSlots counters first and the last of each on one.  Every
+// counter is left at zero.  Bound by launches at the usual sizes: an LNCC loss
+// and gradient takes 97 us at 24^3 and at 128^3 with k_means_warp, 122 and 119
+// with a sum and a division per image and the warp in launches of their own.
+__device__ __forceinline__ void mean_block(const Means& A, int img, int blk, int np) {
   __shared__ double red[4];
+  __shared__ int last;
+  const float* __restrict__ x = img ? A.x[1] : A.x[0];
+  double* part = A.part + (size_t)img * kMeanBlocks;
   double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    s += (double)x[i];
+  for (int64_t i = (int64_t)blk * 256 + threadIdx.x; i < A.n; i += (int64_t)kMeanBlocks * 256) s += (double)x[i];
   s = block_sum<256>(s, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&part[blk], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the sum has to have reached memory before this workgroup counts
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    unsigned* slots = A.tickets + (size_t)img * (kTicketSlots + 1) * kTicketStride;
+    unsigned* slot = slots + (1 + blk % kTicketSlots) * kTicketStride;
+    const unsigned in_slot = (unsigned)(np - blk % kTicketSlots + kTicketSlots - 1) / kTicketSlots;
+    last = 0;
+    if (__hip_atomic_fetch_add(slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == in_slot) {
+      __hip_atomic_store(slot, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned used = (unsigned)min(np, kTicketSlots);
+      if (__hip_atomic_fetch_add(slots, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == used) {
+        __hip_atomic_store(slots, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = 1;
+      }
+    }
+  }
+  __syncthreads();
+  if (!last) return;
+  asm volatile("" ::: "memory");
+  double t = 0.0;
+  for (int i = threadIdx.x; i < np; i += 256)
+    t += __hip_atomic_load(&part[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  t = block_sum<256>(t, red);
+  if (threadIdx.x == 0) *(img ? A.dst[1] : A.dst[0]) = (float)(t / (double)A.n);
+}
+
+// Workgroups with values, of kMeanBlocks (the sums of the others would be zero).
+__host__ __device__ inline int mean_blocks(int64_t n) {
+  const int64_t b = (n + 255) / 256;
+  return b < kMeanBlocks ? (int)b : kMeanBlocks;
+}
+
+__global__ void __launch_bounds__(256) k_means(const Means A, int np) {
+  mean_block(A, blockIdx.x >= (unsigned)np, blockIdx.x % np, np);
+}
+
+// The same together with J (and its slope), which needs neither: workgroups
+// after the means' take `bs` (64, 128 or 256) voxels of 256 / bs rows each.
+template <bool SLOPE>
+__global__ void __launch_bounds__(256) k_means_warp(const Means A, int np, const float* __restrict__ img,
+                                                    const float* __restrict__ d, float* __restrict__ out,
+                                                    float* __restrict__ slope, int n0, int n1, int n2, int bs) {
+  if (blockIdx.x < 2u * np) {
+    mean_block(A, blockIdx.x >= (unsigned)np, blockIdx.x % np, np);
+    return;
+  }
+  const unsigned b = blockIdx.x - 2u * np;
+  unsigned row, x;
+  if (bs) {
+    const unsigned nb = (unsigned)(n2 + bs - 1) / bs, rows = 256u / bs;
+    const unsigned rb = b / nb;
+    row = rb * rows + threadIdx.x / (unsigned)bs;
+    x = (b - rb * nb) * bs + threadIdx.x % (unsigned)bs;
+  } else {   // rows too short: flat
+    const unsigned t = b * 256u + threadIdx.x;
+    row = t / (unsigned)n2;
+    x = t - row * (unsigned)n2;
+  }
+  if (row >= (unsigned)n0 * n1 || x >= (unsigned)n2) return;
+  warp_voxel<SLOPE>(img, d, out, slope, n0, n1, n2, (int)(row / n1), (int)(row % n1), (int)x);
 }
 
 __global__ void k_mean_final(const double* __restrict__ part, int np, double n, float* __restrict__ dst) {
@@ -2941,14 +3041,35 @@ hipError_t launch_soa_to_aos(const float* in, float* out, int64_t n, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_ctl_init(Ctl* ctl, float beta1, float beta2, int t_done, int iter, hipStream_t s) {
-  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, s, ctl, beta1, beta2, t_done, iter);
+hipError_t launch_ctl_init(Ctl* ctl, float beta1, float beta2, int t_done, int iter, unsigned* tickets,
+                           hipStream_t s) {
+  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(128), 0, s, ctl, beta1, beta2, t_done, iter, tickets);
   return hipGetLastError();
 }
 
-hipError_t launch_mean(const float* x, int64_t n, double* scratch, float* dst, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_partial, dim3(kMeanBlocks), dim3(256), 0, s, x, n, scratch);
-  hipLaunchKernelGGL(k_mean_final, dim3(1), dim3(256), 0, s, scratch, kMeanBlocks, (double)n, dst);
+hipError_t launch_start(float* const p[4], int64_t n, Ctl* ctl, float beta1, float beta2, unsigned* tickets,
+                        hipStream_t s) {
+  Clear4 A{{p[0], p[1], p[2], p[3]}};
+  hipLaunchKernelGGL(k_start, dim3(grid1((n + 3) / 4, 256), 4), dim3(256), 0, s, A, n, ctl, beta1, beta2, tickets);
+  return hipGetLastError();
+}
+
+hipError_t launch_means(const Means& A, hipStream_t s) {
+  const int np = mean_blocks(A.n);
+  hipLaunchKernelGGL(k_means, dim3(2 * np), dim3(256), 0, s, A, np);
+  return hipGetLastError();
+}
+
+hipError_t launch_means_warp(const Means& A, const float* img, const float* d, float* out, float* slope, int n0, int n1,
+                             int n2, hipStream_t s) {
+  const int np = mean_blocks(A.n), bs = row_block(n2);
+  const int64_t rows = (int64_t)n0 * n1;
+  const int64_t blocks = bs ? (rows + 256 / bs - 1) / (256 / bs) * ((n2 + bs - 1) / bs) : (rows * n2 + 255) / 256;
+  const dim3 g((unsigned)(2 * np + blocks));
+  if (slope)
+    hipLaunchKernelGGL(k_means_warp<true>, g, dim3(256), 0, s, A, np, img, d, out, slope, n0, n1, n2, bs);
+  else
+    hipLaunchKernelGGL(k_means_warp<false>, g, dim3(256), 0, s, A, np, img, d, out, slope, n0, n1, n2, bs);
   return hipGetLastError();
 }
 

@@ -29,7 +29,8 @@ struct fa_lncc_s {
   fa::Tiling tg{};
   fa::Ctl* ctl = nullptr;
   double* partials = nullptr;   // one per workgroup of the gradient launch
-  double* mean_partials = nullptr;  // kMeanBlocks doubles for the intensity means
+  double* mean_partials = nullptr;  // 2 * kMeanBlocks doubles and the tickets of launch_means_warp
+  unsigned* tickets = nullptr;
   float* warped = nullptr;      // J = I_m(x + d), made by each call
 };
 
@@ -41,6 +42,7 @@ void release(fa_lncc h) {
   if (h->ctl) (void)hipFree(h->ctl);
   if (h->partials) (void)hipFree(h->partials);
   if (h->mean_partials) (void)hipFree(h->mean_partials);
+  if (h->tickets) (void)hipFree(h->tickets);
   if (h->warped) (void)hipFree(h->warped);
   delete h;
 }
@@ -70,17 +72,6 @@ fa_status scratch_address(void** out) {
   return FA_OK;
 }
 
-// J, and with a gradient the slope of the moving image in the caller's gradient
-// buffer: the gradient kernel reads it there only at the voxel it writes.
-fa_status warp_for(const float* moving, const float* d, float* warped, float* grad_dev, const fa_shape& s,
-                   hipStream_t st) {
-  if (grad_dev)
-    FA_HIP(fa::launch_warp_slope(moving, d, warped, grad_dev, s.n0, s.n1, s.n2, st));
-  else
-    FA_HIP(fa::launch_warp(moving, d, warped, s.n0, s.n1, s.n2, st));
-  return FA_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -103,13 +94,14 @@ fa_status fa_lncc_create(fa_shape shape, int window, float cc_eps, void* hip_str
   const int nb = h->tg.blocks();
   if (hipMalloc((void**)&h->ctl, sizeof(fa::Ctl)) != hipSuccess ||
       hipMalloc((void**)&h->partials, (size_t)nb * sizeof(double)) != hipSuccess ||
-      hipMalloc((void**)&h->mean_partials, (size_t)fa::kMeanBlocks * sizeof(double)) != hipSuccess ||
+      hipMalloc((void**)&h->mean_partials, (size_t)2 * fa::kMeanBlocks * sizeof(double)) != hipSuccess ||
+      hipMalloc((void**)&h->tickets, fa::kTicketWords * sizeof(unsigned)) != hipSuccess ||
       hipMalloc((void**)&h->warped, (size_t)h->n * sizeof(float)) != hipSuccess) {
     (void)hipGetLastError();
     release(h);
     return fail(FA_ENOMEM, "device allocation failed");
   }
-  const hipError_t e = fa::launch_ctl_init(h->ctl, 0.9f, 0.999f, 0, 0, h->stream);
+  const hipError_t e = fa::launch_ctl_init(h->ctl, 0.9f, 0.999f, 0, 0, h->tickets, h->stream);
   if (e != hipSuccess) {
     release(h);
     return fail(FA_EHIP, std::string("launch_ctl_init: ") + hipGetErrorString(e));
@@ -125,9 +117,10 @@ fa_status fa_lncc_eval(fa_lncc h, const float* fixed, const float* moving, const
   if (!loss_dev && !grad_dev) return fail(FA_EINVAL, "loss_dev and grad_dev are both NULL");
   // global intensity means: LNCC is invariant to a global shift of either
   // image, and removing it keeps the fp32 window variances well conditioned
-  FA_HIP(fa::launch_mean(fixed, h->n, h->mean_partials, &h->ctl->shift_i, h->stream));
-  FA_HIP(fa::launch_mean(moving, h->n, h->mean_partials, &h->ctl->shift_j, h->stream));
-  FA_TRY(warp_for(moving, d, h->warped, grad_dev, h->shape, h->stream));
+  // J, and with a gradient the slope of the moving image in the caller's gradient
+  // buffer: the gradient kernel reads it there only at the voxel it writes.
+  FA_HIP(fa::launch_means_warp({{fixed, moving}, {&h->ctl->shift_i, &h->ctl->shift_j}, h->n, h->mean_partials, h->tickets},
+                               moving, d, h->warped, grad_dev, h->shape.n0, h->shape.n1, h->shape.n2, h->stream));
   fa::GradArgs ga{};
   ga.fixed = fixed;
   ga.warped = h->warped;
@@ -165,8 +158,9 @@ fa_status fa_lncc_eval_noalloc(fa_shape shape, int window, float cc_eps, const f
   const int64_t n = fa::voxels(shape);
   const fa::Tiling tg = fa::choose_tiling(shape, fa::KIND_GRAD, fa::Tuning(), fa::grad_cube_supported(window));
   const int nb = tg.blocks();
-  // layout of the scratch array: control block | loss partials | mean partials | warped image (the size
-  // accepted is that of the moving image with a border of two voxels, as documented)
+  // layout of the scratch array: control block | loss partials | warped image | mean partials | tickets.  The
+  // size accepted is that of an earlier layout, as documented: one image's mean partials, and the moving image
+  // with a border of two voxels, which leaves more room than the second image's partials and the tickets take.
   const size_t off_part = align256(sizeof(fa::Ctl));
   const size_t off_mean = off_part + align256((size_t)nb * sizeof(double));
   const size_t off_warp = off_mean + align256((size_t)fa::kMeanBlocks * sizeof(double));
@@ -180,16 +174,18 @@ fa_status fa_lncc_eval_noalloc(fa_shape shape, int window, float cc_eps, const f
   unsigned char* b = static_cast<unsigned char*>(base);
   fa::Ctl* ctl = reinterpret_cast<fa::Ctl*>(b);
   double* partials = reinterpret_cast<double*>(b + off_part);
-  double* mean_partials = reinterpret_cast<double*>(b + off_mean);
-  float* warped = reinterpret_cast<float*>(b + off_warp);
+  float* warped = reinterpret_cast<float*>(b + off_mean);
+  const size_t off_means = off_mean + align256((size_t)n * sizeof(float));
+  double* mean_partials = reinterpret_cast<double*>(b + off_means);
+  unsigned* tickets = reinterpret_cast<unsigned*>(b + off_means + 2 * fa::kMeanBlocks * sizeof(double));
+  static_assert(FA_LNCC_NOALLOC_SCRATCH_BYTES >= (1 << 20), "small volumes need the room for the partials");
   const hipStream_t st = (hipStream_t)hip_stream;
   // every scratch word the kernels read is written earlier in this call, on
   // this stream: the control block by its init kernel, the shifts by the
   // means, the warped image by the warp kernel, each partial by its workgroup
-  FA_HIP(fa::launch_ctl_init(ctl, 0.9f, 0.999f, 0, 0, st));
-  FA_HIP(fa::launch_mean(fixed, n, mean_partials, &ctl->shift_i, st));
-  FA_HIP(fa::launch_mean(moving, n, mean_partials, &ctl->shift_j, st));
-  FA_TRY(warp_for(moving, d, warped, grad_dev, shape, st));
+  FA_HIP(fa::launch_ctl_init(ctl, 0.9f, 0.999f, 0, 0, tickets, st));
+  FA_HIP(fa::launch_means_warp({{fixed, moving}, {&ctl->shift_i, &ctl->shift_j}, n, mean_partials, tickets}, moving, d,
+                               warped, grad_dev, shape.n0, shape.n1, shape.n2, st));
   fa::GradArgs ga{};
   ga.fixed = fixed;
   ga.warped = warped;

@@ -137,7 +137,8 @@ struct fa_pair_s {
   int loss_cap = 0;
   double* partials = nullptr;
   int partials_cap = 0;
-  double* scratch = nullptr;  // kMeanBlocks + 1 doubles
+  double* scratch = nullptr;  // 2 * kMeanBlocks + 1 doubles
+  unsigned* tickets = nullptr;  // of launch_means
   float* wts = nullptr;       // device tap tables
   std::vector<float> wts_host;
   std::vector<float> wts_dev;  // the table last copied to wts (empty: none)
@@ -194,6 +195,7 @@ void free_all(fa_pair P) {
   if (P->ctl) (void)hipFree(P->ctl);
   if (P->partials) (void)hipFree(P->partials);
   if (P->scratch) (void)hipFree(P->scratch);
+  if (P->tickets) (void)hipFree(P->tickets);
 }
 
 template <typename T>
@@ -945,7 +947,8 @@ fa_status fa_pair_create(const float* fixed_dev, const float* moving_dev, fa_sha
   if ((st = dalloc(&P->in_fixed, P->n, "fixed")) != FA_OK ||
       (st = dalloc(&P->in_moving, P->n, "moving")) != FA_OK ||
       (st = dalloc(&P->ctl, 1, "control block")) != FA_OK ||
-      (st = dalloc(&P->scratch, fa::kMeanBlocks + 1, "scratch")) != FA_OK) {
+      (st = dalloc(&P->scratch, 2 * fa::kMeanBlocks + 1, "scratch")) != FA_OK ||
+      (st = dalloc(&P->tickets, fa::kTicketWords, "scratch")) != FA_OK) {
     free_all(P);
     delete P;
     return st;
@@ -1138,13 +1141,10 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
 
   // State: phi = id, m = v = 0, t = 0.
   const int64_t n0 = P->levels[0].n;
-  FA_HIP(fa::launch_fill(P->d, 0.0f, 3 * n0, P->stream));
-  FA_HIP(fa::launch_fill(P->m, 0.0f, 3 * n0, P->stream));
-  FA_HIP(fa::launch_fill(P->v, 0.0f, 3 * n0, P->stream));
-  FA_HIP(fa::launch_fill(P->a, 0.0f, 3 * n0, P->stream));
-  FA_HIP(fa::launch_ctl_init(P->ctl, P->p.adam_beta1, P->p.adam_beta2, 0, 0, P->stream));
-  FA_HIP(fa::launch_mean(P->in_fixed, P->n, P->scratch, &P->ctl->shift_i, P->stream));
-  FA_HIP(fa::launch_mean(P->in_moving, P->n, P->scratch, &P->ctl->shift_j, P->stream));
+  float* const zeroed[4] = {P->d, P->m, P->v, P->a};
+  FA_HIP(fa::launch_start(zeroed, 3 * n0, P->ctl, P->p.adam_beta1, P->p.adam_beta2, P->tickets, P->stream));
+  FA_HIP(fa::launch_means({{P->in_fixed, P->in_moving}, {&P->ctl->shift_i, &P->ctl->shift_j}, P->n, P->scratch, P->tickets},
+                          P->stream));
   P->cur_level = 0;
   P->cur_iter = 0;
   P->t_done = 0;
@@ -1313,7 +1313,7 @@ fa_status fa_pair_set_state(fa_pair P, const float* d, const float* m, const flo
   if (d) FA_HIP(hipMemcpyAsync(P->d, d, bytes, hipMemcpyDeviceToDevice, P->stream));
   if (m) FA_HIP(hipMemcpyAsync(P->m, m, bytes, hipMemcpyDeviceToDevice, P->stream));
   if (v) FA_HIP(hipMemcpyAsync(P->v, v, bytes, hipMemcpyDeviceToDevice, P->stream));
-  FA_HIP(fa::launch_ctl_init(P->ctl, P->p.adam_beta1, P->p.adam_beta2, t_done, -1, P->stream));
+  FA_HIP(fa::launch_ctl_init(P->ctl, P->p.adam_beta1, P->p.adam_beta2, t_done, -1, nullptr, P->stream));
   P->t_done = t_done;
   if (d) P->warped_ok = false;
   return FA_OK;
@@ -1353,9 +1353,9 @@ fa_status fa_pair_eval_gradient(fa_pair P, float* g_dev, float* loss_host) {
   FA_TRY(ensure_warped(P, L));
   FA_HIP(fa::launch_grad(ga, P->p.cc_window, L.tg, P->stream));
   if (loss_host) {
-    FA_HIP(fa::launch_sum_partials(P->partials, L.tg.blocks(), P->scratch + fa::kMeanBlocks, P->stream));
+    FA_HIP(fa::launch_sum_partials(P->partials, L.tg.blocks(), P->scratch + 2 * fa::kMeanBlocks, P->stream));
     double s = 0.0;
-    FA_HIP(hipMemcpyAsync(&s, P->scratch + fa::kMeanBlocks, sizeof(double), hipMemcpyDeviceToHost, P->stream));
+    FA_HIP(hipMemcpyAsync(&s, P->scratch + 2 * fa::kMeanBlocks, sizeof(double), hipMemcpyDeviceToHost, P->stream));
     FA_HIP(hipStreamSynchronize(P->stream));
     *loss_host = (float)(-s / (double)L.n);
   }
@@ -1531,7 +1531,7 @@ fa_status fa_pair_autotune(fa_pair P, int trials) {
     return FA_OK;
   };
   if (st == FA_OK) {
-    const hipError_t he = fa::launch_ctl_init(sctl, P->p.adam_beta1, P->p.adam_beta2, 0, 0, P->stream);
+    const hipError_t he = fa::launch_ctl_init(sctl, P->p.adam_beta1, P->p.adam_beta2, 0, 0, nullptr, P->stream);
     if (he != hipSuccess) st = fail(FA_EHIP, hipGetErrorString(he));
   }
   for (size_t li = 0; li < P->levels.size() && st == FA_OK; ++li) {
