@@ -24,6 +24,40 @@ __device__ __forceinline__ float adam_direction(float mm, float vv, float ibc1, 
   return (mm * ibc1) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(vv * ibc2) + eps);
 }
 
+// Workgroups are dispatched round-robin over the 8 XCDs, each with its own
+// L2.  Renumber them so that every XCD works through a contiguous range of
+// tiles: neighbouring tiles then share their halo reads in one L2.
+__device__ __forceinline__ int xcd_tile(int b, int G) {
+  constexpr int X = 8;
+  const int q = G / X, r = G % X;
+  const int x = b % X, k = b / X;
+  return x * q + min(x, r) + k;
+}
+
+// Voxel-wise launches of 256 threads: workgroup b takes bs (64, 128 or 256)
+// neighbours of 256 / bs rows each, so that rows are found without a division
+// per voxel and little of a workgroup hangs over; bs = 0 (rows too short): flat.
+inline int row_span(int n2) { return n2 >= 192 ? 256 : (n2 >= 96 ? 128 : (n2 >= 32 ? 64 : 0)); }
+inline unsigned row_blocks(int64_t rows, int n2, int bs) {
+  return (unsigned)(bs ? (rows + 256 / bs - 1) / (256 / bs) * ((n2 + bs - 1) / bs) : (rows * n2 + 255) / 256);
+}
+__device__ __forceinline__ bool row_voxel(unsigned b, int n0, int n1, int n2, int bs, int& z, int& y, int& x) {
+  unsigned row, col;
+  if (bs) {
+    const unsigned nb = (unsigned)(n2 + bs - 1) / bs, rb = b / nb;
+    row = bs == 256 ? rb : rb * (256u / bs) + threadIdx.x / (unsigned)bs;   // uniform where bs is 256
+    col = (b - rb * nb) * bs + (bs == 256 ? threadIdx.x : threadIdx.x % (unsigned)bs);
+  } else {
+    const unsigned t = b * 256u + threadIdx.x;
+    row = t / (unsigned)n2;
+    col = t - row * (unsigned)n2;
+  }
+  z = (int)(row / n1);
+  y = (int)(row - (unsigned)z * n1);
+  x = (int)col;
+  return z < n0 && x < n2;
+}
+
 // Per-pair control block in device memory.  Kernels of one iteration read
 // and update it so that a whole iteration can be replayed (for example from a
 // captured graph) without host involvement.

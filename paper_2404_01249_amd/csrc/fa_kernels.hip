@@ -163,16 +163,6 @@ __device__ __forceinline__ void tap_pair_x(const float* in, float* out, const fl
   reinterpret_cast<float2*>(out)[0] = make_float2(a, b);
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs, each with its own
-// L2.  Renumber them so that every XCD works through a contiguous range of
-// tiles: neighbouring tiles then share their halo reads in one L2.
-__device__ __forceinline__ int xcd_tile(int b, int G) {
-  constexpr int X = 8;
-  const int q = G / X, r = G % X;
-  const int x = b % X, k = b / X;
-  return x * q + min(x, r) + k;
-}
-
 template <int NT>
 __device__ double block_sum(double v, double* red) {
 #pragma unroll
@@ -316,6 +306,67 @@ struct Gather {
   unsigned mask;
   float t0, t1, t2;
 };
+
+// The same corners as four pairs of row neighbours: half the addresses of
+// gather_issue for the same bytes, for kernels bound by them.  (Composition of
+// two fields of 6.9 M voxels: 87 us against 95.)  A pair is clamped
+// onto the grid, so that both its loads are in bounds (n2 >= 2).
+struct CellPairs {
+  unsigned off[4];
+  bool up, down;   // clamped: both corners' values are the pair's second (first)
+  unsigned mask;
+  float t0, t1, t2;
+};
+
+__device__ __forceinline__ CellPairs pairs_at(int n0, int n1, int n2, int z, int y, int x, float d0, float d1,
+                                              float d2) {
+  CellPairs c;
+  int i0, i1, i2;
+  bool a0, b0, a1, b1, a2, b2;
+  cell_at(z, d0, n0, i0, c.t0, a0, b0);
+  cell_at(y, d1, n1, i1, c.t1, a1, b1);
+  cell_at(x, d2, n2, i2, c.t2, a2, b2);
+  const int x0 = min(max(i2, 0), n2 - 2);
+  c.up = i2 > x0;
+  c.down = i2 < x0;
+  const int za = min(max(i0, 0), n0 - 1), zb = min(max(i0 + 1, 0), n0 - 1);
+  const int ya = min(max(i1, 0), n1 - 1), yb = min(max(i1 + 1, 0), n1 - 1);
+  c.off[0] = (unsigned)((za * n1 + ya) * n2 + x0) * 4u;
+  c.off[1] = (unsigned)((za * n1 + yb) * n2 + x0) * 4u;
+  c.off[2] = (unsigned)((zb * n1 + ya) * n2 + x0) * 4u;
+  c.off[3] = (unsigned)((zb * n1 + yb) * n2 + x0) * 4u;
+  const unsigned mz = (a0 ? 0x0Fu : 0u) | (b0 ? 0xF0u : 0u);
+  const unsigned my = (a1 ? 0x33u : 0u) | (b1 ? 0xCCu : 0u);
+  const unsigned mx = (a2 ? 0x55u : 0u) | (b2 ? 0xAAu : 0u);
+  c.mask = mz & my & mx;
+  return c;
+}
+
+typedef float float2_any __attribute__((ext_vector_type(2), aligned(4)));
+
+struct PairGather {
+  float2_any p[4];
+};
+
+__device__ __forceinline__ void gather_issue(const float* __restrict__ f, const CellPairs& c, PairGather& g) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    g.p[k] = *reinterpret_cast<const float2_any*>(reinterpret_cast<const char*>(f) + c.off[k]);
+}
+
+__device__ __forceinline__ Gather corners_of(const PairGather& p, const CellPairs& c) {
+  Gather g;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    g.c[2 * k] = c.up ? p.p[k].y : p.p[k].x;
+    g.c[2 * k + 1] = c.down ? p.p[k].x : p.p[k].y;
+  }
+  g.mask = c.mask;
+  g.t0 = c.t0;
+  g.t1 = c.t1;
+  g.t2 = c.t2;
+  return g;
+}
 
 __device__ __forceinline__ void gather_issue(const float* __restrict__ f, const Cell8& c, Gather& g) {
 #pragma unroll
@@ -2304,9 +2355,10 @@ __device__ __forceinline__ void warp_voxel(const float* __restrict__ img, const 
                                            int z, int y, int x) {
   const int N = n0 * n1 * n2;
   const unsigned off = (unsigned)((z * n1 + y) * n2 + x) * 4u;
-  const Cell8 c = cell8_at(n0, n1, n2, z, y, x, load_at(d, off), load_at(d + N, off), load_at(d + 2 * N, off));
-  Gather g;
-  gather_issue(img, c, g);
+  const CellPairs c = pairs_at(n0, n1, n2, z, y, x, load_at(d, off), load_at(d + N, off), load_at(d + 2 * N, off));
+  PairGather p;
+  gather_issue(img, c, p);
+  const Gather g = corners_of(p, c);
   if constexpr (SLOPE) {
     float g0, g1, g2;
     store_at(out, off, gather_value_grad(g, g0, g1, g2));
@@ -2318,31 +2370,32 @@ __device__ __forceinline__ void warp_voxel(const float* __restrict__ img, const 
   }
 }
 
-template <bool G3, bool SLOPE>
-__global__ void k_warp(const float* __restrict__ img, const float* __restrict__ d, float* __restrict__ out,
-                       float* __restrict__ slope, int n0, int n1, int n2) {
-  int z, y, x, i;
-  if (!grid_voxel<G3>(n0, n1, n2, z, y, x, i)) return;
-  warp_voxel<SLOPE>(img, d, out, slope, n0, n1, n2, z, y, x);
+template <bool SLOPE>
+__global__ void __launch_bounds__(256) k_warp(const float* __restrict__ img, const float* __restrict__ d,
+                                              float* __restrict__ out, float* __restrict__ slope, int n0, int n1,
+                                              int n2, int bs) {
+  int z, y, x;
+  if (row_voxel(blockIdx.x, n0, n1, n2, bs, z, y, x))
+    warp_voxel<SLOPE>(img, d, out, slope, n0, n1, n2, z, y, x);
 }
 
 // out = u + d(x + u): the displacement of phi o (id + u) for phi = id + d,
 // with d sampled trilinearly per component (zero outside the grid).
-__global__ void k_compose_fields(const float* __restrict__ u, const float* __restrict__ d,
-                                 float* __restrict__ out, int n0, int n1, int n2) {
+__global__ void __launch_bounds__(256) k_compose_fields(const float* __restrict__ u, const float* __restrict__ d,
+                                                        float* __restrict__ out, int n0, int n1, int n2, int bs) {
   const int N = n0 * n1 * n2;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  const int x = i % n2, y = (i / n2) % n1, z = i / (n1 * n2);
+  int z, y, x;
+  if (!row_voxel(blockIdx.x, n0, n1, n2, bs, z, y, x)) return;
+  const int i = (z * n1 + y) * n2 + x;
   const float u0 = u[i], u1 = u[N + i], u2 = u[2 * N + i];
-  const Cell8 c = cell8_at(n0, n1, n2, z, y, x, u0, u1, u2);
-  Gather g0, g1, g2;
-  gather_issue(d, c, g0);
-  gather_issue(d + N, c, g1);
-  gather_issue(d + 2 * N, c, g2);
-  out[i] = u0 + gather_value(g0);
-  out[N + i] = u1 + gather_value(g1);
-  out[2 * N + i] = u2 + gather_value(g2);
+  const CellPairs c = pairs_at(n0, n1, n2, z, y, x, u0, u1, u2);
+  PairGather p0, p1, p2;
+  gather_issue(d, c, p0);
+  gather_issue(d + N, c, p1);
+  gather_issue(d + 2 * N, c, p2);
+  out[i] = u0 + gather_value(corners_of(p0, c));
+  out[N + i] = u1 + gather_value(corners_of(p1, c));
+  out[2 * N + i] = u2 + gather_value(corners_of(p2, c));
 }
 
 __global__ void k_soa_to_aos(const float* __restrict__ in, float* __restrict__ out, int64_t n) {
@@ -2444,8 +2497,8 @@ __global__ void __launch_bounds__(256) k_means(const Means A, int np) {
   mean_block(A, blockIdx.x >= (unsigned)np, blockIdx.x % np, np);
 }
 
-// The same together with J (and its slope), which needs neither: workgroups
-// after the means' take `bs` (64, 128 or 256) voxels of 256 / bs rows each.
+// The same together with J (and its slope), which needs neither, in the
+// workgroups after the means'.
 template <bool SLOPE>
 __global__ void __launch_bounds__(256) k_means_warp(const Means A, int np, const float* __restrict__ img,
                                                     const float* __restrict__ d, float* __restrict__ out,
@@ -2454,20 +2507,9 @@ __global__ void __launch_bounds__(256) k_means_warp(const Means A, int np, const
     mean_block(A, blockIdx.x >= (unsigned)np, blockIdx.x % np, np);
     return;
   }
-  const unsigned b = blockIdx.x - 2u * np;
-  unsigned row, x;
-  if (bs) {
-    const unsigned nb = (unsigned)(n2 + bs - 1) / bs, rows = 256u / bs;
-    const unsigned rb = b / nb;
-    row = rb * rows + threadIdx.x / (unsigned)bs;
-    x = (b - rb * nb) * bs + threadIdx.x % (unsigned)bs;
-  } else {   // rows too short: flat
-    const unsigned t = b * 256u + threadIdx.x;
-    row = t / (unsigned)n2;
-    x = t - row * (unsigned)n2;
-  }
-  if (row >= (unsigned)n0 * n1 || x >= (unsigned)n2) return;
-  warp_voxel<SLOPE>(img, d, out, slope, n0, n1, n2, (int)(row / n1), (int)(row % n1), (int)x);
+  int z, y, x;
+  if (row_voxel(blockIdx.x - 2 * np, n0, n1, n2, bs, z, y, x))
+    warp_voxel<SLOPE>(img, d, out, slope, n0, n1, n2, z, y, x);
 }
 
 __global__ void k_mean_final(const double* __restrict__ part, int np, double n, float* __restrict__ dst) {
@@ -2891,10 +2933,6 @@ hipError_t launch_fill(float* p, float value, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Workgroup size for rows of n items: whole workgroups per row (0: too short,
-// take the flat form).
-static inline int row_block(int64_t n) { return n >= 192 ? 256 : (n >= 96 ? 128 : (n >= 32 ? 64 : 0)); }
-
 template <int R>
 hipError_t blur_axis_run(const Images& im, int count, int n0, int n1, int n2, int axis, const float* wts,
                          hipStream_t s) {
@@ -2914,7 +2952,7 @@ hipError_t blur_pairs(const Images& im, int count, int na, int nm, int n_other, 
   // a thread takes up to eight k while that leaves every CU its 2048 threads
   const int kg = (int)std::min<int64_t>(8, std::max<int64_t>(1, rows * inner * nm / (256 * 2048)));
   const int64_t all = rows * ((nm + kg - 1) / kg);
-  if (const int bs = row_block(inner))
+  if (const int bs = row_span((int)std::min<int64_t>(inner, 256)))
     hipLaunchKernelGGL((k_blur_pairs<AX, RT, true>), dim3((unsigned)(all * ((inner + bs - 1) / bs))), dim3(bs), 0, s,
                        im, count, na, nm, n_other, n2, wts, R, kg);
   else
@@ -2947,7 +2985,7 @@ template <int RT>
 hipError_t level_sample(const Images& im, int count, int n0, int n1, int n2, int m0, int m1, int m2, bool c0, bool c1,
                         const float* rho, const float* wts, int R, hipStream_t s) {
   const int64_t rows = (int64_t)count * m0 * m1;
-  if (const int bs = row_block(m2))
+  if (const int bs = row_span(m2))
     hipLaunchKernelGGL((k_level_sample<RT, true>), dim3((unsigned)(rows * ((m2 + bs - 1) / bs))), dim3(bs), 0, s, im,
                        count, n0, n1, n2, m0, m1, m2, c0, c1, rho[0], rho[1], rho[2], wts, R);
   else
@@ -2997,7 +3035,7 @@ hipError_t launch_resample(const float* const* in, float* const* out, int fields
   const int64_t threads = (int64_t)fields * no[0] * no[1] * no[2];
   const int zc = (int)std::min<int64_t>(16, std::max<int64_t>(4, threads / (256 * 2048)));
   const int64_t rows = (int64_t)fields * no[1] * ((no[0] + zc - 1) / zc);
-  if (const int bs = row_block(no[2]))
+  if (const int bs = row_span(no[2]))
     hipLaunchKernelGGL(k_resample<true>, dim3((unsigned)(rows * ((no[2] + bs - 1) / bs))), dim3(bs), 0, s, A, fields,
                        ni[0], ni[1], ni[2], no[0], no[1], no[2], zc);
   else
@@ -3009,14 +3047,9 @@ hipError_t launch_resample(const float* const* in, float* const* out, int fields
 template <bool SLOPE>
 hipError_t warp_launch(const float* img, const float* d, float* out, float* slope, int n0, int n1, int n2,
                        hipStream_t s) {
-  if (n0 <= 65535 && n1 <= 65535) {
-    const int bs = n2 > 128 ? 256 : (n2 > 64 ? 128 : 64);   // a row's lanes, without a mostly idle workgroup
-    hipLaunchKernelGGL((k_warp<true, SLOPE>), dim3(grid1(n2, bs), n1, n0), dim3(bs), 0, s, img, d, out, slope, n0, n1,
-                       n2);
-  } else {
-    const int64_t n = (int64_t)n0 * n1 * n2;
-    hipLaunchKernelGGL((k_warp<false, SLOPE>), dim3(grid1(n, 256)), dim3(256), 0, s, img, d, out, slope, n0, n1, n2);
-  }
+  const int bs = row_span(n2);
+  hipLaunchKernelGGL((k_warp<SLOPE>), dim3(row_blocks((int64_t)n0 * n1, n2, bs)), dim3(256), 0, s, img, d, out, slope, n0,
+                     n1, n2, bs);
   return hipGetLastError();
 }
 
@@ -3031,8 +3064,9 @@ hipError_t launch_warp_slope(const float* img, const float* d, float* out, float
 
 hipError_t launch_compose_fields(const float* u, const float* d, float* out, int n0, int n1, int n2,
                                 hipStream_t s) {
-  const int64_t n = (int64_t)n0 * n1 * n2;
-  hipLaunchKernelGGL(k_compose_fields, dim3(grid1(n, 256)), dim3(256), 0, s, u, d, out, n0, n1, n2);
+  const int bs = row_span(n2);
+  hipLaunchKernelGGL(k_compose_fields, dim3(row_blocks((int64_t)n0 * n1, n2, bs)), dim3(256), 0, s, u, d, out, n0, n1, n2,
+                     bs);
   return hipGetLastError();
 }
 
@@ -3062,10 +3096,8 @@ hipError_t launch_means(const Means& A, hipStream_t s) {
 
 hipError_t launch_means_warp(const Means& A, const float* img, const float* d, float* out, float* slope, int n0, int n1,
                              int n2, hipStream_t s) {
-  const int np = mean_blocks(A.n), bs = row_block(n2);
-  const int64_t rows = (int64_t)n0 * n1;
-  const int64_t blocks = bs ? (rows + 256 / bs - 1) / (256 / bs) * ((n2 + bs - 1) / bs) : (rows * n2 + 255) / 256;
-  const dim3 g((unsigned)(2 * np + blocks));
+  const int np = mean_blocks(A.n), bs = row_span(n2);
+  const dim3 g(2 * np + row_blocks((int64_t)n0 * n1, n2, bs));
   if (slope)
     hipLaunchKernelGGL(k_means_warp<true>, g, dim3(256), 0, s, A, np, img, d, out, slope, n0, n1, n2, bs);
   else
