@@ -2019,10 +2019,19 @@ __global__ void __launch_bounds__(256) k_field_wide_x(const float* __restrict__ 
   const int x0 = blockIdx.x * 256, y = blockIdx.y, z = blockIdx.z;
   const int64_t N = (int64_t)n0 * n1 * n2;
   const int64_t row = ((int64_t)z * n1 + y) * n2;
+  // L <= 512: two values per thread and component, all loads in flight at once
+  float pre[3][2];
+#pragma unroll
   for (int c = 0; c < 3; ++c)
-    for (int i = threadIdx.x; i < L; i += 256) {
-      const int xx = min(max(x0 - R + i, 0), n2 - 1);
-      wl[c * L + i] = in[c * N + row + xx];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      pre[c][u] = in[c * N + row + min(max(x0 - R + (int)threadIdx.x + 256 * u, 0), n2 - 1)];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = threadIdx.x + 256 * u;
+      if (i < L) wl[c * L + i] = pre[c][u];
     }
   __syncthreads();
   const int x = x0 + threadIdx.x;
@@ -2046,17 +2055,19 @@ __global__ void __launch_bounds__(256) k_field_wide_x(const float* __restrict__ 
 // also runs the smoothing's epilogue (EPI): the max norm M of the result
 // (EPI_SMOOTH_MAX), as the streaming kernels do; E carries the control block.
 // (64 positions: at radius 18 a run of 32 re-read 36 halo positions for
-// every 32 outputs)
-constexpr int kWideRun = 64, kWideThreads = 8 * kWideRun;
+// every 32 outputs; runs of up to 96, as few as cover the axis, hold too few
+// wavefronts: 429 us an iteration at 131x177x219 against 411)
+constexpr int kWideRun = 64, kWideRows = kWideRun / 8, kWideThreads = 64 * kWideRows;
+constexpr int kWideLoads = (kWideRun + (2 * kMaxWideRadius + 8) / 8 * 8) / kWideRows;   // staged values per thread
 template <int AX, int EPI>
 __global__ void __launch_bounds__(kWideThreads) k_field_wide_yz(const float* __restrict__ in, float* __restrict__ out,
                                                        int n0, int n1, int n2, const float* __restrict__ w, int R,
                                                        const GaussArgs E) {
   extern __shared__ float wl[];   // [kWideRun + L8][64], one component at a time
-  __shared__ double red[kWideThreads / 64];
+  __shared__ float red[kWideRows];
   const int L8 = (2 * R + 1 + 7) / 8 * 8;
   const int LS = kWideRun + L8;
-  const int lane = threadIdx.x & 63, j0 = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, j0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: scalar addresses
   const int x = blockIdx.x * 64 + lane;
   const int a0 = blockIdx.y * kWideRun;
   const int na = AX == 0 ? n0 : n1;
@@ -2067,13 +2078,26 @@ __global__ void __launch_bounds__(kWideThreads) k_field_wide_yz(const float* __r
   const bool xin = x < n2;
   const int bo = 8 * j0;          // this thread's outputs, relative to a0
   float v[3][8];
+  // A component's staged values are loaded together, while the one before is
+  // formed: a load and its LDS write in turn cost a memory latency each, 13 per
+  // component.  (An iteration with sigma_grad 6 at 131x177x219: 437 -> 405 us,
+  // at 33x44x55 60 -> 48.)
+  float pre[kWideLoads];
+  auto fetch = [&](int c) {
+    const float* src = in + c * N + base + min(x, n2 - 1);
+#pragma unroll
+    for (int u = 0; u < kWideLoads; ++u)
+      pre[u] = src[min(max(a0 - R + min(j0 + u * kWideRows, LS - 1), 0), na - 1) * astride];
+  };
+  fetch(0);
+#pragma unroll
   for (int c = 0; c < 3; ++c) {
     if (c > 0) __syncthreads();   // the previous component's reads are done
-    for (int i = j0; i < LS; i += kWideThreads / 64) {
-      const int aa = min(max(a0 - R + i, 0), na - 1);
-      wl[i * 64 + lane] = xin ? in[c * N + base + aa * astride + x] : 0.0f;
-    }
+#pragma unroll
+    for (int u = 0; u < kWideLoads; ++u)
+      if (j0 + u * kWideRows < LS) wl[(j0 + u * kWideRows) * 64 + lane] = pre[u];
     __syncthreads();
+    if (c < 2) fetch(c + 1);
     float acc[8], xr[8];
 #pragma unroll
     for (int o = 0; o < 8; ++o) {
@@ -2102,7 +2126,13 @@ __global__ void __launch_bounds__(kWideThreads) k_field_wide_yz(const float* __r
       if (a0 + bo + o < na) mx = fmaxf(mx, v[0][o] * v[0][o] + v[1][o] * v[1][o] + v[2][o] * v[2][o]);
   }
   if (EPI == EPI_SMOOTH_MAX) {
-    const float bm = block_max<kWideThreads>(mx, reinterpret_cast<float*>(red));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_down(mx, o, 64));
+    if (lane == 0) red[j0] = mx;
+    __syncthreads();
+    float bm = 0.0f;
+    if (threadIdx.x == 0)
+      for (int j = 0; j < kWideRows; ++j) bm = fmaxf(bm, red[j]);
     if (threadIdx.x == 0) m_raise(E.ctl, sqrtf(bm), blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
   }
 }
