@@ -1315,39 +1315,74 @@ __device__ __forceinline__ void gauss_body(const GaussArgs& A, const int tile, c
 // ---------------------------------------------------------------------------
 // Brick form of the gradient kernel for small volumes.  A workgroup takes a
 // TZ x TY x TX brick: it loads I and J = I_m(x + d) on the brick plus a 2r
-// halo into LDS, forms the window sums of I, J, I^2, J^2 and IJ with three
-// separable passes (x, y, z), the per-centre coefficients A, B, C on the
+// halo, forms the window sums of I, J, I^2, J^2 and IJ with separable passes
+// (x and y together, then z), the per-centre coefficients A, B, C on the
 // brick plus an r halo, their window sums with three more passes, and the
 // output as in k_grad.  No plane-by-plane march: the launch is a short chain
-// of dependent steps, which is what bounds small volumes (I, J and the slope
-// come from memory as in the march: 19.5 -> 17.9 us at 64^3).  The sums run in a
+// of dependent steps, which is what bounds small volumes.  The sums run in a
 // different order from the streaming form (x, y, z instead of z, x, y), so
 // the two agree to rounding, not bitwise.
+//
+// Bound by LDS traffic and by the waits between the steps.  An item of a pass
+// forms two to four neighbouring sums from one run of values, so a value is
+// read about twice instead of w times.  Two threads per voxel fill the passes
+// over the halo.  The x sums stay in registers and I and J are staged half the
+// planes at a time (held in registers until then), so that two workgroups fit
+// a CU's LDS (79 KiB at window 5 instead of 131) and one computes while the
+// other loads or waits.  (Window 5: 64^3 18.4 -> 13.4 us, eight volumes of
+// 48x56x52 135 -> 75; with the sums along x in LDS and one workgroup per CU
+// 13.4 and 97.)
 // ---------------------------------------------------------------------------
 template <int W, int TZ, int TY, int TX>
 struct GradCubeShape {
   static constexpr int R = W / 2;
   static constexpr int QZ = TZ + 4 * R, QY = TY + 4 * R, QX = TX + 4 * R, NQ = QZ * QY * QX;  // I, J
   static constexpr int CZ = TZ + 2 * R, CY = TY + 2 * R, CX = TX + 2 * R, NC = CZ * CY * CX;  // centres
-  static constexpr int NX1 = QZ * QY * CX;   // stage-1 sums after the x pass
-  static constexpr int NY1 = QZ * CY * CX;   // ... after the y pass
+  static constexpr int HZ = QZ / 2, NH = HZ * QY * QX;   // half the planes of I, J
+  static constexpr int NY1 = QZ * CY * CX;   // stage-1 sums after the x and y passes
   static constexpr int NX2 = CZ * CY * TX;   // stage-2 sums after the x pass
   static constexpr int NY2 = CZ * TY * TX;   // ... after the y pass
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
-  static constexpr int SA = cmax(2 * NQ, cmax(5 * NY1, 3 * NX2));   // I, J -> stage-1 y -> stage-2 x
-  static constexpr int SB = cmax(5 * NX1, cmax(3 * NC, 3 * NY2));   // stage-1 x -> A, B, C -> stage-2 y
+  static constexpr int SA = cmax(5 * NY1, 3 * NX2);   // stage-1 xy -> stage-2 x
+  static constexpr int SB = cmax(2 * NH, cmax(3 * NC, 3 * NY2));   // half of I, J -> A, B, C -> stage-2 y
   static constexpr size_t lds_bytes = sizeof(float) * (size_t)(SA + SB);
+  static constexpr int NT = 2 * TZ * TY * TX;   // threads
+  static constexpr int XT = CX % 4 == 0 ? 4 : 2;   // floats per vector read of a row of centres
+  static_assert(QZ % 2 == 0 && CY % 2 == 0 && CZ % 2 == 0 && CX % XT == 0 && TX % 4 == 0 && TY % 4 == 0, "brick");
+  static_assert(SA % 4 == 0 && NC % 4 == 0 && NX2 % 4 == 0, "vector alignment");
 };
+
+// N consecutive floats from LDS, A of them aligned to their size (2 or 4).
+template <int N, int A>
+__device__ __forceinline__ void lds_run(const float* p, float* v) {
+  typedef float vec __attribute__((ext_vector_type(A)));
+#pragma unroll
+  for (int k = 0; k < N / A; ++k) {
+    const vec u = reinterpret_cast<const vec*>(p)[k];
+#pragma unroll
+    for (int i = 0; i < A; ++i) v[A * k + i] = u[i];
+  }
+#pragma unroll
+  for (int k = N / A * A; k < N; ++k) v[k] = p[k];
+}
+template <int A>
+__device__ __forceinline__ void lds_put(float* p, const float* v) {
+  typedef float vec __attribute__((ext_vector_type(A)));
+  vec u;
+#pragma unroll
+  for (int i = 0; i < A; ++i) u[i] = v[i];
+  *reinterpret_cast<vec*>(p) = u;
+}
 
 // MODE = A.mode (0 gradient and Adam, 1 gradient, 2 loss).
 template <int W, int TZ, int TY, int TX, int MODE>
 __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile) {
   using S = GradCubeShape<W, TZ, TY, TX>;
   constexpr int R = S::R;
-  constexpr int NT = TZ * TY * TX;
+  constexpr int NT = S::NT;
   constexpr int QY = S::QY, QX = S::QX, NQ = S::NQ;
   constexpr int CY = S::CY, CX = S::CX, NC = S::NC;
-  constexpr int NX1 = S::NX1, NY1 = S::NY1, NX2 = S::NX2, NY2 = S::NY2;
+  constexpr int HZ = S::HZ, NH = S::NH, NY1 = S::NY1, NX2 = S::NX2, NY2 = S::NY2, XT = S::XT;
   extern __shared__ float lds[];
   float* bufA = lds;
   float* bufB = lds + S::SA;
@@ -1389,7 +1424,7 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
   const int tz = tid / (TY * TX), tr = tid - tz * (TY * TX);
   const int ty = tr / TX, tx = tr - ty * TX;
   const int oz = z0 + tz, oy = y0 + ty, ox = x0 + tx;
-  const bool own = oz < n0 && oy < n1 && ox < n2;
+  const bool own = tid < TZ * TY * TX && oz < n0 && oy < n1 && ox < n2;
   // byte offset of the own voxel from uniform bases (volumes hold < 2^29 voxels)
   const unsigned ooff = own ? (unsigned)vidx(oz, oy, ox, n1, n2) * 4u : 0u;
   float oI = 0.f, oJ = 0.f;
@@ -1406,68 +1441,91 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
       }
     }
   }
+  // Stage 1, x and y, half of the planes at a time: an item forms the x sums of
+  // I, J, I^2, J^2, IJ of a column's W + 1 rows and from them its two sums along y.
 #pragma unroll
-  for (int j = 0; j < KQ; ++j) {
-    const int c = tid + j * NT;
-    if (c < NQ) {
-      bufA[c] = qI[j] - si;
-      bufA[NQ + c] = qJ[j] - sj;
+  for (int h = 0; h < 2; ++h) {
+    if (h) __syncthreads();   // the first half's reads are done
+#pragma unroll
+    for (int j = 0; j < KQ; ++j) {
+      const int c = tid + j * NT - h * NH;
+      if (c >= 0 && c < NH) {
+        bufB[c] = qI[j] - si;
+        bufB[NH + c] = qJ[j] - sj;
+      }
     }
-  }
-  __syncthreads();
-  // stage 1, x: sums of I, J, I^2, J^2, IJ over w voxels
-  for (int c = tid; c < NX1; c += NT) {
-    const int row = c / CX, xo = c - row * CX;
-    const float* pI = bufA + row * QX + xo;
-    const float* pJ = pI + NQ;
-    const float i0 = pI[0], j0 = pJ[0];
-    float s0 = i0, s1 = j0, s2 = i0 * i0, s3 = j0 * j0, s4 = i0 * j0;
+    __syncthreads();
+    constexpr int YG = CY / 2;
+    for (int c = tid; c < HZ * YG * CX; c += NT) {
+      const int zg = c / CX, xo = c - zg * CX;
+      const int zq = zg / YG, yo = (zg - zq * YG) * 2;
+      const float* pI = bufB + (zq * QY + yo) * QX + xo;
+      const float* pJ = pI + NH;
+      float sum[2][5];
 #pragma unroll
-    for (int k = 1; k < W; ++k) {
-      const float i_ = pI[k], j_ = pJ[k];
-      s0 += i_;
-      s1 += j_;
-      s2 += i_ * i_;
-      s3 += j_ * j_;
-      s4 += i_ * j_;
-    }
-    bufB[c] = s0;
-    bufB[NX1 + c] = s1;
-    bufB[2 * NX1 + c] = s2;
-    bufB[3 * NX1 + c] = s3;
-    bufB[4 * NX1 + c] = s4;
-  }
-  __syncthreads();
-  // stage 1, y
-  for (int c = tid; c < NY1; c += NT) {
-    const int zq = c / (CY * CX), r = c - zq * (CY * CX);
-    const int yo = r / CX, xo = r - yo * CX;
-    const float* src = bufB + (zq * QY + yo) * CX + xo;
+      for (int r = 0; r < W + 1; ++r) {
+        float i_[W], j_[W];
 #pragma unroll
-    for (int q = 0; q < 5; ++q) {
-      const float* p = src + q * NX1;
-      float sum = p[0];
+        for (int k = 0; k < W; ++k) {
+          i_[k] = pI[r * QX + k];
+          j_[k] = pJ[r * QX + k];
+        }
+        // the second product is rounded and the first fused into it: which is
+        // otherwise the compiler's choice and shows in the last bits
+        constexpr int k0 = W > 1 ? 1 : 0;
+        float s[5] = {i_[0], j_[0], i_[k0] * i_[k0], j_[k0] * j_[k0], i_[k0] * j_[k0]};
 #pragma unroll
-      for (int k = 1; k < W; ++k) sum += p[k * CX];
-      bufA[q * NY1 + c] = sum;
+        for (int k = 1; k < W; ++k) {
+          s[0] += i_[k];
+          s[1] += j_[k];
+          const float ia = i_[k == 1 ? 0 : k], ja = j_[k == 1 ? 0 : k];
+          s[2] = __builtin_fmaf(ia, ia, s[2]);
+          s[3] = __builtin_fmaf(ja, ja, s[3]);
+          s[4] = __builtin_fmaf(ia, ja, s[4]);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int q = 0; q < 5; ++q) {
+            if (r == t) sum[t][q] = s[q];
+            if (r > t && r < t + W) sum[t][q] += s[q];
+          }
+      }
+      float* o = bufA + ((h * HZ + zq) * CY + yo) * CX + xo;
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        o[q * NY1] = sum[0][q];
+        o[q * NY1 + CX] = sum[1][q];
+      }
     }
   }
   __syncthreads();
   // stage 1, z, and the per-centre coefficients on the brick plus r
   float lacc = 0.0f;
-  for (int c = tid; c < NC; c += NT) {
-    const int cz = c / (CY * CX), r = c - cz * (CY * CX);
+  constexpr int ZT = 2;   // planes per item
+  for (int ci = tid; ci < NC / ZT; ci += NT) {
+    const int zi = ci / (CY * CX), r = ci - zi * (CY * CX);
     const int cy = r / CX, cx = r - cy * CX;
-    const float* src = bufA + (cz * CY + cy) * CX + cx;
-    float St[5];
+    const float* src = bufA + zi * ZT * CY * CX + r;
+    float Sz[ZT][5];
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
       const float* p = src + q * NY1;
-      float sum = p[0];
+      float v[ZT + W - 1];
 #pragma unroll
-      for (int k = 1; k < W; ++k) sum += p[k * CY * CX];
-      St[q] = sum;
+      for (int k = 0; k < ZT + W - 1; ++k) v[k] = p[k * CY * CX];
+#pragma unroll
+      for (int t = 0; t < ZT; ++t) {
+        float sum = v[t];
+#pragma unroll
+        for (int k = 1; k < W; ++k) sum += v[t + k];
+        Sz[t][q] = sum;
+      }
     }
+#pragma unroll
+    for (int t = 0; t < ZT; ++t) {
+    const int cz = zi * ZT + t, c = cz * (CY * CX) + r;
+    const float* St = Sz[t];
     const int z = z0 - R + cz, y = y0 - R + cy, x = x0 - R + cx;
     const bool ok = z >= 0 && z < n0 && y >= 0 && y < n1 && x >= 0 && x < n2;
     float ca = 0.f, cb = 0.f, cc_ = 0.f;
@@ -1492,35 +1550,44 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
     bufB[c] = ca;
     bufB[NC + c] = cb;
     bufB[2 * NC + c] = cc_;
+    }
   }
   if constexpr (MODE != 2) {
   __syncthreads();
   // stage 2 (sums of A, B, C over the window around each brick voxel), x
-  for (int c = tid; c < NX2; c += NT) {
-    const int row = c / TX, xo = c - row * TX;
-    const float* src = bufB + row * CX + xo;
+  constexpr int G2 = TX / 4, NXI = NX2 / 4;
+  for (int c = tid; c < 3 * NXI; c += NT) {
+    const int q = c / NXI, cq = c - q * NXI;
+    const int row = cq / G2, xo = (cq - row * G2) * 4;
+    float v[4 + W - 1], o[4];
+    lds_run<4 + W - 1, XT>(bufB + q * NC + row * CX + xo, v);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const float* p = src + q * NC;
-      float sum = p[0];
+    for (int t = 0; t < 4; ++t) {
+      float sum = v[t];
 #pragma unroll
-      for (int k = 1; k < W; ++k) sum += p[k];
-      bufA[q * NX2 + c] = sum;
+      for (int k = 1; k < W; ++k) sum += v[t + k];
+      o[t] = sum;
     }
+    lds_put<4>(bufA + q * NX2 + row * TX + xo, o);
   }
   __syncthreads();
   // stage 2, y
-  for (int c = tid; c < NY2; c += NT) {
-    const int zc = c / (TY * TX), r = c - zc * (TY * TX);
-    const int yo = r / TX, xo = r - yo * TX;
-    const float* src = bufA + (zc * CY + yo) * TX + xo;
+  constexpr int G3 = TY / 4, NYJ = NY2 / 4;
+  for (int c = tid; c < 3 * NYJ; c += NT) {
+    const int q = c / NYJ, cq = c - q * NYJ;
+    const int zg = cq / TX, xo = cq - zg * TX;
+    const int zc = zg / G3, yo = (zg - zc * G3) * 4;
+    const float* p = bufA + q * NX2 + (zc * CY + yo) * TX + xo;
+    float v[4 + W - 1];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const float* p = src + q * NX2;
-      float sum = p[0];
+    for (int k = 0; k < 4 + W - 1; ++k) v[k] = p[k * TX];
+    float* o = bufB + q * NY2 + (zc * TY + yo) * TX + xo;
 #pragma unroll
-      for (int k = 1; k < W; ++k) sum += p[k * TX];
-      bufB[q * NY2 + c] = sum;
+    for (int t = 0; t < 4; ++t) {
+      float sum = v[t];
+#pragma unroll
+      for (int k = 1; k < W; ++k) sum += v[t + k];
+      o[t * TX] = sum;
     }
   }
   __syncthreads();
@@ -1871,12 +1938,12 @@ __global__ void __launch_bounds__(TY * TX) k_gauss_batch(const BatchEntry<GaussA
 }
 
 template <int W, int TZ, int TY, int TX, int MODE>
-__global__ void __launch_bounds__(TZ * TY * TX) k_grad_cube(const GradArgs A) {
+__global__ void __launch_bounds__((GradCubeShape<W, TZ, TY, TX>::NT)) k_grad_cube(const GradArgs A) {
   grad_cube_body<W, TZ, TY, TX, MODE>(A, xcd_tile(blockIdx.x, gridDim.x));
 }
 
 template <int W, int TZ, int TY, int TX, int MODE>
-__global__ void __launch_bounds__(TZ * TY * TX) k_grad_cube_batch(const BatchEntry<GradArgs>* __restrict__ E,
+__global__ void __launch_bounds__((GradCubeShape<W, TZ, TY, TX>::NT)) k_grad_cube_batch(const BatchEntry<GradArgs>* __restrict__ E,
                                                                   const int* __restrict__ owner) {
   GradArgs A;
   int nb;
@@ -2678,7 +2745,7 @@ hipError_t grad_cube_m(const GradArgs& a, const Tiling& t, hipStream_t s) {
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  k_grad_cube<W, TZ, TY, TX, MODE><<<dim3(t.blocks()), dim3(TZ * TY * TX), sh, s>>>(a);
+  k_grad_cube<W, TZ, TY, TX, MODE><<<dim3(t.blocks()), dim3(GradCubeShape<W, TZ, TY, TX>::NT), sh, s>>>(a);
   return hipGetLastError();
 }
 
@@ -2734,7 +2801,7 @@ hipError_t grad_cube_batch_m(const BatchEntry<GradArgs>* E, const int* owner, in
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  k_grad_cube_batch<W, TZ, TY, TX, MODE><<<dim3(total), dim3(TZ * TY * TX), sh, s>>>(E, owner);
+  k_grad_cube_batch<W, TZ, TY, TX, MODE><<<dim3(total), dim3(GradCubeShape<W, TZ, TY, TX>::NT), sh, s>>>(E, owner);
   return hipGetLastError();
 }
 
