@@ -1633,10 +1633,30 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
 // streaming form).  With no march along n0, a launch is a few dependent
 // steps long instead of one step per plane of a chunk plus its halo.
 // ---------------------------------------------------------------------------
+// Threads of a brick launch of the smoothing.  Two per voxel fill the passes
+// over the halo (R = 3, 64^3: 5.9 us against 6.2 with one); where half of them
+// would then wait for the others' samples, one (R = 2, eight volumes of
+// 48x56x52: 22 us against 26 with two).  An item of a pass forms four sums from
+// one run of values, of which each is then read from LDS two to three times
+// instead of 2R + 1 (with one sum per item: 7.5 us and 23).
+template <int TZ, int TY, int TX, int EPI>
+constexpr int kCubeThreads = (EPI == EPI_SMOOTH_MAX ? 2 : 1) * TZ * TY * TX;
+
+// Sum of L taps.  The second product is rounded and the first fused into it:
+// which is otherwise the compiler's choice and shows in the last bits.
+template <int L>
+__device__ __forceinline__ float tap_sum(const float* w, const float* v) {
+  if constexpr (L == 1) return w[0] * v[0];
+  float s = __builtin_fmaf(w[0], v[0], w[1] * v[1]);
+#pragma unroll
+  for (int k = 2; k < L; ++k) s = __builtin_fmaf(w[k], v[k], s);
+  return s;
+}
+
 template <int R, int TZ, int TY, int TX, int EPI>
 __device__ __forceinline__ void gauss_cube_body(const GaussArgs& A, const int tile, const int nblocks) {
   constexpr int L = 2 * R + 1;
-  constexpr int NT = TZ * TY * TX;
+  constexpr int NT = kCubeThreads<TZ, TY, TX, EPI>;
   constexpr int RZ = TZ + 2 * R, RY = TY + 2 * R, RX = TX + 2 * R;
   constexpr int NR = RZ * RY * RX;   // halo region
   constexpr int NX = RZ * RY * TX;   // after the x-pass
@@ -1689,50 +1709,48 @@ __device__ __forceinline__ void gauss_cube_body(const GaussArgs& A, const int ti
     }
   }
   __syncthreads();
-  for (int c = tid; c < NX; c += NT) {
-    const int row = c / TX, xx = c - row * TX;
-    const float* src = reg + row * RX + xx;
-    float s0 = w[0] * src[0], s1 = w[0] * src[NR], s2 = w[0] * src[2 * NR];
+  // x, four neighbours of a row and one component per item
+  constexpr int XG = TX / 4, NXI = NX / 4;
+  for (int c = tid; c < 3 * NXI; c += NT) {
+    const int q = c / NXI, cq = c - q * NXI;
+    const int row = cq / XG, xx = (cq - row * XG) * 4;
+    float v[4 + L - 1], o[4];
+    lds_run<4 + L - 1, 2>(reg + q * NR + row * RX + xx, v);
 #pragma unroll
-    for (int k = 1; k < L; ++k) {
-      s0 += w[k] * src[k];
-      s1 += w[k] * src[NR + k];
-      s2 += w[k] * src[2 * NR + k];
-    }
-    xo[c] = s0;
-    xo[NX + c] = s1;
-    xo[2 * NX + c] = s2;
+    for (int t = 0; t < 4; ++t) o[t] = tap_sum<L>(w, v + t);
+    lds_put<4>(xo + q * NX + row * TX + xx, o);
   }
   __syncthreads();
-  for (int c = tid; c < NY; c += NT) {
-    const int zz = c / (TY * TX), r = c - zz * (TY * TX);
-    const int yy = r / TX, xx = r - yy * TX;
-    const float* src = xo + (zz * RY + yy) * TX + xx;
-    float s0 = w[0] * src[0], s1 = w[0] * src[NX], s2 = w[0] * src[2 * NX];
+  // y, four outputs of a column per item
+  constexpr int YG = TY / 4, NYI = NY / 4;
+  for (int c = tid; c < 3 * NYI; c += NT) {
+    const int q = c / NYI, cq = c - q * NYI;
+    const int zg = cq / TX, xx = cq - zg * TX;
+    const int zz = zg / YG, yy = (zg - zz * YG) * 4;
+    const float* src = xo + q * NX + (zz * RY + yy) * TX + xx;
+    float v[4 + L - 1];
 #pragma unroll
-    for (int k = 1; k < L; ++k) {
-      s0 += w[k] * src[k * TX];
-      s1 += w[k] * src[NX + k * TX];
-      s2 += w[k] * src[2 * NX + k * TX];
-    }
-    reg[c] = s0;
-    reg[NY + c] = s1;
-    reg[2 * NY + c] = s2;
+    for (int k = 0; k < 4 + L - 1; ++k) v[k] = src[k * TX];
+    float* o = reg + q * NY + (zz * TY + yy) * TX + xx;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) o[t * TX] = tap_sum<L>(w, v + t);
   }
   __syncthreads();
   const int tz = tid / (TY * TX), r = tid - tz * (TY * TX);
   const int ty = r / TX, tx = r - ty * TX;
   const int gz = z0 + tz, gy = y0 + ty, gx = x0 + tx;
   float mx = 0.0f;
-  if (gz < n0 && gy < n1 && gx < n2) {
+  if (tid < TZ * TY * TX && gz < n0 && gy < n1 && gx < n2) {
     const float* src = reg + (tz * TY + ty) * TX + tx;
-    float v0 = w[0] * src[0], v1 = w[0] * src[NY], v2 = w[0] * src[2 * NY];
+    float vz[3];
 #pragma unroll
-    for (int j = 1; j < L; ++j) {
-      v0 += w[j] * src[j * TY * TX];
-      v1 += w[j] * src[NY + j * TY * TX];
-      v2 += w[j] * src[2 * NY + j * TY * TX];
+    for (int q = 0; q < 3; ++q) {
+      float v[L];
+#pragma unroll
+      for (int j = 0; j < L; ++j) v[j] = src[q * NY + j * TY * TX];
+      vz[q] = tap_sum<L>(w, v);
     }
+    const float v0 = vz[0], v1 = vz[1], v2 = vz[2];
     const unsigned off = (unsigned)vidx(gz, gy, gx, n1, n2) * 4u;
     store_at(A.out, off, v0);
     store_at(A.out + N, off, v1);
@@ -1952,12 +1970,12 @@ __global__ void __launch_bounds__((GradCubeShape<W, TZ, TY, TX>::NT)) k_grad_cub
 }
 
 template <int R, int TZ, int TY, int TX, int EPI>
-__global__ void __launch_bounds__(TZ * TY * TX) k_gauss_cube(const GaussArgs A) {
+__global__ void __launch_bounds__((kCubeThreads<TZ, TY, TX, EPI>)) k_gauss_cube(const GaussArgs A) {
   gauss_cube_body<R, TZ, TY, TX, EPI>(A, xcd_tile(blockIdx.x, gridDim.x), gridDim.x);
 }
 
 template <int R, int TZ, int TY, int TX, int EPI>
-__global__ void __launch_bounds__(TZ * TY * TX) k_gauss_cube_batch(const BatchEntry<GaussArgs>* __restrict__ E,
+__global__ void __launch_bounds__((kCubeThreads<TZ, TY, TX, EPI>)) k_gauss_cube_batch(const BatchEntry<GaussArgs>* __restrict__ E,
                                                                    const int* __restrict__ owner) {
   GaussArgs A;
   int nb;
@@ -2706,11 +2724,11 @@ hipError_t gauss_cube_r(const GaussArgs& a, int epi, const Tiling& t, hipStream_
   constexpr size_t sh = sizeof(float) * 3 *
                         ((TZ + 2 * R) * (TY + 2 * R) * (TX + 2 * R) + (TZ + 2 * R) * (TY + 2 * R) * TX);
   static_assert(sh <= 65536, "brick smoothing LDS exceeds 64 KiB");
-  const dim3 g(t.blocks()), blk(TZ * TY * TX);
+  const dim3 g(t.blocks()), one(kCubeThreads<TZ, TY, TX, EPI_STORE>), two(kCubeThreads<TZ, TY, TX, EPI_SMOOTH_MAX>);
   switch (epi) {
-    case EPI_SMOOTH_MAX: k_gauss_cube<R, TZ, TY, TX, EPI_SMOOTH_MAX><<<g, blk, sh, s>>>(a); break;
-    case EPI_STORE: k_gauss_cube<R, TZ, TY, TX, EPI_STORE><<<g, blk, sh, s>>>(a); break;
-    case EPI_STORE_WARP: k_gauss_cube<R, TZ, TY, TX, EPI_STORE_WARP><<<g, blk, sh, s>>>(a); break;
+    case EPI_SMOOTH_MAX: k_gauss_cube<R, TZ, TY, TX, EPI_SMOOTH_MAX><<<g, two, sh, s>>>(a); break;
+    case EPI_STORE: k_gauss_cube<R, TZ, TY, TX, EPI_STORE><<<g, one, sh, s>>>(a); break;
+    case EPI_STORE_WARP: k_gauss_cube<R, TZ, TY, TX, EPI_STORE_WARP><<<g, one, sh, s>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -2853,10 +2871,10 @@ hipError_t gauss_cube_batch_r(const BatchEntry<GaussArgs>* E, const int* owner, 
   constexpr int TZ = kCubeZ, TY = kCubeY, TX = kCubeX;
   constexpr size_t sh = sizeof(float) * 3 *
                         ((TZ + 2 * R) * (TY + 2 * R) * (TX + 2 * R) + (TZ + 2 * R) * (TY + 2 * R) * TX);
-  const dim3 g(total), blk(TZ * TY * TX);
+  const dim3 g(total), one(kCubeThreads<TZ, TY, TX, EPI_STORE>), two(kCubeThreads<TZ, TY, TX, EPI_SMOOTH_MAX>);
   switch (epi) {
-    case EPI_SMOOTH_MAX: k_gauss_cube_batch<R, TZ, TY, TX, EPI_SMOOTH_MAX><<<g, blk, sh, s>>>(E, owner); break;
-    case EPI_STORE_WARP: k_gauss_cube_batch<R, TZ, TY, TX, EPI_STORE_WARP><<<g, blk, sh, s>>>(E, owner); break;
+    case EPI_SMOOTH_MAX: k_gauss_cube_batch<R, TZ, TY, TX, EPI_SMOOTH_MAX><<<g, two, sh, s>>>(E, owner); break;
+    case EPI_STORE_WARP: k_gauss_cube_batch<R, TZ, TY, TX, EPI_STORE_WARP><<<g, one, sh, s>>>(E, owner); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
