@@ -9,7 +9,7 @@ The inputs are `rocprof_csv_summary.py pmc` tables of one run each of
 threads besides torch's fill) gives the bytes per counter unit, and every
 per-dispatch figure is scaled by it.  The JSON records the gradient kernel at
 the finest level of the 160x192x224 workload (the launch with a grid of
-258,048 threads) with the SHA-256 of the kernel and runtime sources, so that
+516,096 threads) with the SHA-256 of the kernel and runtime sources, so that
 bench.py reports it only while those sources are unchanged.
 """
 import hashlib
@@ -20,7 +20,7 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
 SOURCES = ["paper_2404_01249_amd/csrc/fa_kernels.hip", "paper_2404_01249_amd/csrc/fa_runtime.hip"]
 CALIB_GRID = "16777216"
-FINEST_GRAD_GRID = "258048"
+FINEST_GRAD_GRID = "516096"
 ALGORITHMIC = 80 * 160 * 192 * 224
 
 
