@@ -67,8 +67,10 @@ fa_status fa_sym_get_loss(fa_sym h, float* host_out, int capacity, int* n_writte
  * (eta, sigmas, Adam) over the given inverse schedule (as
  * fa_inverse_set_schedule), then d_out = the displacement of phi_M o psi
  * (device, float32 [3][n0][n1][n2] of the input grid).  *inv_cost (may be
- * NULL) receives the inverse fit's last cost.  Synchronises.  FA_EINVAL,
- * FA_ESTATE (schedule not complete), FA_ENOMEM, FA_EHIP. */
+ * NULL) receives the inverse fit's last cost.  Synchronises.  The handle keeps
+ * the inverse's buffers (about 140 bytes per voxel) for the next call, until
+ * it is destroyed.  FA_EINVAL, FA_ESTATE (schedule not complete), FA_ENOMEM,
+ * FA_EHIP. */
 fa_status fa_sym_finish(fa_sym h, const fa_params* inv_params, int n_levels, const float* scales,
                         const int* iters, float* d_out, float* inv_cost);
 
