@@ -2235,7 +2235,7 @@ __device__ __forceinline__ float aligned_pos(int i, int nin, int nout) {
 // eight corners it samples.  The taps, their order and the sample are those of
 // the full blur, so the values are the same.  At scale 8 the first pass writes
 // a quarter of the volume and the second a sixteenth.  (512^3, scales 8, 4, 2,
-// two images: 2.7 ms; 13.9 when every entry was blurred and then resampled, the
+// two images: 2.2 ms; 13.9 when every entry was blurred and then resampled, the
 // radius-12 passes 10.3 of them.)  Up to three images go through one launch per pass.
 struct Images {
   const float* in[3];
@@ -2345,6 +2345,8 @@ __global__ void __launch_bounds__(256) k_blur_axis_run(const Images im, int n0, 
 // The blur along n2 of the eight corners of each sample, and the sample, times
 // rho[image].  im.in holds the images after the passes along n0 and n1,
 // [p0][p1][n2] (p0 = 2 m0 where compact, else n0; p1 likewise).
+// Bound by the addresses of its loads, 32 to 104 per sample with one per value:
+// four neighbours to a load took the three levels of 512^3 from 958 to 475 us.
 template <int RT, bool BLK>
 __global__ void __launch_bounds__(256) k_level_sample(const Images im, unsigned count, int n0, int n1, int n2, int m0, int m1, int m2,
                                                       bool c0, bool c1, float rho0, float rho1, float rho2,
@@ -2357,25 +2359,66 @@ __global__ void __launch_bounds__(256) k_level_sample(const Images im, unsigned 
   const int k1 = (int)(r % m1), k0 = (int)(r / m1), k2 = (int)item;
   Corners c = make_corners(n0, n1, n2, aligned_pos(k0, n0, m0), aligned_pos(k1, n1, m1), aligned_pos(k2, n2, m2));
   const int p1 = c1 ? 2 * m1 : n1;
-  float v[8];
+  const float* rows[4];
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
-    const int b0 = b >> 1, b1 = b & 1;
-    const int z = c0 ? 2 * k0 + b0 : min(max(c.i0 + b0, 0), n0 - 1);
-    const int y = c1 ? 2 * k1 + b1 : min(max(c.i1 + b1, 0), n1 - 1);
-    const float* src = im.in[img] + ((size_t)z * p1 + y) * n2;
-    float s0 = 0.0f, s1 = 0.0f;
-    float x = src[min(max(c.i2 - R, 0), n2 - 1)];
-#pragma unroll(RT ? 2 * RT + 1 : 4)
-    for (int j = 0; j <= 2 * R; ++j) {
-      const float t = src[min(max(c.i2 - R + 1 + j, 0), n2 - 1)];
-      s0 += w[j] * x;
-      s1 += w[j] * t;
-      x = t;
-    }
-    const bool in0 = b0 ? c.b0 : c.a0, in1 = b1 ? c.b1 : c.a1;
+    const int z = c0 ? 2 * k0 + (b >> 1) : min(max(c.i0 + (b >> 1), 0), n0 - 1);
+    const int y = c1 ? 2 * k1 + (b & 1) : min(max(c.i1 + (b & 1), 0), n1 - 1);
+    rows[b] = im.in[img] + ((size_t)z * p1 + y) * n2;
+  }
+  float v[8];
+  auto corner = [&](int b, float s0, float s1) {
+    const bool in0 = b >> 1 ? c.b0 : c.a0, in1 = b & 1 ? c.b1 : c.a1;
     v[2 * b] = in0 & in1 & c.a2 ? s0 : 0.0f;
     v[2 * b + 1] = in0 & in1 & c.b2 ? s1 : 0.0f;
+  };
+  if constexpr (RT > 0) {
+    // a row's 2R + 2 neighbours, four to a load (any 4-byte alignment) but near the ends of a row
+    typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int NV = 2 * RT + 2;
+    float x[4][NV];
+    if (c.i2 >= RT && c.i2 + RT + 1 < n2) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const float* p = rows[b] + (c.i2 - RT);
+#pragma unroll
+        for (int j = 0; j + 4 <= NV; j += 4) {
+          const float4_any q = *reinterpret_cast<const float4_any*>(p + j);
+          x[b][j] = q.x, x[b][j + 1] = q.y, x[b][j + 2] = q.z, x[b][j + 3] = q.w;
+        }
+#pragma unroll
+        for (int j = NV / 4 * 4; j < NV; ++j) x[b][j] = p[j];
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int j = 0; j < NV; ++j) x[b][j] = rows[b][min(max(c.i2 - RT + j, 0), n2 - 1)];
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+      for (int j = 0; j <= 2 * RT; ++j) {
+        s0 += w[j] * x[b][j];
+        s1 += w[j] * x[b][j + 1];
+      }
+      corner(b, s0, s1);
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      float s0 = 0.0f, s1 = 0.0f;
+      float x = rows[b][min(max(c.i2 - R, 0), n2 - 1)];
+#pragma unroll 4
+      for (int j = 0; j <= 2 * R; ++j) {
+        const float t = rows[b][min(max(c.i2 - R + 1 + j, 0), n2 - 1)];
+        s0 += w[j] * x;
+        s1 += w[j] * t;
+        x = t;
+      }
+      corner(b, s0, s1);
+    }
   }
   const float rho = img == 0 ? rho0 : (img == 1 ? rho1 : rho2);
   im.out[img][(size_t)r * m2 + k2] = rho * tri(v, c);
