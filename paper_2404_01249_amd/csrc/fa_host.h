@@ -63,6 +63,21 @@ void batch_chunks(KernelKind kind, int halo, const std::vector<Tiling*>& ts, con
 // parameters; its buffers stay.  A schedule has to be set next.
 fa_status inverse_restart(fa_inverse_s* H, const float* d, const fa_params* params);
 
+// Whether work put on s is being captured into a graph instead of run.  What a
+// captured launch writes is there only after a replay, and replays come when
+// the host does not know of it: state that one call leaves for the next
+// (a pair's J, an inverse's lists) has to be made again inside the capture and,
+// on a handle that was captured once, in every later call.
+inline bool capturing(hipStream_t s) {
+  if (!s) return false;   // the null stream cannot be captured
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 }  // namespace fa
 
 #define FA_HIP(call)                                                                   \

@@ -130,6 +130,7 @@ struct fa_pair_s {
   float* warped = nullptr;    // J = I_m o phi at the current level, [n], and its slope dI_m/dp, [3][n]:
   float* slope = nullptr;     // made by the warp smoothing for the next iteration
   bool warped_ok = false;     // whether the queued work leaves them at the current d
+  bool captured = false;      // a call was captured: replays may move d unseen, so each call makes its own J
   float* tmp = nullptr;       // smoothed direction s, then the composed d'
   float* wide = nullptr;      // [3][cap] scratch of the smoothing passes with a radius above 6
   float* blur = nullptr;      // pyramid scratch (two input volumes), where the state's buffers are too small for it
@@ -382,12 +383,19 @@ fa_status make_row_pairs(fa_pair P, Level& L) {
 }
 
 // J = I_m o phi and its slope at the pair's current d, unless the last
-// iteration's warp smoothing has made them.
+// iteration's warp smoothing has made them.  (The batched iteration captures
+// this only where they are made, in a graph that lives and ends in its call.)
 fa_status ensure_warped(fa_pair P, const Level& L) {
   if (!P->warped_ok)
     FA_HIP(fa::launch_warp_slope(L.moving, P->d, P->warped, P->slope, L.shape.n0, L.shape.n1, L.shape.n2, P->stream));
   P->warped_ok = true;
   return FA_OK;
+}
+
+// Before ensure_warped in a call that a caller may capture.
+void note_capture(fa_pair P) {
+  P->captured |= fa::capturing(P->stream);
+  if (P->captured) P->warped_ok = false;
 }
 
 fa_status launch_eulerian(fa_pair P, const Level& L) {
@@ -406,7 +414,8 @@ fa_status launch_iteration(fa_pair P, const Level& L, const float* fixed = nullp
   IterPlan it;
   plan_iteration(P, L, it, fixed);
   // a level's last iteration leaves no J: the next level's differs
-  const bool last = P->cur_iter + 1 >= L.iters;
+  note_capture(P);
+  const bool last = P->cur_iter + 1 >= L.iters || P->captured;
   if (last) it.epi[2] = fa::EPI_STORE;
   FA_TRY(ensure_warped(P, L));
   FA_HIP(fa::launch_grad(it.ga, it.window, it.tg, P->stream));
@@ -738,6 +747,8 @@ fa_status run_batch_fused(fa_pair* pairs, int n, int max_iters, hipStream_t s) {
   std::vector<std::pair<int, int>> sig, last;
   std::vector<fa_pair> live;
   fa_status st = FA_OK;
+  for (int i = 0; i < n; ++i)
+    if (pairs[i]->captured) pairs[i]->warped_ok = false;
   for (int k = 0; k < max_iters && st == FA_OK; ++k) {
     live.clear();
     sig.clear();
@@ -808,6 +819,8 @@ fa_status run_batch_fused(fa_pair* pairs, int n, int max_iters, hipStream_t s) {
     if (st == FA_OK) st = st2;
   }
   if (gexec) (void)hipGraphExecDestroy(gexec);
+  if (st != FA_OK)   // what was queued may not have run
+    for (int i = 0; i < n; ++i) pairs[i]->warped_ok = false;
   return st;
 }
 
@@ -1376,6 +1389,7 @@ fa_status fa_pair_eval_gradient(fa_pair P, float* g_dev, float* loss_host) {
   ga.eps_cc = P->p.cc_eps;
   ga.inv_n = (float)(1.0 / (double)L.n);
   ga.mode = 1;
+  note_capture(P);
   FA_TRY(ensure_warped(P, L));
   FA_HIP(fa::launch_grad(ga, P->p.cc_window, L.tg, P->stream));
   if (loss_host) {
@@ -1759,7 +1773,10 @@ fa_status fa_sym_step(fa_sym H, int max_iters, int* iters_done, int* finished) {
     if (st == FA_OK && e1 != hipSuccess) st = fail(FA_EHIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(e1));
     bt.recycle();
   }
-  if (st != FA_OK) return st;
+  if (st != FA_OK) {   // what was queued may not have run
+    F->warped_ok = M->warped_ok = false;
+    return st;
+  }
   if (iters_done) *iters_done = done;
   if (finished) *finished = schedule_done(M) ? 1 : 0;
   return FA_OK;
