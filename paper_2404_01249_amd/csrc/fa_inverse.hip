@@ -563,7 +563,8 @@ struct fa_inverse_s {
   Plan plan{};             // voxels by cell of level plan_level
   size_t plan_cells = 0;   // capacities of its buffers
   int plan_bricks = 0;
-  int plan_level = -1;
+  int plan_level = -1;     // -1: none listed (or only inside a captured graph)
+  bool captured = false;   // a call was captured: its replays list their own level, so each call lists anew
   Ctl* ctl = nullptr;
   float* loss_hist = nullptr;
   int loss_cap = 0;
@@ -699,11 +700,12 @@ fa_status launch_direction(fa_inverse H, const ILevel& L, float* out, int grad_o
   Plan P = H->plan;
   P.cells = (size_t)cells_of(s);
   P.bricks = bricks_of(s);
-  if (H->plan_level != H->cur_level) {
+  H->captured |= fa::capturing(H->stream);
+  if (H->captured || H->plan_level != H->cur_level) {
     FA_HIP(fa::launch_fill(reinterpret_cast<float*>(P.count), 0.0f, (int64_t)P.cells, H->stream));
     hipLaunchKernelGGL(k_inv_plan, dim3(b), dim3(kInvThreads), 0, H->stream, L.d, P, s.n0, s.n1, s.n2);
     FA_HIP(hipGetLastError());
-    H->plan_level = H->cur_level;
+    H->plan_level = H->captured ? -1 : H->cur_level;
   }
   const FastDiv by_row = fast_divisor(s.n2), by_plane = fast_divisor((unsigned)(s.n1 * s.n2));
   if (small_tiles(s))

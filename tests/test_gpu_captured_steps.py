@@ -5,7 +5,7 @@ behind that a later step would take for made.  Against eager runs, bit for bit."
 import pytest
 import torch
 
-from paper_2404_01249_amd import Pair, fa, synth
+from paper_2404_01249_amd import Inverse, Pair, fa, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -109,3 +109,21 @@ def test_captured_gradient_follows_the_displacement(shape):
             torch.cuda.synchronize()
             assert torch.equal(g, p.eval_gradient()[0])
             torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_inverse_captures(shape):
+    d = state(shape, 6)
+    want = trajectory(lambda: Inverse(d), 6)
+    torch.cuda.synchronize()
+    with Inverse(d, stream=torch.cuda.Stream()) as inv:
+        inv.set_schedule([1.0], [10])
+        captured(inv, lambda: inv.step(1))   # never launched
+        inv.step(2)
+        assert torch.equal(field(inv), want[2])
+        graph = captured(inv, lambda: inv.step(1))
+        for k in range(3):
+            replay(inv, graph)
+            assert torch.equal(field(inv), want[3 + k])
+        inv.step(1)
+        assert torch.equal(field(inv), want[6])
