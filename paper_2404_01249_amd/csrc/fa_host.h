@@ -36,11 +36,8 @@ enum KernelKind { KIND_GRAD = 0, KIND_SMOOTH_MAX = 1, KIND_WARP_SMOOTH = 2, KIND
 // In-plane tile and n0 chunking of one launch of kernel `kind` over a volume
 // of shape s (tu overrides the automatic choice).  cube_ok: a brick launch
 // exists for the kernel's radius and epilogue (smoothing and composition
-// kinds only).  whole_rounds: chunks may lengthen to avoid a round of few
-// workgroups; off for registrations with windows 7 and 9, whose last bits
-// depend on where chunks begin.
-Tiling choose_tiling(const fa_shape& s, KernelKind kind, const Tuning& tu = Tuning(), bool cube_ok = false,
-                     bool whole_rounds = true);
+// kinds only).
+Tiling choose_tiling(const fa_shape& s, KernelKind kind, const Tuning& tu = Tuning(), bool cube_ok = false);
 
 // Sampled Gaussian taps exp(-k^2 / 2 sigma^2), |k| <= ceil(3 sigma), normalised
 // to sum 1 (in double); sigma <= 0 gives the single tap 1.  tap_radius: the

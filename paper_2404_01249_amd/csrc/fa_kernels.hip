@@ -680,10 +680,6 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
   // sits at a slot fixed at compile time and no entry moves.  The sums run
   // oldest first.
   constexpr int UNZ = (W == 7 && TY == 16) ? W : 1;   // not the 8-row tiles of thin volumes
-  constexpr bool SWAP = W >= 7 && TY == 16;
-  // phase of the first step: a loss-only march starts W / 2 planes later
-  constexpr int PH0 = H1 == 2 * (W / 2) ? 0 : W / 2;
-  int wphase = PH0;   // plane step modulo W (rolled march)
   auto step = [&](const int zin, auto PH) __attribute__((always_inline)) {
     constexpr int ph = decltype(PH)::value;
     // slot of the j-th oldest entry of the I/J rings
@@ -715,21 +711,11 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
           float s0 = i0, s1 = j0, s2 = i0 * i0, s3 = j0 * j0, s4 = i0 * j0;
           // Fused multiply-adds spelled out: which of the oldest two planes'
           // products is rounded and which fused into it is otherwise the
-          // compiler's choice and shows in the last bits.  The oldest's is
-          // rounded, except in two of the W phases of the wide windows'
-          // 16-row marches, so that every window's results stay the same.
-          if constexpr (W > 1) {
-            const float i1 = ringI[k][ri(1)], j1 = ringJ[k][ri(1)];
-            const bool sw = SWAP && (UNZ == 1 ? wphase : (ph + PH0) % W) >= W - 2;
-            const float ia = sw ? i1 : i0, ib = sw ? i0 : i1, ja = sw ? j1 : j0, jb = sw ? j0 : j1;
-            s0 += i1;
-            s1 += j1;
-            s2 = __builtin_fmaf(ib, ib, ia * ia);
-            s3 = __builtin_fmaf(jb, jb, ja * ja);
-            s4 = __builtin_fmaf(ib, jb, ia * ja);
-          }
+          // compiler's choice, in an unrolled march one by phase, and shows in
+          // the last bits.  The oldest's is rounded at every plane, so that a
+          // voxel's sums do not depend on where its chunk begins.
 #pragma unroll
-          for (int j = 2; j < W; ++j) {
+          for (int j = 1; j < W; ++j) {
             const float i_ = ringI[k][ri(j)], j_ = ringJ[k][ri(j)];
             s0 += i_;
             s1 += j_;
@@ -903,10 +889,7 @@ __device__ __forceinline__ void grad_body(const GradArgs& A, const int tile) {
     }
   };
   if constexpr (UNZ == 1) {
-    for (int zin = zs; zin < ze; ++zin) {
-      step(zin, std::integral_constant<int, 0>{});
-      if constexpr (SWAP) wphase = wphase == W - 1 ? 0 : wphase + 1;
-    }
+    for (int zin = zs; zin < ze; ++zin) step(zin, std::integral_constant<int, 0>{});
   } else {
     // the guard is uniform across the workgroup, so the barriers inside
     // are reached by every thread or by none

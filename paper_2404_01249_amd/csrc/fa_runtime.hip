@@ -852,7 +852,7 @@ fa_status check_shape(const fa_shape& s) {
 // the two smoothing kernels make chunks below 4 planes wasteful.  (Measured
 // on the 160x192x224 pyramid: each level's time over chunks of 1 to 40
 // planes.)
-Tiling choose_tiling(const fa_shape& s, KernelKind kind, const Tuning& tu, bool cube_ok, bool whole_rounds) {
+Tiling choose_tiling(const fa_shape& s, KernelKind kind, const Tuning& tu, bool cube_ok) {
   static const int kSlots[4] = {512, 1024, 512, 512};
   static const int kMinChunk[4] = {1, 4, 4, 1};
   // Small volumes take bricks: there a launch is bound by the length of its
@@ -894,7 +894,7 @@ Tiling choose_tiling(const fa_shape& s, KernelKind kind, const Tuning& tu, bool 
   // by fewer of them take back (LNCC loss and gradient, window 5: 103 -> 85 us
   // there, 306 -> 269 at 100x320x320, 40 planes -> 50; 481 -> 491 at 120x240x640
   // for 71 -> 120, so not there).
-  if (whole_rounds && zc < s.n0 && (int64_t)plane_tiles * ((s.n0 + zc - 1) / zc) > kSlots[kind]) {
+  if (zc < s.n0 && (int64_t)plane_tiles * ((s.n0 + zc - 1) / zc) > kSlots[kind]) {
     const int most = std::max(1, kSlots[kind] / plane_tiles), fit = (s.n0 + most - 1) / most;
     if (2 * fit <= 3 * zc) zc = fit;
   }
@@ -1021,8 +1021,7 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
     lv[i].n = voxels(lv[i].shape);
     if (lv[i].shape.n0 < 2 || lv[i].shape.n1 < 2 || lv[i].shape.n2 < 2)
       return fail(FA_ESHAPE, "level " + std::to_string(i) + " has a dimension < 2");
-    lv[i].tg = choose_tiling(lv[i].shape, fa::KIND_GRAD, P->tune[0], fa::grad_cube_supported(P->p.cc_window),
-                            P->p.cc_window <= 5);
+    lv[i].tg = choose_tiling(lv[i].shape, fa::KIND_GRAD, P->tune[0], fa::grad_cube_supported(P->p.cc_window));
     lv[i].tsg = choose_tiling(lv[i].shape, fa::KIND_SMOOTH_MAX, P->tune[1],
                               fa::gauss_cube_supported(P->rg, fa::EPI_SMOOTH_MAX));
     lv[i].tsw = choose_tiling(lv[i].shape, fa::KIND_WARP_SMOOTH, P->tune[2],
