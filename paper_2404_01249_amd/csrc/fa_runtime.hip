@@ -1587,6 +1587,9 @@ fa_status fa_pair_autotune(fa_pair P, int trials) {
       if ((st = dalloc(&P->partials, (size_t)need, "loss partials")) != FA_OK) break;
       P->partials_cap = need;
     }
+    // a level of one iteration has formed no row pairs, but what is kept for its
+    // grid also serves schedules whose warp smoothing samples them
+    if ((st = make_row_pairs(P, L)) != FA_OK) break;
     IterPlan it;
     plan_iteration(P, L, it);
     fa::GradArgs ga = it.ga;
