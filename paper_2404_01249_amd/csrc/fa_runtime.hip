@@ -494,9 +494,10 @@ struct BatchTables {
   std::vector<unsigned char> host;
   std::vector<int> jac;   // live pairs with use_jac (their Eulerian launch follows stage 0)
   void* dev = nullptr;    // the uploaded copy of host, within the current chunk
-  // Every upload of a call takes a region of its own, and its host copy is
-  // kept, so that neither waits for the launches already queued; the call's
-  // closing synchronisation makes them all free again (recycle).
+  // An upload takes a region of its own, and its host copy is kept, so that
+  // neither waits for the launches already queued; a synchronisation (the call's
+  // closing one, or one when kTableBudget is full) makes them all free again
+  // (recycle).
   struct Chunk {
     unsigned char* base;
     size_t cap;
@@ -509,7 +510,12 @@ struct BatchTables {
     sent.clear();
   }
 };
+// Regions are cut from chunks of kTableChunk (or a table's size) and may take
+// kTableBudget or two tables in all: a search whose registrations end one by one
+// sends a table per end (16 bytes per workgroup of a launch: 0.9 MB for 256 of
+// 48^3).
 constexpr size_t kTableChunk = 1 << 18;
+constexpr size_t kTableBudget = 1 << 22;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -649,13 +655,29 @@ fa_status build_batch_tables(const std::vector<fa_pair>& live, BatchTables& bt) 
   return FA_OK;
 }
 
-// Copies the host image to the device.  Synchronises: the launches already
-// queued read the previous tables, and the host image may change after this.
+fa_status free_batch_tables(BatchTables& bt);
+
+// Copies the host image to a region that no queued launch reads.  Does not
+// synchronise unless the budget is full.  bt.dev and the region hold until the
+// caller has synchronised and recycles or frees them; a graph that was captured
+// on an earlier upload must not be launched after this one.
 fa_status upload_batch_tables(BatchTables& bt, hipStream_t s) {
   const size_t need = align256(std::max<size_t>(bt.host.size(), 256));
-  while (bt.chunk < bt.chunks.size() && need > bt.chunks[bt.chunk].cap - bt.used) {
-    ++bt.chunk;
-    bt.used = 0;
+  auto find = [&]() {
+    while (bt.chunk < bt.chunks.size() && need > bt.chunks[bt.chunk].cap - bt.used) {
+      ++bt.chunk;
+      bt.used = 0;
+    }
+    return bt.chunk < bt.chunks.size();
+  };
+  if (!find()) {
+    size_t held = 0;
+    for (const auto& c : bt.chunks) held += c.cap;
+    if (held + std::max(need, kTableChunk) > std::max(kTableBudget, 2 * need)) {
+      FA_HIP(hipStreamSynchronize(s));
+      bt.recycle();
+      if (!find()) FA_TRY(free_batch_tables(bt));   // every chunk is smaller than the table
+    }
   }
   if (bt.chunk == bt.chunks.size()) {
     BatchTables::Chunk c{nullptr, std::max(need, kTableChunk)};
