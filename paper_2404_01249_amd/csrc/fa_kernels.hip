@@ -1366,7 +1366,7 @@ __device__ __forceinline__ void grad_cube_body(const GradArgs& A, const int tile
   constexpr int QY = S::QY, QX = S::QX, NQ = S::NQ;
   constexpr int CY = S::CY, CX = S::CX, NC = S::NC;
   constexpr int HZ = S::HZ, NH = S::NH, NY1 = S::NY1, NX2 = S::NX2, NY2 = S::NY2, XT = S::XT;
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   float* bufA = lds;
   float* bufB = lds + S::SA;
   __shared__ double red[NT / 64];
@@ -1645,7 +1645,8 @@ __device__ __forceinline__ void gauss_cube_body(const GaussArgs& A, const int ti
   constexpr int NX = RZ * RY * TX;   // after the x-pass
   constexpr int NY = RZ * TY * TX;   // after the y-pass
   static_assert(NY <= NR, "y-pass output reuses the region buffer");
-  extern __shared__ float lds[];
+  static_assert(RX % 2 == 0 && NR % 2 == 0 && 3 * NR % 4 == 0 && NX % 4 == 0, "vector alignment");
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   float* reg = lds;            // [3][NR], later [3][NY]
   float* xo = lds + 3 * NR;    // [3][NX]
   __shared__ double red[NT / 64];
@@ -1758,7 +1759,7 @@ template <int TZ, int TY, int TX>
 __device__ __forceinline__ void compose_cube_body(const GaussArgs& A, const int tile) {
   constexpr int NT = TZ * TY * TX;
   constexpr int DZ = TZ + 2, DY = TY + 2, DX = TX + 2, DE = DZ * DY * DX;
-  extern __shared__ float lds[];   // [3][DE]
+  extern __shared__ __attribute__((aligned(16))) float lds[];   // [3][DE]
   const int tid = threadIdx.x;
   // the first brick records the iteration before its own work
   if (A.partials && tile == 0) record_iteration<NT>(A);
