@@ -21,9 +21,13 @@
  * 64-bit fixed point, so that results do not depend on the order of the
  * summation and are bitwise reproducible; that of |phi(psi(x)) - x|^2; Adam),
  * and the registration's smoothing and composition kernels.  The first
- * iteration of a level lists the level's voxels by the cell they map into.  The splat accumulates in units of 2^-32 and holds
- * sums of magnitude below 2^31, which bounds |d| and |e| far beyond any
- * volume's size.
+ * iteration of a level lists the level's voxels by the cell they map into.  The
+ * splat accumulates in units of 2^-32 and holds sums of magnitude below 2^31,
+ * which bounds |d| and |e| far beyond any volume's size.
+ *
+ * A handle holds about 135 bytes per voxel: 72 for the fields (84 with a sigma
+ * above 2), 36 per cell for the lists and 24 for sums that only a contracting
+ * warp's splat takes.
  */
 #ifndef FA_INVERSE_H_
 #define FA_INVERSE_H_
@@ -76,8 +80,8 @@ fa_status fa_inverse_get_loss(fa_inverse h, float* host_out, int capacity, int* 
 fa_status fa_inverse_eval_gradient(fa_inverse h, float* g_dev, float* loss_host);
 
 /* Splat form (a tuning and test switch): 0 (default) sums the contributions to
- * each tile of nodes in LDS; 1 adds every contribution with its own global
- * atomic (and holds an accumulator of 24 bytes per voxel).  Both add the same
+ * each tile of nodes in LDS (where the warp contracts, those of each brick of
+ * voxels); 1 adds every contribution with its own global atomic.  Both add the same
  * fixed-point integers, so results are bitwise equal.  FA_EINVAL, FA_ENOMEM,
  * FA_EHIP. */
 fa_status fa_inverse_set_splat(fa_inverse h, int direct);

@@ -58,6 +58,24 @@ __device__ __forceinline__ bool row_voxel(unsigned b, int n0, int n1, int n2, in
   return z < n0 && x < n2;
 }
 
+// Counters of a launch's workgroups, each in a 128-byte line: one, and
+// kTicketSlots below it (a counter takes about 10 ns per workgroup).
+constexpr int kTicketSlots = 32, kTicketStride = 32;
+
+// Counts workgroup blk of np in; true for the last.  One thread of each calls
+// it, after what the workgroup stores for the last one has reached memory.
+// Every counter is left at zero.
+__device__ __forceinline__ bool last_workgroup(unsigned* tickets, int blk, int np) {
+  unsigned* slot = tickets + (1 + blk % kTicketSlots) * kTicketStride;
+  const unsigned in_slot = (unsigned)(np - blk % kTicketSlots + kTicketSlots - 1) / kTicketSlots;
+  if (__hip_atomic_fetch_add(slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u != in_slot) return false;
+  __hip_atomic_store(slot, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned used = (unsigned)(np < kTicketSlots ? np : kTicketSlots);
+  if (__hip_atomic_fetch_add(tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u != used) return false;
+  __hip_atomic_store(tickets, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
 // Per-pair control block in device memory.  Kernels of one iteration read
 // and update it so that a whole iteration can be replayed (for example from a
 // captured graph) without host involvement.
@@ -243,9 +261,8 @@ hipError_t launch_partials_ratio(const double* partials, int n, double denom, fl
 // of each thread (a few per thread at 160x192x224) are not latency-bound
 // (256 workgroups took 33 us for 6.9 M values, 2048 take 9 us).
 constexpr int kMeanBlocks = 2048;
-// Counters of the means' workgroups, each in a 128-byte line: per image one and
-// kTicketSlots below it.
-constexpr int kTicketSlots = 32, kTicketStride = 32, kTicketCount = 2 * (kTicketSlots + 1);
+// Counters of the means' workgroups (last_workgroup), per image.
+constexpr int kTicketCount = 2 * (kTicketSlots + 1);
 constexpr size_t kTicketWords = (size_t)kTicketCount * kTicketStride;
 
 bool grad_tile_supported(int ty, int tx);

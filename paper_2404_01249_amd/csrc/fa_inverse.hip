@@ -7,6 +7,7 @@
 #include <cmath>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "fa.h"
@@ -31,7 +32,7 @@ constexpr float kFixClamp = 1073741824.0f;
 constexpr int kInvThreads = 256;
 constexpr int kInvMaxBlocks = 4096;
 constexpr int64_t kSmallTileVoxels = 300000;
-constexpr int kDirMaxBlocks = 2 * kInvMaxBlocks;   // loss partials of k_inv_direction
+constexpr int kDirMaxBlocks = 2 * kInvMaxBlocks;   // workgroups of k_inv_direction; one loss partial more
 
 // Trilinear cell of position p on an n0 x n1 x n2 grid: flat corner indices
 // and weights in the order (b0, b1, b2) = 000, 001, ..., 111; corners off the
@@ -271,24 +272,37 @@ __global__ void __launch_bounds__(kInvThreads) k_inv_dir(const DirArgs A, unsign
 // number in `count`.  k_inv_direction then gives each tile of nodes to one
 // workgroup, which takes every voxel listed in the tile's cells, sums its
 // contributions in LDS and goes on to the direction: no global atomics and no
-// accumulator in memory.  (Gradient at 160x192x224: 904 us when bricks of
+// sums in memory.  (Gradient at 160x192x224: 904 us when bricks of
 // voxels were summed in LDS and added to memory with one 64-bit atomic per
 // touched node and component, six per voxel, and a second kernel read the sums;
 // 297 us here.  96x112x112: 174 -> 64; 40x48x56: 35 -> 25.)
 //
-// A cell with more than kSlots voxels (a strongly contracting or wild warp) is
-// not walked through its list: its tile goes over the bricks of voxels whose
-// box of cells meets the tile.
+// A cell with more than kSlots voxels (a contracting or wild warp) is "crowded":
+// it is not walked through its list, its tile goes over the bricks of voxels
+// whose box of cells meets the tile.  Where a map contracts, that would give a
+// few tiles all of the work, so a level with many such voxels (crowded_level)
+// takes the bricks themselves as items (brick_body).
 constexpr int kSlots = 8;
 constexpr int kBZ = 4, kBY = 8, kBX = 16, kBrick = kBZ * kBY * kBX;
+constexpr int kTX = 16;         // nodes of a tile along n2
+constexpr int kBoxTiles = 128;  // tiles that a brick's box may meet in a crowded level
+constexpr int kReady = 16;      // tiles whose nodes a workgroup takes between barriers
 
 struct Plan {
   unsigned* count;      // [cells]
+  int* need;            // [tiles]: bricks whose box meets the tile
+  int* left;            // [tiles]: of them, done so far; left at zero
+  int* crowded;         // [tiles]: whether a cell of the tile is crowded
+  int* total;           // voxels past kSlots of their cells, whether a box meets more than kBoxTiles tiles
+                        // (count, need, left, crowded and total lie one after the other and are cleared for each level)
   int4* slots;          // [2][cells]
   int4* box;            // [2][bricks]: lowest cell, highest cell (+1 each), empty where low > high
   double* outside;      // [blocks]: sum of |d|^2 over voxels whose sample has no corner on the grid
+  double* tile_loss;    // [tiles]
+  unsigned* tickets;    // of a crowded level's tiles
   size_t cells;
-  int bricks;
+  int bricks, tiles;
+  int tile_log;         // tiles are 2^tile_log nodes along n0 and n1
 };
 
 // Cells are numbered -1 .. n-1 per axis; cell index of (c0, c1, c2).
@@ -305,6 +319,44 @@ __device__ __forceinline__ bool plan_cell(float p0, float p1, float p2, int n0, 
   return c0 >= -1 && c0 < n0 && c1 >= -1 && c1 < n1 && c2 >= -1 && c2 < n2;
 }
 
+// Adds one to *c and returns what this thread found; one atomic where the whole
+// wavefront counts into one cell.
+__device__ __forceinline__ unsigned count_in(unsigned* c) {
+  const unsigned long long active = __ballot(true);
+  unsigned* const first = reinterpret_cast<unsigned*>(
+      ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned long long)c >> 32)) << 32) |
+      (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned long long)c));
+  if (__ballot(c == first) != active) return atomicAdd(c, 1u);
+  const int lane = threadIdx.x & 63, before = __popcll(active & ((1ull << lane) - 1));
+  unsigned r = 0u;
+  if (before == 0) r = atomicAdd(c, (unsigned)__popcll(active));
+  return (unsigned)__builtin_amdgcn_readfirstlane((int)r) + before;
+}
+
+// The tiles that hold a node which a brick contributes to: its box of cells
+// (Plan::box) widened by one node above, clipped to the grid.
+struct TileRange {
+  int z, y, x, nz, ny, nx;   // first tile, and how many per axis
+  __device__ __forceinline__ int count() const { return nz * ny * nx; }
+};
+__device__ __forceinline__ TileRange tiles_of(int4 lo, int4 hi, int n0, int n1, int n2, int tile_log) {
+  auto axis = [](int l, int h, int n, int size, int& first, int& many) {
+    first = max(l - 1, 0) / size;
+    many = min(h, n - 1) / size - first + 1;
+  };
+  TileRange r;
+  const int size = 1 << tile_log;
+  axis(lo.x, hi.x, n0, size, r.z, r.nz);
+  axis(lo.y, hi.y, n1, size, r.y, r.ny);
+  axis(lo.z, hi.z, n2, kTX, r.x, r.nx);
+  if (lo.x > hi.x) r.nz = 0;   // no voxel of the brick falls on the grid
+  return r;
+}
+__device__ __forceinline__ int tile_at(const TileRange& r, int k, int tiles_y, int tiles_x) {
+  const int x = k % r.nx, y = k / r.nx % r.ny, z = k / (r.nx * r.ny);
+  return ((r.z + z) * tiles_y + r.y + y) * tiles_x + r.x + x;
+}
+
 __global__ void __launch_bounds__(kInvThreads) k_inv_plan(const float* __restrict__ d, const Plan P, int n0, int n1,
                                                           int n2) {
   __shared__ int bb[kInvThreads / 64][6];
@@ -312,7 +364,10 @@ __global__ void __launch_bounds__(kInvThreads) k_inv_plan(const float* __restric
   const int N = n0 * n1 * n2;
   const int ty = (n1 + kBY - 1) / kBY, tx = (n2 + kBX - 1) / kBX;
   const int tid = threadIdx.x;
+  const int size = 1 << P.tile_log;
+  const int tzs = (n0 + size - 1) / size, tys = (n1 + size - 1) / size, txs = (n2 + kTX - 1) / kTX;
   double outside = 0.0;
+  int past = 0;
   for (int b = blockIdx.x; b < P.bricks; b += gridDim.x) {
     const int bx = b % tx, by = (b / tx) % ty, bz = b / (tx * ty);
     int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {-1, -1, -1};
@@ -328,7 +383,13 @@ __global__ void __launch_bounds__(kInvThreads) k_inv_plan(const float* __restric
         continue;
       }
       const size_t ci = cell_index(c[0], c[1], c[2], n1, n2);
-      const unsigned r = atomicAdd(&P.count[ci], 1u);
+      const unsigned r = count_in(&P.count[ci]);
+      past += r >= kSlots;
+      if (r == kSlots)   // the cell's own tile, and those whose lower border it is
+        for (int q = max(c[0], 0) >> P.tile_log; q <= min((c[0] + 1) >> P.tile_log, tzs - 1); ++q)
+          for (int v = max(c[1], 0) >> P.tile_log; v <= min((c[1] + 1) >> P.tile_log, tys - 1); ++v)
+            for (int u = max(c[2], 0) / kTX; u <= min((c[2] + 1) / kTX, txs - 1); ++u)
+              P.crowded[(q * tys + v) * txs + u] = 1;
       if (r < kSlots) reinterpret_cast<int*>(P.slots + (r < 4 ? 0 : P.cells) + ci)[r & 3] = i;
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
@@ -350,17 +411,185 @@ __global__ void __launch_bounds__(kInvThreads) k_inv_plan(const float* __restric
         bb[tid >> 6][3 + a] = hi[a];
       }
     __syncthreads();
-    if (tid < 2) {   // thread 0: lowest cell, thread 1: highest
-      int v[3] = {bb[0][3 * tid], bb[0][3 * tid + 1], bb[0][3 * tid + 2]};
-      for (int w = 1; w < kInvThreads / 64; ++w)
+    int4 low = make_int4(bb[0][0], bb[0][1], bb[0][2], 0), high = make_int4(bb[0][3], bb[0][4], bb[0][5], 0);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) v[a] = tid == 0 ? min(v[a], bb[w][a]) : max(v[a], bb[w][3 + a]);
-      P.box[(size_t)tid * P.bricks + b] = make_int4(v[0], v[1], v[2], 0);
+    for (int w = 1; w < kInvThreads / 64; ++w) {
+      low = make_int4(min(low.x, bb[w][0]), min(low.y, bb[w][1]), min(low.z, bb[w][2]), 0);
+      high = make_int4(max(high.x, bb[w][3]), max(high.y, bb[w][4]), max(high.z, bb[w][5]), 0);
+    }
+    if (tid == 0) {
+      P.box[b] = low;
+      P.box[(size_t)P.bricks + b] = high;
+    }
+    const TileRange r = tiles_of(low, high, n0, n1, n2, P.tile_log);
+    if (r.count() > kBoxTiles) {
+      if (tid == 0) P.total[1] = 1;
+    } else if (tid < r.count()) {
+      atomicAdd(&P.need[tile_at(r, tid, tys, txs)], 1);
     }
     __syncthreads();
   }
   const double s = block_sum<kInvThreads>(outside, red);
   if (tid == 0) P.outside[blockIdx.x] = s;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) past += __shfl_xor(past, o, 64);
+  if ((tid & 63) == 0 && past) atomicAdd(&P.total[0], past);
+}
+
+// Whether the bricks are the items of a level of N voxels: where one in 128 is
+// past kSlots of its cell, and no brick's box meets more tiles than kBoxTiles
+// (a wild map; its direction then walks, however crowded it is).  Maps p -> c +
+// (1 - k)(p - c) with some noise, gradient in us by lists and by bricks: at
+// 160x192x224 k = 0.48 (one in 360) 592 and 694, k = 0.5 (one in 42) 822 and 788;
+// at 128^3 k = 0.48 276 and 291, k = 0.5 320 and 291; at 64^3 k = 0.45 (one in 145)
+// 84 and 86, k = 0.48 (one in 33) 105 and 87.
+__device__ __forceinline__ bool crowded_level(const Plan& P, int N) {
+  return __builtin_amdgcn_readfirstlane(P.total[0]) > N / 128 && __builtin_amdgcn_readfirstlane(P.total[1]) == 0;
+}
+
+// The splat by bricks, for a crowded level.  A brick's voxels go into a box of few
+// nodes: the workgroup sums them there in LDS (the same integers, so the sums are
+// the same) and adds the box to acc with one atomic per node and component; a
+// brick whose box is larger than that adds directly.  Then it counts itself in at
+// the tiles that its box meets, and a tile whose last brick this is goes on to the
+// direction here.  Which workgroup that is differs from run to run, so a tile's
+// loss goes to memory and the last tile's workgroup sums them in order; nothing
+// waits for another workgroup.  Tiles that no brick meets come at the end.  (The
+// maps above, k = 0.55, 0.7, 0.9 and all voxels in one cell: at 160x192x224 639,
+// 606, 654 and 905 us, with the tiles' walks alone 897, 1158, 10277 and 26706, as
+// two kernels with an accumulator for every map 629, 609, 688 and 891; at 128^3
+// 249, 221, 217 and 298, 386, 727, 3636 and 8136, 203, 200, 221 and 263; at 64^3
+// 69, 63, 55 and 80, 118, 191, 703 and 1586, 37, 38, 45 and 53: few bricks, whose
+// steps wait for one another here.)
+template <int TZ, int TY, int NT, int BOX>   // BOX: nodes that `box` holds
+__device__ __forceinline__ void brick_body(const DirArgs& A, const Plan& P, unsigned long long* __restrict__ acc,
+                                           unsigned long long* box, int* ready, int* word, double* red, float ibc1,
+                                           float ibc2, double& loss) {
+  constexpr int VPT = kBrick / NT;
+  const int n0 = A.n0, n1 = A.n1, n2 = A.n2, N = n0 * n1 * n2;
+  const int tys = (n1 + TY - 1) / TY, txs = (n2 + kTX - 1) / kTX;
+  const int bty = (n1 + kBY - 1) / kBY, btx = (n2 + kBX - 1) / kBX;
+  const int tid = threadIdx.x;
+
+  // the direction at the nodes of the n tiles in `ready`, whose sums are complete
+  __shared__ double part[kReady][NT / 64];
+  auto finish = [&](int n) {
+    for (int k0 = 0; k0 < n; k0 += kReady) {
+      const int m = min(kReady, n - k0);
+      for (int k = 0; k < m; ++k) {
+        const int t = __builtin_amdgcn_readfirstlane(ready[k0 + k]);
+        const int x0 = t % txs * kTX, y0 = t / txs % tys * TY, z0 = t / (txs * tys) * TZ;
+        double mine = 0.0;
+        for (int q = tid; q < TZ * TY * kTX; q += NT) {
+          const int z = z0 + q / (TY * kTX), y = y0 + q / kTX % TY, x = x0 + q % kTX;
+          if (z >= n0 || y >= n1 || x >= n2) continue;
+          const int i = (z * n1 + y) * n2 + x;
+          float s[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            unsigned long long* const sum = &acc[(size_t)c * N + i];
+            const unsigned long long v = __hip_atomic_load(sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (v) __hip_atomic_store(sum, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s[c] = from_fixed(v);
+          }
+          mine += (double)node_direction(A, z, y, x, s, A.e[i], A.e[N + i], A.e[2 * N + i], ibc1, ibc2);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mine += __shfl_down(mine, o, 64);
+        if ((tid & 63) == 0) part[k][tid >> 6] = mine;
+      }
+      if (tid == 0) *word = 0;
+      __syncthreads();
+      if (tid < m) {
+        double tile = 0.0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) tile += part[tid][w];
+        const int t = ready[k0 + tid];
+        __hip_atomic_store(&P.tile_loss[t], tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (fa::last_workgroup(P.tickets, t, P.tiles)) *word = 1;
+      }
+      __syncthreads();
+      if (*word) {
+        double all = 0.0;
+        for (int k = tid; k < P.tiles; k += NT)
+          all += __hip_atomic_load(&P.tile_loss[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        all = block_sum<NT>(all, red);
+        if (tid == 0) A.part[gridDim.x] = -all;
+      }
+      __syncthreads();   // part, word and ready are written again
+    }
+  };
+
+  for (int b = blockIdx.x; b < P.bricks; b += gridDim.x) {
+    const int4 lo = P.box[b], hi = P.box[(size_t)P.bricks + b];   // cells + 1
+    const TileRange tr = tiles_of(lo, hi, n0, n1, n2, P.tile_log);
+    if (tr.count() == 0) continue;   // its voxels' loss is in P.outside
+    // the box's nodes, clipped to the grid
+    const int b0 = max(lo.x - 1, 0), b1 = max(lo.y - 1, 0), b2 = max(lo.z - 1, 0);
+    const int s0 = min(hi.x, n0 - 1) - b0 + 1, s1 = min(hi.y, n1 - 1) - b1 + 1, s2 = min(hi.z, n2 - 1) - b2 + 1;
+    const int nb = s0 * s1 * s2;
+    const bool in_lds = nb <= BOX;
+    if (in_lds)
+      for (int q = tid; q < 3 * nb; q += NT) box[q] = 0ull;
+    if (tid == 0) *word = 0;
+    __syncthreads();
+    const int bx = b % btx, by = b / btx % bty, bz = b / (btx * bty);
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+      const int l = tid + u * NT;
+      const int z = bz * kBZ + l / (kBY * kBX), y = by * kBY + (l / kBX) % kBY, x = bx * kBX + l % kBX;
+      if (z >= n0 || y >= n1 || x >= n2) continue;
+      const int i = (z * n1 + y) * n2 + x;
+      const float d0 = A.d[i], d1 = A.d[N + i], d2 = A.d[2 * N + i];
+      const float p0 = (float)z + d0, p1 = (float)y + d1, p2 = (float)x + d2;
+      int cz, cy, cx;
+      if (!plan_cell(p0, p1, p2, n0, n1, n2, cz, cy, cx)) continue;
+      const Cell c = cell_of(p0, p1, p2, n0, n1, n2);
+      const float r[3] = {d0 + sample(A.e, c), d1 + sample(A.e + N, c), d2 + sample(A.e + 2 * N, c)};
+      loss += (double)(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (!((c.ok >> k) & 1u) || c.w[k] == 0.0f) continue;
+        const float w2 = 2.0f * c.w[k];
+        if (in_lds) {
+          const int q = ((cz + (k >> 2) - b0) * s1 + (cy + ((k >> 1) & 1) - b1)) * s2 + (cx + (k & 1) - b2);
+#pragma unroll
+          for (int a = 0; a < 3; ++a) atomicAdd(&box[a * nb + q], to_fixed(w2 * r[a]));
+        } else {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) atomicAdd(&acc[(size_t)a * N + c.idx[k]], to_fixed(w2 * r[a]));
+        }
+      }
+    }
+    __syncthreads();
+    if (in_lds)
+      for (int q = tid; q < nb; q += NT) {
+        const int x = b2 + q % s2, y = b1 + q / s2 % s1, z = b0 + q / (s1 * s2);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+          if (const unsigned long long v = box[a * nb + q]) atomicAdd(&acc[(size_t)a * N + (z * n1 + y) * n2 + x], v);
+      }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's sums have reached memory
+    __syncthreads();
+    if (tid < tr.count()) {
+      const int t = tile_at(tr, tid, tys, txs);
+      if (__hip_atomic_fetch_add(&P.left[t], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == P.need[t]) {
+        __hip_atomic_store(&P.left[t], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ready[atomicAdd(word, 1)] = t;
+      }
+    }
+    __syncthreads();
+    const int n = __builtin_amdgcn_readfirstlane(*word);
+    __syncthreads();   // word is written again
+    finish(n);
+  }
+  for (int t = blockIdx.x; t < P.tiles; t += gridDim.x)
+    if (__builtin_amdgcn_readfirstlane(P.need[t]) == 0) {
+      if (tid == 0) ready[0] = t;
+      __syncthreads();
+      finish(1);
+    }
 }
 
 // Exact i / dv for 0 <= i < 2^31 (launch: mul = floor(2^(31 + s) / dv) + 1, s = ceil(log2 dv)).
@@ -378,14 +607,18 @@ __device__ __forceinline__ int fast_div(int i, FastDiv f) { return (int)(__umulh
 // per SIMD (80 VGPRs, a few spilled) hide more of the latency than the five of
 // an unbounded allocation (322 us); 4 x 8 x 16 tiles take 355, 8 x 8 x 32 575.
 template <int TZ, int TY, int TX, int NT>
-__global__ void __launch_bounds__(NT, 6) k_inv_direction(const DirArgs A, const Plan P, FastDiv by_row, FastDiv by_plane) {
+__global__ void __launch_bounds__(NT, 6) k_inv_direction(const DirArgs A, const Plan P, unsigned long long* all_acc,
+                                                         FastDiv by_row, FastDiv by_plane) {
+  static_assert(TX == kTX && kBrick % NT == 0 && NT >= kBoxTiles, "tile and workgroup shape");
   constexpr int CY = TY + 1, CX = TX + 1, CELLS = (TZ + 1) * CY * CX, NODES = TZ * TY * TX;
   constexpr int SY = TY + 2, SX = TX + 2, SN = (TZ + 2) * SY * SX;
-  __shared__ unsigned long long acc[3 * NODES];
+  constexpr int BOX = NODES < 512 ? 512 : NODES;   // nodes that a brick's box may have in LDS
+  __shared__ unsigned long long acc[3 * BOX];
   __shared__ float es[3 * SN];
+  __shared__ int ready[kBoxTiles];
   __shared__ double red[NT / 64];
   __shared__ unsigned long long hit[NT / 64];
-  __shared__ int crowded;
+  __shared__ int word;
   const int n0 = A.n0, n1 = A.n1, n2 = A.n2, N = n0 * n1 * n2;
   const int tid = threadIdx.x;
   if (!A.grad_only && blockIdx.x == 0 && tid < fa::kMSlots) A.ctl->mslot[tid * fa::kMStride] = 0u;
@@ -394,8 +627,13 @@ __global__ void __launch_bounds__(NT, 6) k_inv_direction(const DirArgs A, const 
   const int ty = (n1 + TY - 1) / TY, tx = (n2 + TX - 1) / TX, tiles = (n0 + TZ - 1) / TZ * ty * tx;
   double loss = tid == 0 ? P.outside[blockIdx.x] : 0.0;
   // every XCD takes a contiguous range of tiles (neighbours share border cells and gathers in its L2)
-  const int G = gridDim.x, xq = G / 8, xr = G % 8, xb = blockIdx.x % 8;
-  for (int t = xb * xq + min(xb, xr) + blockIdx.x / 8; t < tiles; t += G) {
+  const int G = gridDim.x;
+  const int past = __builtin_amdgcn_readfirstlane(P.total[0]);
+
+  // The nodes of tile t, from the lists of its cells or, where one is crowded, from
+  // the bricks (walk).  Two bodies, as the walk in the middle of the one for lists
+  // cost it registers (328 us against 319 at 160x192x224).
+  auto body = [&](int t, auto walk) __attribute__((always_inline)) {
     const int x0 = t % tx * TX, y0 = t / tx % ty * TY, z0 = t / (tx * ty) * TZ;
     for (int q = tid; q < 3 * NODES; q += NT) acc[q] = 0ull;
     for (int q = tid; q < SN; q += NT) {
@@ -405,7 +643,6 @@ __global__ void __launch_bounds__(NT, 6) k_inv_direction(const DirArgs A, const 
 #pragma unroll
       for (int c = 0; c < 3; ++c) es[c * SN + q] = in ? A.e[c * N + i] : 0.0f;
     }
-    if (tid == 0) crowded = 0;
     __syncthreads();
 
     // voxel with displacement (d0, d1, d2) to position p in the tile's cell (lz, ly, lx), 0 = the border
@@ -440,36 +677,33 @@ __global__ void __launch_bounds__(NT, 6) k_inv_direction(const DirArgs A, const 
       }
     };
 
-    for (int q = tid; q < CELLS; q += NT) {
-      const int lz = q / (CY * CX), ly = q / CX % CY, lx = q % CX;
-      const int cz = z0 - 1 + lz, cy = y0 - 1 + ly, cx = x0 - 1 + lx;
-      if (cz >= n0 || cy >= n1 || cx >= n2) continue;
-      const size_t ci = cell_index(cz, cy, cx, n1, n2);
-      const int4 a = P.slots[ci];   // not waiting for the count: entries past it are ignored
-      const int n = (int)min(P.count[ci], (unsigned)kSlots + 1u);
-      if (n == 0) continue;
-      if (n > kSlots) {
-        crowded = 1;
-        continue;
-      }
-      // in the order of the voxels, so that the loss does not depend on the order of the listing
-      int i = -1;
-      for (int j = 0; j < n; ++j) {
-        int next = 0x7fffffff;
-        auto after = [&](int v, int k) { next = k < n && v > i ? min(next, v) : next; };
-        after(a.x, 0), after(a.y, 1), after(a.z, 2), after(a.w, 3);
-        if (n > 4) {
-          const int4 b = P.slots[P.cells + ci];
-          after(b.x, 4), after(b.y, 5), after(b.z, 6), after(b.w, 7);
+    if constexpr (!decltype(walk)::value) {
+      for (int q = tid; q < CELLS; q += NT) {
+        const int lz = q / (CY * CX), ly = q / CX % CY, lx = q % CX;
+        const int cz = z0 - 1 + lz, cy = y0 - 1 + ly, cx = x0 - 1 + lx;
+        if (cz >= n0 || cy >= n1 || cx >= n2) continue;
+        const size_t ci = cell_index(cz, cy, cx, n1, n2);
+        const int4 a = P.slots[ci];   // not waiting for the count: entries past it are ignored
+        const int n = (int)min(P.count[ci], (unsigned)kSlots);   // never more in a tile that is not crowded
+        if (n == 0) continue;
+        // in the order of the voxels, so that the loss does not depend on the order of the listing
+        int i = -1;
+        for (int j = 0; j < n; ++j) {
+          int next = 0x7fffffff;
+          auto after = [&](int v, int k) { next = k < n && v > i ? min(next, v) : next; };
+          after(a.x, 0), after(a.y, 1), after(a.z, 2), after(a.w, 3);
+          if (n > 4) {
+            const int4 b = P.slots[P.cells + ci];
+            after(b.x, 4), after(b.y, 5), after(b.z, 6), after(b.w, 7);
+          }
+          i = next;
+          const int z = fast_div(i, by_plane), yx = i - z * (n1 * n2), y = fast_div(yx, by_row), x = yx - y * n2;
+          const float d0 = A.d[i], d1 = A.d[N + i], d2 = A.d[2 * N + i];
+          take(d0, d1, d2, (float)z + d0, (float)y + d1, (float)x + d2, lz, ly, lx);
         }
-        i = next;
-        const int z = fast_div(i, by_plane), yx = i - z * (n1 * n2), y = fast_div(yx, by_row), x = yx - y * n2;
-        const float d0 = A.d[i], d1 = A.d[N + i], d2 = A.d[2 * N + i];
-        take(d0, d1, d2, (float)z + d0, (float)y + d1, (float)x + d2, lz, ly, lx);
       }
-    }
-    __syncthreads();
-    if (crowded) {
+      __syncthreads();
+    } else {
       const int bty = (n1 + kBY - 1) / kBY, btx = (n2 + kBX - 1) / kBX;
       for (int b0 = 0; b0 < P.bricks; b0 += NT) {
         bool meets = false;
@@ -494,7 +728,7 @@ __global__ void __launch_bounds__(NT, 6) k_inv_direction(const DirArgs A, const 
               if (!plan_cell(p0, p1, p2, n0, n1, n2, cz, cy, cx)) continue;
               const int lz = cz - z0 + 1, ly = cy - y0 + 1, lx = cx - x0 + 1;
               if ((unsigned)lz > (unsigned)TZ || (unsigned)ly > (unsigned)TY || (unsigned)lx > (unsigned)TX) continue;
-              if (P.count[cell_index(cz, cy, cx, n1, n2)] > (unsigned)kSlots) take(d0, d1, d2, p0, p1, p2, lz, ly, lx);
+              take(d0, d1, d2, p0, p1, p2, lz, ly, lx);
             }
           }
         __syncthreads();   // hit is written again
@@ -510,6 +744,20 @@ __global__ void __launch_bounds__(NT, 6) k_inv_direction(const DirArgs A, const 
       loss += (double)node_direction(A, z, y, x, s, es[u], es[SN + u], es[2 * SN + u], ibc1, ibc2);
     }
     __syncthreads();   // acc and es are written again
+  };
+
+  if (crowded_level(P, N)) {
+    brick_body<TZ, TY, NT, BOX>(A, P, all_acc, acc, ready, &word, red, ibc1, ibc2, loss);
+  } else {
+    // every XCD takes a contiguous range of tiles (neighbours share border cells and gathers in its L2)
+    const int G = gridDim.x, xq = G / 8, xr = G % 8, xb = blockIdx.x % 8;
+    const int first = xb * xq + min(xb, xr) + blockIdx.x / 8;
+    for (int t = first; t < tiles; t += G)
+      if (past == 0 || __builtin_amdgcn_readfirstlane(P.crowded[t]) == 0) body(t, std::false_type{});
+    if (past)
+      for (int t = first; t < tiles; t += G)
+        if (__builtin_amdgcn_readfirstlane(P.crowded[t])) body(t, std::true_type{});
+    if (blockIdx.x == 0 && tid == 0) A.part[G] = 0.0;
   }
   const double s = block_sum<NT>(loss, red);
   if (tid == 0) A.part[blockIdx.x] = -s;
@@ -559,10 +807,10 @@ struct fa_inverse_s {
   float* a = nullptr;      // Adam direction
   float* tmp = nullptr;    // smoothed direction, then the composed field
   float* wide = nullptr;   // [3][cap] scratch of the smoothing passes with a radius above 6
-  unsigned long long* acc = nullptr;   // accumulator of the direct splat [3][cap], zero between iterations
+  unsigned long long* acc = nullptr;   // sums of the splat by bricks and the direct one [3][cap], zero between iterations
   Plan plan{};             // voxels by cell of level plan_level
-  size_t plan_cells = 0;   // capacities of its buffers
-  int plan_bricks = 0;
+  size_t plan_words = 0, plan_cells = 0;   // capacities of its buffers
+  int plan_bricks = 0, plan_tiles = 0;
   int plan_level = -1;     // -1: none listed (or only inside a captured graph)
   bool captured = false;   // a call was captured: its replays list their own level, so each call lists anew
   Ctl* ctl = nullptr;
@@ -575,7 +823,7 @@ struct fa_inverse_s {
   int rg = 0, rw = 0, off_g = 0, off_w = 0, off_one = 0;
   int cur_level = 0, cur_iter = 0, t_done = 0, iters_done = 0;
   bool scheduled = false;
-  bool splat_direct = false;   // the per-voxel global-atomic splat instead of the brick form
+  bool splat_direct = false;   // the per-voxel global-atomic splat instead of the listed one
 };
 
 namespace {
@@ -587,13 +835,13 @@ void free_levels(fa_inverse H) {
 }
 
 void free_plan(fa_inverse H) {
-  if (H->plan.count) (void)hipFree(H->plan.count);
-  if (H->plan.slots) (void)hipFree(H->plan.slots);
-  if (H->plan.box) (void)hipFree(H->plan.box);
-  if (H->plan.outside) (void)hipFree(H->plan.outside);
+  const Plan& P = H->plan;
+  void* const bufs[] = {P.count, P.slots, P.box, P.outside, P.tile_loss, P.tickets};
+  for (void* b : bufs)
+    if (b) (void)hipFree(b);
   H->plan = Plan{};
-  H->plan_cells = 0;
-  H->plan_bricks = 0;
+  H->plan_words = H->plan_cells = 0;
+  H->plan_bricks = H->plan_tiles = 0;
   H->plan_level = -1;
 }
 
@@ -602,7 +850,35 @@ int bricks_of(const fa_shape& s) {
   return (s.n0 + kBZ - 1) / kBZ * ((s.n1 + kBY - 1) / kBY) * ((s.n2 + kBX - 1) / kBX);
 }
 
-// The direct splat's accumulator, zeroed.
+// Tiles of k_inv_direction: 8 x 8 x 16 nodes, or 4 x 4 x 16 below
+// kSmallTileVoxels, where the larger ones give a CU less than one workgroup
+// (40x48x56: 25 us against 30 with the larger; 80x96x112, 860,000 voxels: 58
+// with either).
+bool small_tiles(const fa_shape& s) { return fa::voxels(s) < kSmallTileVoxels; }
+
+int dir_tiles(const fa_shape& s) {
+  const int t = small_tiles(s) ? 4 : 8;
+  return (s.n0 + t - 1) / t * ((s.n1 + t - 1) / t) * ((s.n2 + kTX - 1) / kTX);
+}
+int dir_blocks(const fa_shape& s) { return std::min(dir_tiles(s), kDirMaxBlocks); }
+
+// Words that are cleared for each level: Plan::count, need, left, crowded and total.
+size_t plan_words(const fa_shape& s) { return (size_t)cells_of(s) + 3 * (size_t)dir_tiles(s) + 2; }
+
+// The lists' extents on a level, in buffers that hold its largest.
+Plan plan_of(Plan P, const fa_shape& s) {
+  P.cells = (size_t)cells_of(s);
+  P.bricks = bricks_of(s);
+  P.tiles = dir_tiles(s);
+  P.tile_log = small_tiles(s) ? 2 : 3;
+  P.need = reinterpret_cast<int*>(P.count) + P.cells;
+  P.left = P.need + P.tiles;
+  P.crowded = P.left + P.tiles;
+  P.total = P.crowded + P.tiles;
+  return P;
+}
+
+// The sums in memory, zeroed.
 fa_status ensure_acc(fa_inverse H) {
   if (H->acc) return FA_OK;
   FA_TRY(ialloc(&H->acc, (size_t)(3 * H->cap), "splat accumulator"));
@@ -645,21 +921,9 @@ bool schedule_done(const fa_inverse H) {
   return H->cur_level == (int)H->levels.size() - 1 && H->cur_iter >= H->levels.back().iters;
 }
 
-// Tiles of k_inv_direction: 8 x 8 x 16 nodes, or 4 x 4 x 16 below
-// kSmallTileVoxels, where the larger ones give a CU less than one workgroup
-// (40x48x56: 25 us against 30 with the larger; 80x96x112, 860,000 voxels: 58
-// with either).
-bool small_tiles(const fa_shape& s) { return fa::voxels(s) < kSmallTileVoxels; }
-
-int dir_blocks(const fa_shape& s) {
-  const int t = small_tiles(s) ? 4 : 8;
-  const int64_t tiles = (int64_t)((s.n0 + t - 1) / t) * ((s.n1 + t - 1) / t) * ((s.n2 + 15) / 16);
-  return (int)std::min<int64_t>(tiles, kDirMaxBlocks);
-}
-
 // Loss partials of one direction (launch_direction).
 int direction_partials(const fa_inverse H, const ILevel& L) {
-  return H->splat_direct ? 2 * inv_blocks(L.n) : dir_blocks(L.shape);
+  return H->splat_direct ? 2 * inv_blocks(L.n) : dir_blocks(L.shape) + 1;
 }
 
 FastDiv fast_divisor(unsigned dv) {   // dv >= 2
@@ -697,21 +961,19 @@ fa_status launch_direction(fa_inverse H, const ILevel& L, float* out, int grad_o
     return FA_OK;
   }
   const int b = dir_blocks(s);
-  Plan P = H->plan;
-  P.cells = (size_t)cells_of(s);
-  P.bricks = bricks_of(s);
+  const Plan P = plan_of(H->plan, s);
   H->captured |= fa::capturing(H->stream);
   if (H->captured || H->plan_level != H->cur_level) {
-    FA_HIP(fa::launch_fill(reinterpret_cast<float*>(P.count), 0.0f, (int64_t)P.cells, H->stream));
+    FA_HIP(fa::launch_fill(reinterpret_cast<float*>(P.count), 0.0f, (int64_t)plan_words(s), H->stream));
     hipLaunchKernelGGL(k_inv_plan, dim3(b), dim3(kInvThreads), 0, H->stream, L.d, P, s.n0, s.n1, s.n2);
     FA_HIP(hipGetLastError());
     H->plan_level = H->captured ? -1 : H->cur_level;
   }
   const FastDiv by_row = fast_divisor(s.n2), by_plane = fast_divisor((unsigned)(s.n1 * s.n2));
   if (small_tiles(s))
-    hipLaunchKernelGGL((k_inv_direction<4, 4, 16, 256>), dim3(b), dim3(256), 0, H->stream, A, P, by_row, by_plane);
+    hipLaunchKernelGGL((k_inv_direction<4, 4, 16, 256>), dim3(b), dim3(256), 0, H->stream, A, P, H->acc, by_row, by_plane);
   else
-    hipLaunchKernelGGL((k_inv_direction<8, 8, 16, 512>), dim3(b), dim3(512), 0, H->stream, A, P, by_row, by_plane);
+    hipLaunchKernelGGL((k_inv_direction<8, 8, 16, 512>), dim3(b), dim3(512), 0, H->stream, A, P, H->acc, by_row, by_plane);
   FA_HIP(hipGetLastError());
   return FA_OK;
 }
@@ -900,30 +1162,37 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
     H->partials = nullptr;
     H->cap = 0;
     for (int k = 0; k < (wide ? 6 : 5); ++k) FA_TRY(ialloc(bufs[k], (size_t)(3 * need), "state"));
-    FA_TRY(ialloc(&H->partials, (size_t)kDirMaxBlocks, "cost partials"));
+    FA_TRY(ialloc(&H->partials, (size_t)kDirMaxBlocks + 1, "cost partials"));
     H->cap = need;
   }
-  size_t cells = 0;
-  int bricks = 0;
+  size_t words = 0, cells = 0;
+  int bricks = 0, tiles = 0;
   for (auto& L : lv) {
+    words = std::max(words, plan_words(L.shape));
     cells = std::max(cells, (size_t)cells_of(L.shape));
     bricks = std::max(bricks, bricks_of(L.shape));
+    tiles = std::max(tiles, dir_tiles(L.shape));
   }
-  if (cells > H->plan_cells || bricks > H->plan_bricks) {
+  if (words > H->plan_words || cells > H->plan_cells || bricks > H->plan_bricks || tiles > H->plan_tiles) {
     FA_HIP(hipStreamSynchronize(H->stream));
     free_plan(H);
-    FA_TRY(ialloc(&H->plan.count, cells, "cell counts"));
+    const size_t tickets = (size_t)(fa::kTicketSlots + 1) * fa::kTicketStride;
+    FA_TRY(ialloc(&H->plan.count, words, "cell counts"));
     FA_TRY(ialloc(&H->plan.slots, 2 * cells, "voxels by cell"));
     FA_TRY(ialloc(&H->plan.box, (size_t)(2 * bricks), "brick boxes"));
     FA_TRY(ialloc(&H->plan.outside, (size_t)kDirMaxBlocks, "cost partials"));
+    FA_TRY(ialloc(&H->plan.tile_loss, (size_t)tiles, "cost partials"));
+    FA_TRY(ialloc(&H->plan.tickets, tickets, "tickets"));
+    FA_HIP(fa::launch_fill(reinterpret_cast<float*>(H->plan.tickets), 0.0f, (int64_t)tickets, H->stream));
+    H->plan_words = words;
     H->plan_cells = cells;
     H->plan_bricks = bricks;
+    H->plan_tiles = tiles;
   }
   H->plan_level = -1;
-  if (H->splat_direct) {
-    FA_TRY(ensure_acc(H));
+  FA_TRY(ensure_acc(H));
+  if (H->splat_direct)
     FA_HIP(hipMemsetAsync(H->acc, 0, (size_t)(3 * H->cap) * sizeof(unsigned long long), H->stream));
-  }
   if (total > H->loss_cap) {
     FA_HIP(hipStreamSynchronize(H->stream));
     if (H->loss_hist) (void)hipFree(H->loss_hist);

@@ -2589,9 +2589,7 @@ __global__ void __launch_bounds__(256) k_start(const Clear4 A, int64_t n, Ctl* c
 
 // The means of two images in one launch: the sums of each image's workgroups go
 // to memory, and the last workgroup to finish adds them up, in the order of the
-// workgroups.  A counter takes about 10 ns per workgroup, so an image's 2048
-// count on kTicketSlots counters first and the last of each on one.  Every
-// counter is left at zero.  Bound by launches at the usual sizes: an LNCC loss
+// workgroups.  Bound by launches at the usual sizes: an LNCC loss
 // and gradient takes 97 us at 24^3 and at 128^3 with k_means_warp, 122 and 119
 // with a sum and a division per image and the warp in launches of their own.
 __device__ __forceinline__ void mean_block(const Means& A, int img, int blk, int np) {
@@ -2606,18 +2604,7 @@ __device__ __forceinline__ void mean_block(const Means& A, int img, int blk, int
     __hip_atomic_store(&part[blk], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // the sum has to have reached memory before this workgroup counts
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    unsigned* slots = A.tickets + (size_t)img * (kTicketSlots + 1) * kTicketStride;
-    unsigned* slot = slots + (1 + blk % kTicketSlots) * kTicketStride;
-    const unsigned in_slot = (unsigned)(np - blk % kTicketSlots + kTicketSlots - 1) / kTicketSlots;
-    last = 0;
-    if (__hip_atomic_fetch_add(slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == in_slot) {
-      __hip_atomic_store(slot, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned used = (unsigned)min(np, kTicketSlots);
-      if (__hip_atomic_fetch_add(slots, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == used) {
-        __hip_atomic_store(slots, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last = 1;
-      }
-    }
+    last = last_workgroup(A.tickets + (size_t)img * (kTicketSlots + 1) * kTicketStride, blk, np);
   }
   __syncthreads();
   if (!last) return;
