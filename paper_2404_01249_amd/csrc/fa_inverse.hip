@@ -1143,7 +1143,12 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
     H->wts = nullptr;
     FA_TRY(ialloc(&H->wts, host.size(), "tap tables"));
     H->wts_host = host;
-    FA_HIP(hipMemcpyAsync(H->wts, H->wts_host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice, H->stream));
+    const hipError_t e = hipMemcpyAsync(H->wts, H->wts_host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice,
+                                        H->stream);
+    if (e != hipSuccess) {   // wts holds nothing: the next schedule uploads again
+      H->wts_host.clear();
+      return fail(FA_EHIP, std::string("copying the tap tables: ") + hipGetErrorString(e));
+    }
   }
 
   // state (sized for the largest level) and the splat accumulator
