@@ -759,7 +759,7 @@ def main():
     fin = len(p.scales) - 1
     n_fin = lv[fin][0]
     g_ms, g_n = prof[fin][0]
-    roof = {"bound": "hbm", "kernel": "k_grad (warp+LNCC+adjoint+Adam), finest level", "achieved": None,
+    roof = {"bound": "hbm", "kernel": "k_grad (LNCC+adjoint+Adam), finest level", "achieved": None,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None, "traffic": measured_traffic(),
             "bytes_per_launch": GRAD_BYTES_PER_VOXEL * n_fin, "avg_launch_us": None, "launches": g_n}
     split, steady = {}, None

@@ -42,7 +42,8 @@ fa_status fa_lncc_create(fa_shape shape, int window, float cc_eps, void* hip_str
 /* Evaluate at (fixed, moving, d), all device pointers of the evaluator's shape.
  *   loss_dev:  device float receiving L (may be NULL).
  *   grad_dev:  device [3][n0][n1][n2] receiving dL/dd, or NULL for the loss only
- *              (written twice: the slope of the moving image passes through it).
+ *              (written twice: the slope of the moving image passes through it,
+ *              so it must not overlap fixed, moving or d).
  *   grad_scale_dev: device float multiplying the gradient (the upstream
  *              derivative of a chain rule), or NULL for 1.
  * At least one of loss_dev and grad_dev must be non-NULL.  Enqueued; calls on

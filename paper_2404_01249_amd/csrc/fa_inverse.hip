@@ -1151,7 +1151,7 @@ fa_status fa_inverse_set_schedule(fa_inverse H, int n_levels, const float* scale
     }
   }
 
-  // state (sized for the largest level) and the splat accumulator
+  // state, sized for the largest level, and the sums in memory
   const int64_t need = std::max(nmax, H->n);   // m and e hold three input volumes each below
   const bool wide = H->rg > fa::kMaxRadius || H->rw > fa::kMaxRadius;
   if (need > H->cap || (wide && !H->wide)) {

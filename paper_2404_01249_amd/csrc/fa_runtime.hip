@@ -911,11 +911,13 @@ Tiling choose_tiling(const fa_shape& s, KernelKind kind, const Tuning& tu, bool 
   int zc = (int)(((int64_t)s.n0 * plane_tiles + kSlots[kind] - 1) / kSlots[kind]);
   // Rounded up, chunks can still be one too many for the slots (97x131x203: 63
   // tiles in nine chunks of 12 planes), and the last few workgroups then take a
-  // round of their own.  Fewer and longer chunks (eight of 13) save it, as long
-  // as they leave no more than a third of the workgroups out, which slots shared
-  // by fewer of them take back (LNCC loss and gradient, window 5: 103 -> 85 us
-  // there, 306 -> 269 at 100x320x320, 40 planes -> 50; 481 -> 491 at 120x240x640
-  // for 71 -> 120, so not there).
+  // round of their own.  Fewer and longer chunks (eight of 13) save it, unless
+  // they leave a third of the workgroups out.  Over 45 shapes of 0.6 to 40 million
+  // voxels, the longer chunk against the other, by how much longer it is:
+  //   gradient      1.1-1.25  15% to 40% faster   1.25-1.5  7% to 23%   1.7-2  -10% to 8%
+  //   sigma_grad smoothing    -3% to 17%                    -2% to 7%
+  //   warp smoothing          5% to 40%                     -2% to 10%         -19% to 2%
+  //   composition             -6% to 39%                    -2% to 18%         -31% to 0%
   if (zc < s.n0 && (int64_t)plane_tiles * ((s.n0 + zc - 1) / zc) > kSlots[kind]) {
     const int most = std::max(1, kSlots[kind] / plane_tiles), fit = (s.n0 + most - 1) / most;
     if (2 * fit <= 3 * zc) zc = fit;
@@ -1192,8 +1194,8 @@ fa_status fa_pair_set_schedule(fa_pair P, int n_levels, const float* scales, con
   }
 
   // A level's last iteration does not sample, so one of a single iteration
-  // needs no row pairs (512^3 with single iterations at scales 2 and 1: 15.2 ->
-  // 14.3 ms).
+  // needs no row pairs: 0.6 ms to form and 1.1 GB to hold at 512^3.  (Levels of
+  // more iterations always have them.)
   for (auto& L : P->levels) {
     L.pairs_ok = false;
     if (L.iters >= 2) FA_TRY(make_row_pairs(P, L));
@@ -1727,7 +1729,8 @@ struct fa_sym_s {
   fa_shape shape{};
   BatchTables tables;          // its device memory is kept between calls
   // The inversion of finish, kept for the next one: allocating and releasing its
-  // twenty buffers and the tables took 1.1 ms of a 2.8 ms registration at 96x112x112.
+  // buffers and the tables took 1.1 ms of a 2.8 ms registration at 96x112x112, as
+  // it still does once in a handle's first.
   fa_inverse inv = nullptr;
 };
 

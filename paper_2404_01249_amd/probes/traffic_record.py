@@ -66,7 +66,7 @@ def main():
         with open(os.path.join(ROOT, src), "rb") as fh:
             h.update(fh.read())
     rd, wr = rec[1] * 1024 * ff, rec[2] * 1024 * wf
-    json.dump({"kernel": f"{rec[0]} at 160x192x224 (fused warp + LNCC + adjoint + Adam)",
+    json.dump({"kernel": f"{rec[0]} at 160x192x224 (fused LNCC + adjoint + Adam)",
                "source_sha256": h.hexdigest(), "source_files": SOURCES,
                "fetch_kib_per_dispatch": rec[1], "write_kib_per_dispatch": rec[2],
                "calibration": {"kernel": "torch.add(x, 1.0, out=y) on 64 Mi float32 (256 MiB read, 256 MiB write)",
