@@ -42,8 +42,9 @@ fa_status fa_lncc_create(fa_shape shape, int window, float cc_eps, void* hip_str
 /* Evaluate at (fixed, moving, d), all device pointers of the evaluator's shape.
  *   loss_dev:  device float receiving L (may be NULL).
  *   grad_dev:  device [3][n0][n1][n2] receiving dL/dd, or NULL for the loss only
- *              (written twice: the slope of the moving image passes through it,
- *              so it must not overlap fixed, moving or d).
+ *              (written twice: the slope of the moving image passes through it).
+ *              It must not overlap fixed or d; where it overlaps moving, the
+ *              call samples a copy, which the evaluator then keeps.
  *   grad_scale_dev: device float multiplying the gradient (the upstream
  *              derivative of a chain rule), or NULL for 1.
  * At least one of loss_dev and grad_dev must be non-NULL.  Enqueued; calls on
@@ -69,7 +70,8 @@ void fa_lncc_destroy(fa_lncc h);
  * besides the caller's inputs and outputs (control block, reduction partials,
  * warped image) lives in a fixed device array of
  * FA_LNCC_NOALLOC_SCRATCH_BYTES.  Volumes with 4 (n0+4)(n1+4)(n2+4) bytes plus
- * a few KB within it are accepted (160x192x224 counts 29.3 MB).  A larger one is
+ * a few KB within it are accepted (160x192x224 counts 29.3 MB), half as many
+ * where grad_dev overlaps moving, whose copy lies there too.  A larger one is
  * rejected with FA_EINVAL before any work is enqueued.  The first call on a
  * device looks up the array's address on that device (hipGetSymbolAddress).
  *

@@ -32,9 +32,18 @@ struct fa_lncc_s {
   double* mean_partials = nullptr;  // 2 * kMeanBlocks doubles and the tickets of launch_means_warp
   unsigned* tickets = nullptr;
   float* warped = nullptr;      // J = I_m(x + d), made by each call
+  float* copy = nullptr;        // the moving image, where a call's gradient overlaps it
 };
 
 namespace {
+
+// Whether the gradient [3][n] overlaps the moving image: the slope, which passes
+// through the gradient's buffer, would then be written over the image that is
+// still being sampled.  Such a call samples a copy.
+bool overlaps(const float* moving, const float* grad, int64_t n) {
+  const uintptr_t m = (uintptr_t)moving, g = (uintptr_t)grad, size = (uintptr_t)n * sizeof(float);
+  return grad && m < g + 3 * size && g < m + size;
+}
 
 void release(fa_lncc h) {
   if (!h) return;
@@ -44,6 +53,7 @@ void release(fa_lncc h) {
   if (h->mean_partials) (void)hipFree(h->mean_partials);
   if (h->tickets) (void)hipFree(h->tickets);
   if (h->warped) (void)hipFree(h->warped);
+  if (h->copy) (void)hipFree(h->copy);
   delete h;
 }
 
@@ -119,6 +129,16 @@ fa_status fa_lncc_eval(fa_lncc h, const float* fixed, const float* moving, const
   // image, and removing it keeps the fp32 window variances well conditioned
   // J, and with a gradient the slope of the moving image in the caller's gradient
   // buffer: the gradient kernel reads it there only at the voxel it writes.
+  if (overlaps(moving, grad_dev, h->n)) {
+    const size_t bytes = (size_t)h->n * sizeof(float);
+    if (!h->copy && hipMalloc((void**)&h->copy, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      h->copy = nullptr;
+      return fail(FA_ENOMEM, "device allocation failed");
+    }
+    FA_HIP(hipMemcpyAsync(h->copy, moving, bytes, hipMemcpyDeviceToDevice, h->stream));
+    moving = h->copy;
+  }
   FA_HIP(fa::launch_means_warp({{fixed, moving}, {&h->ctl->shift_i, &h->ctl->shift_j}, h->n, h->mean_partials, h->tickets},
                                moving, d, h->warped, grad_dev, h->shape.n0, h->shape.n1, h->shape.n2, h->stream));
   fa::GradArgs ga{};
@@ -169,17 +189,26 @@ fa_status fa_lncc_eval_noalloc(fa_shape shape, int window, float cc_eps, const f
     return fail(FA_EINVAL, "volume too large for the allocation-free evaluation: needs " + std::to_string(need) +
                                " bytes of scratch, the library holds " +
                                std::to_string((size_t)FA_LNCC_NOALLOC_SCRATCH_BYTES));
+  const size_t off_means = off_mean + align256((size_t)n * sizeof(float));
+  const size_t off_copy = off_means + align256(2 * fa::kMeanBlocks * sizeof(double) + fa::kTicketWords * sizeof(unsigned));
+  const bool copied = overlaps(moving, grad_dev, n);
+  if (copied && off_copy + (size_t)n * sizeof(float) > (size_t)FA_LNCC_NOALLOC_SCRATCH_BYTES)
+    return fail(FA_EINVAL, "grad_dev overlaps moving, and the library's scratch has no room for a copy of it");
   void* base = nullptr;
   FA_TRY(scratch_address(&base));
   unsigned char* b = static_cast<unsigned char*>(base);
   fa::Ctl* ctl = reinterpret_cast<fa::Ctl*>(b);
   double* partials = reinterpret_cast<double*>(b + off_part);
   float* warped = reinterpret_cast<float*>(b + off_mean);
-  const size_t off_means = off_mean + align256((size_t)n * sizeof(float));
   double* mean_partials = reinterpret_cast<double*>(b + off_means);
   unsigned* tickets = reinterpret_cast<unsigned*>(b + off_means + 2 * fa::kMeanBlocks * sizeof(double));
   static_assert(FA_LNCC_NOALLOC_SCRATCH_BYTES >= (1 << 20), "small volumes need the room for the partials");
   const hipStream_t st = (hipStream_t)hip_stream;
+  if (copied) {
+    float* const copy = reinterpret_cast<float*>(b + off_copy);
+    FA_HIP(hipMemcpyAsync(copy, moving, (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, st));
+    moving = copy;
+  }
   // every scratch word the kernels read is written earlier in this call, on
   // this stream: the control block by its init kernel, the shifts by the
   // means, the warped image by the warp kernel, each partial by its workgroup
